@@ -50,7 +50,7 @@ static void release(bingo_graph* g) {
         if (g->slot_ev[i]) hipEventDestroy(g->slot_ev[i]);
     for (hipEvent_t e : {g->ppr_done, g->ppr_h0, g->ppr_h1})
         if (e) hipEventDestroy(e);
-    hipFree(g->hdr);
+    hipFree(g->hdr_mem);
     hipFree(g->alias);
     hipFree(g->pool);
     hipFree(g->d_ctl);
@@ -92,14 +92,15 @@ int bingo_build(const bingo_config* cfg, uint32_t n, uint64_t m, const uint32_t*
     g->pool_words = cfg->pool_bytes / 4;
     g->pool_auto = cfg->pool_bytes == 0;
     g->radix_base = radix;
-    const size_t hdr_words = radix == 4 ? (size_t)H4_WORDS : (size_t)HDR_WORDS;
-    g->hdr = nullptr; g->pool = nullptr; g->d_ctl = nullptr; g->d_err = nullptr; g->alias = nullptr;
-    if (hipMalloc(&g->hdr, (size_t)n * hdr_words * 4) != hipSuccess ||
+    const uint64_t hdr_words = radix == 4 ? (uint64_t)n * H4_WORDS : hdr_total_words(n);
+    g->hdr = g->hdr_mem = nullptr; g->pool = nullptr; g->d_ctl = nullptr; g->d_err = nullptr; g->alias = nullptr;
+    if (hipMalloc(&g->hdr_mem, hdr_words * 4) != hipSuccess ||
         hipMalloc(&g->d_ctl, CTL_WORDS * 8) != hipSuccess || hipMalloc(&g->d_err, 4) != hipSuccess) {
         release(g);
         return BINGO_E_OOM;
     }
-    if (hipMemsetAsync(g->hdr, 0, (size_t)n * hdr_words * 4, st) != hipSuccess ||
+    g->hdr = radix == 4 ? g->hdr_mem : g->hdr_mem + hdr_front_words(n);
+    if (hipMemsetAsync(g->hdr_mem, 0, hdr_words * 4, st) != hipSuccess ||
         hipMemsetAsync(g->d_ctl, 0, CTL_WORDS * 8, st) != hipSuccess) {
         release(g);
         return BINGO_E_HIP;

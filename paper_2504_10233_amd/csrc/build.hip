@@ -100,9 +100,9 @@ __global__ void __launch_bounds__(WB) k_header(uint32_t n, const uint32_t* __res
     }
     const uint64_t mask = __ballot(cnt > 0) & 0xFFFFFFFFull;
     const uint32_t hi = mask_hi((uint32_t)mask);
-    uint32_t* h = hdr + (size_t)u * HDR_WORDS;
+    const HdrRef h = hdr_ref(hdr, u);
     if (lane < 32) {
-        if (lane <= hi) h[H_CNT + (hi - lane)] = cnt;
+        hdr_put_slots(h, lane, hi, cnt);
         h[H_INFO + lane] = (t == GT_ONE) ? last : 0u;
     }
     if (lane == 0) {
@@ -131,7 +131,7 @@ __global__ void __launch_bounds__(WB) k_fill(uint32_t n, const uint32_t* __restr
     if (u >= n) return;
     const uint32_t lane = lane_id();
     const uint32_t b = start[u], d = start[u + 1] - b;
-    uint32_t* h = hdr + (size_t)u * HDR_WORDS;
+    const HdrRef h = hdr_ref(hdr, u);
     if (d == 0) {
         if (lane == 0) { h[H_ADJLO] = 0; h[H_ADJHI] = 0; }
         if (lane < 8) h[H_LCAPLOG + lane] = 0;
@@ -164,7 +164,7 @@ __global__ void __launch_bounds__(WB) k_fill(uint32_t n, const uint32_t* __restr
     const uint32_t smask = (uint32_t)(__ballot(t == GT_SPARSE) & 0xFFFFFFFFull);
     // one-element groups: the member's destination in the count slot
     const bool one = lane < 32 && t == GT_ONE;
-    if (one) h[H_CNT + (hi - lane)] = cdst[b + h[H_INFO + lane]];
+    if (one) h.slot(hi - lane) = cdst[b + h[H_INFO + lane]];
     const uint32_t onemask = (uint32_t)(__ballot(one) & 0xFFFFFFFFull);
     if (lane == 0) h[H_ONEMASK] = onemask;
     // list capacity exponents, one byte per group, packed four per word
@@ -369,7 +369,7 @@ __global__ void __launch_bounds__(ALIAS_TB) k_alias_rows(const uint32_t* __restr
     for (uint64_t i = (uint64_t)blockIdx.x * ALIAS_TB + tx; i < total; i += (uint64_t)gridDim.x * ALIAS_TB) {
         const uint32_t u = list ? list[i] : (uint32_t)i;
         if (u >= n) continue;  // a rejected stream's bad source id
-        const uint32_t* h = hdr + (size_t)u * HDR_WORDS;
+        const HdrCRef h = hdr_ref(hdr, u);
         uint4* row = alias + (size_t)u * ALIAS_ENTRIES;
         const uint32_t onem = h[H_ONEMASK], hi = hdr_hi(h);
         uint64_t W = 0;
@@ -468,7 +468,7 @@ __global__ void k_sr_compact(uint32_t n, const uint32_t* __restrict__ hdr, const
         if (dirty && !dirty[it]) continue;
         const uint32_t u = list ? list[it] : (uint32_t)it;
         if (u >= n) continue;
-        const uint32_t d = hdr[(size_t)u * HDR_WORDS + H_DEG];
+        const uint32_t d = hdr_ref(hdr, u)[H_DEG];
         bool small = d <= SR_BIG;
         if (!small) {
             const uint32_t nch = (d + SR_CHUNK - 1) / SR_CHUNK;
@@ -505,7 +505,7 @@ __global__ void k_sr_compact(uint32_t n, const uint32_t* __restrict__ hdr, const
 
 // The sparse mask of vertex u and, in LDS, each group's count, list block and
 // capacity (wave 0 of the block; the caller synchronizes).
-__device__ __forceinline__ void sr_groups(const uint32_t* __restrict__ h, uint32_t d, GroupRule rule,
+__device__ __forceinline__ void sr_groups(const HdrCRef& h, uint32_t d, GroupRule rule,
                                           uint32_t* g_c, uint32_t* g_info, uint32_t* g_lcap, uint32_t* s_smask) {
     const uint32_t lane = lane_id();
     const uint32_t mask = h[H_MASK], onem = h[H_ONEMASK];
@@ -535,7 +535,7 @@ __global__ void __launch_bounds__(SRC_TB) k_sr_count(const uint32_t* __restrict_
         if (b == SR_NO_OWNER) continue;
         const uint32_t* e = work + sr_big_off(maxc) + 3ull * b;
         const uint32_t u = e[0], j = c - e[1];
-        const uint32_t* h = hdr + (size_t)u * HDR_WORDS;
+        const HdrCRef h = hdr_ref(hdr, u);
         const uint32_t d = h[H_DEG];
         // sparse mask from the final header (every lane of a wave computes it)
         const uint32_t mask = h[H_MASK], onem = h[H_ONEMASK], hi = hdr_hi(h);
@@ -578,7 +578,7 @@ __global__ void __launch_bounds__(SRC_TB) k_sr_write(uint32_t* __restrict__ hdr,
         if (b == SR_NO_OWNER) continue;
         const uint32_t* e = work + sr_big_off(maxc) + 3ull * b;
         const uint32_t u = e[0], cb = e[1], nch = e[2], j = c - cb;
-        uint32_t* h = hdr + (size_t)u * HDR_WORDS;
+        const HdrRef h = hdr_ref(hdr, u);
         const uint32_t d = h[H_DEG];
         const uint32_t mask = h[H_MASK], onem = h[H_ONEMASK], hi = hdr_hi(h);
         const bool ne = lane < 32 && ((mask >> lane) & 1u);
@@ -640,7 +640,7 @@ __global__ void __launch_bounds__(SRC_TB) k_sr_index(const uint32_t* __restrict_
         if (b == SR_NO_OWNER) continue;
         const uint32_t* e = work + sr_big_off(maxc) + 3ull * b;
         const uint32_t u = e[0], nch = e[2], j = c - e[1];
-        const uint32_t* h = hdr + (size_t)u * HDR_WORDS;
+        const HdrCRef h = hdr_ref(hdr, u);
         const uint32_t d = h[H_DEG];
         __syncthreads();  // the previous chunk is done with the shared arrays
         if ((tid >> 6) == 0) sr_groups(h, d, rule, g_c, g_info, g_lcap, &s_smask);
@@ -704,7 +704,7 @@ __global__ void __launch_bounds__(SR_TB) k_srebuild(uint32_t* __restrict__ hdr, 
     const uint32_t nt = work[0];
     for (uint32_t q = blockIdx.x; q < nt; q += gridDim.x) {
         const uint32_t u = work[SR_LIST0 + q];
-        uint32_t* h = hdr + (size_t)u * HDR_WORDS;
+        const HdrRef h = hdr_ref(hdr, u);
         const uint32_t d = h[H_DEG];
         __syncthreads();  // the previous vertex is done with the shared arrays
         if (wave == 0) {
@@ -818,7 +818,7 @@ __global__ void __launch_bounds__(SRW_TB) k_srebuild_wave(uint32_t* __restrict__
     const uint32_t nt = work[3];
     for (uint64_t q = (uint64_t)blockIdx.x * (SRW_TB / 64) + wave; q < nt; q += (uint64_t)gridDim.x * (SRW_TB / 64)) {
         const uint32_t u = work[SR_LIST0 + maxc - 1 - q];
-        uint32_t* h = hdr + (size_t)u * HDR_WORDS;
+        const HdrRef h = hdr_ref(hdr, u);
         const uint32_t d = h[H_DEG];
         const uint32_t mask = h[H_MASK], onem = h[H_ONEMASK];
         const bool ne = lane < 32 && ((mask >> lane) & 1u);

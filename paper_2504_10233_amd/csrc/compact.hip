@@ -14,7 +14,7 @@ constexpr int WB = 256;
 
 // Lane k < 32: the block words (list and index) of group k if it is listed;
 // lane 32: the S(u) block; other lanes 0.
-__device__ __forceinline__ uint64_t lane_list_words(const uint32_t* __restrict__ h, uint32_t d, uint32_t mask,
+__device__ __forceinline__ uint64_t lane_list_words(const HdrCRef& h, uint32_t d, uint32_t mask,
                                                     uint32_t lane, GroupRule rule) {
     if (lane == 32) return h[H_SCAP];
     if (lane >= 32 || !((mask >> lane) & 1u)) return 0ull;
@@ -36,7 +36,7 @@ __global__ void __launch_bounds__(WB) k_cmp_size(const uint32_t* __restrict__ hd
                                                  uint64_t* __restrict__ need) {
     const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
     for (uint64_t u = (uint64_t)blockIdx.x * (WB / 64) + wave; u < n; u += (uint64_t)gridDim.x * (WB / 64)) {
-        const uint32_t* h = hdr + (size_t)u * HDR_WORDS;
+        const HdrCRef h = hdr_ref(hdr, u);
         const uint64_t w = wave_sum64(lane_list_words(h, h[H_DEG], h[H_MASK], lane, rule));
         if (lane == 0) need[u] = w + adj_block_words(h[H_ACAP]);
     }
@@ -58,10 +58,10 @@ __global__ void __launch_bounds__(WB) k_cmp_copy(uint32_t* __restrict__ hdr, con
                                                  const uint64_t* __restrict__ off) {
     const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
     for (uint64_t u = (uint64_t)blockIdx.x * (WB / 64) + wave; u < n; u += (uint64_t)gridDim.x * (WB / 64)) {
-        uint32_t* h = hdr + (size_t)u * HDR_WORDS;
+        const HdrRef h = hdr_ref(hdr, u);
         const uint32_t d = h[H_DEG], mask = h[H_MASK], cap = h[H_ACAP];
         const uint64_t adj = hdr_adj(h);
-        const uint64_t lw = lane_list_words(h, d, mask, lane, rule);
+        const uint64_t lw = lane_list_words(hdr_ref((const uint32_t*)hdr, u), d, mask, lane, rule);
         const uint32_t info = lane < 32 ? h[H_INFO + lane] : (lane == 32 ? h[H_SBLK] : 0u);
         uint64_t o = off[u];
         if (cap) {

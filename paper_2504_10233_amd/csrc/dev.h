@@ -7,43 +7,55 @@
 #include "bingo.h"
 
 // ---------------------------------------------------------------------------
-// Per-vertex header: the inter-group sampling space of Sec. 3 / Sec. 4.1, one
-// fixed 384-byte slot (three 128-byte lines) per vertex, 128-byte aligned.
-//   words 0..5: mask of one-element groups, degree d, W = sum_k c_k 2^k (u64),
-//           adjacency block offset (u64, in pool words; bits 24..28 of its
+// Per-vertex header: the inter-group sampling space of Sec. 3 / Sec. 4.1, 96
+// words per vertex in two arrays of one allocation.  The hot line (16 words, 64
+// bytes) of vertex u is at hdr + 16 u, its cold part (80 words) at
+// hdr - 80 (u + 1), so one pointer reaches both.
+//   hot, words 0..5: mask of one-element groups, degree d, W = sum_k c_k 2^k
+//           (u64), adjacency block offset (u64, in pool words; bits 24..28 of its
 //           high word hold hi, the highest non-empty group)
-//   words 6..37: the group slots by rank from the top: word 6 + r holds the
-//           slot of group hi - r (r = 0..hi)
-//   words 38..69: info_k, k = 0..31
-//   line 2: adjacency capacity, next sequence number, log2 of each listed
-//           group's list capacity (bytes), mask of non-empty groups, the
-//           reduced list S(u) (block offset, length, capacity), spare
+//   hot, words 6..15: the slots of the ten highest groups by rank: word 6 + r
+//           holds the slot of group hi - r (0 for r > hi)
+//   cold, words 16..31: adjacency capacity, next sequence number, mask of
+//           non-empty groups, the reduced list S(u) (block offset, length,
+//           capacity), log2 of each listed group's list capacity (bytes), spare
+//   cold, words 32..63: info_k, k = 0..31
+//   cold, words 64..85: the slots of ranks 10..31 (valid for ranks up to hi)
 // Slot k holds c_k, except for a one-element group (c_k = 1), whose slot holds
 // its member's destination vertex: a step that selects such a group ends in
 // the header without touching the adjacency.  info_k is the member index of a
 // one-element group, or the offset of a listed group's list block in 32-byte
-// units of the pool.  Dense and empty groups have no info.  The first 64 bytes
-// hold W, d, the offset and the ten highest groups, which carry all but a
-// fraction 2^-10 or less of W's mass when the top group is full; a walk step
-// picks its group from the top (suffix sums) and reads further only when the
-// draw falls below them.
+// units of the pool.  Dense and empty groups have no info.  The hot line holds
+// W, d, the offset and the ten highest groups, which carry all but a fraction
+// 2^-10 or less of W's mass when the top group is full; a walk step picks its
+// group from the top (suffix sums) and reads further only when the draw falls
+// below them.
+// Why two arrays: a random read is bound by address translation once the
+// touched range passes a few GiB (64-byte lines: 3.1 TB/s from 1 GiB, 1.3 TB/s
+// from 8 GiB), and a walk touches the hot lines only.  Packed they span 1 GiB
+// for 2^24 vertices; inside 384-byte slots they spanned 6.4 GiB, and each shared
+// its 128-byte L2 line with words that no walk reads.
 // ---------------------------------------------------------------------------
 #define HDR_WORDS 96
+#define HDR_HOT 16   // words of the hot line
+#define HDR_COLD 80  // words of the cold part
+#define HOT_RANKS 10 // slots in the hot line
 #define H_ONEMASK 0
-#define H_MASK 80
 #define H_DEG 1
 #define H_WLO 2
 #define H_WHI 3
 #define H_ADJLO 4
 #define H_ADJHI 5
-#define H_CNT 6        // 32 words
-#define H_INFO 38      // 32 words
-#define H_ACAP 70
-#define H_NSEQ 71
-#define H_LCAPLOG 72   // 32 bytes = 8 words
-#define H_SBLK 81      // S(u) block offset in 32-byte units (valid when H_SCAP > 0)
-#define H_SLEN 82      // |S(u)|
-#define H_SCAP 83      // S(u) capacity in entries (0: the vertex has no sparse group)
+#define H_SLOT 6       // ranks 0..9
+#define H_ACAP 16
+#define H_NSEQ 17
+#define H_MASK 18
+#define H_SBLK 19      // S(u) block offset in 32-byte units (valid when H_SCAP > 0)
+#define H_SLEN 20      // |S(u)|
+#define H_SCAP 21      // S(u) capacity in entries (0: the vertex has no sparse group)
+#define H_LCAPLOG 22   // 32 bytes = 8 words
+#define H_INFO 32      // 32 words
+#define H_SLOT10 64    // ranks 10..31
 #define H_HI_SHIFT 24  // hi in the high word of the adjacency offset
 #define H_ADJHI_MASK 0x00FFFFFFu
 #define STOP_VERTEX 0xFFFFFFFFu
@@ -83,13 +95,42 @@ __host__ __device__ inline uint32_t slot_count(uint32_t slot, uint32_t onemask, 
 }
 // the highest non-empty group of a mask (0 for an empty one)
 __host__ __device__ inline uint32_t mask_hi(uint32_t mask) { return mask ? 31u - (uint32_t)__builtin_clz(mask) : 0u; }
+// a vertex's header: word i of the layout above, whichever array holds it
+template <class T>
+struct HdrRefT {
+    T* hot;
+    T* cold;
+    __host__ __device__ T& operator[](uint32_t i) const { return i < HDR_HOT ? hot[i] : cold[i - HDR_HOT]; }
+    // the slot of rank r (group hi - r)
+    __host__ __device__ T& slot(uint32_t r) const {
+        return r < HOT_RANKS ? hot[H_SLOT + r] : cold[H_SLOT10 - HDR_HOT - HOT_RANKS + r];
+    }
+};
+template <class T>
+__host__ __device__ inline HdrRefT<T> hdr_ref(T* hdr, uint64_t u) {
+    return HdrRefT<T>{hdr + u * HDR_HOT, hdr - (u + 1) * HDR_COLD};
+}
+typedef HdrRefT<uint32_t> HdrRef;
+typedef HdrRefT<const uint32_t> HdrCRef;
+// words in front of the hot lines (n cold parts, rounded to a 128-byte line)
+inline uint64_t hdr_front_words(uint64_t n) { return (n * HDR_COLD + 31) & ~31ull; }
+inline uint64_t hdr_total_words(uint64_t n) { return hdr_front_words(n) + n * HDR_HOT; }
 // header fields: adjacency offset, hi, and the slot of group k (0 above hi: those groups are empty)
-__host__ __device__ inline uint64_t hdr_adj(const uint32_t* h) {
+template <class H>
+__host__ __device__ inline uint64_t hdr_adj(const H& h) {
     return ((uint64_t)(h[H_ADJHI] & H_ADJHI_MASK) << 32) | h[H_ADJLO];
 }
-__host__ __device__ inline uint32_t hdr_hi(const uint32_t* h) { return h[H_ADJHI] >> H_HI_SHIFT; }
-__host__ __device__ inline uint32_t hdr_slot(const uint32_t* h, uint32_t k, uint32_t hi) {
-    return k <= hi ? h[H_CNT + (hi - k)] : 0u;
+template <class H>
+__host__ __device__ inline uint32_t hdr_hi(const H& h) { return h[H_ADJHI] >> H_HI_SHIFT; }
+template <class H>
+__host__ __device__ inline uint32_t hdr_slot(const H& h, uint32_t k, uint32_t hi) {
+    return k <= hi ? h.slot(hi - k) : 0u;
+}
+// Lane k < 32 writes group k's slot; the lanes above hi clear the unused ranks of
+// the hot line, whose slots a walk step adds up without looking at hi.
+__device__ __forceinline__ void hdr_put_slots(const HdrRef& h, uint32_t lane, uint32_t hi, uint32_t slot) {
+    if (lane <= hi) h.slot(hi - lane) = slot;
+    else if (lane < HOT_RANKS) h.slot(lane) = 0u;
 }
 // the high word of the adjacency offset with hi
 __host__ __device__ inline uint32_t adjhi_word(uint64_t adj, uint32_t hi) {
@@ -200,17 +241,26 @@ __device__ __forceinline__ void philox_block(uint32_t c0, uint32_t c1, uint32_t 
                                              uint32_t& o2, uint32_t& o3) {
 #pragma unroll
     for (int i = 0; i < 10; ++i) {
-        const uint32_t lo_a = 0xD2511F53u * c0;
-        const uint32_t hi_a = __umulhi(0xD2511F53u, c0);
-        const uint32_t lo_b = 0xCD9E8D57u * c2;
-        const uint32_t hi_b = __umulhi(0xCD9E8D57u, c2);
-        const uint32_t n0 = hi_b ^ c1 ^ k0;
-        const uint32_t n2 = hi_a ^ c3 ^ k1;
-        c0 = n0; c1 = lo_b; c2 = n2; c3 = lo_a;
+        // whole 64-bit products: one multiply instruction each instead of a low and a high one
+        const uint64_t a = (uint64_t)0xD2511F53u * c0;
+        const uint64_t b = (uint64_t)0xCD9E8D57u * c2;
+        const uint32_t n0 = (uint32_t)(b >> 32) ^ c1 ^ k0;
+        const uint32_t n2 = (uint32_t)(a >> 32) ^ c3 ^ k1;
+        c0 = n0; c1 = (uint32_t)b; c2 = n2; c3 = (uint32_t)a;
         k0 += 0x9E3779B9u;
         k1 += 0xBB67AE85u;
     }
     o0 = c0; o1 = c1; o2 = c2; o3 = c3;
+}
+
+// The same block for a key that is uniform over the wave, in scalar registers.  The
+// key is made opaque at each use: hoisted out of a walk's loop, the ten rounds'
+// keys would hold twenty scalar registers that the loop's masks need.
+__device__ __forceinline__ void philox_uniform(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint64_t seed,
+                                               uint32_t& o0, uint32_t& o1, uint32_t& o2, uint32_t& o3) {
+    uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+    asm volatile("" : "+s"(k0), "+s"(k1));
+    philox_block(c0, c1, c2, c3, k0, k1, o0, o1, o2, o3);
 }
 
 __device__ __forceinline__ void rs_init(RandStream& s, uint64_t seed, uint64_t walk, uint32_t step) {
@@ -289,7 +339,8 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
 struct bingo_graph {
     uint32_t n;
     GroupRule rule;
-    uint32_t* hdr;          // n * HDR_WORDS
+    uint32_t* hdr;          // hot lines (the cold parts lie in front of them); radix base 4: n * H4_WORDS
+    uint32_t* hdr_mem;      // the allocation that holds hdr
     uint4* alias = nullptr;  // alias-table mode: n * ALIAS_ENTRIES entries
     uint32_t alias_mode = 0;
     uint32_t* pool;         // device arena, pool_words u32

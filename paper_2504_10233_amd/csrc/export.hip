@@ -18,7 +18,7 @@ __global__ void k_dump_size(const uint32_t* __restrict__ hdr, uint32_t u0, uint3
                             uint64_t* __restrict__ sz) {
     const uint32_t u = u0 + blockIdx.x * blockDim.x + threadIdx.x;
     if (u >= u1) return;
-    const uint32_t* h = hdr + (size_t)u * HDR_WORDS;
+    const HdrCRef h = hdr_ref(hdr, u);
     const uint32_t d = h[H_DEG], mask = h[H_MASK], onem = h[H_ONEMASK], hi = hdr_hi(h);
     uint64_t s = 3 + 3ull * d;
     for (uint32_t mm = mask; mm; mm &= mm - 1) {
@@ -35,7 +35,7 @@ __global__ void __launch_bounds__(WB) k_dump_write(const uint32_t* __restrict__ 
     const uint32_t u = u0 + blockIdx.x * (WB / 64) + (threadIdx.x >> 6);
     if (u >= u1) return;
     const uint32_t lane = lane_id();
-    const uint32_t* h = hdr + (size_t)u * HDR_WORDS;
+    const HdrCRef h = hdr_ref(hdr, u);
     const uint32_t d = h[H_DEG], mask = h[H_MASK];
     uint32_t* o = out + off[u - u0];
     if (lane == 0) { o[0] = d; o[1] = h[H_NSEQ]; o[2] = mask; }
@@ -91,7 +91,7 @@ __global__ void k_idx_size(const uint32_t* __restrict__ hdr, uint32_t u0, uint32
                            uint64_t* __restrict__ sz) {
     const uint32_t u = u0 + blockIdx.x * blockDim.x + threadIdx.x;
     if (u >= u1) return;
-    const uint32_t* h = hdr + (size_t)u * HDR_WORDS;
+    const HdrCRef h = hdr_ref(hdr, u);
     const uint32_t d = h[H_DEG], mask = h[H_MASK], onem = h[H_ONEMASK], hi = hdr_hi(h);
     const uint32_t slen = h[H_SCAP] ? h[H_SLEN] : 0u;
     uint64_t s = 1 + (uint64_t)slen;
@@ -111,7 +111,7 @@ __global__ void __launch_bounds__(WB) k_idx_write(const uint32_t* __restrict__ h
     const uint32_t u = u0 + blockIdx.x * (WB / 64) + (threadIdx.x >> 6);
     if (u >= u1) return;
     const uint32_t lane = lane_id();
-    const uint32_t* h = hdr + (size_t)u * HDR_WORDS;
+    const HdrCRef h = hdr_ref(hdr, u);
     const uint32_t d = h[H_DEG], mask = h[H_MASK];
     const uint32_t slen = h[H_SCAP] ? h[H_SLEN] : 0u;
     const uint32_t* S = pool + (uint64_t)h[H_SBLK] * LIST_UNIT_WORDS;
@@ -166,7 +166,7 @@ __global__ void __launch_bounds__(WB) k_mem(const uint32_t* __restrict__ hdr, co
 #pragma unroll
     for (int i = 0; i < MEM_CTRS; ++i) tot[i] = 0;
     for (uint64_t u = (uint64_t)blockIdx.x * (WB / 64) + wave; u < n; u += (uint64_t)gridDim.x * (WB / 64)) {
-        const uint32_t* h = hdr + (size_t)u * HDR_WORDS;
+        const HdrCRef h = hdr_ref(hdr, u);
         const uint32_t d = h[H_DEG], mask = h[H_MASK];
         const bool ne = lane < 32 && ((mask >> lane) & 1u);
         const uint32_t c = ne ? slot_count(hdr_slot(h, lane, hdr_hi(h)), h[H_ONEMASK], lane) : 0u;
@@ -192,9 +192,12 @@ __global__ void __launch_bounds__(WB) k_mem(const uint32_t* __restrict__ hdr, co
         if (ne) {
             if (type_listed(t)) {
                 v[0] = 4ull * c;
-                v[1] = 4ull << capb;
+                // a 32-bit shift: 64-bit shifts have returned wrong values here with the amount in the last
+                // register of the kernel's allocation, where this kernel's register count put it
+                const uint64_t cap4 = (uint64_t)(1u << capb) * 4u;
+                v[1] = cap4;
                 v[4] = t == GT_REGULAR ? 4ull * d : 4ull * slen;
-                v[5] = list_block_words(1u << capb, index_cap_for(t, acap, scap)) * 4ull - (4ull << capb);
+                v[5] = list_block_words(1u << capb, index_cap_for(t, acap, scap)) * 4ull - cap4;
             }
             v[2] = t == GT_ONE ? 4ull : (t == GT_SPARSE ? 4ull * c + 4ull * S : (t == GT_REGULAR ? 4ull * (c + (uint64_t)d) : 0));
             v[3] = 4ull * (c + (uint64_t)d);

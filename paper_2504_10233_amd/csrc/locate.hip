@@ -20,7 +20,7 @@ __global__ void __launch_bounds__(WB) k_loc_build(const uint32_t* __restrict__ h
     const uint32_t lane = lane_id();
     uint32_t edges = 0, fail = 0;
     for (uint64_t u = (uint64_t)blockIdx.x * (WB / 64) + (threadIdx.x >> 6); u < n; u += (uint64_t)gridDim.x * (WB / 64)) {
-        const uint32_t* h = hdr + (size_t)u * HDR_WORDS;
+        const HdrCRef h = hdr_ref(hdr, u);
         const uint32_t d = h[H_DEG];
         const uint64_t adj = hdr_adj(h);
         for (uint32_t i = lane; i < d; i += 64) {
@@ -44,7 +44,7 @@ __global__ void __launch_bounds__(WB) k_loc_check_edges(const uint32_t* __restri
     const uint32_t lane = lane_id();
     uint32_t bad = 0;
     for (uint64_t u = (uint64_t)blockIdx.x * (WB / 64) + (threadIdx.x >> 6); u < n; u += (uint64_t)gridDim.x * (WB / 64)) {
-        const uint32_t* h = hdr + (size_t)u * HDR_WORDS;
+        const HdrCRef h = hdr_ref(hdr, u);
         const uint32_t d = h[H_DEG];
         const uint64_t adj = hdr_adj(h);
         for (uint32_t i = lane; i < d; i += 64)
@@ -109,7 +109,7 @@ uint64_t pow2_ge(uint64_t x) {
 __global__ void k_loc_edges(const uint32_t* __restrict__ hdr, uint32_t n, unsigned long long* __restrict__ cnt) {
     uint64_t s = 0;
     for (uint64_t u = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += (uint64_t)gridDim.x * blockDim.x)
-        s += hdr[(size_t)u * HDR_WORDS + H_DEG];
+        s += hdr_ref(hdr, u)[H_DEG];
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
     if (lane_id() == 0 && s) atomicAdd(cnt, (unsigned long long)s);

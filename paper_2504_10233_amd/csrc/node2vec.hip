@@ -32,7 +32,7 @@ inline uint32_t grid_for(uint64_t n) {
 
 __global__ void k_n2v_deg(const uint32_t* __restrict__ hdr, uint32_t n, uint32_t* __restrict__ deg) {
     for (uint64_t u = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; u < n; u += (uint64_t)gridDim.x * blockDim.x)
-        deg[u] = hdr[u * HDR_WORDS + H_DEG];
+        deg[u] = hdr_ref(hdr, u)[H_DEG];
 }
 
 // (u << 32 | dst) for every live edge, one wave per vertex
@@ -42,7 +42,7 @@ __global__ void __launch_bounds__(TB) k_n2v_keys(const uint32_t* __restrict__ hd
     const uint32_t lane = lane_id();
     for (uint64_t u = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; u < n;
          u += ((uint64_t)gridDim.x * blockDim.x) >> 6) {
-        const uint32_t* h = hdr + u * HDR_WORDS;
+        const HdrCRef h = hdr_ref(hdr, u);
         const uint32_t d = h[H_DEG];
         const uint64_t adj = hdr_adj(h);
         const uint64_t o = off[u];

@@ -82,8 +82,7 @@ __global__ void __launch_bounds__(PB) k_probe_replay(const uint32_t* __restrict_
         for (uint64_t i = c * chain; i < e; ++i) {
             const uint32_t v = DEP ? visits[i] ^ (acc & zero) : visits[i];
             if (v >= n) continue;
-            const uint32_t* h = hdr + (size_t)v * HDR_WORDS;
-            const uint4* hl = (const uint4*)h;
+            const uint4* hl = (const uint4*)hdr_ref(hdr, v).hot;
             const uint4 x0 = hl[0], x1 = hl[1], x2 = hl[2], x3 = hl[3];
             acc ^= x0.x ^ x1.y ^ x2.z ^ x3.w;
             ++lines;

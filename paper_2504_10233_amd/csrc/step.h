@@ -42,7 +42,7 @@ __device__ __forceinline__ uint32_t dense_round(const uint64_t* __restrict__ edg
 // consistent structure and only keeps a corrupted one from spinning.
 constexpr uint32_t DEC_MAX_ATTEMPTS = 1u << 24;
 
-__device__ __forceinline__ uint32_t decimal_pick(const uint32_t* __restrict__ h, const uint32_t* __restrict__ pool,
+__device__ __forceinline__ uint32_t decimal_pick(const HdrCRef& h, const uint32_t* __restrict__ pool,
                                                  uint64_t adj, uint32_t d, uint32_t slot0, uint32_t onem,
                                                  GroupRule rule, RandStream& rs) {
     if (onem & 1u) return slot0;  // one member: its destination sits in the slot
@@ -83,8 +83,9 @@ struct GroupPick {
 template <int MODE>
 __device__ __forceinline__ bool pick_group(const uint32_t* __restrict__ hdr, uint32_t u, RandStream& rs,
                                            GroupRule rule, GroupPick& g) {
-    const uint32_t* __restrict__ h = hdr + (size_t)u * HDR_WORDS;
-    const uint4* h4 = reinterpret_cast<const uint4*>(h);
+    const HdrCRef h = hdr_ref(hdr, u);
+    const uint4* h4 = reinterpret_cast<const uint4*>(h.hot);
+    const uint4* x4 = reinterpret_cast<const uint4*>(h.cold + (H_SLOT10 - HDR_HOT));  // ranks 10..31, 2 spare words
     const uint4 q0 = h4[0], q1 = h4[1], q2 = h4[2], q3 = h4[3];
     g.d = q0.y;
     if (g.d == 0) return false;
@@ -112,13 +113,13 @@ __device__ __forceinline__ bool pick_group(const uint32_t* __restrict__ hdr, uin
             for (int q = 0; q < 10; ++q)
                 if ((uint32_t)q == r) raw = sl[q];
         } else {
-            raw = h[H_CNT + r];
+            raw = h.slot(r);
         }
         g.sel = (int)k;
         g.raw = raw;
         g.csel = ((g.onem >> k) & 1u) ? 1u : raw;
     } else if constexpr (MODE == 1) {
-        const uint4 q4 = h4[4], q5 = h4[5], q6 = h4[6], q7 = h4[7], q8 = h4[8], q9 = h4[9];
+        const uint4 q4 = x4[0], q5 = x4[1], q6 = x4[2], q7 = x4[3], q8 = x4[4], q9 = x4[5];
         sl[10] = q4.x; sl[11] = q4.y; sl[12] = q4.z; sl[13] = q4.w;
         sl[14] = q5.x; sl[15] = q5.y; sl[16] = q5.z; sl[17] = q5.w;
         sl[18] = q6.x; sl[19] = q6.y; sl[20] = q6.z; sl[21] = q6.w;
@@ -151,7 +152,7 @@ __device__ __forceinline__ bool pick_group(const uint32_t* __restrict__ hdr, uin
             }
         }
         if (g.sel < 0 && g.hi >= 10) {
-            const uint4 q4 = h4[4], q5 = h4[5], q6 = h4[6], q7 = h4[7];
+            const uint4 q4 = x4[0], q5 = x4[1], q6 = x4[2], q7 = x4[3];
             sl[10] = q4.x; sl[11] = q4.y; sl[12] = q4.z; sl[13] = q4.w;
             sl[14] = q5.x; sl[15] = q5.y; sl[16] = q5.z; sl[17] = q5.w;
             sl[18] = q6.x; sl[19] = q6.y; sl[20] = q6.z; sl[21] = q6.w;
@@ -166,7 +167,7 @@ __device__ __forceinline__ bool pick_group(const uint32_t* __restrict__ hdr, uin
                 }
             }
             if (g.sel < 0 && g.hi >= 26) {
-                const uint4 q8 = h4[8], q9 = h4[9];
+                const uint4 q8 = x4[4], q9 = x4[5];
                 sl[26] = q8.x; sl[27] = q8.y; sl[28] = q8.z; sl[29] = q8.w;
                 sl[30] = q9.x; sl[31] = q9.y;
 #pragma unroll
@@ -195,7 +196,7 @@ __device__ __forceinline__ uint32_t walk_step_body(const uint32_t* __restrict__ 
     GroupPick g;
     if (!pick_group<MODE>(hdr, u, rs, rule, g)) return STOP_VERTEX;
     if (MODE == 1 && g.sel < 0)
-        return decimal_pick(hdr + (size_t)u * HDR_WORDS, pool, g.adj, g.d, g.slot0, g.onem, rule, rs);
+        return decimal_pick(hdr_ref(hdr, u), pool, g.adj, g.d, g.slot0, g.onem, rule, rs);
     if (g.sel < 0) return STOP_VERTEX;  // only on an inconsistent header
     if ((g.onem >> g.sel) & 1u) return g.raw;  // one-element group: the step ends in the header
     const uint64_t* __restrict__ edges = reinterpret_cast<const uint64_t*>(pool + g.adj);
@@ -211,9 +212,488 @@ __device__ __forceinline__ uint32_t walk_step_body(const uint32_t* __restrict__ 
         }
         return STOP_VERTEX;
     }
-    const uint32_t info = hdr[(size_t)u * HDR_WORDS + H_INFO + g.sel];
+    const uint32_t info = hdr_ref(hdr, u)[H_INFO + (uint32_t)g.sel];
     const uint32_t i = pool[(uint64_t)info * LIST_UNIT_WORDS + rs_below32(rs, g.csel)];
     return pool[g.adj + 2ull * i];
+}
+
+// The same transition word by word from block blk0 of the stream (skip words passed
+// over), as one loop around one Philox block: small code and few registers, for
+// the rare steps that the lean kernels below hand over.
+template <int MODE>
+__device__ __forceinline__ uint32_t odd_step(const uint32_t* __restrict__ hdr, const uint32_t* __restrict__ pool,
+                                             uint32_t u, uint64_t seed, uint64_t id, uint32_t s, uint32_t blk0,
+                                             uint32_t skip, GroupRule rule) {
+    const HdrCRef h = hdr_ref(hdr, u);
+    const uint32_t d = h[H_DEG], onem = h[H_ONEMASK], hi = hdr_hi(h);
+    if (d == 0) return STOP_VERTEX;
+    const uint64_t W = ((uint64_t)h[H_WHI] << 32) | h[H_WLO], adj = hdr_adj(h);
+    const uint64_t* __restrict__ edges = reinterpret_cast<const uint64_t*>(pool + adj);
+    // what the next word is: the alias slot, the group draw's halves, then a member draw of one of
+    // the forms below; an index draw of the decimal group is followed by its acceptance word
+    enum { ALIAS, HIGH, LOW, DENSE, LIST, DEC_INDEX, DEC_TEST };
+    uint32_t want = MODE == 2 ? ALIAS : HIGH, b0 = 0, b1 = 0, b2 = 0, b3 = 0, slot = 0, sel = 0, n = 0, att = 0;
+    uint64_t x = 0, list = 0, e = 0;
+#pragma unroll 1
+    for (uint32_t pos = skip;; ++pos) {
+        if (pos == skip || (pos & 3u) == 0)
+            philox_uniform((uint32_t)id, (uint32_t)(id >> 32), s, blk0 + (pos >> 2), seed, b0, b1, b2, b3);
+        const uint32_t w = (pos & 2u) ? ((pos & 1u) ? b3 : b2) : ((pos & 1u) ? b1 : b0);
+        if (want == ALIAS) {
+            slot = w >> 27;
+            want = HIGH;
+        } else if (want == HIGH) {
+            x = (uint64_t)w << 32;
+            want = LOW;
+        } else if (want == LOW) {
+            x |= w;
+            want = HIGH;
+            const uint64_t low = x * W;
+            if (low < W && low < (0ull - W) % W) continue;  // Lemire: draw again
+            const uint64_t r = __umul64hi(x, W);
+            sel = 32u;
+            if constexpr (MODE == 2) {
+                const uint4 a = rule.alias[(size_t)u * ALIAS_ENTRIES + slot];
+                const uint32_t k = r < (((uint64_t)a.y << 32) | a.x) ? slot : a.z;
+                if (k <= hi) sel = k;
+            } else {
+                uint64_t acc = 0;
+#pragma unroll 1
+                for (uint32_t k = MODE == 1 ? rule.fbits : 0u; k <= hi && sel == 32u; ++k) {
+                    acc += (uint64_t)slot_count(h.slot(hi - k), onem, k) << k;
+                    if (r < acc) sel = k;
+                }
+            }
+            const bool dec = MODE == 1 && sel == 32u;
+            if (dec) sel = 0;
+            if (sel == 32u) return STOP_VERTEX;  // only on an inconsistent header
+            const uint32_t raw = h.slot(hi - sel);
+            if ((onem >> sel) & 1u) return raw;
+            const uint32_t t = group_type(raw, d, rule);
+            list = (uint64_t)h[H_INFO + sel] * LIST_UNIT_WORDS;
+            n = type_listed(t) ? raw : d;
+            want = dec ? DEC_INDEX : (type_listed(t) ? LIST : DENSE);
+            if (dec && !type_listed(t)) list = ~0ull;
+        } else if (want == DEC_TEST) {
+            // accepted when the top F bits are below the fraction (see decimal_pick)
+            const uint32_t fm = (1u << rule.fbits) - 1u;
+            if ((w >> (32 - rule.fbits)) < ((uint32_t)(e >> 32) & fm)) return (uint32_t)e;
+            if (++att >= DEC_MAX_ATTEMPTS) return STOP_VERTEX;
+            want = DEC_INDEX;
+        } else {
+            const uint64_t m = (uint64_t)w * n;
+            const uint32_t low = (uint32_t)m;
+            if (low < n && low < (0u - n) % n) continue;
+            const uint32_t i = (uint32_t)(m >> 32);
+            if (want == DENSE) {
+                const uint64_t y = edges[i];
+                if ((y >> (32 + sel)) & 1ull) return (uint32_t)y;
+                if (++att >= (1u << 16)) return STOP_VERTEX;
+            } else {
+                e = edges[list == ~0ull ? i : pool[list + i]];
+                if (want == LIST) return (uint32_t)e;
+                want = DEC_TEST;
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The lean step.  walk_step_body above draws word by word from a RandStream,
+// whose refills sit behind tests that the lanes of a wave answer differently:
+// a wave then runs Philox several times per step, each for a few lanes.  Here a
+// lane computes one whole block per iteration, all lanes together, and the
+// words have fixed places in it: the termination word (TERM, walks that have
+// one), the alias slot (MODE 2), the 64-bit group draw, then one word per dense
+// attempt.  What a draw needs beyond that is rare and goes through
+// odd_step: a group draw in Lemire's biased zone (probability
+// W / 2^64), a redraw of a list position, and vertices of 2^21 edges and more,
+// whose sums pass 32 bits.
+// ---------------------------------------------------------------------------
+constexpr uint32_t LEAN_MAX_DEG = 1u << 21;
+
+// The group choice of the hot line by 32-bit sums.  With t = W - r (r the draw),
+// the group is the first rank q whose total from the top, A_q 2^(hi - q) with
+// A_q = 2 A_(q-1) + c_q, reaches t; that is A_q > (t - 1) >> (hi - q).  A_q stays
+// below d 2^10 < 2^31 for ten ranks.  A draw below the ten highest groups
+// continues with the remainder, ten ranks at a time.  Returns the rank (32: none,
+// only on an inconsistent header); raw: its slot.
+__device__ __forceinline__ uint32_t lean_rank(const HdrCRef& h, const uint32_t (&sl)[HOT_RANKS], uint64_t tm1,
+                                              uint32_t hi, uint32_t onem, uint32_t& raw) {
+    uint32_t om = onem << (31 - hi);  // bit 31 - q: rank q is a one-element group
+    const uint32_t t9 = hi >= 9 ? (uint32_t)(tm1 >> (hi - 9)) : (uint32_t)tm1 << (9 - hi);
+    uint32_t A = 0, cnt = 0;
+    raw = sl[0];
+#pragma unroll
+    for (int q = 0; q < HOT_RANKS; ++q) {
+        A = 2 * A + ((om >> (31 - q)) & 1u ? 1u : sl[q]);
+        const bool below = A <= (t9 >> (9 - q));
+        cnt += below ? 1u : 0u;
+        if (q + 1 < HOT_RANKS) raw = below ? sl[q + 1 < HOT_RANKS ? q + 1 : 0] : raw;
+    }
+    if (cnt < HOT_RANKS) return cnt;
+    uint64_t rest = tm1;
+    uint32_t top = hi;  // group of the chunk's first rank
+    for (uint32_t base = HOT_RANKS; base <= hi; base += HOT_RANKS) {
+        rest -= (uint64_t)A << (top - 9);  // the ranks so far; top >= 10 here
+        top = hi - base;
+        om <<= HOT_RANKS;
+        uint32_t x[HOT_RANKS];
+        const uint2* c2 = reinterpret_cast<const uint2*>(h.cold + (H_SLOT10 - HDR_HOT - HOT_RANKS) + base);
+#pragma unroll
+        for (int q = 0; q < HOT_RANKS / 2; ++q) {
+            const uint2 y = c2[q];
+            x[2 * q] = y.x;
+            x[2 * q + 1] = y.y;
+        }
+        const uint32_t t = top >= 9 ? (uint32_t)(rest >> (top - 9)) : (uint32_t)rest << (9 - top);
+        uint32_t n = 0;
+        A = 0;
+        raw = x[0];
+#pragma unroll
+        for (int q = 0; q < HOT_RANKS; ++q) {
+            const uint32_t c = base + q > hi ? 0u : ((om >> (31 - q)) & 1u ? 1u : x[q]);
+            A = 2 * A + c;
+            const bool below = A <= (t >> (9 - q));
+            n += below ? 1u : 0u;
+            if (q + 1 < HOT_RANKS) raw = below ? x[q + 1 < HOT_RANKS ? q + 1 : 0] : raw;
+        }
+        if (n < HOT_RANKS) return base + n;
+    }
+    return 32u;
+}
+
+// type of a group known to have members and not to be one-element (d < LEAN_MAX_DEG)
+__device__ __forceinline__ bool lean_dense(uint32_t c, uint32_t d, GroupRule r) {
+    return r.adaptive && c * 100u > r.alpha * d;
+}
+
+// What a step comes to after its group choice.
+enum : uint32_t { LK_DONE = 0, LK_DENSE = 1, LK_LIST = 2, LK_ODD = 3 };
+struct LeanPick {
+    uint32_t kind;  // LK_DONE: the next vertex is v; LK_ODD: take the step through odd_step
+    uint32_t v, sel, csel, d;
+    uint64_t adj;
+};
+
+// The header words a group choice needs, loaded ahead of their use.
+struct HotLine {
+    uint4 q0, q1, q2, q3;
+};
+__device__ __forceinline__ HotLine load_hot(const uint32_t* __restrict__ hdr, uint32_t u) {
+    const uint4* h4 = reinterpret_cast<const uint4*>(hdr_ref(hdr, u).hot);
+    return HotLine{h4[0], h4[1], h4[2], h4[3]};
+}
+
+// Group choice from the words of the step's stream behind the termination word:
+// MODE 0 and 1: x = a << 32 | b; MODE 2: slot from a, x = b << 32 | c.
+template <int MODE>
+__device__ __forceinline__ LeanPick lean_pick(const uint32_t* __restrict__ hdr, uint32_t u, const HotLine& q,
+                                              uint32_t a, uint32_t b, uint32_t c, GroupRule rule) {
+    LeanPick p;
+    p.kind = LK_DONE;
+    p.v = STOP_VERTEX;
+    p.sel = p.csel = 0;
+    p.d = q.q0.y;
+    p.adj = ((uint64_t)(q.q1.y & H_ADJHI_MASK) << 32) | q.q1.x;
+    if (p.d == 0) return p;
+    const HdrCRef h = hdr_ref(hdr, u);
+    const uint64_t W = ((uint64_t)q.q0.w << 32) | q.q0.z;
+    const uint32_t onem = q.q0.x, hi = q.q1.y >> H_HI_SHIFT;
+    const uint64_t x = MODE == 2 ? ((uint64_t)b << 32) | c : ((uint64_t)a << 32) | b;
+    if (x * W < W || p.d >= LEAN_MAX_DEG) {
+        p.kind = LK_ODD;
+        return p;
+    }
+    const uint64_t r = __umul64hi(x, W);
+    const uint32_t sl[HOT_RANKS] = {q.q1.z, q.q1.w, q.q2.x, q.q2.y, q.q2.z, q.q2.w, q.q3.x, q.q3.y, q.q3.z, q.q3.w};
+    uint32_t rank, raw;
+    if constexpr (MODE == 0) {
+        rank = lean_rank(h, sl, W - 1 - r, hi, onem, raw);
+    } else if constexpr (MODE == 2) {
+        const uint32_t j = a >> 27;
+        const uint4 e = rule.alias[(size_t)u * ALIAS_ENTRIES + j];
+        const uint32_t k = r < (((uint64_t)e.y << 32) | e.x) ? j : e.z;
+        rank = k > hi ? 32u : hi - k;  // above hi: only on an inconsistent structure
+        raw = 0;
+        if (rank < HOT_RANKS) {
+#pragma unroll
+            for (int i = 0; i < HOT_RANKS; ++i)
+                if ((uint32_t)i == rank) raw = sl[i];
+        } else if (rank < 32u) {
+            raw = h.slot(rank);
+        }
+    } else {
+        // integer groups F..31 ascending, the decimal group last: from the top, with I the integer
+        // groups' total, a draw r >= I picks the decimal group and t = I - r picks as in MODE 0
+        const uint32_t nint = hi + 1 > rule.fbits ? hi + 1 - rule.fbits : 0u;  // ranks of integer groups
+        uint64_t I = 0;
+#pragma unroll
+        for (int i = 0; i < HOT_RANKS; ++i)
+            if ((uint32_t)i < nint) I += (uint64_t)((onem >> (hi - i)) & 1u ? 1u : sl[i]) << (hi - i);
+        if (nint > HOT_RANKS) {
+            const uint2* c2 = reinterpret_cast<const uint2*>(h.cold + (H_SLOT10 - HDR_HOT));
+            uint2 y[11];
+#pragma unroll
+            for (int i = 0; i < 11; ++i) y[i] = c2[i];
+#pragma unroll
+            for (int i = 0; i < 22; ++i) {
+                const uint32_t c = i & 1 ? y[i / 2].y : y[i / 2].x;
+                if ((uint32_t)i + HOT_RANKS < nint)
+                    I += (uint64_t)((onem >> (hi - HOT_RANKS - i)) & 1u ? 1u : c) << (hi - HOT_RANKS - i);
+            }
+        }
+        if (r >= I) {
+            p.kind = LK_ODD;
+            return p;
+        }
+        // ranks below the integer groups are not reached: their groups' totals lie beyond t
+        rank = lean_rank(h, sl, I - 1 - r, hi, onem, raw);
+    }
+    if (rank > hi) return p;  // only on an inconsistent header
+    p.sel = hi - rank;
+    if ((onem >> p.sel) & 1u) {
+        p.v = raw;  // one-element group: the step ends in the header
+        return p;
+    }
+    p.csel = raw;
+    p.kind = lean_dense(raw, p.d, rule) ? LK_DENSE : LK_LIST;
+    return p;
+}
+
+// Word w as a draw on [0, n) (Lemire): true when it is rejected, else i is the draw.
+__device__ __forceinline__ bool lean_reject(uint32_t w, uint32_t n, uint32_t& i) {
+    const uint64_t m = (uint64_t)w * n;
+    i = (uint32_t)(m >> 32);
+    const uint32_t low = (uint32_t)m;
+    return low < n && low < (0u - n) % n;
+}
+
+// A walk's step in progress in one lane.  Between iterations only dense steps
+// whose attempts have all been rejected so far remain.
+struct LaneStep {
+    uint64_t adj;
+    uint32_t d, sel;
+    uint32_t blk;    // next block of the step's stream
+    bool pending;
+};
+
+// Up to four attempts of a dense step from one block's words (the first `skip` of
+// them are none), SPEC loads at a time; PENDING when none is accepted.
+template <int SPEC>
+__device__ __forceinline__ uint32_t lane_attempts(const uint32_t* __restrict__ pool, const LaneStep& ls, uint32_t w0,
+                                                  uint32_t w1, uint32_t w2, uint32_t w3, uint32_t skip) {
+    const uint64_t* __restrict__ edges = reinterpret_cast<const uint64_t*>(pool + ls.adj);
+    const uint32_t w[4] = {w0, w1, w2, w3};
+    uint32_t v = PENDING;
+#pragma unroll
+    for (int r = 0; r < 4; r += SPEC) {
+        if (v == PENDING && skip < (uint32_t)(r + SPEC)) {
+            uint64_t e[SPEC];
+            bool ok[SPEC];
+#pragma unroll
+            for (int a = 0; a < SPEC; ++a) {
+                uint32_t i;
+                ok[a] = !lean_reject(w[r + a], ls.d, i) && skip <= (uint32_t)(r + a);
+                e[a] = 0;
+                if (ok[a]) e[a] = edges[i];
+            }
+#pragma unroll
+            for (int a = SPEC - 1; a >= 0; --a)
+                if (ok[a] && ((e[a] >> (32 + ls.sel)) & 1ull)) v = (uint32_t)e[a];
+        }
+    }
+    return v;
+}
+
+// One iteration of a lane's step at u: a new step (ls.pending false) or more
+// attempts of the one in progress, from one Philox block either way.  Returns
+// PENDING when the step goes on, STOP_VERTEX at a vertex without out-edges,
+// else the next vertex; `ended` when the termination word (TERM = 1) ends the
+// walk before the step.  blk0: first block of the step's stream (node2vec
+// proposals).  With WAVE a dense step of a vertex of degree >= wave_deg is
+// returned as PENDING with serve set, ls.blk * 4 - left words of its stream used.
+// SPEC attempts are loaded together.  All lanes of the wave call; mid() runs
+// between the issue of the header loads and their first use.
+template <int SPEC, int MODE, int TERM, bool WAVE, class Mid>
+__device__ __forceinline__ uint32_t lane_advance(const uint32_t* __restrict__ hdr, const uint32_t* __restrict__ pool,
+                                                 bool act, uint32_t u, LaneStep& ls, uint64_t seed, uint64_t id,
+                                                 uint32_t s, uint32_t blk0, uint32_t thr, GroupRule rule,
+                                                 uint32_t wave_deg, bool& ended, bool& serve, uint32_t& left, Mid mid) {
+    constexpr uint32_t HEAD = TERM + (MODE == 2 ? 3 : 2);  // words before the first attempt
+    ended = serve = false;
+    left = 0;
+    uint32_t v = PENDING;
+    const bool begin = act && !ls.pending;
+    HotLine q;
+    if (begin) q = load_hot(hdr, u);
+    mid();
+    uint32_t w0 = 0, w1 = 0, w2 = 0, w3 = 0;
+    if (act) {
+        const uint32_t blk = begin ? 0u : ls.blk;
+        philox_uniform((uint32_t)id, (uint32_t)(id >> 32), s, blk0 + blk, seed, w0, w1, w2, w3);
+        ls.blk = blk + 1;
+    }
+    uint32_t skip = act ? 0u : 4u;  // words of the block that are no attempts
+    uint32_t lcnt = 0, linfo = 0;
+    bool odd = false;
+    if (begin) {
+        skip = HEAD;
+        if (TERM && w0 < thr) {
+            ended = true;
+            skip = 4;
+        } else {
+            const LeanPick p = TERM ? lean_pick<MODE>(hdr, u, q, w1, w2, w3, rule)
+                                    : lean_pick<MODE>(hdr, u, q, w0, w1, w2, rule);
+            if (p.kind == LK_DENSE) {
+                ls.adj = p.adj; ls.d = p.d; ls.sel = p.sel; ls.pending = true;
+                if (WAVE && p.d >= wave_deg) {
+                    serve = true;
+                    left = 4 - HEAD;
+                }
+            } else if (p.kind == LK_LIST) {
+                ls.adj = p.adj;
+                lcnt = p.csel;
+                linfo = hdr_ref(hdr, u)[H_INFO + p.sel];  // used behind the attempts of the other lanes
+            } else if (p.kind == LK_ODD) {
+                odd = true;
+            } else {
+                v = p.v;
+            }
+        }
+    }
+    if (ls.pending && act && !serve) {
+        v = lane_attempts<SPEC>(pool, ls, w0, w1, w2, w3, skip);
+        if (TERM && v == PENDING) {
+            // a walk with a termination word has one word left in block 0 for its first attempt; a
+            // second block here spares every other step an iteration of its own
+            philox_uniform((uint32_t)id, (uint32_t)(id >> 32), s, blk0 + ls.blk, seed, w0, w1, w2, w3);
+            ++ls.blk;
+            v = lane_attempts<SPEC>(pool, ls, w0, w1, w2, w3, 0u);
+        }
+        // acceptance is above alpha % per attempt: the bound only keeps a corrupted structure from spinning
+        if (v == PENDING && ls.blk >= (1u << 14)) v = STOP_VERTEX;
+        if (v != PENDING) ls.pending = false;
+    }
+    if (lcnt) {
+        // the list position's word follows the group draw
+        const uint32_t w = HEAD == 2 ? w2 : w3;
+        uint32_t i;
+        if (HEAD > 3 || lean_reject(w, lcnt, i)) {
+            odd = true;
+        } else {
+            const uint32_t e = pool[(uint64_t)linfo * LIST_UNIT_WORDS + i];
+            v = pool[ls.adj + 2ull * e];
+        }
+    }
+    if (odd) v = odd_step<MODE>(hdr, pool, u, seed, id, s, blk0, (uint32_t)TERM, rule);
+    return v;
+}
+
+// ---------------------------------------------------------------------------
+// Cooperative stepping: G lanes per walk.  With fewer walks than the chip has
+// lanes a query's time is its longest chain of steps, and a step's time the
+// loads it waits for one after the other.  The lanes of a walk therefore take
+// apart what one lane does in turn: lane i computes block i of the step's stream
+// (ahead, while the step before it waits for memory), so 4 G words are there at
+// once; all member infos are loaded beside the header; and the first six or so
+// dense attempts are loaded together.  A step waits for the header and one edge
+// word (dense), or the header, a list entry and an edge word (listed).
+// ---------------------------------------------------------------------------
+template <int G>
+struct CoopWords {
+    uint32_t w[4];  // this lane's block (block `sub` of the step's stream)
+    uint32_t z[4];  // block 0
+};
+template <int G>
+__device__ __forceinline__ CoopWords<G> coop_words(uint64_t seed, uint64_t id, uint32_t s, uint32_t sub) {
+    CoopWords<G> c;
+    philox_uniform((uint32_t)id, (uint32_t)(id >> 32), s, sub, seed, c.w[0], c.w[1], c.w[2], c.w[3]);
+    const int l0 = (int)(lane_id() - sub);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c.z[i] = __shfl(c.w[i], l0, 64);
+    return c;
+}
+
+// One whole step at u of the walk that the G lanes share (act, u, id and s are
+// the same in them; every lane of the wave calls).  Returns the next vertex or
+// STOP_VERTEX in all G lanes.  mid() runs while the header loads are in flight.
+template <int G, int MODE, int TERM, class Mid>
+__device__ __forceinline__ uint32_t coop_step(const uint32_t* __restrict__ hdr, const uint32_t* __restrict__ pool,
+                                              bool act, uint32_t u, uint64_t seed, uint64_t id, uint32_t s,
+                                              const CoopWords<G>& cw, GroupRule rule, Mid mid) {
+    constexpr uint32_t HEAD = TERM + (MODE == 2 ? 3 : 2);
+    constexpr int IPL = G >= 32 ? 1 : 32 / G;  // infos per lane
+    const uint32_t lane = lane_id(), sub = lane & (G - 1);
+    const int l0 = (int)(lane - sub);
+    uint32_t v = STOP_VERTEX;
+    HotLine q;
+    uint32_t inf[IPL];
+    if (act) {
+        q = load_hot(hdr, u);
+        const uint32_t* I = hdr_ref(hdr, u).cold + (H_INFO - HDR_HOT);
+#pragma unroll
+        for (int i = 0; i < IPL; ++i) inf[i] = G <= 32 || sub < 32 ? I[sub * IPL + i] : 0u;
+    }
+    mid();
+    LeanPick p;
+    p.kind = LK_DONE;
+    p.v = STOP_VERTEX;
+    if (act)
+        p = TERM ? lean_pick<MODE>(hdr, u, q, cw.z[1], cw.z[2], cw.z[3], rule)
+                 : lean_pick<MODE>(hdr, u, q, cw.z[0], cw.z[1], cw.z[2], rule);
+    // the list position's word, the list's offset
+    uint32_t li = 0, info = 0;
+    bool list = act && p.kind == LK_LIST;
+    if (__ballot(list)) {
+        const uint32_t w = HEAD < 4 ? cw.z[HEAD & 3] : __shfl(cw.w[0], l0 + 1, 64);
+#pragma unroll
+        for (int i = 0; i < IPL; ++i) {
+            const uint32_t y = __shfl(inf[i], l0 + (int)(p.sel / IPL), 64);
+            if (i == 0 || (p.sel % IPL) == (uint32_t)i) info = y;
+        }
+        if (list && lean_reject(w, p.csel, li)) {
+            p.kind = LK_ODD;
+            list = false;
+        }
+    }
+    uint32_t le = 0;
+    if (list) le = pool[(uint64_t)info * LIST_UNIT_WORDS + li];
+    bool dense = act && p.kind == LK_DENSE;
+    uint64_t dm = __ballot(dense);
+    if (dm) {
+        const uint64_t* __restrict__ edges = reinterpret_cast<const uint64_t*>(pool + p.adj);
+#pragma unroll
+        for (int round = 0; round < (G > 2 ? 2 : 1); ++round) {
+            const bool mine = dense && (round == 0 ? sub < 2 : sub >= 2);
+            uint64_t e[4];
+            bool ok[4];
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                uint32_t i;
+                ok[a] = mine && !lean_reject(cw.w[a], p.d, i) && (sub > 0 || (uint32_t)a >= HEAD);
+                e[a] = 0;
+                if (ok[a]) e[a] = edges[i];
+            }
+            uint32_t got = PENDING;
+#pragma unroll
+            for (int a = 3; a >= 0; --a)
+                if (ok[a] && ((e[a] >> (32 + p.sel)) & 1ull)) got = (uint32_t)e[a];
+            const uint64_t am = (__ballot(got != PENDING) >> l0) & (G == 64 ? ~0ull : (1ull << (G & 63)) - 1);
+            const int src = am ? l0 + __ffsll((long long)am) - 1 : (int)lane;
+            const uint32_t y = __shfl(got, src, 64);
+            if (dense && am) {
+                v = y;
+                dense = false;
+            }
+            if (__ballot(dense) == 0) break;
+        }
+        if (dense) p.kind = LK_ODD;  // all the words at hand were rejected: again, one by one
+    }
+    if (list) v = pool[p.adj + 2ull * le];
+    if (act && p.kind == LK_DONE) v = p.v;
+    if (act && p.kind == LK_ODD) v = odd_step<MODE>(hdr, pool, u, seed, id, s, 0u, (uint32_t)TERM, rule);
+    return v;
 }
 
 // Walk ids are handed to waves in chunks: one atomic per QCHUNK ids, and the

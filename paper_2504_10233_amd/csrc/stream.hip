@@ -537,7 +537,7 @@ __device__ bool st_delete(SV& s, uint32_t v, GroupRule rule, uint32_t* __restric
 __device__ __forceinline__ void st_load(SV& s, uint32_t u, const uint32_t* __restrict__ hdr) {
     const uint32_t lane = lane_id();
     s.u = u;
-    const uint32_t* h = hdr + (size_t)u * HDR_WORDS;
+    const HdrCRef h = hdr_ref(hdr, u);
     s.d = h[H_DEG]; s.cap = h[H_ACAP]; s.nseq = h[H_NSEQ];
     s.adj = hdr_adj(h);
     s.W = ((uint64_t)h[H_WHI] << 32) | h[H_WLO];
@@ -559,7 +559,7 @@ __device__ void st_store(const SV& s, bool ok, uint32_t stop, uint32_t e, const 
         if (lane == 0) atomicOr(errw, ERR_OOM);
         for (uint32_t q = stop + lane; q < e; q += 64) left[sv[q]] = 1u;  // this source's records not applied
     }
-    uint32_t* h = hdr + (size_t)s.u * HDR_WORDS;
+    const HdrRef h = hdr_ref(hdr, s.u);
     const bool ne = lane < 32 && s.c > 0;
     const uint32_t nmask = (uint32_t)(__ballot(ne) & 0xFFFFFFFFull);
     const uint32_t t = lane < 32 ? group_type(s.c, s.d, rule) : GT_EMPTY;
@@ -568,8 +568,8 @@ __device__ void st_store(const SV& s, bool ok, uint32_t stop, uint32_t e, const 
     const uint32_t onemask = (uint32_t)(__ballot(onek) & 0xFFFFFFFFull);
     const uint32_t nhi = mask_hi(nmask);
     if (lane < 32) {
-        if (lane <= nhi)
-            h[H_CNT + (nhi - lane)] = onek ? (uint32_t)reinterpret_cast<const uint64_t*>(pool + s.adj)[s.info] : s.c;
+        const uint32_t slot = onek ? (uint32_t)reinterpret_cast<const uint64_t*>(pool + s.adj)[s.info] : s.c;
+        hdr_put_slots(h, lane, nhi, slot);
         h[H_INFO + lane] = (type_listed(t) || t == GT_ONE) ? s.info : 0u;
     }
     const uint32_t lg = (lane < 32 && type_listed(t)) ? (31 - __clz(s.lcap)) : 0u;
@@ -620,7 +620,7 @@ __global__ void __launch_bounds__(TB) k_st_apply(const uint32_t* __restrict__ er
         const uint32_t b = seg_start[sg];
         const uint32_t e = sg + 1 < nseg ? seg_start[sg + 1] : (uint32_t)m;
         const uint32_t u = sk[b];
-        if (hdr[(size_t)u * HDR_WORDS + H_DEG] >= ST_BIG_D) {
+        if (hdr_ref(hdr, u)[H_DEG] >= ST_BIG_D) {
             if (lane == 0) big[atomicAdd(nbig, 1ull)] = (uint32_t)sg;
             continue;
         }

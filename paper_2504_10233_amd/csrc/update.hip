@@ -165,7 +165,7 @@ __global__ void k_flat_size(unsigned long long* __restrict__ uc, uint64_t rmax, 
         if (t < T) {
             const uint32_t nd = te[t] - tdl[t];
             const uint32_t ni = tdl[t] - ts[t];
-            const uint32_t* h = hdr + (size_t)tv[t] * HDR_WORDS;
+            const HdrCRef h = hdr_ref(hdr, tv[t]);
             const uint32_t d = h[H_DEG];
             dold[t] = d;
             vacap[t] = h[H_ACAP];
@@ -871,7 +871,7 @@ __device__ void load_state(VState& s, uint32_t t, const uint32_t* __restrict__ t
                            const uint32_t* __restrict__ pool, const uint32_t* __restrict__ wv, GroupRule rule) {
     const uint32_t lane = lane_id();
     s.u = tv[t];
-    const uint32_t* h = hdr + (size_t)s.u * HDR_WORDS;
+    const HdrCRef h = hdr_ref(hdr, s.u);
     s.d = h[H_DEG]; s.cap = h[H_ACAP]; s.nseq = h[H_NSEQ]; s.mask = h[H_MASK];
     s.adj = hdr_adj(h);
     s.ts = ts[t]; s.ni = tdl[t] - ts[t]; s.nd = te[t] - tdl[t];
@@ -1629,7 +1629,7 @@ __device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, uint64_t abase0, co
     }
 
     // ---- header: the inter-group sampling space of the vertex
-    uint32_t* h = A.hdr + (size_t)s.u * HDR_WORDS;
+    const HdrRef h = hdr_ref(A.hdr, s.u);
     const bool ne = lane < 32 && s.cn > 0;
     const uint64_t wsum = fb ? s.W : wave_sum(ne ? ((uint64_t)s.cn << lane) : 0ull);
     const uint32_t nmask = (uint32_t)(__ballot(ne) & 0xFFFFFFFFull);
@@ -1642,7 +1642,7 @@ __device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, uint64_t abase0, co
     const uint32_t onemask = (uint32_t)(__ballot(onek) & 0xFFFFFFFFull);
     const uint32_t nhi = mask_hi(nmask);
     if (lane < 32) {
-        if (lane <= nhi) h[H_CNT + (nhi - lane)] = slot;
+        hdr_put_slots(h, lane, nhi, slot);
         uint32_t inf = 0;
         if (type_listed(s.tnew)) inf = newinfo;
         else if (s.tnew == GT_ONE) inf = member;
@@ -1915,7 +1915,7 @@ __global__ void __launch_bounds__(256) k_big_pass(const unsigned long long* __re
                 const uint64_t b = __ballot(hit);
                 if (b) { first = q0 + (uint32_t)(__ffsll((long long)b) - 1); break; }
             }
-            if (lane == 0 && first != NF) atomicMin(hdr + (size_t)bi.u * HDR_WORDS + H_INFO + bi.k, first);
+            if (lane == 0 && first != NF) atomicMin(&hdr_ref(hdr, bi.u)[H_INFO + bi.k], first);
         } else {
             const uint32_t* Lold = pool + bi.a;
             uint32_t* Lnew = pool + bi.b;
@@ -2002,9 +2002,9 @@ __global__ void __launch_bounds__(256) k_big_one_dst(const unsigned long long* _
          it += (uint64_t)gridDim.x * blockDim.x) {
         const BigItem& bi = bc.items[it];
         if (bi.kind != BK_ONE) continue;
-        uint32_t* h = hdr + (size_t)bi.u * HDR_WORDS;
+        const HdrRef h = hdr_ref(hdr, bi.u);
         const uint32_t member = h[H_INFO + bi.k];
-        if (member < bi.n) h[H_CNT + (mask_hi(h[H_MASK]) - bi.k)] = pool[bi.a + 2ull * member];
+        if (member < bi.n) h.slot(mask_hi(h[H_MASK]) - bi.k) = pool[bi.a + 2ull * member];
     }
 }
 

@@ -23,49 +23,10 @@ constexpr int TB = 256;
 constexpr uint32_t VPAD = 0xFFFFFFFFu;
 
 // ---------------------------------------------------------------------------
-// Attempt-interleaved stepping.  A step is split into "begin" (header, group
-// choice; one-element and listed groups finish here) and "attempt" (one dense
-// rejection try).  In every loop iteration a lane either begins a step and
-// makes its first attempt, or makes one more attempt, so the lanes of a wave do
-// not wait for the lane with the longest rejection run.
+// Attempt-interleaved stepping (lane_advance, step.h).  In every loop iteration a
+// lane either begins a step and makes its first attempts, or makes more attempts,
+// so the lanes of a wave do not wait for the lane with the longest rejection run.
 // ---------------------------------------------------------------------------
-struct StepState {
-    RandStream rs;
-    uint64_t adj;
-    uint32_t d, sel, tries;
-    bool pending;
-    bool wave;  // a dense group of a vertex of degree >= the wave threshold: the wave serves it
-};
-
-template <int MODE>
-__device__ __forceinline__ uint32_t step_begin(const uint32_t* __restrict__ hdr, const uint32_t* __restrict__ pool,
-                                               uint32_t u, StepState& ss, GroupRule rule, uint32_t wave_deg = 0) {
-    GroupPick g;
-    if (!pick_group<MODE>(hdr, u, ss.rs, rule, g)) return STOP_VERTEX;
-    if (MODE == 1 && g.sel < 0)
-        return decimal_pick(hdr + (size_t)u * HDR_WORDS, pool, g.adj, g.d, g.slot0, g.onem, rule, ss.rs);
-    if (g.sel < 0) return STOP_VERTEX;  // only on an inconsistent header
-    if ((g.onem >> g.sel) & 1u) return g.raw;  // one-element group: the step ends in the header
-    const uint32_t t = group_type(g.csel, g.d, rule);
-    if (t == GT_DENSE) {
-        ss.adj = g.adj; ss.d = g.d; ss.sel = (uint32_t)g.sel; ss.tries = 0; ss.pending = true;
-        ss.wave = wave_deg != 0 && g.d >= wave_deg;
-        return PENDING;
-    }
-    const uint32_t info = hdr[(size_t)u * HDR_WORDS + H_INFO + g.sel];
-    const uint32_t i = pool[(uint64_t)info * LIST_UNIT_WORDS + rs_below32(ss.rs, g.csel)];
-    return pool[g.adj + 2ull * i];
-}
-
-template <int SPEC>
-__device__ __forceinline__ uint32_t step_attempt(const uint32_t* __restrict__ pool, StepState& ss) {
-    const uint32_t v = dense_round<SPEC>(reinterpret_cast<const uint64_t*>(pool + ss.adj), ss.d, ss.sel, ss.rs);
-    if (v != PENDING) { ss.pending = false; return v; }
-    // bounded only against a corrupted structure (acceptance is above alpha % per try)
-    ss.tries += SPEC;
-    if (ss.tries >= (1u << 16)) { ss.pending = false; return STOP_VERTEX; }
-    return PENDING;
-}
 
 // ---------------------------------------------------------------------------
 // Wave-per-vertex dense rejection.  The lanes whose step selected a dense group
@@ -82,7 +43,8 @@ __device__ __forceinline__ uint32_t step_attempt(const uint32_t* __restrict__ po
 constexpr int WAVE_ROUND = 8;
 constexpr uint32_t DENSE_MAX_ATTEMPTS = 1u << 16;
 
-__device__ __forceinline__ uint32_t wave_dense_serve(const uint32_t* __restrict__ pool, const StepState& ss,
+__device__ __forceinline__ uint32_t wave_dense_serve(const uint32_t* __restrict__ pool, const LaneStep& ls,
+                                                     uint64_t seed, uint64_t id, uint32_t step, uint32_t left,
                                                      bool want) {
     uint64_t m = __ballot(want);
     if (!m) return PENDING;
@@ -91,14 +53,14 @@ __device__ __forceinline__ uint32_t wave_dense_serve(const uint32_t* __restrict_
     while (m) {
         const int ld = __ffsll((long long)m) - 1;
         m &= m - 1;
-        const uint64_t adj = ((uint64_t)__shfl((uint32_t)(ss.adj >> 32), ld, 64) << 32) |
-                             __shfl((uint32_t)ss.adj, ld, 64);
-        const uint32_t d = __shfl(ss.d, ld, 64), sel = __shfl(ss.sel, ld, 64);
-        const uint32_t k0 = __shfl(ss.rs.k0, ld, 64), k1 = __shfl(ss.rs.k1, ld, 64);
-        const uint32_t w0 = __shfl(ss.rs.w0, ld, 64), w1 = __shfl(ss.rs.w1, ld, 64);
-        const uint32_t stp = __shfl(ss.rs.step, ld, 64);
+        const uint64_t adj = ((uint64_t)__shfl((uint32_t)(ls.adj >> 32), ld, 64) << 32) |
+                             __shfl((uint32_t)ls.adj, ld, 64);
+        const uint32_t d = __shfl(ls.d, ld, 64), sel = __shfl(ls.sel, ld, 64);
+        const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+        const uint32_t w0 = __shfl((uint32_t)id, ld, 64), w1 = __shfl((uint32_t)(id >> 32), ld, 64);
+        const uint32_t stp = __shfl(step, ld, 64);
         // position of the next word of the served stream
-        uint64_t pos = (uint64_t)__shfl(ss.rs.blk, ld, 64) * 4u - __shfl(ss.rs.left, ld, 64);
+        uint64_t pos = (uint64_t)__shfl(ls.blk, ld, 64) * 4u - __shfl(left, ld, 64);
         const uint64_t* __restrict__ edges = reinterpret_cast<const uint64_t*>(pool + adj);
         const uint32_t zone = (0u - d) % d;
         uint32_t tries = 0, found = PENDING;
@@ -138,6 +100,22 @@ __device__ __forceinline__ uint32_t wave_dense_serve(const uint32_t* __restrict_
 }
 
 // ------------------------------------------------------------------ DeepWalk
+// The rest of a path after a vertex without out-edges, entries [from, L] of row,
+// for every lane with `stop` set: written by the whole wave, 64 entries per
+// store.  By its own lane alone it is a store of one word per entry (on an R-MAT
+// graph more than half of all path entries are such padding).  Every lane of the
+// wave must call this.
+__device__ __forceinline__ void wave_pad_row(bool stop, uint32_t* row, uint32_t from, uint32_t L) {
+    const uint32_t lane = lane_id();
+    for (uint64_t m = __ballot(stop); m; m &= m - 1) {
+        const int l = __ffsll((long long)m) - 1;
+        const uint64_t r = ((uint64_t)__shfl((uint32_t)((uint64_t)row >> 32), l, 64) << 32) |
+                           __shfl((uint32_t)(uint64_t)row, l, 64);
+        uint32_t* p = reinterpret_cast<uint32_t*>(r);
+        for (uint32_t x = __shfl(from, l, 64) + lane; x <= L; x += 64) p[x] = STOP_VERTEX;
+    }
+}
+
 template <int SPEC, int MODE>
 __global__ void __launch_bounds__(TB) k_deepwalk_persistent(const uint32_t* __restrict__ hdr,
                                                             const uint32_t* __restrict__ pool, uint32_t n,
@@ -197,8 +175,8 @@ __global__ void __launch_bounds__(TB) k_deepwalk_persistent(const uint32_t* __re
     wave_add_u64(ctl + 1, steps);
 }
 
-template <int SPEC, int MODE>
-__global__ void __launch_bounds__(TB) k_deepwalk_interleaved(const uint32_t* __restrict__ hdr,
+template <int SPEC, int MODE, bool WAVE>
+__global__ void __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(MODE == 1 ? 5 : 7, 8))) k_deepwalk_interleaved(const uint32_t* __restrict__ hdr,
                                                              const uint32_t* __restrict__ pool, uint32_t n,
                                                              uint64_t nw, const uint32_t* __restrict__ starts,
                                                              uint64_t base, uint32_t L, uint64_t seed,
@@ -208,9 +186,8 @@ __global__ void __launch_bounds__(TB) k_deepwalk_interleaved(const uint32_t* __r
                                                              uint32_t wave_deg) {
     WaveQueue wq;
     wq.chunk = qchunk;
-    StepState ss;
-    ss.pending = false;
-    ss.wave = false;
+    LaneStep ls;
+    ls.pending = false;
     uint64_t j = NO_WALK, steps = 0;
     uint32_t u = 0, s = 0;
     uint32_t* row = nullptr;
@@ -226,7 +203,7 @@ __global__ void __launch_bounds__(TB) k_deepwalk_interleaved(const uint32_t* __r
                 row = paths + j * (uint64_t)(L + 1);
                 u = starts[j];
                 s = 0;
-                ss.pending = false;
+                ls.pending = false;
                 row[0] = u;
                 if (u >= n) {
                     atomicOr(err, ERR_RANGE);
@@ -238,27 +215,69 @@ __global__ void __launch_bounds__(TB) k_deepwalk_interleaved(const uint32_t* __r
             }
         }
         if (__ballot(!done) == 0) break;
-        uint32_t v = PENDING;
-        if (j != NO_WALK && !ss.pending) {
-            rs_init(ss.rs, seed, base + j, s);
-            v = step_begin<MODE>(hdr, pool, u, ss, rule, wave_deg);
+        bool ended, serve;
+        uint32_t left;
+        uint32_t v = lane_advance<SPEC, MODE, 0, WAVE>(hdr, pool, j != NO_WALK, u, ls, seed, base + j, s, 0u, 0u, rule,
+                                                 wave_deg, ended, serve, left, [] {});
+        if (WAVE) {
+            const uint32_t wv = wave_dense_serve(pool, ls, seed, base + j, s, left, serve);
+            if (serve) { v = wv; ls.pending = false; }
         }
-        if (j != NO_WALK && ss.pending && !ss.wave) v = step_attempt<SPEC>(pool, ss);
-        {
-            const bool served = j != NO_WALK && ss.pending && ss.wave;
-            const uint32_t wv = wave_dense_serve(pool, ss, served);
-            if (served) { v = wv; ss.pending = false; }
+        const bool stop = j != NO_WALK && v == STOP_VERTEX;
+        wave_pad_row(stop, row, s + 1, L);
+        if (stop) {
+            j = NO_WALK;
+        } else if (j != NO_WALK && v != PENDING) {
+            row[s + 1] = v;
+            u = v;
+            ++s;
+            ++steps;
+            if (s == L) j = NO_WALK;
         }
-        if (j != NO_WALK && v != PENDING) {
+    }
+    wave_add_u64(ctl + 1, steps);
+}
+
+// G lanes per walk (coop_step): for queries of fewer walks than the chip holds lanes.  The
+// grid covers all walks, one group of G lanes each, so there is no queue.  ctl[1] = transitions.
+template <int G, int MODE>
+__global__ void __launch_bounds__(TB) k_deepwalk_coop(const uint32_t* __restrict__ hdr,
+                                                      const uint32_t* __restrict__ pool, uint32_t n, uint64_t nw,
+                                                      const uint32_t* __restrict__ starts, uint64_t base, uint32_t L,
+                                                      uint64_t seed, uint32_t* __restrict__ paths, GroupRule rule,
+                                                      unsigned long long* __restrict__ ctl,
+                                                      uint32_t* __restrict__ err) {
+    const uint64_t j = ((uint64_t)blockIdx.x * TB + threadIdx.x) / G;
+    const uint32_t sub = threadIdx.x & (G - 1);
+    bool act = j < nw;
+    uint32_t u = 0;
+    uint32_t* row = paths + j * (uint64_t)(L + 1);
+    if (act) {
+        u = starts[j];
+        if (sub == 0) row[0] = u;
+        if (u >= n) {
+            if (sub == 0) atomicOr(err, ERR_RANGE);
+            for (uint32_t x = 1 + sub; x <= L; x += G) row[x] = STOP_VERTEX;
+            act = false;
+        }
+    }
+    CoopWords<G> cw = coop_words<G>(seed, base + j, 0u, sub);
+    uint64_t steps = 0;
+    for (uint32_t s = 0; s < L && __ballot(act); ++s) {
+        CoopWords<G> nx;
+        const uint32_t v = coop_step<G, MODE, 0>(hdr, pool, act, u, seed, base + j, s, cw, rule,
+                                                 [&] { nx = coop_words<G>(seed, base + j, s + 1, sub); });
+        cw = nx;
+        if (act) {
             if (v == STOP_VERTEX) {
-                for (uint32_t x = s + 1; x <= L; ++x) row[x] = STOP_VERTEX;
-                j = NO_WALK;
+                for (uint32_t x = s + 1 + sub; x <= L; x += G) row[x] = STOP_VERTEX;
+                act = false;
             } else {
-                row[s + 1] = v;
+                if (sub == 0) {
+                    row[s + 1] = v;
+                    ++steps;
+                }
                 u = v;
-                ++s;
-                ++steps;
-                if (s == L) j = NO_WALK;
             }
         }
     }
@@ -507,8 +526,8 @@ __global__ void __launch_bounds__(TB) k_ppr_persistent(const uint32_t* __restric
     wave_add_u64(ctl + 1, steps);
 }
 
-template <int SPEC, int MODE>
-__global__ void __launch_bounds__(TB) k_ppr_interleaved(const uint32_t* __restrict__ hdr, const uint32_t* __restrict__ pool,
+template <int SPEC, int MODE, bool WAVE>
+__global__ void __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(MODE == 1 ? 5 : 5, 8))) k_ppr_interleaved(const uint32_t* __restrict__ hdr, const uint32_t* __restrict__ pool,
                                                         uint32_t n, uint32_t nsrc, const uint32_t* __restrict__ sources,
                                                         uint32_t R, uint64_t seed, uint64_t base, GroupRule rule,
                                                         const uint64_t* __restrict__ seg,
@@ -519,9 +538,8 @@ __global__ void __launch_bounds__(TB) k_ppr_interleaved(const uint32_t* __restri
     const uint64_t nw = (uint64_t)nsrc * R;
     WaveQueue wq;
     wq.chunk = qchunk;
-    StepState ss;
-    ss.pending = false;
-    ss.wave = false;
+    LaneStep ls;
+    ls.pending = false;
     uint64_t j = NO_WALK, pos = 0, lim = 0, steps = 0;
     uint32_t u = 0, s = 0;
     bool done = false;
@@ -537,7 +555,7 @@ __global__ void __launch_bounds__(TB) k_ppr_interleaved(const uint32_t* __restri
                 s = 0;
                 pos = seg[j];
                 lim = pos + len[j];
-                ss.pending = false;
+                ls.pending = false;
                 if (u >= n) {
                     atomicOr(err, ERR_RANGE);
                     for (uint64_t x = pos; x < lim; ++x) vis[x] = VPAD;
@@ -549,17 +567,14 @@ __global__ void __launch_bounds__(TB) k_ppr_interleaved(const uint32_t* __restri
             }
         }
         if (__ballot(!done) == 0) break;
-        uint32_t v = PENDING;
-        if (j != NO_WALK && !ss.pending) {
-            rs_init(ss.rs, seed, base + j, s);
-            rs_next32(ss.rs);  // the termination word, known to be >= thr here
-            v = step_begin<MODE>(hdr, pool, u, ss, rule, wave_deg);
-        }
-        if (j != NO_WALK && ss.pending && !ss.wave) v = step_attempt<SPEC>(pool, ss);
-        {
-            const bool served = j != NO_WALK && ss.pending && ss.wave;
-            const uint32_t wv = wave_dense_serve(pool, ss, served);
-            if (served) { v = wv; ss.pending = false; }
+        bool ended, serve;
+        uint32_t left;
+        // the termination word of every step of a segment is known to be >= the threshold
+        uint32_t v = lane_advance<SPEC, MODE, 1, WAVE>(hdr, pool, j != NO_WALK, u, ls, seed, base + j, s, 0u, 0u, rule,
+                                                 wave_deg, ended, serve, left, [] {});
+        if (WAVE) {
+            const uint32_t wv = wave_dense_serve(pool, ls, seed, base + j, s, left, serve);
+            if (serve) { v = wv; ls.pending = false; }
         }
         if (j != NO_WALK && v != PENDING) {
             if (v == STOP_VERTEX) {
@@ -578,16 +593,86 @@ __global__ void __launch_bounds__(TB) k_ppr_interleaved(const uint32_t* __restri
 }
 
 // Binned PPR: the visits of source q go to bin q (capacity C, fill count
-// cnt[q]) in any order, since only their multiset matters.  The termination
-// word is tested in the walk itself (no length pass), and in every iteration
-// the lanes of a wave that produced a visit append it to their source's bin
-// with one atomic per source present in the wave; lanes of a wave hold
-// consecutive walk ids, so the appends of an iteration land as one or two
-// contiguous runs instead of one partial-sector store per lane.  A bin that
+// cnt[q BIN_STRIDE]) in any order, since only their multiset matters.  The
+// termination word is tested in the walk itself (no length pass).  A bin that
 // would overflow sets a flag and the query is rerun with exact per-walk
 // segments.  ctl[0] queue head, ctl[1] transitions, ctl[2] overflow.
-template <int SPEC, int MODE>
-__global__ void __launch_bounds__(TB) k_ppr_binned(const uint32_t* __restrict__ hdr, const uint32_t* __restrict__ pool,
+//
+// A wave collects its visits in LDS and moves them to the bins a few hundred at
+// a time: one atomic per source among them (a wave's walks have consecutive ids,
+// so mostly one or two sources) and whole runs of stores.  An atomic per
+// iteration instead made all waves of a source queue for its count, at about
+// 10 ns an atomic on one line; the counts of different sources lie in different
+// lines for the same reason.
+constexpr uint32_t BIN_STRIDE = 16;
+constexpr uint32_t STAGE = 256;  // visits a wave holds
+
+struct BinStage {
+    uint32_t *v, *q;  // the wave's LDS
+    uint32_t n;       // visits held (the same in every lane)
+    // every lane of the wave calls; at most 64 more visits than before
+    __device__ __forceinline__ void add(bool emit, uint32_t vertex, uint32_t src) {
+        const uint64_t m = __ballot(emit);
+        if (emit) {
+            const uint32_t p = n + (uint32_t)__popcll(m & lanemask_lt());
+            v[p] = vertex;
+            q[p] = src;
+        }
+        n += (uint32_t)__popcll(m);
+    }
+    __device__ __forceinline__ bool full() const { return n > STAGE - 64; }
+    __device__ __forceinline__ void flush(uint32_t* __restrict__ cnt, uint32_t* __restrict__ vis, uint64_t C,
+                                          bool& ovf) {
+        constexpr int K = STAGE / 64;
+        const uint32_t lane = lane_id();
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the wave's own LDS writes
+        uint32_t ev[K], eq[K];
+        uint64_t left[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const uint32_t p = k * 64 + lane;
+            ev[k] = p < n ? v[p] : 0u;
+            eq[k] = p < n ? q[p] : 0u;
+            left[k] = __ballot(p < n);
+        }
+        for (;;) {
+            uint32_t qq = 0;
+            bool any = false;
+#pragma unroll
+            for (int k = K - 1; k >= 0; --k)
+                if (left[k]) {
+                    qq = __shfl(eq[k], __ffsll((long long)left[k]) - 1, 64);
+                    any = true;
+                }
+            if (!any) break;
+            uint64_t same[K];
+            uint32_t tot = 0;
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                same[k] = __ballot(eq[k] == qq) & left[k];
+                tot += (uint32_t)__popcll(same[k]);
+            }
+            uint32_t b = 0;
+            if (lane == 0) b = atomicAdd(cnt + (uint64_t)qq * BIN_STRIDE, tot);
+            uint64_t pos = __shfl(b, 0, 64);
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                if ((same[k] >> lane) & 1ull) {
+                    const uint64_t p = pos + (uint64_t)__popcll(same[k] & lanemask_lt());
+                    if (p < C) vis[(uint64_t)qq * C + p] = ev[k];
+                    else ovf = true;
+                }
+                pos += (uint64_t)__popcll(same[k]);
+                left[k] &= ~same[k];
+            }
+        }
+        n = 0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+};
+
+template <int SPEC, int MODE, bool WAVE>
+__global__ void __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(MODE == 1 ? 5 : 5, 8))) k_ppr_binned(const uint32_t* __restrict__ hdr, const uint32_t* __restrict__ pool,
                                                    uint32_t n, uint32_t nsrc, const uint32_t* __restrict__ sources,
                                                    uint32_t R, uint64_t seed, uint64_t base, uint32_t thr,
                                                    uint32_t cap, GroupRule rule, uint64_t C,
@@ -598,9 +683,10 @@ __global__ void __launch_bounds__(TB) k_ppr_binned(const uint32_t* __restrict__ 
     const uint32_t lane = lane_id();
     WaveQueue wq;
     wq.chunk = qchunk;
-    StepState ss;
-    ss.pending = false;
-    ss.wave = false;
+    LaneStep ls;
+    ls.pending = false;
+    __shared__ uint32_t sv[TB / 64][STAGE], sq[TB / 64][STAGE];
+    BinStage stage{sv[threadIdx.x >> 6], sq[threadIdx.x >> 6], 0u};
     uint64_t j = NO_WALK, steps = 0;
     uint32_t u = 0, s = 0, q = 0;
     bool done = false, ovf = false;
@@ -608,77 +694,100 @@ __global__ void __launch_bounds__(TB) k_ppr_binned(const uint32_t* __restrict__ 
         const bool need = !done && j == NO_WALK;
         const uint64_t got = wave_take_chunked(need, wq, ctl);
         bool emit = false;
-        uint32_t ev = 0;
         if (need) {
             if (got >= nw) {
                 done = true;
             } else {
                 j = got;
-                q = (uint32_t)(j / R);
+                q = nw >> 32 ? (uint32_t)(j / R) : (uint32_t)j / R;
                 u = sources[q];
                 s = 0;
-                ss.pending = false;
+                ls.pending = false;
                 if (u >= n) {
                     atomicOr(err, ERR_RANGE);
                     j = NO_WALK;
                 } else {
                     emit = true;  // the start counts as a visit; the walk steps from the next iteration
-                    ev = u;
                 }
             }
         }
         if (__ballot(!done) == 0) break;
-        uint32_t v = PENDING;
-        if (j != NO_WALK && !emit) {
-            if (!ss.pending) {
-                // before every transition: the cap, then the termination word
-                if (s >= cap) {
-                    j = NO_WALK;
-                } else {
-                    rs_init(ss.rs, seed, base + j, s);
-                    if (rs_next32(ss.rs) < thr) j = NO_WALK;
-                    else v = step_begin<MODE>(hdr, pool, u, ss, rule, wave_deg);
-                }
-            }
-            if (j != NO_WALK && ss.pending && !ss.wave) v = step_attempt<SPEC>(pool, ss);
+        // before every transition: the cap, then the termination word
+        bool act = j != NO_WALK && !emit;
+        if (act && !ls.pending && s >= cap) {
+            act = false;
+            j = NO_WALK;
         }
-        {
-            const bool served = j != NO_WALK && !emit && ss.pending && ss.wave;
-            const uint32_t wv = wave_dense_serve(pool, ss, served);
-            if (served) { v = wv; ss.pending = false; }
+        bool ended, serve;
+        uint32_t left;
+        uint32_t v = lane_advance<SPEC, MODE, 1, WAVE>(hdr, pool, act, u, ls, seed, base + j, s, 0u, thr, rule, wave_deg,
+                                                 ended, serve, left, [] {});
+        if (WAVE) {
+            const uint32_t wv = wave_dense_serve(pool, ls, seed, base + j, s, left, serve);
+            if (serve) { v = wv; ls.pending = false; }
         }
-        if (j != NO_WALK && !emit) {
-            if (v != PENDING) {
-                if (v == STOP_VERTEX) {
-                    j = NO_WALK;
-                } else {
-                    emit = true;
-                    ev = v;
-                    u = v;
-                    ++s;
-                    ++steps;
-                }
+        if (act && (ended || v != PENDING)) {
+            if (ended || v == STOP_VERTEX) {
+                j = NO_WALK;
+            } else {
+                emit = true;
+                u = v;
+                ++s;
+                ++steps;
             }
         }
-        // append this iteration's visits: one atomic per source present in the wave
-        uint64_t m = __ballot(emit);
-        while (m) {
-            const int leader = __ffsll((long long)m) - 1;
-            const uint32_t qq = __shfl(q, leader, 64);
-            const uint64_t same = __ballot(emit && q == qq) & m;
-            uint32_t b = 0;
-            if ((int)lane == leader) b = atomicAdd(cnt + qq, (uint32_t)__popcll(same));
-            b = __shfl(b, leader, 64);
-            if ((same >> lane) & 1ull) {
-                const uint64_t pos = (uint64_t)b + __popcll(same & lanemask_lt());
-                if (pos < C) vis[(uint64_t)qq * C + pos] = ev;
-                else ovf = true;
-            }
-            m &= ~same;
-        }
+        stage.add(emit, u, q);
+        if (stage.full()) stage.flush(cnt, vis, C, ovf);
     }
+    stage.flush(cnt, vis, C, ovf);
     wave_add_u64(ctl + 1, steps);
     if (__ballot(ovf) && lane == 0) atomicOr(ctl + 2, 1ull);
+}
+
+// G lanes per walk (coop_step), one group of lanes for every walk of the query.
+template <int G, int MODE>
+__global__ void __launch_bounds__(TB) k_ppr_coop(const uint32_t* __restrict__ hdr, const uint32_t* __restrict__ pool,
+                                                 uint32_t n, uint32_t nsrc, const uint32_t* __restrict__ sources,
+                                                 uint32_t R, uint64_t seed, uint64_t base, uint32_t thr, uint32_t cap,
+                                                 GroupRule rule, uint64_t C, uint32_t* __restrict__ cnt,
+                                                 uint32_t* __restrict__ vis, unsigned long long* __restrict__ ctl,
+                                                 uint32_t* __restrict__ err) {
+    __shared__ uint32_t sv[TB / 64][STAGE], sq[TB / 64][STAGE];
+    BinStage stage{sv[threadIdx.x >> 6], sq[threadIdx.x >> 6], 0u};
+    const uint64_t nw = (uint64_t)nsrc * R;
+    const uint64_t j = ((uint64_t)blockIdx.x * TB + threadIdx.x) / G;
+    const uint32_t sub = threadIdx.x & (G - 1);
+    bool act = j < nw, ovf = false;
+    uint32_t u = 0, q = 0;
+    if (act) {
+        q = (uint32_t)(j / R);
+        u = sources[q];
+        if (u >= n) {
+            if (sub == 0) atomicOr(err, ERR_RANGE);
+            act = false;
+        }
+    }
+    stage.add(act && sub == 0, u, q);
+    CoopWords<G> cw = coop_words<G>(seed, base + j, 0u, sub);
+    uint64_t steps = 0;
+    for (uint32_t s = 0; s < cap; ++s) {
+        if (cw.z[0] < thr) act = false;
+        if (__ballot(act) == 0) break;
+        CoopWords<G> nx;
+        const uint32_t v = coop_step<G, MODE, 1>(hdr, pool, act, u, seed, base + j, s, cw, rule,
+                                                 [&] { nx = coop_words<G>(seed, base + j, s + 1, sub); });
+        cw = nx;
+        if (act) {
+            if (v == STOP_VERTEX) act = false;
+            else u = v;
+        }
+        steps += act && sub == 0 ? 1u : 0u;
+        stage.add(act && sub == 0, u, q);
+        if (stage.full()) stage.flush(cnt, vis, C, ovf);
+    }
+    stage.flush(cnt, vis, C, ovf);
+    wave_add_u64(ctl + 1, steps);
+    if (__ballot(ovf) && lane_id() == 0) atomicOr(ctl + 2, 1ull);
 }
 
 // Per-step PPR: active walks are (walk id, current vertex) pairs compacted into
@@ -895,7 +1004,7 @@ __global__ void __launch_bounds__(HSB) k_hist_seg(uint32_t* __restrict__ vis, ui
     const uint32_t q = blockIdx.x, t = threadIdx.x, lane = lane_id(), wave = t >> 6;
     // the source's range: its bin, or the segments of its R walks
     const uint64_t S0 = C ? (uint64_t)q * C : seg[(uint64_t)q * R];
-    const uint64_t S1 = C ? S0 + bin_cnt[q] : ((q + 1 < nsrc) ? seg[(uint64_t)(q + 1) * R] : total);
+    const uint64_t S1 = C ? S0 + bin_cnt[(uint64_t)q * BIN_STRIDE] : ((q + 1 < nsrc) ? seg[(uint64_t)(q + 1) * R] : total);
     if (S1 - S0 > N) {
         if (t == 0) { ucount[q] = 0; atomicOr(too_big, 1ull); }
         return;
@@ -1003,7 +1112,7 @@ __global__ void __launch_bounds__(256) k_bin_max(const uint32_t* __restrict__ cn
     __shared__ unsigned long long m[4];
     unsigned long long best = 0;
     for (uint64_t q = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; q < nsrc; q += (uint64_t)gridDim.x * blockDim.x)
-        best = std::max<unsigned long long>(best, cnt[q]);
+        best = std::max<unsigned long long>(best, cnt[q * BIN_STRIDE]);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) best = std::max<unsigned long long>(best, __shfl_xor(best, o));
     if (lane_id() == 0) m[threadIdx.x >> 6] = best;
@@ -1040,9 +1149,11 @@ inline uint32_t grid_for(uint64_t n) {
 }
 
 int resident_grid(const void* kernel, uint32_t blocks_per_cu) {
+    static std::mutex mu;
     static int cus = 0;
-    static const void* seen[32] = {};
-    static int occ[32] = {};
+    static const void* seen[64] = {};
+    static int occ[64] = {};
+    std::lock_guard<std::mutex> lk(mu);
     if (!cus) {
         int dev = 0;
         hipGetDevice(&dev);
@@ -1050,16 +1161,42 @@ int resident_grid(const void* kernel, uint32_t blocks_per_cu) {
         if (cus <= 0) cus = 256;
     }
     int per_cu = 0;
-    for (int i = 0; i < 32; ++i)
+    for (int i = 0; i < 64; ++i)
         if (seen[i] == kernel) per_cu = occ[i];
     if (!per_cu) {
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, TB, 0) != hipSuccess || per_cu <= 0)
             per_cu = 4;
-        for (int i = 0; i < 32; ++i)
+        for (int i = 0; i < 64; ++i)
             if (!seen[i]) { seen[i] = kernel; occ[i] = per_cu; break; }
     }
     if (blocks_per_cu && (int)blocks_per_cu < per_cu) per_cu = (int)blocks_per_cu;
     return cus * per_cu;
+}
+
+// Walk ids per queue atomic of a persistent launch: the tuned chunk, but no more than leaves every
+// wave of the grid two chunks, down to one id per lane.  (A query of 50,000 walks has 784 waves: with
+// chunks of 256 ids three of four would find the queue empty, and the fourth walk four times in turn.)
+uint32_t chunk_for(const bingo_graph* g, uint64_t nw, uint32_t grid) {
+    const uint64_t per_wave = nw / std::max<uint64_t>((uint64_t)grid * (TB / 64), 1);
+    uint32_t c = g->queue_chunk;
+    while (c > 64 && 1ull * c > per_wave) c >>= 1;
+    return c;
+}
+
+// Lanes per walk for a query of nw walks (1: a lane each, by the persistent kernels), with
+// `resident_blocks` of them on the chip at once.  Measured on R-MAT 18 / 22, walks of 40 steps with
+// 1, 8, 16 and 64 lanes, in us: 1000 walks 155 / 111 / 108 / 102; 4000 walks 214 / 139 / 135 / 144;
+// 16,000 walks 215 / 157 / 173 / 285; 32,000 walks 185 / 165 / 227 / 337; 65,000 walks 200 / 257.
+// Personalized PageRank, 10 x 1000 walks: 145 / 98 / 93 / 175; 60 x 1000: 219 / 171 / 262.  So the wide
+// forms end where they fill a quarter of the lanes; the last one, of 8, where it fills them all
+// (walks that end at random leave lanes idle) or five eighths (walks of one length).
+int coop_lanes(const bingo_graph* g, uint64_t nw, int resident_blocks, bool ends_early) {
+    if (!g->walk_variant || g->wave_degree) return 1;
+    const uint64_t lanes = (uint64_t)resident_blocks * TB;
+    if (nw * 64 <= lanes / 4) return 64;
+    if (nw * 16 <= lanes / 4) return 16;
+    if (nw * 8 <= (ends_early ? lanes : lanes / 8 * 5)) return 8;
+    return 1;
 }
 
 int bits_for(uint64_t v) {
@@ -1082,15 +1219,24 @@ void deepwalk_kernels(bingo_graph* g, uint64_t nw, const uint32_t* starts, uint6
             hipLaunchKernelGGL((k_deepwalk_step<SPEC, MODE>), dim3(grid), dim3(TB), 0, st, g->hdr, g->pool, g->n, nw, starts, base,
                                L, s, seed, paths, g->rule, ctl, g->d_err);
     } else {
-        const void* kern = g->walk_variant ? (const void*)k_deepwalk_interleaved<SPEC, MODE> : (const void*)k_deepwalk_persistent<SPEC, MODE>;
+        auto* lanes = g->wave_degree ? k_deepwalk_interleaved<SPEC, MODE, true> : k_deepwalk_interleaved<SPEC, MODE, false>;
+        const void* kern = g->walk_variant ? (const void*)lanes : (const void*)k_deepwalk_persistent<SPEC, MODE>;
         const int rg = resident_grid(kern, g->blocks_per_cu);
         const uint32_t grid = (uint32_t)std::min<uint64_t>((uint64_t)rg, (nw + TB - 1) / TB);
-        if (g->walk_variant)
-            hipLaunchKernelGGL((k_deepwalk_interleaved<SPEC, MODE>), dim3(grid), dim3(TB), 0, st, g->hdr, g->pool, g->n, nw, starts,
-                               base, L, seed, paths, g->rule, ctl, g->d_err, g->queue_chunk, g->wave_degree);
+#define BINGO_COOP(G_)                                                                                              \
+    hipLaunchKernelGGL((k_deepwalk_coop<G_, MODE>), dim3((uint32_t)((nw * G_ + TB - 1) / TB)), dim3(TB), 0, st, g->hdr, \
+                       g->pool, g->n, nw, starts, base, L, seed, paths, g->rule, ctl, g->d_err)
+        const int G = coop_lanes(g, nw, rg, false);
+        if (G == 64) BINGO_COOP(64);
+        else if (G == 16) BINGO_COOP(16);
+        else if (G == 8) BINGO_COOP(8);
+#undef BINGO_COOP
+        else if (g->walk_variant)
+            hipLaunchKernelGGL(lanes, dim3(grid), dim3(TB), 0, st, g->hdr, g->pool, g->n, nw, starts,
+                               base, L, seed, paths, g->rule, ctl, g->d_err, chunk_for(g, nw, grid), g->wave_degree);
         else
             hipLaunchKernelGGL((k_deepwalk_persistent<SPEC, MODE>), dim3(grid), dim3(TB), 0, st, g->hdr, g->pool, g->n, nw, starts,
-                               base, L, seed, paths, g->rule, ctl, g->d_err, g->queue_chunk);
+                               base, L, seed, paths, g->rule, ctl, g->d_err, chunk_for(g, nw, grid));
     }
 }
 
@@ -1112,15 +1258,16 @@ void ppr_kernels(bingo_graph* g, uint32_t nsrc, const uint32_t* sources, uint32_
                                in_slot ? vA : vB, ctl, in_slot, vis);
         }
     } else {
-        const void* kern = g->walk_variant ? (const void*)k_ppr_interleaved<SPEC, MODE> : (const void*)k_ppr_persistent<SPEC, MODE>;
+        auto* lanes = g->wave_degree ? k_ppr_interleaved<SPEC, MODE, true> : k_ppr_interleaved<SPEC, MODE, false>;
+        const void* kern = g->walk_variant ? (const void*)lanes : (const void*)k_ppr_persistent<SPEC, MODE>;
         const int rg = resident_grid(kern, g->blocks_per_cu);
         const uint32_t grid = std::max<uint32_t>((uint32_t)std::min<uint64_t>((uint64_t)rg, (nw + TB - 1) / TB), 1);
         if (g->walk_variant)
-            hipLaunchKernelGGL((k_ppr_interleaved<SPEC, MODE>), dim3(grid), dim3(TB), 0, st, g->hdr, g->pool, g->n, nsrc, sources, R,
-                               seed, base, g->rule, seg, len, ctl, vis, g->d_err, g->queue_chunk, g->wave_degree);
+            hipLaunchKernelGGL(lanes, dim3(grid), dim3(TB), 0, st, g->hdr, g->pool, g->n, nsrc, sources, R,
+                               seed, base, g->rule, seg, len, ctl, vis, g->d_err, chunk_for(g, nw, grid), g->wave_degree);
         else
             hipLaunchKernelGGL((k_ppr_persistent<SPEC, MODE>), dim3(grid), dim3(TB), 0, st, g->hdr, g->pool, g->n, nsrc, sources, R,
-                               seed, base, g->rule, seg, len, ctl, vis, g->d_err, g->queue_chunk);
+                               seed, base, g->rule, seg, len, ctl, vis, g->d_err, chunk_for(g, nw, grid));
     }
 }
 
@@ -1133,7 +1280,7 @@ void deepwalk_batch_kernel(bingo_graph* g, const WalkQueryTable& tab, uint32_t n
     const int rg = resident_grid((const void*)k_deepwalk_batch<SPEC, MODE>, g->blocks_per_cu);
     const uint32_t grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)rg, (nw + TB - 1) / TB));
     hipLaunchKernelGGL((k_deepwalk_batch<SPEC, MODE>), dim3(grid), dim3(TB), 0, st, g->hdr, g->pool, g->n, tab, nq, nw,
-                       g->rule, ctl, g->d_err, g->queue_chunk);
+                       g->rule, ctl, g->d_err, chunk_for(g, nw, grid));
 }
 }  // namespace
 
@@ -1350,27 +1497,36 @@ static int run_ppr_binned(bingo_graph* g, uint32_t nsrc, const uint32_t* sources
     const uint64_t worst = (uint64_t)R * ((uint64_t)cap + 1);
     const uint64_t C = std::min<uint64_t>(worst, (uint64_t)(1.25 * mean * R) + 1024);
     const uint64_t cells = (uint64_t)nsrc * C;
-    char* ws = (char*)ws_get(g, 2 * al(cells * 4) + 2 * al((uint64_t)nsrc * 4) + scan_temp_bytes(nsrc) + 1024);
+    char* ws = (char*)ws_get(g, 2 * al(cells * 4) + al((uint64_t)nsrc * BIN_STRIDE * 4) + al((uint64_t)nsrc * 4) + scan_temp_bytes(nsrc) + 1024);
     if (!ws) return BINGO_E_OOM;
     uint32_t* vis = (uint32_t*)ws;      ws += al(cells * 4);
     uint32_t* hcnt = (uint32_t*)ws;     ws += al(cells * 4);
-    uint32_t* bin_cnt = (uint32_t*)ws;  ws += al((uint64_t)nsrc * 4);
+    uint32_t* bin_cnt = (uint32_t*)ws;  ws += al((uint64_t)nsrc * BIN_STRIDE * 4);
     uint32_t* ucount = (uint32_t*)ws;   ws += al((uint64_t)nsrc * 4);
     void* tmp = ws;
     unsigned long long* ctl = g->d_ctl + 2;  // [0] queue, [1] transitions, [2] overflow, [3] largest bin
     HIPCHK(hipMemsetAsync(ctl, 0, 32, st));
     HIPCHK(hipMemsetAsync(g->d_err, 0, 4, st));
     phase_mark(g, st, true);
-    HIPCHK(hipMemsetAsync(bin_cnt, 0, (uint64_t)nsrc * 4, st));
+    HIPCHK(hipMemsetAsync(bin_cnt, 0, (uint64_t)nsrc * BIN_STRIDE * 4, st));
     phase_mark(g, st, false);
+    const uint64_t nw = (uint64_t)nsrc * R;
+#define BINGO_COOP(G_, M_)                                                                                            \
+    hipLaunchKernelGGL((k_ppr_coop<G_, M_>), dim3((uint32_t)((nw * G_ + TB - 1) / TB)), dim3(TB), 0, st, g->hdr, g->pool, \
+                       g->n, nsrc, sources, R, seed, base, thr, cap, g->rule, C, bin_cnt, vis, ctl, g->d_err)
 #define BINGO_BINNED(S_, M_)                                                                                          \
     do {                                                                                                           \
-        const int rg = resident_grid((const void*)k_ppr_binned<S_, M_>, g->blocks_per_cu);                             \
-        const uint64_t nw = (uint64_t)nsrc * R;                                                                    \
+        auto* lanes = g->wave_degree ? k_ppr_binned<S_, M_, true> : k_ppr_binned<S_, M_, false>;                     \
+        const int rg = resident_grid((const void*)lanes, g->blocks_per_cu);                                         \
         const uint32_t grid = std::max<uint32_t>((uint32_t)std::min<uint64_t>((uint64_t)rg, (nw + TB - 1) / TB), 1); \
-        hipLaunchKernelGGL((k_ppr_binned<S_, M_>), dim3(grid), dim3(TB), 0, st, g->hdr, g->pool, g->n, nsrc, sources, R, \
-                           seed, base, thr, cap, g->rule, C, bin_cnt, vis, ctl, g->d_err, g->queue_chunk,         \
-                           g->wave_degree);                                                                         \
+        const int G = coop_lanes(g, nw, rg, true);                                                                 \
+        if (G == 64) BINGO_COOP(64, M_);                                                                           \
+        else if (G == 16) BINGO_COOP(16, M_);                                                                      \
+        else if (G == 8) BINGO_COOP(8, M_);                                                                        \
+        else                                                                                                       \
+            hipLaunchKernelGGL(lanes, dim3(grid), dim3(TB), 0, st, g->hdr, g->pool, g->n, nsrc,                        \
+                               sources, R, seed, base, thr, cap, g->rule, C, bin_cnt, vis, ctl, g->d_err,          \
+                               chunk_for(g, nw, grid), g->wave_degree);                                            \
     } while (0)
     switch (g->dense_spec) {
         case 1: if (walk_mode(g) == 1) BINGO_BINNED(1, 1); else if (walk_mode(g) == 2) BINGO_BINNED(1, 2); else BINGO_BINNED(1, 0); break;
@@ -1378,6 +1534,7 @@ static int run_ppr_binned(bingo_graph* g, uint32_t nsrc, const uint32_t* sources
         default: if (walk_mode(g) == 1) BINGO_BINNED(2, 1); else if (walk_mode(g) == 2) BINGO_BINNED(2, 2); else BINGO_BINNED(2, 0); break;
     }
 #undef BINGO_BINNED
+#undef BINGO_COOP
     phase_mark(g, st, false);
     hipLaunchKernelGGL(k_bin_max, dim3((uint32_t)std::min<uint64_t>((nsrc + 255) / 256, 1024)), dim3(256), 0, st,
                        bin_cnt, nsrc, ctl + 3);

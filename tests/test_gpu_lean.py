@@ -1,0 +1,72 @@
+"""The lean walk kernels (one Philox block per lane and iteration; several lanes per walk for small
+queries) against the per-step form, which draws word by word, and the oracle."""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _graph(mode, **kw):
+    """A graph whose vertices hold groups of every type and of ranks past the ten and twenty highest:
+    a few heavy edges over many light ones, degrees 0 to 3000."""
+    import torch
+    from paper_2504_10233_amd import Graph, quantize_biases
+    n, m = 600, 30000
+    src = (synth.below(1, 1, m, n) * synth.below(1, 2, m, n)) // n
+    src[:3000] = 5
+    dst = synth.below(1, 3, m, n)
+    w = torch.where(synth.below(1, 4, m, 50) == 0, synth.weights_uniform(m, 1 << 20, 1 << 23, 2),
+                    synth.weights_zipf(m, 1.3, (1 << 18) - 1, 3))
+    if mode == "float":
+        bias = (w.double() + synth.uniform_f64(4, 1, m)).float().cuda()
+        return n, Graph(n, src, dst, quantize_biases(bias, 1.0, 8), frac_bits=8)
+    return n, Graph(n, src, dst, w, alias_table=mode == "alias", adaptive=mode != "plain")
+
+
+# one lane group each up to a few thousand walks (64, 16, then 8 lanes a walk), the persistent kernel above
+@pytest.mark.parametrize("mode", ["int", "plain", "float", "alias"])
+def test_walks_equal_the_per_step_form(mode):
+    import torch
+    from paper_2504_10233_amd import MODE_PER_STEP
+    n, g = _graph(mode)
+    for nw in (1, 3, 257, 1999, 2049, 7001, 8200, 30001, 70003):
+        starts = synth.below(9, nw, nw, n).to(torch.int32)
+        a, sa = g.walk(starts, 17, 77, base=nw)
+        b, sb = g.walk(starts, 17, 77, base=nw, mode=MODE_PER_STEP)
+        assert torch.equal(a, b) and int(sa) == int(sb), nw
+    g.close()
+
+
+@pytest.mark.parametrize("mode", ["int", "float", "alias"])
+@pytest.mark.parametrize("sources,per_source,stop", [(1, 1, 0.15), (3, 700, 0.15), (7, 1001, 0.02), (50, 999, 0.15),
+                                                     (300, 301, 0.15), (40, 40, 1.0)])
+def test_ppr_equals_the_per_step_form(mode, sources, per_source, stop):
+    import torch
+    from paper_2504_10233_amd import MODE_PER_STEP
+    n, g = _graph(mode)
+    src = synth.below(8, 1, sources, n).to(torch.int32)
+    thr = min(int(stop * 2**32), 2**32 - 1)
+    a = g.ppr(src, per_source, thr, 200, 5, base=1 << 33)
+    b = g.ppr(src, per_source, thr, 200, 5, base=1 << 33, mode=MODE_PER_STEP)
+    assert all(torch.equal(x, y) for x, y in zip(a[:3], b[:3])) and a[3] == b[3]
+    g.close()
+
+
+def test_a_vertex_past_the_32_bit_sums():
+    """2^21 + 5 edges: the sums of its groups take the 64-bit path."""
+    import torch
+    import oracle as O
+    from paper_2504_10233_amd import Graph
+    n, hub = 64, (1 << 21) + 5
+    src = torch.cat([torch.zeros(hub, dtype=torch.int64), synth.below(3, 1, 500, n)])
+    dst = torch.cat([synth.below(3, 2, hub, n), torch.zeros(500, dtype=torch.int64)])
+    w = synth.weights_uniform(src.numel(), 1, 1 << 24, 4)
+    g = Graph(n, src, dst, w)
+    og = O.Graph(n, src.numpy(), dst.numpy(), w.numpy())
+    starts = torch.zeros(300, dtype=torch.int32)
+    p, _ = g.walk(starts, 12, 3)
+    q, _ = og.deepwalk(starts.numpy(), 12, seed=3)
+    assert np.array_equal(p.cpu().numpy().view(np.uint32), q)
+    g.close()
