@@ -85,27 +85,46 @@ __device__ __forceinline__ bool has_edge(const uint32_t* __restrict__ nidx, cons
     return l < H && nidx[l] == v;
 }
 
-// One lane per walk from the chunked device queue (as the DeepWalk kernel); in
-// every iteration a lane makes one proposal, so a rejected lane retries while
-// the others move on.  ctl[0] queue head, ctl[1] transitions, ctl[2] proposals.
-template <int SPEC, int MODE>
-__global__ void __launch_bounds__(TB) k_node2vec(const uint32_t* __restrict__ hdr, const uint32_t* __restrict__ pool,
-                                                 const uint32_t* __restrict__ nidx,
-                                                 const uint64_t* __restrict__ noff, uint32_t n, uint64_t nw,
-                                                 const uint32_t* __restrict__ starts, uint64_t base, uint32_t L,
-                                                 uint64_t seed, uint32_t thr0, uint32_t thr1, uint32_t thr2,
-                                                 uint32_t full, uint32_t* __restrict__ paths, GroupRule rule,
-                                                 unsigned long long* __restrict__ ctl, uint32_t* __restrict__ err,
-                                                 uint32_t qchunk) {
+// G lanes per walk, each with a proposal of its own: lane i of the walk's lanes
+// makes proposal t + i of the current step (the proposals of a step draw from
+// disjoint blocks of its stream, so they are independent), and the first accepted
+// one in proposal order is the step's, as if they had been made in turn.  G = 1
+// takes walks from the chunked device queue; G > 1 is for queries of fewer walks
+// than the chip has lanes, where a step's time is its chain of rejected proposals
+// (3.8 of them with p = 0.5, q = 2), and has a group of lanes for every walk.
+//
+// The acceptance word is drawn before the edge test: a word below both classes'
+// thresholds accepts, one above both rejects, and only between them does it matter
+// whether w -> v is an edge (a quarter of the proposals with p = 0.5, q = 2; the
+// test is a chain of about eight dependent reads).
+// ctl[0] queue head, ctl[1] transitions, ctl[2] proposals.
+template <int SPEC, int MODE, int G>
+__global__ void __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(5, 8)))
+k_node2vec(const uint32_t* __restrict__ hdr, const uint32_t* __restrict__ pool, const uint32_t* __restrict__ nidx,
+           const uint64_t* __restrict__ noff, uint32_t n, uint64_t nw, const uint32_t* __restrict__ starts,
+           uint64_t base, uint32_t L, uint64_t seed, uint32_t thr0, uint32_t thr1, uint32_t thr2, uint32_t full,
+           uint32_t* __restrict__ paths, GroupRule rule, unsigned long long* __restrict__ ctl,
+           uint32_t* __restrict__ err, uint32_t qchunk) {
+    const uint32_t sub = threadIdx.x & (G - 1);
+    const int l0 = (int)(lane_id() - sub);
+    constexpr uint32_t ALL = (1u << G) - 1u;  // G <= 16
     WaveQueue wq;
     wq.chunk = qchunk;
+    LaneStep ls;
+    ls.pending = false;
     uint64_t j = NO_WALK, steps = 0, props = 0;
-    uint32_t u = 0, prev = STOP_VERTEX, s = 0, t = 0;
+    uint32_t u = 0, prev = STOP_VERTEX, s = 0, t = 0, v = STOP_VERTEX;
     uint32_t* row = nullptr;
-    bool done = false;
+    bool done = false, fin = false, acc = false;  // fin: this lane's proposal is decided
     for (;;) {
         const bool need = !done && j == NO_WALK;
-        const uint64_t got = wave_take_chunked(need, wq, ctl);
+        uint64_t got;
+        if constexpr (G == 1) {
+            got = wave_take_chunked(need, wq, ctl);
+        } else {
+            got = row ? NO_WALK : ((uint64_t)blockIdx.x * TB + threadIdx.x) / G;  // one walk each
+        }
+        bool pad = false;
         if (need) {
             if (got >= nw) {
                 done = true;
@@ -116,10 +135,11 @@ __global__ void __launch_bounds__(TB) k_node2vec(const uint32_t* __restrict__ hd
                 prev = STOP_VERTEX;
                 s = 0;
                 t = 0;
-                row[0] = u;
+                fin = ls.pending = false;
+                if (sub == 0) row[0] = u;
                 if (u >= n) {
-                    atomicOr(err, ERR_RANGE);
-                    for (uint32_t x = 1; x <= L; ++x) row[x] = STOP_VERTEX;
+                    if (sub == 0) atomicOr(err, ERR_RANGE);
+                    pad = true;
                     j = NO_WALK;
                 } else if (L == 0) {
                     j = NO_WALK;
@@ -127,41 +147,70 @@ __global__ void __launch_bounds__(TB) k_node2vec(const uint32_t* __restrict__ hd
             }
         }
         if (__ballot(!done) == 0) break;
-        if (j != NO_WALK) {
-            const uint64_t id = base + j;
-            RandStream rs;
-            rs_init_blk(rs, seed, id, s, t << 16);
-            uint32_t v = walk_step_body<SPEC, MODE>(hdr, pool, u, rs, rule);
-            ++props;
-            bool accept = true;
+        const bool on = j != NO_WALK;
+        const uint64_t id = base + j;
+        bool ended, serve;
+        uint32_t left;
+        const uint32_t x = lane_advance<SPEC, MODE, 0, false>(hdr, pool, on && !fin, u, ls, seed, id, s,
+                                                              (t + sub) << 16, 0u, rule, 0u, ended, serve, left, [] {});
+        if (on && !fin && x != PENDING) {
+            fin = acc = true;
+            v = x;
             if (v != STOP_VERTEX && prev != STOP_VERTEX) {
-                const uint32_t c = v == prev ? 0u : (has_edge(nidx, noff, prev, v) ? 1u : 2u);
-                if (!((full >> c) & 1u)) {
+                const bool f1 = (full >> 1) & 1u, f2 = (full >> 2) & 1u;
+                const bool back = v == prev;
+                if (back ? !(full & 1u) : !(f1 && f2)) {
                     uint32_t a0, a1, a2, a3;
-                    philox_block((uint32_t)id, (uint32_t)(id >> 32), s, (t << 16) | ACCEPT_BLOCK, (uint32_t)seed,
-                                 (uint32_t)(seed >> 32), a0, a1, a2, a3);
-                    accept = a0 < (c == 0 ? thr0 : (c == 1 ? thr1 : thr2));
+                    philox_uniform((uint32_t)id, (uint32_t)(id >> 32), s, ((t + sub) << 16) | ACCEPT_BLOCK, seed, a0,
+                                   a1, a2, a3);
+                    if (back) {
+                        acc = a0 < thr0;
+                    } else {
+                        const bool near = f1 || a0 < thr1, far = f2 || a0 < thr2;
+                        acc = near == far ? near : (has_edge(nidx, noff, prev, v) ? near : far);
+                    }
                 }
             }
-            if (!accept && ++t >= MAX_PROPOSALS) {
-                v = STOP_VERTEX;
-                accept = true;
+        }
+        // the first accepted proposal, once every earlier one is known to be rejected
+        uint32_t first = acc ? 0u : 1u;
+        bool won = fin && acc, lost = fin && !acc;
+        uint32_t y = v;
+        if constexpr (G > 1) {
+            const uint32_t fm = (uint32_t)(__ballot(fin) >> l0) & ALL, am = (uint32_t)(__ballot(fin && acc) >> l0) & ALL;
+            first = am ? (uint32_t)__ffs(am) - 1 : 0u;
+            won = am && ((~fm) & ((1u << first) - 1u)) == 0u;
+            lost = !am && fm == ALL;
+            y = __shfl(v, l0 + (int)first, 64);
+        }
+        if (on && (won || lost)) {
+            if (sub == 0) props += won ? first + 1 : (uint32_t)G;
+            fin = acc = ls.pending = false;
+            if (lost) {
+                t += G;
+                if (t >= MAX_PROPOSALS) {
+                    y = STOP_VERTEX;
+                    won = true;
+                }
             }
-            if (accept) {
-                if (v == STOP_VERTEX) {
-                    for (uint32_t x = s + 1; x <= L; ++x) row[x] = STOP_VERTEX;
+            if (won) {
+                if (y == STOP_VERTEX) {
+                    pad = true;
                     j = NO_WALK;
                 } else {
-                    row[s + 1] = v;
+                    if (sub == 0) {
+                        row[s + 1] = y;
+                        ++steps;
+                    }
                     prev = u;
-                    u = v;
+                    u = y;
                     ++s;
                     t = 0;
-                    ++steps;
                     if (s == L) j = NO_WALK;
                 }
             }
         }
+        wave_pad_row(pad && sub == 0, row, s + 1, L);
     }
     wave_add_u64(ctl + 1, steps);
     wave_add_u64(ctl + 2, props);
@@ -218,14 +267,36 @@ int build_index(bingo_graph* g, hipStream_t st) {
     return BINGO_OK;
 }
 
+// Lanes per walk for nw walks: as many as the resident lanes allow, since a step then waits for one
+// round of proposals instead of several in turn.  R-MAT 20, walks of 40 steps, p = 0.5, q = 2, with 1, 2,
+// 4, 8 and 16 lanes, in us: 1000 walks 1613 / 899 / 673 / 552 / 483; 32,000 walks 1720 / 1105 / 827 / 715 /
+// 1051; 100,000 walks 1970 / 1353 / 1562; 200,000 walks 2259 / 2423 (327,680 lanes are resident).  Where
+// the commonest proposals, those without an edge from the previous vertex, are always accepted
+// (full, bit 2: q < 1), four lanes are enough: 32,000 walks with q = 0.5 532 / 498 / 529 / 571 / 907.
+int n2v_lanes(uint64_t nw, uint64_t lanes, uint32_t full) {
+    for (int G : {16, 8, 4, 2})
+        if (nw * (uint64_t)G <= lanes && (G <= 4 || !((full >> 2) & 1u))) return G;
+    return 1;
+}
+
 template <int SPEC, int MODE>
 void launch_n2v(bingo_graph* g, uint64_t nw, const uint32_t* starts, uint64_t base, uint32_t L, uint64_t seed,
                 const uint32_t thr[3], uint32_t full, uint32_t* paths, unsigned long long* ctl, hipStream_t st) {
-    const int rg = resident_blocks((const void*)k_node2vec<SPEC, MODE>);
-    const uint32_t grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)rg, (nw + TB - 1) / TB));
-    hipLaunchKernelGGL((k_node2vec<SPEC, MODE>), dim3(grid), dim3(TB), 0, st, g->hdr, g->pool, g->n2v_idx, g->n2v_off,
-                       g->n, nw, starts, base, L, seed, thr[0], thr[1], thr[2], full, paths, g->rule, ctl, g->d_err,
-                       g->queue_chunk);
+    const uint64_t lanes = (uint64_t)resident_blocks((const void*)k_node2vec<SPEC, MODE, 1>) * TB;
+    // chunks as small as leaves every wave some, down to an id per lane
+    uint32_t chunk = g->queue_chunk;
+    while (chunk > 64 && chunk > nw / std::max<uint64_t>(std::min(lanes, nw) / 64, 1)) chunk >>= 1;
+#define BINGO_N2V(S_, G_, BLOCKS_)                                                                                \
+    hipLaunchKernelGGL((k_node2vec<S_, MODE, G_>), dim3((uint32_t)std::max<uint64_t>(1, BLOCKS_)), dim3(TB), 0, st, \
+                       g->hdr, g->pool, g->n2v_idx, g->n2v_off, g->n, nw, starts, base, L, seed, thr[0], thr[1],  \
+                       thr[2], full, paths, g->rule, ctl, g->d_err, chunk)
+    const int G = n2v_lanes(nw, lanes, full);
+    if (G == 16) BINGO_N2V(2, 16, (nw * 16 + TB - 1) / TB);
+    else if (G == 8) BINGO_N2V(2, 8, (nw * 8 + TB - 1) / TB);
+    else if (G == 4) BINGO_N2V(2, 4, (nw * 4 + TB - 1) / TB);
+    else if (G == 2) BINGO_N2V(2, 2, (nw * 2 + TB - 1) / TB);
+    else BINGO_N2V(SPEC, 1, std::min<uint64_t>(lanes / TB, (nw + TB - 1) / TB));
+#undef BINGO_N2V
 }
 
 }  // namespace

@@ -696,6 +696,22 @@ __device__ __forceinline__ uint32_t coop_step(const uint32_t* __restrict__ hdr, 
     return v;
 }
 
+// The rest of a path after a vertex without out-edges, entries [from, L] of row,
+// for every lane with `stop` set: written by the whole wave, 64 entries per
+// store.  By its own lane alone it is a store of one word per entry (on an R-MAT
+// graph more than half of all path entries are such padding).  Every lane of the
+// wave must call this.
+__device__ __forceinline__ void wave_pad_row(bool stop, uint32_t* row, uint32_t from, uint32_t L) {
+    const uint32_t lane = lane_id();
+    for (uint64_t m = __ballot(stop); m; m &= m - 1) {
+        const int l = __ffsll((long long)m) - 1;
+        const uint64_t r = ((uint64_t)__shfl((uint32_t)((uint64_t)row >> 32), l, 64) << 32) |
+                           __shfl((uint32_t)(uint64_t)row, l, 64);
+        uint32_t* p = reinterpret_cast<uint32_t*>(r);
+        for (uint32_t x = __shfl(from, l, 64) + lane; x <= L; x += 64) p[x] = STOP_VERTEX;
+    }
+}
+
 // Walk ids are handed to waves in chunks: one atomic per QCHUNK ids, and the
 // lanes of a wave that need a walk take consecutive ids from the chunk.
 struct WaveQueue {

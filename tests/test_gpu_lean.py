@@ -70,3 +70,27 @@ def test_a_vertex_past_the_32_bit_sums():
     q, _ = og.deepwalk(starts.numpy(), 12, seed=3)
     assert np.array_equal(p.cpu().numpy().view(np.uint32), q)
     g.close()
+
+
+@pytest.mark.parametrize("p,q", [(0.5, 2.0), (4.0, 0.5), (1.0, 1.0), (0.25, 1.0)])
+def test_node2vec_lanes_per_walk(p, q):
+    """16, 8, 4, 2 lanes per walk and one: the first and last 600 walks of each size equal the oracle's."""
+    import torch
+    import oracle as O
+    from paper_2504_10233_amd import Graph
+    n, m = 500, 9000
+    src = (synth.below(1, 1, m, n) * synth.below(1, 2, m, n)) // n
+    dst = (synth.below(1, 3, m, n) * synth.below(1, 5, m, n)) // n
+    w = synth.weights_uniform(m, 1, 1 << 16, 2)
+    g = Graph(n, src, dst, w)
+    og = O.Graph(n, src.numpy(), dst.numpy(), w.numpy())
+    for nw in (1, 600, 20481, 41001, 90000, 170003, 340000):
+        starts = synth.below(9, 1, nw, n).to(torch.int32)
+        a, c = g.node2vec(starts, 9, 77, p, q, base=5)
+        k = min(nw, 600)
+        for lo in (0, nw - k):
+            b = og.node2vec(starts[lo:lo + k].numpy(), 9, 77, p, q, base=5 + lo)[0]
+            assert np.array_equal(a[lo:lo + k].cpu().numpy().view(np.uint32), b), (nw, lo)
+        if nw == 600:
+            assert c.tolist() == list(og.node2vec(starts.numpy(), 9, 77, p, q, base=5, with_proposals=True)[1:])
+    g.close()
