@@ -11,10 +11,6 @@ namespace {
 
 constexpr int WB = 256;  // block of 4 waves, one vertex per wave
 
-__device__ __forceinline__ uint32_t next_pow2(uint32_t x) {
-    return x <= 1 ? 1u : 1u << (32 - __clz(x - 1));
-}
-
 __global__ void k_validate(uint64_t m, uint32_t n, const uint32_t* __restrict__ src, const uint32_t* __restrict__ dst,
                            const uint32_t* __restrict__ w, uint32_t* __restrict__ err) {
     uint32_t bad = 0;
@@ -26,20 +22,6 @@ __global__ void k_validate(uint64_t m, uint32_t n, const uint32_t* __restrict__ 
     bad |= __shfl_xor(bad, 1); bad |= __shfl_xor(bad, 2); bad |= __shfl_xor(bad, 4);
     bad |= __shfl_xor(bad, 8); bad |= __shfl_xor(bad, 16); bad |= __shfl_xor(bad, 32);
     if (bad && lane_id() == 0) atomicOr(err, bad);
-}
-
-__global__ void k_iota(uint32_t* __restrict__ v, uint64_t m) {
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (uint64_t)gridDim.x * blockDim.x)
-        v[i] = (uint32_t)i;
-}
-
-__global__ void k_gather(uint64_t m, const uint32_t* __restrict__ ids, const uint32_t* __restrict__ dst,
-                         const uint32_t* __restrict__ w, uint32_t* __restrict__ cdst, uint32_t* __restrict__ cw) {
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t e = ids[i];
-        cdst[i] = dst[e];
-        cw[i] = w[e];
-    }
 }
 
 // start[u] = first position of key u in the sorted keys (u = 0..n).
@@ -54,49 +36,77 @@ __global__ void k_row_start(const uint32_t* __restrict__ keys, uint64_t m, uint3
     start[u] = (uint32_t)lo;
 }
 
-// Pass 1: counts, totals, one-element members, types; block sizes.
-__global__ void __launch_bounds__(WB) k_header(uint32_t n, const uint32_t* __restrict__ start,
-                                               const uint32_t* __restrict__ cw, uint32_t* __restrict__ hdr,
-                                               uint64_t* __restrict__ adjw, uint64_t* __restrict__ listw,
-                                               GroupRule rule) {
-    const uint32_t u = blockIdx.x * (WB / 64) + (threadIdx.x >> 6);
-    if (u >= n) return;
+// The construction takes a wave per vertex, and a block per vertex of more than
+// HUB_DEG edges (HB / 64 waves, each with a share of the edges): a wave alone spends
+// about 1.6 us per 64 edges waiting for its loads, so that an R-MAT graph's largest
+// hub (0.4 % of the edges of R-MAT 20) kept one wave busy for the whole time of the
+// pass (k_header 1.8 ms, k_fill 2.8 ms).  Every range keeps EB_ROWS rows of 64 edges
+// in flight.  hub[0]: the number of hubs, then their ids.
+constexpr uint32_t HUB_DEG = 2048;
+constexpr int HB = 1024;
+constexpr int HW = HB / 64;
+constexpr uint32_t EB_ROWS = 4;
+constexpr uint32_t HUB_GRID = 1024;
+
+// Group counts over the edges [lo, hi) of the vertex whose edges start at e: lane k < 32
+// gets group k's count and the last index with the bit, wraw this lane's share of the
+// weights.
+__device__ __forceinline__ void count_range(const uint64_t* __restrict__ e, uint32_t lo, uint32_t hi, uint32_t fbits,
+                                            uint32_t& cnt, uint32_t& last, uint64_t& wraw) {
     const uint32_t lane = lane_id();
-    const uint32_t b = start[u], d = start[u + 1] - b;
-    uint32_t cnt = 0, last = 0;  // lane k < 32 owns bit k
-    uint64_t wraw = 0;           // this lane's share of sum(weights)
-    for (uint32_t c0 = 0; c0 < d; c0 += 64) {
-        const uint32_t i = c0 + lane;
-        const uint32_t w = i < d ? cw[b + i] : 0u;
-        wraw += w;
-        const uint32_t wv = member_word(w, rule.fbits);
+    for (uint32_t c0 = lo; c0 < hi; c0 += 64 * EB_ROWS) {
+        uint32_t w[EB_ROWS];
 #pragma unroll
-        for (int k = 0; k < 32; ++k) {
-            const uint64_t bal = __ballot((wv >> k) & 1u);
-            if (lane == (uint32_t)k && bal) {
-                cnt += __popcll(bal);
-                last = c0 + 63 - __clzll(bal);
+        for (uint32_t r = 0; r < EB_ROWS; ++r) {
+            const uint32_t i = c0 + r * 64 + lane;
+            w[r] = i < hi ? (uint32_t)(e[i] >> 32) : 0u;
+        }
+#pragma unroll
+        for (uint32_t r = 0; r < EB_ROWS; ++r) {
+            if (c0 + r * 64 >= hi) break;
+            wraw += w[r];
+            const uint32_t wv = member_word(w[r], fbits);
+#pragma unroll
+            for (int k = 0; k < 32; ++k) {
+                const uint64_t bal = __ballot((wv >> k) & 1u);
+                if (lane == (uint32_t)k && bal) {
+                    cnt += (uint32_t)__popcll(bal);
+                    last = c0 + r * 64 + 63 - (uint32_t)__clzll(bal);
+                }
             }
         }
     }
-    const uint32_t t = lane < 32 ? group_type(cnt, d, rule) : GT_EMPTY;
-    // |S(u)|: the edges in at least one sparse group (Sec. 5.1)
-    const uint32_t smask = (uint32_t)(__ballot(t == GT_SPARSE) & 0xFFFFFFFFull);
-    uint32_t slen = 0;
-    for (uint32_t c0 = 0; smask && c0 < d; c0 += 64) {
-        const uint32_t i = c0 + lane;
-        const bool in = i < d && (member_word(cw[b + i], rule.fbits) & smask);
-        slen += __popcll(__ballot(in));
+}
+
+// Edges of [lo, hi) with a bit of `mask` (the same in every lane).
+__device__ __forceinline__ uint32_t count_masked(const uint64_t* __restrict__ e, uint32_t lo, uint32_t hi,
+                                                 uint32_t fbits, uint32_t mask) {
+    const uint32_t lane = lane_id();
+    uint32_t n = 0;
+    for (uint32_t c0 = lo; c0 < hi; c0 += 64 * EB_ROWS) {
+        uint32_t w[EB_ROWS];
+#pragma unroll
+        for (uint32_t r = 0; r < EB_ROWS; ++r) {
+            const uint32_t i = c0 + r * 64 + lane;
+            w[r] = i < hi ? (uint32_t)(e[i] >> 32) : 0u;
+        }
+#pragma unroll
+        for (uint32_t r = 0; r < EB_ROWS; ++r) n += (uint32_t)__popcll(__ballot((member_word(w[r], fbits) & mask) != 0u));
     }
+    return n;
+}
+
+// The header of vertex u from its counts (a wave): types, block sizes.
+__device__ __forceinline__ void write_header(uint32_t u, uint32_t d, uint32_t cnt, uint32_t last, uint64_t wsum,
+                                             uint32_t t, uint32_t slen, uint32_t* __restrict__ hdr,
+                                             uint64_t* __restrict__ adjw, uint64_t* __restrict__ listw) {
+    const uint32_t lane = lane_id();
     const uint32_t cap = adj_cap_for(d), scap = s_cap_for(slen);
-    // W = sum of the weights (= sum_k c_k 2^k for integer biases)
-    uint64_t wsum = wraw;
     // pool words: each listed group's block (list, then index), then the S(u) block
     uint64_t lw = type_listed(t) ? list_block_words(list_cap_for(cnt), index_cap_for(t, cap, scap)) : 0ull;
+    if (__ballot(lw != 0)) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        wsum += __shfl_xor(wsum, o);
-        lw += __shfl_xor(lw, o);
+        for (int o = 16; o > 0; o >>= 1) lw += __shfl_xor(lw, o);  // lanes 0..31
     }
     const uint64_t mask = __ballot(cnt > 0) & 0xFFFFFFFFull;
     const uint32_t hi = mask_hi((uint32_t)mask);
@@ -120,95 +130,233 @@ __global__ void __launch_bounds__(WB) k_header(uint32_t n, const uint32_t* __res
     }
 }
 
-// Pass 2: adjacency blocks (edge words and sequence numbers), listed-group
-// lists (ascending neighbor indices) with their indexes, and S(u).
-__global__ void __launch_bounds__(WB) k_fill(uint32_t n, const uint32_t* __restrict__ start,
-                                             const uint32_t* __restrict__ cdst, const uint32_t* __restrict__ cw,
-                                             const uint64_t* __restrict__ adj_off, const uint64_t* __restrict__ list_off,
-                                             uint64_t list_base, uint32_t* __restrict__ hdr, uint32_t* __restrict__ pool,
-                                             GroupRule rule) {
+// Pass 1: counts, totals, one-element members, types; block sizes.
+__global__ void __launch_bounds__(WB) k_header(uint32_t n, const uint32_t* __restrict__ start,
+                                               const uint64_t* __restrict__ ce, uint32_t* __restrict__ hdr,
+                                               uint64_t* __restrict__ adjw, uint64_t* __restrict__ listw,
+                                               uint32_t* __restrict__ hub, GroupRule rule) {
     const uint32_t u = blockIdx.x * (WB / 64) + (threadIdx.x >> 6);
     if (u >= n) return;
     const uint32_t lane = lane_id();
     const uint32_t b = start[u], d = start[u + 1] - b;
-    const HdrRef h = hdr_ref(hdr, u);
-    if (d == 0) {
-        if (lane == 0) { h[H_ADJLO] = 0; h[H_ADJHI] = 0; }
-        if (lane < 8) h[H_LCAPLOG + lane] = 0;
+    if (d > HUB_DEG) {
+        if (lane == 0) hub[1 + atomicAdd(hub, 1u)] = u;
         return;
     }
-    const uint32_t cap = h[H_ACAP];
-    const uint64_t ao = adj_off[u];
-    const uint32_t hi = mask_hi(h[H_MASK]);
-    if (lane == 0) { h[H_ADJLO] = (uint32_t)ao; h[H_ADJHI] = adjhi_word(ao, hi); }
-    uint64_t* edges = (uint64_t*)(pool + ao);
-    uint32_t* seqs = pool + ao + 2ull * cap;
+    if (d == 0) {  // the header stays cleared
+        if (lane == 0) { adjw[u] = 0; listw[u] = 0; }
+        return;
+    }
+    uint32_t cnt = 0, last = 0;  // lane k < 32 owns bit k
+    uint64_t wraw = 0;           // this lane's share of sum(weights)
+    count_range(ce + b, 0, d, rule.fbits, cnt, last, wraw);
+    const uint32_t t = lane < 32 ? group_type(cnt, d, rule) : GT_EMPTY;
+    // |S(u)|: the edges in at least one sparse group (Sec. 5.1)
+    const uint32_t smask = (uint32_t)(__ballot(t == GT_SPARSE) & 0xFFFFFFFFull);
+    const uint32_t slen = smask ? count_masked(ce + b, 0, d, rule.fbits, smask) : 0u;
+    // W = sum of the weights (= sum_k c_k 2^k for integer biases)
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) wraw += __shfl_xor(wraw, o);
+    write_header(u, d, cnt, last, wraw, t, slen, hdr, adjw, listw);
+}
+
+// Pass 1 of the hubs, a block each.
+__global__ void __launch_bounds__(HB) k_header_hub(const uint32_t* __restrict__ start, const uint64_t* __restrict__ ce,
+                                                   uint32_t* __restrict__ hdr, uint64_t* __restrict__ adjw,
+                                                   uint64_t* __restrict__ listw, const uint32_t* __restrict__ hub,
+                                                   GroupRule rule) {
+    __shared__ uint32_t s_cnt[HW][32], s_last[HW][32], s_len[HW], s_mask;
+    __shared__ uint64_t s_w[HW];
+    const uint32_t lane = lane_id(), wave = threadIdx.x >> 6, nh = hub[0];
+    for (uint32_t q = blockIdx.x; q < nh; q += gridDim.x) {
+        const uint32_t u = hub[1 + q], b = start[u], d = start[u + 1] - b;
+        const uint32_t share = ((d + HW - 1) / HW + 63) & ~63u;
+        const uint32_t lo = min(d, wave * share), hi = min(d, lo + share);
+        uint32_t cnt = 0, last = 0;
+        uint64_t wraw = 0;
+        count_range(ce + b, lo, hi, rule.fbits, cnt, last, wraw);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) wraw += __shfl_xor(wraw, o);
+        if (lane < 32) { s_cnt[wave][lane] = cnt; s_last[wave][lane] = last; }
+        if (lane == 0) s_w[wave] = wraw;
+        __syncthreads();
+        uint32_t t = GT_EMPTY;
+        if (wave == 0) {
+            cnt = last = 0;
+            wraw = 0;
+            for (int w = 0; w < HW; ++w) {
+                if (lane < 32 && s_cnt[w][lane]) {
+                    cnt += s_cnt[w][lane];
+                    last = s_last[w][lane];
+                }
+                wraw += s_w[w];
+            }
+            t = lane < 32 ? group_type(cnt, d, rule) : GT_EMPTY;
+            const uint32_t sm = (uint32_t)(__ballot(t == GT_SPARSE) & 0xFFFFFFFFull);
+            if (lane == 0) s_mask = sm;
+        }
+        __syncthreads();
+        const uint32_t smask = s_mask;
+        const uint32_t sl = smask ? count_masked(ce + b, lo, hi, rule.fbits, smask) : 0u;
+        if (lane == 0) s_len[wave] = sl;
+        __syncthreads();
+        if (wave == 0) {
+            uint32_t slen = 0;
+            for (int w = 0; w < HW; ++w) slen += s_len[w];
+            write_header(u, d, cnt, last, wraw, t, slen, hdr, adjw, listw);
+        }
+        __syncthreads();  // the next hub overwrites the shared arrays
+    }
+}
+
+// Where vertex u's blocks go, from its header (a wave; lane k < 32 holds group k).
+struct FillPlan {
+    uint64_t ao, my_block, sblk;
+    uint32_t cap, lcap, lmask, smask;
+};
+__device__ __forceinline__ FillPlan fill_plan(uint32_t u, uint32_t d, uint32_t b, const uint64_t* __restrict__ ce,
+                                              const uint64_t* __restrict__ adj_off,
+                                              const uint64_t* __restrict__ list_off, uint64_t list_base,
+                                              uint32_t* __restrict__ hdr, GroupRule rule, bool write) {
+    const uint32_t lane = lane_id();
+    const HdrRef h = hdr_ref(hdr, u);
+    FillPlan f;
+    f.cap = adj_cap_for(d);
+    f.ao = adj_off[u];
+    const uint32_t mask = h[H_MASK], hi = mask_hi(mask);
     // list blocks of the listed groups, in ascending k
-    const uint32_t cnt = lane < 32 ? hdr_slot(h, lane, hi) : 0u;
+    uint32_t cnt = 0;
+    if (lane < 32 && lane <= hi) cnt = h.slot(hi - lane);
     const uint32_t t = lane < 32 ? group_type(cnt, d, rule) : GT_EMPTY;
     const bool lst = type_listed(t);
-    const uint32_t lcap = lst ? list_cap_for(cnt) : 0u;
+    f.lcap = lst ? list_cap_for(cnt) : 0u;
     const uint32_t scap = h[H_SCAP];
     // lanes 0..31: the group blocks (list, then index); lane 32: the S(u) block
-    const uint64_t bw = lst ? list_block_words(lcap, index_cap_for(t, cap, scap)) : (lane == 32 ? scap : 0ull);
+    const uint64_t bw = lst ? list_block_words(f.lcap, index_cap_for(t, f.cap, scap)) : (lane == 32 ? scap : 0ull);
     uint64_t x = bw;  // inclusive scan over lanes
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
         const uint64_t y = __shfl_up(x, o, 64);
         if (lane >= (uint32_t)o) x += y;
     }
-    const uint64_t my_block = list_base + list_off[u] + (x - bw);  // words
-    if (lane < 32 && lst) h[H_INFO + lane] = (uint32_t)(my_block / LIST_UNIT_WORDS);
-    if (lane == 32) h[H_SBLK] = (uint32_t)(my_block / LIST_UNIT_WORDS);
-    const uint64_t sblk = __shfl(my_block, 32, 64);
-    const uint32_t smask = (uint32_t)(__ballot(t == GT_SPARSE) & 0xFFFFFFFFull);
+    f.my_block = list_base + list_off[u] + (x - bw);  // words
+    f.sblk = __shfl(f.my_block, 32, 64);
+    f.smask = (uint32_t)(__ballot(t == GT_SPARSE) & 0xFFFFFFFFull);
+    f.lmask = (uint32_t)(__ballot(lst) & 0xFFFFFFFFull);
+    if (!write) return f;
+    if (lane == 0) { h[H_ADJLO] = (uint32_t)f.ao; h[H_ADJHI] = adjhi_word(f.ao, hi); }
+    if (lane == 32) h[H_SBLK] = (uint32_t)(f.my_block / LIST_UNIT_WORDS);
     // one-element groups: the member's destination in the count slot
     const bool one = lane < 32 && t == GT_ONE;
-    if (one) h.slot(hi - lane) = cdst[b + h[H_INFO + lane]];
+    if (one) h.slot(hi - lane) = (uint32_t)ce[b + h[H_INFO + lane]];
+    if (lst) h[H_INFO + lane] = (uint32_t)(f.my_block / LIST_UNIT_WORDS);
     const uint32_t onemask = (uint32_t)(__ballot(one) & 0xFFFFFFFFull);
     if (lane == 0) h[H_ONEMASK] = onemask;
     // list capacity exponents, one byte per group, packed four per word
-    const uint32_t lg = lst ? (31 - __clz(lcap)) : 0u;
+    const uint32_t lg = lst ? (31 - __clz(f.lcap)) : 0u;
     const uint32_t byte = lg << (8 * (lane & 3));
     uint32_t packed = byte;
     packed |= __shfl_xor(packed, 1);
     packed |= __shfl_xor(packed, 2);
     if (lane < 32 && (lane & 3) == 0) h[H_LCAPLOG + (lane >> 2)] = packed;
-    const uint32_t lmask = (uint32_t)(__ballot(lst) & 0xFFFFFFFFull);
-    uint32_t fill = 0;   // lane k: entries written so far into group k
-    uint32_t sfill = 0;  // entries written so far into S(u) (uniform)
-    for (uint32_t c0 = 0; c0 < d; c0 += 64) {
-        const uint32_t i = c0 + lane;
-        uint32_t wv = 0;
-        if (i < d) {
-            const uint32_t w = cw[b + i];
-            edges[i] = (uint64_t)cdst[b + i] | ((uint64_t)w << 32);
-            seqs[i] = i;
-            wv = member_word(w, rule.fbits);
+    return f;
+}
+
+// Edges [lo, hi) into the adjacency block, the lists with their indexes, and S(u).  fill (lane
+// k) and sfill: the entries that earlier edges put into group k and S(u).
+__device__ __forceinline__ void fill_range(const uint64_t* __restrict__ e, uint32_t lo, uint32_t hi, const FillPlan& f,
+                                           uint32_t fbits, uint32_t fill, uint32_t sfill, uint32_t* __restrict__ pool) {
+    const uint32_t lane = lane_id();
+    uint64_t* edges = (uint64_t*)(pool + f.ao);
+    uint32_t* seqs = pool + f.ao + 2ull * f.cap;
+    for (uint32_t c0 = lo; c0 < hi; c0 += 64 * EB_ROWS) {
+        uint64_t x[EB_ROWS];
+#pragma unroll
+        for (uint32_t r = 0; r < EB_ROWS; ++r) {
+            const uint32_t i = c0 + r * 64 + lane;
+            x[r] = i < hi ? e[i] : 0ull;
         }
-        // S(u) in ascending index order; spos is this edge's position in it
-        const bool sb = (wv & smask) != 0u;
-        const uint64_t sbal = __ballot(sb);
-        const uint32_t spos = sfill + __popcll(sbal & lanemask_lt());
-        if (sb) pool[sblk + spos] = i;
-        sfill += __popcll(sbal);
-        uint32_t mm = lmask;
-        while (mm) {
-            const int k = __ffs(mm) - 1;
-            mm &= mm - 1;
-            const bool bit = (wv >> k) & 1u;
-            const uint64_t bal = __ballot(bit);
-            const uint64_t blk = __shfl(my_block, k, 64);
-            const uint32_t f = __shfl(fill, k, 64);
-            const uint32_t lk = __shfl(lcap, k, 64);
-            const bool reg = ((smask >> k) & 1u) == 0u;  // a listed group that is not sparse is regular
-            if (bit) {
-                const uint32_t pos = f + __popcll(bal & lanemask_lt());
-                pool[blk + pos] = i;
-                pool[blk + lk + (reg ? i : spos)] = pos;  // the group's index entry
+#pragma unroll
+        for (uint32_t r = 0; r < EB_ROWS; ++r) {
+            if (c0 + r * 64 >= hi) break;
+            const uint32_t i = c0 + r * 64 + lane;
+            if (i < hi) {
+                edges[i] = x[r];
+                seqs[i] = i;
             }
-            if (lane == (uint32_t)k) fill += __popcll(bal);
+            const uint32_t wv = i < hi ? member_word((uint32_t)(x[r] >> 32), fbits) : 0u;
+            // S(u) in ascending index order; spos is this edge's position in it
+            uint32_t spos = 0;
+            if (f.smask) {
+                const bool sb = (wv & f.smask) != 0u;
+                const uint64_t sbal = __ballot(sb);
+                spos = sfill + (uint32_t)__popcll(sbal & lanemask_lt());
+                if (sb) pool[f.sblk + spos] = i;
+                sfill += (uint32_t)__popcll(sbal);
+            }
+            for (uint32_t mm = f.lmask; mm; mm &= mm - 1) {
+                const int k = __ffs(mm) - 1;
+                const bool bit = (wv >> k) & 1u;
+                const uint64_t bal = __ballot(bit);
+                if (!bal) continue;
+                const uint32_t at = lane_get(fill, k);
+                if (bit) {
+                    uint32_t* L = pool + lane_get64(f.my_block, k);
+                    const uint32_t pos = at + (uint32_t)__popcll(bal & lanemask_lt());
+                    L[pos] = i;
+                    // the group's index entry: a listed group that is not sparse is regular
+                    L[lane_get(f.lcap, k) + (((f.smask >> k) & 1u) ? spos : i)] = pos;
+                }
+                if (lane == (uint32_t)k) fill += (uint32_t)__popcll(bal);
+            }
         }
+    }
+}
+
+// Pass 2: adjacency blocks (edge words and sequence numbers), listed-group
+// lists (ascending neighbor indices) with their indexes, and S(u).
+__global__ void __launch_bounds__(WB) k_fill(uint32_t n, const uint32_t* __restrict__ start,
+                                             const uint64_t* __restrict__ ce, const uint64_t* __restrict__ adj_off,
+                                             const uint64_t* __restrict__ list_off, uint64_t list_base,
+                                             uint32_t* __restrict__ hdr, uint32_t* __restrict__ pool, GroupRule rule) {
+    const uint32_t u = blockIdx.x * (WB / 64) + (threadIdx.x >> 6);
+    if (u >= n) return;
+    const uint32_t b = start[u], d = start[u + 1] - b;
+    if (d == 0 || d > HUB_DEG) return;
+    const FillPlan f = fill_plan(u, d, b, ce, adj_off, list_off, list_base, hdr, rule, true);
+    fill_range(ce + b, 0, d, f, rule.fbits, 0u, 0u, pool);
+}
+
+// Pass 2 of the hubs, a block each: every wave counts its share's members, then writes them
+// behind those of the waves before it.
+__global__ void __launch_bounds__(HB) k_fill_hub(const uint32_t* __restrict__ start, const uint64_t* __restrict__ ce,
+                                                 const uint64_t* __restrict__ adj_off,
+                                                 const uint64_t* __restrict__ list_off, uint64_t list_base,
+                                                 uint32_t* __restrict__ hdr, uint32_t* __restrict__ pool,
+                                                 const uint32_t* __restrict__ hub, GroupRule rule) {
+    __shared__ uint32_t s_cnt[HW][32], s_len[HW];
+    const uint32_t lane = lane_id(), wave = threadIdx.x >> 6, nh = hub[0];
+    for (uint32_t q = blockIdx.x; q < nh; q += gridDim.x) {
+        const uint32_t u = hub[1 + q], b = start[u], d = start[u + 1] - b;
+        const uint32_t share = ((d + HW - 1) / HW + 63) & ~63u;
+        const uint32_t lo = min(d, wave * share), hi = min(d, lo + share);
+        // every wave reads the plan; the slots still hold counts until wave 0 writes it below
+        const FillPlan f = fill_plan(u, d, b, ce, adj_off, list_off, list_base, hdr, rule, false);
+        uint32_t cnt = 0, last = 0;
+        uint64_t wraw = 0;
+        count_range(ce + b, lo, hi, rule.fbits, cnt, last, wraw);
+        const uint32_t sl = f.smask ? count_masked(ce + b, lo, hi, rule.fbits, f.smask) : 0u;
+        if (lane < 32) s_cnt[wave][lane] = cnt;
+        if (lane == 0) s_len[wave] = sl;
+        __syncthreads();
+        if (wave == 0) fill_plan(u, d, b, ce, adj_off, list_off, list_base, hdr, rule, true);
+        uint32_t fill = 0, sfill = 0;
+        for (uint32_t w = 0; w < wave; ++w) {
+            if (lane < 32) fill += s_cnt[w][lane];
+            sfill += s_len[w];
+        }
+        fill_range(ce + b, lo, hi, f, rule.fbits, fill, sfill, pool);
+        __syncthreads();  // the next hub overwrites the shared arrays
     }
 }
 
@@ -220,7 +368,7 @@ __global__ void __launch_bounds__(WB) k_fill(uint32_t n, const uint32_t* __restr
 // destinations, and each listed subgroup's ascending list.
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(WB) k_header4(uint32_t n, const uint32_t* __restrict__ start,
-                                                const uint32_t* __restrict__ cw, uint32_t* __restrict__ hdr,
+                                                const uint64_t* __restrict__ ce, uint32_t* __restrict__ hdr,
                                                 uint64_t* __restrict__ adjw, uint64_t* __restrict__ listw,
                                                 GroupRule rule) {
     const uint32_t u = blockIdx.x * (WB / 64) + (threadIdx.x >> 6);
@@ -231,7 +379,7 @@ __global__ void __launch_bounds__(WB) k_header4(uint32_t n, const uint32_t* __re
     uint64_t wraw = 0;
     for (uint32_t c0 = 0; c0 < d; c0 += 64) {
         const uint32_t i = c0 + lane;
-        const uint32_t w = i < d ? cw[b + i] : 0u;
+        const uint32_t w = i < d ? (uint32_t)(ce[b + i] >> 32) : 0u;
         wraw += w;
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
@@ -276,7 +424,7 @@ __global__ void __launch_bounds__(WB) k_header4(uint32_t n, const uint32_t* __re
 }
 
 __global__ void __launch_bounds__(WB) k_fill4(uint32_t n, const uint32_t* __restrict__ start,
-                                              const uint32_t* __restrict__ cdst, const uint32_t* __restrict__ cw,
+                                              const uint64_t* __restrict__ ce,
                                               const uint64_t* __restrict__ adj_off, const uint64_t* __restrict__ list_off,
                                               uint64_t list_base, uint32_t* __restrict__ hdr, uint32_t* __restrict__ pool,
                                               GroupRule rule) {
@@ -300,7 +448,7 @@ __global__ void __launch_bounds__(WB) k_fill4(uint32_t n, const uint32_t* __rest
     }
     const uint64_t my_block = list_base + list_off[u] + (x - lcap);
     if (lst) h[H4_INFO + lane] = (uint32_t)(my_block / LIST_UNIT_WORDS);
-    if (lane < R4_SUB && t == GT_ONE) h[H4_SLOT + lane] = cdst[b + h[H4_INFO + lane]];
+    if (lane < R4_SUB && t == GT_ONE) h[H4_SLOT + lane] = (uint32_t)ce[b + h[H4_INFO + lane]];
     const uint32_t lg = lst ? (31 - __clz(lcap)) : 0u;
     uint32_t packed = lg << (8 * (lane & 3));
     packed |= __shfl_xor(packed, 1);
@@ -312,8 +460,8 @@ __global__ void __launch_bounds__(WB) k_fill4(uint32_t n, const uint32_t* __rest
         const uint32_t i = c0 + lane;
         uint32_t w = 0;
         if (i < d) {
-            w = cw[b + i];
-            edges[i] = (uint64_t)cdst[b + i] | ((uint64_t)w << 32);
+            edges[i] = ce[b + i];
+            w = (uint32_t)(ce[b + i] >> 32);
         }
         for (uint64_t mm = lmask; mm; mm &= mm - 1) {
             const int sg = __ffsll((long long)mm) - 1;
@@ -929,35 +1077,37 @@ int build_graph(bingo_graph* g, uint64_t m, const uint32_t* src, const uint32_t*
     // scratch layout
     auto al = [](uint64_t x) { return (x + 255) & ~255ull; };
     const uint64_t mm = m ? m : 1;
-    const size_t sort_tmp = sort_temp_bytes(mm, false);
+    const size_t sort_tmp = sort_records_temp_bytes(mm);
     const size_t scan_tmp = scan_temp_bytes((uint64_t)n + 1);
-    const size_t need = al(mm * 4) * 4 + al(((uint64_t)n + 1) * 4) + 2 * al(((uint64_t)n + 1) * 8) * 2 +
-                        std::max(sort_tmp, scan_tmp) + 1024;
+    const size_t need = al(mm * 4) + al(mm * 8) + al(((uint64_t)n + 1) * 4) + 2 * al(((uint64_t)n + 1) * 8) * 2 +
+                        al((m / HUB_DEG + 2) * 4) + std::max(sort_tmp, scan_tmp) + 1024;
     char* ws = (char*)ws_get(g, need);
     if (!ws) return BINGO_E_OOM;
-    uint32_t* ids = (uint32_t*)ws;            ws += al(mm * 4);
     uint32_t* skeys = (uint32_t*)ws;          ws += al(mm * 4);
-    uint32_t* sids = (uint32_t*)ws;           ws += al(mm * 4);
-    uint32_t* cdst = ids;                     // ids are dead after the sort
-    uint32_t* cw = (uint32_t*)ws;             ws += al(mm * 4);
+    uint64_t* ce = (uint64_t*)ws;             ws += al(mm * 8);  // the edges by source: dst | weight << 32
     uint32_t* start = (uint32_t*)ws;          ws += al(((uint64_t)n + 1) * 4);
     uint64_t* adjw = (uint64_t*)ws;           ws += al(((uint64_t)n + 1) * 8);
     uint64_t* listw = (uint64_t*)ws;          ws += al(((uint64_t)n + 1) * 8);
     uint64_t* adj_off = (uint64_t*)ws;        ws += al(((uint64_t)n + 1) * 8);
     uint64_t* list_off = (uint64_t*)ws;       ws += al(((uint64_t)n + 1) * 8);
+    uint32_t* hub = (uint32_t*)ws;            ws += al((m / HUB_DEG + 2) * 4);
     unsigned long long* totals = (unsigned long long*)ws;  ws += 256;
     void* tmp = ws;
 
-    if (m) {
-        hipLaunchKernelGGL(k_iota, dim3(grid_for(m, 256)), dim3(256), 0, st, ids, m);
-        sort_pairs_u32(src, ids, skeys, sids, m, bits_for(n - 1), tmp, st);
-        hipLaunchKernelGGL(k_gather, dim3(grid_for(m, 256)), dim3(256), 0, st, m, sids, dst, w, cdst, cw);
-    }
+    if (m) sort_records_u32(src, dst, w, skeys, ce, m, std::max(1, bits_for(n - 1)), tmp, st);
     hipLaunchKernelGGL(k_row_start, dim3(((uint64_t)n + 1 + 255) / 256), dim3(256), 0, st, skeys, m, n, start);
     const uint32_t vgrid = (uint32_t)(((uint64_t)n + 3) / 4);
     const bool r4 = g->radix_base == 4;
-    if (r4) hipLaunchKernelGGL(k_header4, dim3(vgrid), dim3(WB), 0, st, n, start, cw, g->hdr, adjw, listw, g->rule);
-    else hipLaunchKernelGGL(k_header, dim3(vgrid), dim3(WB), 0, st, n, start, cw, g->hdr, adjw, listw, g->rule);
+    const uint32_t hgrid = (uint32_t)std::min<uint64_t>(m / HUB_DEG, HUB_GRID);  // no hub without so many edges
+    if (r4) {
+        hipLaunchKernelGGL(k_header4, dim3(vgrid), dim3(WB), 0, st, n, start, ce, g->hdr, adjw, listw, g->rule);
+    } else {
+        HIPCHK(hipMemsetAsync(hub, 0, 4, st));
+        hipLaunchKernelGGL(k_header, dim3(vgrid), dim3(WB), 0, st, n, start, ce, g->hdr, adjw, listw, hub, g->rule);
+        if (hgrid)
+            hipLaunchKernelGGL(k_header_hub, dim3(hgrid), dim3(HB), 0, st, start, ce, g->hdr, adjw, listw,
+                               (const uint32_t*)hub, g->rule);
+    }
     scan_u64(adjw, adj_off, n, tmp, totals, st);
     scan_u64(listw, list_off, n, tmp, totals + 1, st);
     unsigned long long tot[2];
@@ -974,12 +1124,16 @@ int build_graph(bingo_graph* g, uint64_t m, const uint32_t* src, const uint32_t*
         return BINGO_E_OOM;
     }
     g->pool_words = pool_words;
-    if (r4)
-        hipLaunchKernelGGL(k_fill4, dim3(vgrid), dim3(WB), 0, st, n, start, cdst, cw, adj_off, list_off,
-                           (uint64_t)tot[0], g->hdr, g->pool, g->rule);
-    else
-        hipLaunchKernelGGL(k_fill, dim3(vgrid), dim3(WB), 0, st, n, start, cdst, cw, adj_off, list_off,
-                           (uint64_t)tot[0], g->hdr, g->pool, g->rule);
+    if (r4) {
+        hipLaunchKernelGGL(k_fill4, dim3(vgrid), dim3(WB), 0, st, n, start, ce, adj_off, list_off, (uint64_t)tot[0],
+                           g->hdr, g->pool, g->rule);
+    } else {
+        hipLaunchKernelGGL(k_fill, dim3(vgrid), dim3(WB), 0, st, n, start, ce, adj_off, list_off, (uint64_t)tot[0],
+                           g->hdr, g->pool, g->rule);
+        if (hgrid)
+            hipLaunchKernelGGL(k_fill_hub, dim3(hgrid), dim3(HB), 0, st, start, ce, adj_off, list_off,
+                               (uint64_t)tot[0], g->hdr, g->pool, (const uint32_t*)hub, g->rule);
+    }
     if (g->alias_mode) {
         if (hipMalloc(&g->alias, (size_t)n * ALIAS_ENTRIES * sizeof(uint4)) != hipSuccess) {
             g->alias = nullptr;

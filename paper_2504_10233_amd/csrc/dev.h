@@ -327,6 +327,11 @@ __device__ __forceinline__ uint64_t rs_below64(RandStream& s, uint64_t n) {
 // Wave helpers (wave64).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
+// lane l's value, l the same in every lane (a scalar read, not a shuffle through the LDS crossbar)
+__device__ __forceinline__ uint32_t lane_get(uint32_t v, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); }
+__device__ __forceinline__ uint64_t lane_get64(uint64_t v, int l) {
+    return ((uint64_t)lane_get((uint32_t)(v >> 32), l) << 32) | lane_get((uint32_t)v, l);
+}
 __device__ __forceinline__ uint64_t lanemask_lt() {
     const uint32_t l = __lane_id();
     return l == 0 ? 0ull : (~0ull >> (64 - l));
@@ -450,6 +455,10 @@ void sort_pairs_u64(const uint64_t* keys_in, const uint32_t* vals_in, uint64_t* 
                     uint64_t n, int bits, void* temp, hipStream_t st);
 void sort_keys_u64(const uint64_t* keys_in, uint64_t* keys_out, uint64_t n, int bits, void* temp,
                    hipStream_t st);
+// records by a 32-bit key, a 64-bit value given as two arrays of halves: keys_out, vals_out (lo | hi << 32)
+size_t sort_records_temp_bytes(uint64_t n);
+void sort_records_u32(const uint32_t* keys, const uint32_t* lo, const uint32_t* hi, uint32_t* keys_out,
+                      uint64_t* vals_out, uint64_t n, int bits, void* temp, hipStream_t st);
 // the same on the first min(nmax, *dn) entries, with launches sized by nmax (capturable)
 void sort_pairs_u64_dn(const uint64_t* keys_in, const uint32_t* vals_in, uint64_t* keys_out, uint32_t* vals_out,
                        uint64_t nmax, const unsigned long long* dn, int bits, void* temp, hipStream_t st);

@@ -145,9 +145,11 @@ __global__ void __launch_bounds__(SORT_BLOCK) k_digit_hist(const K* __restrict__
     if (threadIdx.x < RADIX) hist[(uint64_t)threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
 }
 
-template <typename K, bool HAS_V>
-__global__ void __launch_bounds__(SORT_BLOCK) k_digit_scatter(const K* __restrict__ kin, const uint32_t* __restrict__ vin,
-                                                              K* __restrict__ kout, uint32_t* __restrict__ vout,
+// V: the value type; vhi: the first pass of 64-bit values given as two arrays of halves (low, high)
+template <typename K, bool HAS_V, typename V = uint32_t>
+__global__ void __launch_bounds__(SORT_BLOCK) k_digit_scatter(const K* __restrict__ kin, const V* __restrict__ vin,
+                                                              const uint32_t* __restrict__ vhi,
+                                                              K* __restrict__ kout, V* __restrict__ vout,
                                                               uint64_t n, const unsigned long long* __restrict__ dn,
                                                               int sh, const uint64_t* __restrict__ offs,
                                                               uint32_t nblocks) {
@@ -165,12 +167,18 @@ __global__ void __launch_bounds__(SORT_BLOCK) k_digit_scatter(const K* __restric
     const uint64_t below = lanemask_lt();
     // the tile's keys and values, all loads issued before the first subtile is ranked
     K keys[SORT_SUBTILES];
-    uint32_t vals[SORT_SUBTILES];
+    V vals[SORT_SUBTILES];
 #pragma unroll
     for (int i = 0; i < SORT_SUBTILES; ++i) {
         const uint64_t idx = base + (uint64_t)i * SORT_BLOCK + tid;
         keys[i] = idx < n ? kin[idx] : (K)0;
-        vals[i] = (HAS_V && idx < n) ? vin[idx] : 0u;
+        vals[i] = 0;
+        if (HAS_V && idx < n) {
+            if (sizeof(V) == 8 && vhi)
+                vals[i] = (V)(reinterpret_cast<const uint32_t*>(vin)[idx] | ((uint64_t)vhi[idx] << 32));
+            else
+                vals[i] = vin[idx];
+        }
     }
     __syncthreads();
 #pragma unroll
@@ -178,7 +186,7 @@ __global__ void __launch_bounds__(SORT_BLOCK) k_digit_scatter(const K* __restric
         const uint64_t idx = base + (uint64_t)i * SORT_BLOCK + tid;
         const bool valid = idx < n;
         const K key = keys[i];
-        const uint32_t val = vals[i];
+        const V val = vals[i];
         const uint32_t dg = digit_of(key, sh);
         uint64_t peers = __ballot(valid);
 #pragma unroll
@@ -301,14 +309,51 @@ void sort_impl(const K* kin, const uint32_t* vin, K* kout, uint32_t* vout, uint6
         hipLaunchKernelGGL((k_digit_hist<K>), dim3((uint32_t)nb), dim3(SORT_BLOCK), 0, st, ck, n, dn, sh, hist,
                            (uint32_t)nb);
         scan_impl<uint32_t>(hist, offs, nb * RADIX, scratch, nullptr, st);
-        hipLaunchKernelGGL((k_digit_scatter<K, HAS_V>), dim3((uint32_t)nb), dim3(SORT_BLOCK), 0, st, ck, cv, nk,
-                           nv, n, dn, sh, (const uint64_t*)offs, (uint32_t)nb);
+        hipLaunchKernelGGL((k_digit_scatter<K, HAS_V>), dim3((uint32_t)nb), dim3(SORT_BLOCK), 0, st, ck, cv,
+                           (const uint32_t*)nullptr, nk, nv, n, dn, sh, (const uint64_t*)offs, (uint32_t)nb);
         ck = nk;
         cv = nv;
     }
 }
 
 }  // namespace
+
+// Records sorted by a 32-bit key with both 32-bit halves of a 64-bit value carried through
+// the passes: 24 bytes read and written per record and pass, all of it in order, where
+// sorting record numbers and then gathering costs two random sectors per record.
+size_t sort_records_temp_bytes(uint64_t n) {
+    const uint64_t nb = cdiv(n ? n : 1, SORT_TILE);
+    return align256(nb * RADIX * 4) + align256(nb * RADIX * 8) + 2 * align256(n * 4) + align256(n * 8) +
+           scan_temp_bytes(nb * RADIX) + 256;
+}
+// keys_out (n u32) and vals_out (n u64: lo | hi << 32); bits in 1..32
+void sort_records_u32(const uint32_t* keys, const uint32_t* lo, const uint32_t* hi, uint32_t* keys_out,
+                      uint64_t* vals_out, uint64_t n, int bits, void* temp, hipStream_t st) {
+    if (n == 0) return;
+    const int passes = (bits + 7) / 8;
+    const uint64_t nb = cdiv(n, SORT_TILE);
+    char* t = (char*)temp;
+    uint32_t* hist = (uint32_t*)t;  t += align256(nb * RADIX * 4);
+    uint64_t* offs = (uint64_t*)t;  t += align256(nb * RADIX * 8);
+    uint32_t* ktmp = (uint32_t*)t;  t += align256(n * 4);
+    uint64_t* vtmp = (uint64_t*)t;  t += align256(n * 8);
+    void* scratch = t;
+    const uint32_t* ck = keys;
+    const uint64_t* cv = reinterpret_cast<const uint64_t*>(lo);  // first pass: halves (never read as u64)
+    for (int p = 0; p < passes; ++p) {
+        const bool to_out = ((passes - 1 - p) % 2) == 0;
+        uint32_t* nk = to_out ? keys_out : ktmp;
+        uint64_t* nv = to_out ? vals_out : vtmp;
+        hipLaunchKernelGGL((k_digit_hist<uint32_t>), dim3((uint32_t)nb), dim3(SORT_BLOCK), 0, st, ck, n,
+                           (const unsigned long long*)nullptr, 8 * p, hist, (uint32_t)nb);
+        scan_impl<uint32_t>(hist, offs, nb * RADIX, scratch, nullptr, st);
+        hipLaunchKernelGGL((k_digit_scatter<uint32_t, true, uint64_t>), dim3((uint32_t)nb), dim3(SORT_BLOCK), 0, st, ck,
+                           cv, p == 0 ? hi : nullptr, nk, nv, n, (const unsigned long long*)nullptr, 8 * p,
+                           (const uint64_t*)offs, (uint32_t)nb);
+        ck = nk;
+        cv = nv;
+    }
+}
 
 size_t scan_temp_bytes(uint64_t n) {
     size_t b = 0;

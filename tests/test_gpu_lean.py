@@ -94,3 +94,23 @@ def test_node2vec_lanes_per_walk(p, q):
         if nw == 600:
             assert c.tolist() == list(og.node2vec(starts.numpy(), 9, 77, p, q, base=5, with_proposals=True)[1:])
     g.close()
+
+
+@pytest.mark.parametrize("degree", [2047, 2048, 2049, 2112, 16385, 40001])
+@pytest.mark.parametrize("frac", [0, 8])
+def test_build_around_the_hub_threshold(degree, frac):
+    """A vertex at the edges of the block-per-hub construction, with groups of every type, beside others."""
+    import oracle as O
+    import torch
+    from paper_2504_10233_amd import Graph
+    n = 40
+    src = torch.cat([torch.full((degree,), 7), synth.below(1, 1, 3000, n), torch.full((2500,), 39)])
+    dst = synth.below(1, 2, src.numel(), n)
+    w = synth.weights_zipf(src.numel(), 1.2, (1 << 30) - 1, 5)
+    perm = torch.argsort(synth.uniform_u32(6, 1, src.numel()), stable=True)
+    src, dst, w = src[perm], dst[perm], w[perm]
+    g = Graph(n, src, dst, w, frac_bits=frac)
+    og = O.Graph(n, src.numpy(), dst.numpy(), w.numpy(), frac_bits=frac)
+    assert np.array_equal(g.export(), og.dump())
+    assert np.array_equal(g.export_index(), og.index_dump())
+    g.close()
