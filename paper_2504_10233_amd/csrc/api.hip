@@ -6,20 +6,129 @@
 #include <new>
 #include <stdlib.h>
 #include <cmath>
+#include <mutex>
+#include <unordered_map>
+#include <vector>
+
+// ---------------------------------------------------------------------------
+// Large blocks between graphs.  The driver clears freed device memory before it
+// hands it out again, at about 25 GB/s once the memory that was clean from the
+// start is used up, so a program that builds and destroys graphs in turn waits for
+// that: 77 ms per graph of 2^20 vertices and 2^24 edges (2 GB in all), whose build
+// takes 3 ms of device time.  A destroyed graph's headers, pool and workspace
+// are therefore kept for the next one: at most DEV_KEEP bytes in the process, a
+// block of at most a quarter more than is asked for, and not for longer than
+// DEV_AGE later frees; they are given back as well when an allocation fails.  Blocks
+// under 1 MiB are not kept.  A block belongs to the device that was current at
+// its allocation, and is kept only by calls that have waited for that device.
+// ---------------------------------------------------------------------------
+namespace {
+constexpr size_t DEV_KEEP = 4ull << 30;
+constexpr uint64_t DEV_AGE = 32;
+struct DevBlock {
+    void* p;
+    size_t bytes;
+    int dev;
+    uint64_t tick;
+};
+struct DevBlocks {
+    std::mutex mu;
+    std::vector<DevBlock> idle;
+    std::unordered_map<void*, DevBlock> live;
+    size_t idle_bytes = 0;
+    uint64_t tick = 0;
+    // give back idle blocks: all, or those past the bounds
+    void trim(bool all) {
+        size_t keep = 0;
+        for (size_t i = 0; i < idle.size(); ++i) {
+            DevBlock& b = idle[i];
+            // the oldest come first (idle is in order of freeing)
+            if (all || idle_bytes > DEV_KEEP || tick - b.tick > DEV_AGE) {
+                hipFree(b.p);
+                idle_bytes -= b.bytes;
+            } else {
+                idle[keep++] = b;
+            }
+        }
+        idle.resize(keep);
+    }
+};
+DevBlocks& dev_blocks() {
+    static DevBlocks* b = new DevBlocks();  // never destroyed: the process's end gives the memory back
+    return *b;
+}
+// sizes in steps of an eighth of their power of two, so that graphs of about one size share blocks
+size_t dev_round(size_t bytes) {
+    size_t step = 1ull << 17;
+    while ((step << 4) <= bytes) step <<= 1;
+    return (bytes + step - 1) & ~(step - 1);
+}
+}  // namespace
+
+void* dev_alloc(size_t bytes) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return nullptr;
+    const bool large = bytes >= (1u << 20);
+    const size_t want = large ? dev_round(bytes) : bytes;
+    DevBlocks& d = dev_blocks();
+    std::lock_guard<std::mutex> lk(d.mu);
+    size_t best = d.idle.size();
+    for (size_t i = 0; large && i < d.idle.size(); ++i) {
+        const DevBlock& b = d.idle[i];
+        if (b.dev == dev && b.bytes >= want && b.bytes <= want + want / 4 &&
+            (best == d.idle.size() || b.bytes < d.idle[best].bytes))
+            best = i;
+    }
+    DevBlock b{nullptr, want, dev, 0};
+    if (best < d.idle.size()) {
+        b = d.idle[best];
+        d.idle.erase(d.idle.begin() + (long)best);
+        d.idle_bytes -= b.bytes;
+    } else {
+        hipError_t e = hipMalloc(&b.p, want);
+        if (e != hipSuccess && !d.idle.empty()) {
+            (void)hipGetLastError();
+            d.trim(true);
+            e = hipMalloc(&b.p, want);
+        }
+        if (e != hipSuccess) return nullptr;
+    }
+    if (large) d.live[b.p] = b;
+    return b.p;
+}
+
+void dev_free(void* p, bool idle) {
+    if (!p) return;
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess) dev = -1;
+    DevBlocks& d = dev_blocks();
+    std::lock_guard<std::mutex> lk(d.mu);
+    auto it = d.live.find(p);
+    if (it == d.live.end() || !idle || it->second.dev != dev || it->second.bytes > DEV_KEEP) {
+        if (it != d.live.end()) d.live.erase(it);
+        hipFree(p);
+    } else {
+        DevBlock b = it->second;
+        d.live.erase(it);
+        b.tick = d.tick;
+        d.idle.push_back(b);
+        d.idle_bytes += b.bytes;
+    }
+    ++d.tick;
+    d.trim(false);
+}
 
 void* ws_get(bingo_graph* g, size_t bytes) {
     // a pending asynchronous PPR histogram still reads its visit bins here
     if (ppr_drain(g) != BINGO_OK) return nullptr;
     if (bytes <= g->ws_bytes && g->ws) return g->ws;
     hipDeviceSynchronize();
-    if (g->ws) hipFree(g->ws);
+    dev_free(g->ws, true);
     g->ws = nullptr;
     g->ws_bytes = 0;
     const size_t want = bytes + bytes / 4 + 4096;
-    if (hipMalloc(&g->ws, want) != hipSuccess) {
-        g->ws = nullptr;
-        return nullptr;
-    }
+    g->ws = dev_alloc(want);
+    if (!g->ws) return nullptr;
     g->ws_bytes = want;
     return g->ws;
 }
@@ -40,6 +149,7 @@ int err_to_code(uint32_t bits) {
     return BINGO_OK;
 }
 
+// Free everything the handle owns; nothing on the current device uses it any more.
 static void release(bingo_graph* g) {
     if (!g) return;
     update_release(g);
@@ -50,15 +160,15 @@ static void release(bingo_graph* g) {
         if (g->slot_ev[i]) hipEventDestroy(g->slot_ev[i]);
     for (hipEvent_t e : {g->ppr_done, g->ppr_h0, g->ppr_h1})
         if (e) hipEventDestroy(e);
-    hipFree(g->hdr_mem);
+    dev_free(g->hdr_mem, true);
     hipFree(g->alias);
-    hipFree(g->pool);
+    dev_free(g->pool, true);
     hipFree(g->d_ctl);
     hipFree(g->d_err);
     hipFree(g->ppr_off);
     hipFree(g->ppr_vtx);
     hipFree(g->ppr_cnt);
-    hipFree(g->ws);
+    dev_free(g->ws, true);
     hipFree(g->aux);
     hipFree(g->n2v_idx);
     hipFree(g->n2v_off);
@@ -94,7 +204,7 @@ int bingo_build(const bingo_config* cfg, uint32_t n, uint64_t m, const uint32_t*
     g->radix_base = radix;
     const uint64_t hdr_words = radix == 4 ? (uint64_t)n * H4_WORDS : hdr_total_words(n);
     g->hdr = g->hdr_mem = nullptr; g->pool = nullptr; g->d_ctl = nullptr; g->d_err = nullptr; g->alias = nullptr;
-    if (hipMalloc(&g->hdr_mem, hdr_words * 4) != hipSuccess ||
+    if (!(g->hdr_mem = (uint32_t*)dev_alloc(hdr_words * 4)) ||
         hipMalloc(&g->d_ctl, CTL_WORDS * 8) != hipSuccess || hipMalloc(&g->d_err, 4) != hipSuccess) {
         release(g);
         return BINGO_E_OOM;

@@ -1119,10 +1119,8 @@ int build_graph(bingo_graph* g, uint64_t m, const uint32_t* src, const uint32_t*
     if (pool_words < used + 1024) return BINGO_E_OOM;
     if (pool_words > (1ull << 35)) pool_words = std::max<uint64_t>(1ull << 35, used + 1024);
     if (used + 1024 > (1ull << 35)) return BINGO_E_OOM;  // list offsets are 32-bit in 32-byte units
-    if (hipMalloc(&g->pool, pool_words * 4) != hipSuccess) {
-        g->pool = nullptr;
-        return BINGO_E_OOM;
-    }
+    g->pool = (uint32_t*)dev_alloc(pool_words * 4);
+    if (!g->pool) return BINGO_E_OOM;
     g->pool_words = pool_words;
     if (r4) {
         hipLaunchKernelGGL(k_fill4, dim3(vgrid), dim3(WB), 0, st, n, start, ce, adj_off, list_off, (uint64_t)tot[0],

@@ -118,8 +118,8 @@ int compact_pool(bingo_graph* g, uint64_t pool_words, hipStream_t st) {
     HIPCHK(hipMemcpyAsync(&live, total, 8, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     if (live > pool_words) return BINGO_E_OOM;
-    uint32_t* fresh = nullptr;
-    if (hipMalloc(&fresh, pool_words * 4) != hipSuccess) {
+    uint32_t* fresh = (uint32_t*)dev_alloc(pool_words * 4);
+    if (!fresh) {
         (void)hipGetLastError();
         return BINGO_E_OOM;
     }
@@ -127,7 +127,7 @@ int compact_pool(bingo_graph* g, uint64_t pool_words, hipStream_t st) {
                        g->rule, (const uint64_t*)off);
     hipLaunchKernelGGL(k_cmp_ctl, dim3(1), dim3(1), 0, st, g->d_ctl, (const unsigned long long*)total);
     HIPCHK(hipStreamSynchronize(st));
-    HIPCHK(hipFree(g->pool));
+    dev_free(g->pool, false);
     g->pool = fresh;
     g->pool_words = pool_words;
     // captured update graphs hold the old arena's address
