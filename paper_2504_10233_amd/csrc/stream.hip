@@ -61,33 +61,50 @@ __global__ void k_st_starts(const uint32_t* __restrict__ head, const uint64_t* _
         if (head[p]) { seg_start[hx[p]] = (uint32_t)p; seg_src[hx[p]] = sk[p]; }
 }
 
-// Pool words for the current record.  Each wave takes the pool in chunks of ST_CHUNK words (or
-// the request, if larger) from the bump counter (ctl[0]) by compare-and-swap, so that a failed
-// reservation leaves the counter unchanged, and serves its records from the chunk; one global
-// operation per chunk instead of per record keeps thousands of waves from contending on the
-// counter.  The unused tail of a chunk is garbage (counted in `waste`, reclaimed by compaction).
-// Near the end of the pool a chunk that does not fit falls back to the exact request.  Every
-// lane calls with the same values; the result (NF64 on failure) is uniform.
+// Pool words for the current record.  A wave takes the pool in chunks of ST_CHUNK
+// words (or the request, if larger) from the bump counter (ctl[0]) and serves its
+// records from the chunk.  The unused tail of a chunk is garbage (counted in
+// `waste`, reclaimed by compaction).
+//
+// Taking a chunk by compare-and-swap, so that a failed reservation leaves the
+// counter unchanged, makes the waves retry against each other: 1800 chunks of a
+// pass of 20,000 records took 5 ms.  A fetch-and-add never retries, but must not
+// pass the end of the pool.  So a wave adds only after it has read the counter at
+// or below a line that lies one chunk per wave before the end, and every other reservation
+// keeps below that line: each wave has at most one add under way, so all of them
+// together stay within the pool.  Records that find no room below the line are
+// left over, as those that find the pool full are, and the pass after it (`exact`)
+// takes every reservation by compare-and-swap up to the end.
+// Every lane calls with the same values; the result (NF64 on failure) is uniform.
 constexpr uint64_t NF64 = ~0ull;
-constexpr uint64_t ST_CHUNK = 1u << 14;
+constexpr uint64_t ST_CHUNK = 1u << 9;
+struct StPool {
+    unsigned long long* ctl;
+    uint64_t words;  // the pool's end
+    uint64_t line;   // exact: 0 (no adds); else the end less a chunk per wave of the grid
+};
 struct StChunk {
     uint64_t cur = 0, end = 0;
 };
-__device__ uint64_t st_reserve(unsigned long long* ctl, uint64_t pool_words, uint64_t words) {
+__device__ uint64_t st_reserve(const StPool& P, uint64_t words) {
     unsigned long long got = 0;
     if (lane_id() == 0) {
-        unsigned long long cur = *reinterpret_cast<volatile unsigned long long*>(ctl);
-        for (;;) {
-            if (cur + words > pool_words) { got = NF64; break; }
-            const unsigned long long prev = atomicCAS(ctl, cur, cur + words);
-            if (prev == cur) { got = cur; break; }
-            cur = prev;
+        unsigned long long cur = __hip_atomic_load(P.ctl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (P.line && words <= ST_CHUNK) {
+            got = cur <= P.line ? atomicAdd(P.ctl, (unsigned long long)words) : NF64;
+        } else {
+            const uint64_t lim = P.line ? P.line : P.words;
+            for (;;) {
+                if (cur + words > lim) { got = NF64; break; }
+                const unsigned long long prev = atomicCAS(P.ctl, cur, cur + words);
+                if (prev == cur) { got = cur; break; }
+                cur = prev;
+            }
         }
     }
     return __shfl(got, 0, 64);
 }
-__device__ uint64_t st_alloc(StChunk& ch, unsigned long long* ctl, uint64_t pool_words, uint64_t words,
-                             uint64_t& waste) {
+__device__ uint64_t st_alloc(StChunk& ch, const StPool& P, uint64_t words, uint64_t& waste) {
     if (!words) return 0;
     if (ch.cur + words <= ch.end) {
         const uint64_t r = ch.cur;
@@ -95,13 +112,14 @@ __device__ uint64_t st_alloc(StChunk& ch, unsigned long long* ctl, uint64_t pool
         return r;
     }
     const uint64_t take = words > ST_CHUNK ? words : ST_CHUNK;
-    uint64_t got = st_reserve(ctl, pool_words, take);
+    uint64_t got = st_reserve(P, take);
     uint64_t end = got + take;
-    if (got == NF64 && take > words) {
-        got = st_reserve(ctl, pool_words, words);
+    if (got == NF64 && take > words && !P.line) {
+        got = st_reserve(P, words);
         end = got + words;
     }
     if (got == NF64) return NF64;  // the current chunk stays for smaller requests
+    if (words > ST_CHUNK) return got;  // a block of its own: the chunk stays
     if (lane_id() == 0) waste += ch.end - ch.cur;  // the old chunk's unused tail
     ch.cur = got + words;
     ch.end = end;
@@ -250,7 +268,7 @@ __device__ void st_count(uint32_t code, unsigned long long* acc) {
 // (a regular group's inverted index spans the adjacency capacity, a sparse
 // group's index the S(u) capacity).
 __device__ bool st_insert(SV& s, uint32_t v, uint32_t w, GroupRule rule, uint32_t* __restrict__ pool,
-                          unsigned long long* ctl, uint64_t pool_words, StChunk& ch, uint64_t& freed,
+                          const StPool& P, StChunk& ch, uint64_t& freed,
                           unsigned long long* acc) {
     const uint32_t lane = lane_id();
     const uint32_t fb = rule.fbits;
@@ -283,7 +301,7 @@ __device__ bool st_insert(SV& s, uint32_t v, uint32_t w, GroupRule rule, uint32_
         if (lane >= (uint32_t)o) x += y;
     }
     const uint64_t total = aw + __shfl(x, 63, 64);
-    const uint64_t base = st_alloc(ch, ctl, pool_words, total, freed);
+    const uint64_t base = st_alloc(ch, P, total, freed);
     if (base == NF64) return false;
     const uint64_t myblk = base + aw + (x - lw);
     // adjacency
@@ -392,7 +410,7 @@ __device__ uint64_t st_scan_oldest(const uint64_t* __restrict__ edges, const uin
 // One delete record whose oldest occurrence (best, from st_scan_oldest over the whole adjacency)
 // and occurrence count are known.
 __device__ bool st_delete_at(SV& s, uint32_t v, uint64_t best, uint32_t hits, GroupRule rule,
-                             uint32_t* __restrict__ pool, unsigned long long* ctl, uint64_t pool_words, StChunk& ch,
+                             uint32_t* __restrict__ pool, const StPool& P, StChunk& ch,
                              uint64_t& freed, unsigned long long* acc, uint32_t* __restrict__ errw) {
     const uint32_t lane = lane_id();
     const uint32_t fb = rule.fbits;
@@ -436,7 +454,7 @@ __device__ bool st_delete_at(SV& s, uint32_t v, uint64_t best, uint32_t hits, Gr
         if (lane >= (uint32_t)o) x += y;
     }
     const uint64_t total = __shfl(x, 63, 64);
-    const uint64_t base = st_alloc(ch, ctl, pool_words, total, freed);
+    const uint64_t base = st_alloc(ch, P, total, freed);
     if (base == NF64) return false;
     const uint64_t myblk = base + (x - lw);
     // adjacency: the tail entry takes the deleted slot
@@ -523,14 +541,13 @@ __device__ bool st_delete_at(SV& s, uint32_t v, uint64_t best, uint32_t hits, Gr
 }
 
 // One delete record, the whole adjacency scanned by the wave.
-__device__ bool st_delete(SV& s, uint32_t v, GroupRule rule, uint32_t* __restrict__ pool, unsigned long long* ctl,
-                          uint64_t pool_words, StChunk& ch, uint64_t& freed, unsigned long long* acc,
+__device__ bool st_delete(SV& s, uint32_t v, GroupRule rule, uint32_t* __restrict__ pool, const StPool& P, StChunk& ch, uint64_t& freed, unsigned long long* acc,
                           uint32_t* __restrict__ errw) {
     const uint64_t* edges = reinterpret_cast<const uint64_t*>(pool + s.adj);
     const uint32_t* seqs = pool + s.adj + 2ull * s.cap;
     uint32_t hits;
     const uint64_t best = st_scan_oldest(edges, seqs, 0, s.d, v, hits);
-    return st_delete_at(s, v, best, hits, rule, pool, ctl, pool_words, ch, freed, acc, errw);
+    return st_delete_at(s, v, best, hits, rule, pool, P, ch, freed, acc, errw);
 }
 
 // The state of source u's vertex from its header (lane k < 32: group k).
@@ -601,8 +618,8 @@ __global__ void __launch_bounds__(TB) k_st_apply(const uint32_t* __restrict__ er
                                                  const uint32_t* __restrict__ sv, const uint32_t* __restrict__ seg_start,
                                                  const uint32_t* __restrict__ op, const uint32_t* __restrict__ dst,
                                                  const uint32_t* __restrict__ w, uint32_t* __restrict__ hdr,
-                                                 uint32_t* __restrict__ pool, unsigned long long* ctl,
-                                                 uint64_t pool_words, GroupRule rule, uint32_t* __restrict__ errw,
+                                                 uint32_t* __restrict__ pool, StPool P, GroupRule rule,
+                                                 uint32_t* __restrict__ errw,
                                                  unsigned long long* __restrict__ out, uint32_t* __restrict__ left,
                                                  uint32_t* __restrict__ sdirty, uint32_t* __restrict__ big,
                                                  unsigned long long* __restrict__ nbig) {
@@ -630,8 +647,8 @@ __global__ void __launch_bounds__(TB) k_st_apply(const uint32_t* __restrict__ er
         uint32_t stop = e;  // first record not applied
         for (uint32_t p = b; p < e && ok; ++p) {
             const uint32_t r = sv[p];
-            if (op[r] == OP_INSERT) ok = st_insert(s, dst[r], w[r], rule, pool, ctl, pool_words, ch, freed, acc);
-            else ok = st_delete(s, dst[r], rule, pool, ctl, pool_words, ch, freed, acc, errw);
+            if (op[r] == OP_INSERT) ok = st_insert(s, dst[r], w[r], rule, pool, P, ch, freed, acc);
+            else ok = st_delete(s, dst[r], rule, pool, P, ch, freed, acc, errw);
             if (!ok) stop = p;
             __threadfence_block();
         }
@@ -641,7 +658,7 @@ __global__ void __launch_bounds__(TB) k_st_apply(const uint32_t* __restrict__ er
     if (lane == 0) freed += ch.end - ch.cur;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) freed += __shfl_xor(freed, o);
-    if (lane == 0 && freed) atomicAdd(ctl + 1, (unsigned long long)freed);
+    if (lane == 0 && freed) atomicAdd(P.ctl + 1, (unsigned long long)freed);
     __syncthreads();
     if (threadIdx.x < ST_CTRS) {
         unsigned long long v = 0;
@@ -660,8 +677,8 @@ __global__ void __launch_bounds__(STB) k_st_apply_big(const uint32_t* __restrict
                                                       const uint32_t* __restrict__ seg_start,
                                                       const uint32_t* __restrict__ op, const uint32_t* __restrict__ dst,
                                                       const uint32_t* __restrict__ w, uint32_t* __restrict__ hdr,
-                                                      uint32_t* __restrict__ pool, unsigned long long* ctl,
-                                                      uint64_t pool_words, GroupRule rule, uint32_t* __restrict__ errw,
+                                                      uint32_t* __restrict__ pool, StPool P, GroupRule rule,
+                                                 uint32_t* __restrict__ errw,
                                                       unsigned long long* __restrict__ out,
                                                       uint32_t* __restrict__ left, uint32_t* __restrict__ sdirty,
                                                       const uint32_t* __restrict__ big,
@@ -714,9 +731,9 @@ __global__ void __launch_bounds__(STB) k_st_apply_big(const uint32_t* __restrict
                         best = w_best[x] < best ? w_best[x] : best;
                         hits += w_hits[x];
                     }
-                    ok = st_delete_at(s, v, best, hits, rule, pool, ctl, pool_words, ch, freed, acc, errw);
+                    ok = st_delete_at(s, v, best, hits, rule, pool, P, ch, freed, acc, errw);
                 } else {
-                    ok = st_insert(s, v, w[r], rule, pool, ctl, pool_words, ch, freed, acc);
+                    ok = st_insert(s, v, w[r], rule, pool, P, ch, freed, acc);
                 }
                 __threadfence_block();
                 if (lane == 0) { s_d = s.d; s_cap = s.cap; s_adj = s.adj; s_ok = ok ? 1u : 0u; }
@@ -733,7 +750,7 @@ __global__ void __launch_bounds__(STB) k_st_apply_big(const uint32_t* __restrict
         if (lane == 0) freed += ch.end - ch.cur;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) freed += __shfl_xor(freed, o);
-        if (lane == 0 && freed) atomicAdd(ctl + 1, (unsigned long long)freed);
+        if (lane == 0 && freed) atomicAdd(P.ctl + 1, (unsigned long long)freed);
     }
     __syncthreads();
     if (threadIdx.x < ST_CTRS && acc[threadIdx.x]) atomicAdd(out + threadIdx.x, acc[threadIdx.x]);
@@ -780,7 +797,7 @@ void add_stats(bingo_update_stats* a, const bingo_update_stats& b) {
 // library-sized pool) as long as each pass applies some of the records, at most this often.
 constexpr uint32_t STREAM_RETRIES = 8;
 int apply_stream(bingo_graph* g, uint64_t m, const uint32_t* op, const uint32_t* src, const uint32_t* dst,
-                 const uint32_t* w, bingo_update_stats* h_stats, uint32_t retries, hipStream_t st);
+                 const uint32_t* w, bingo_update_stats* h_stats, uint32_t retries, bool exact, hipStream_t st);
 }  // namespace
 
 int update_stream(bingo_graph* g, uint64_t m, const uint32_t* op, const uint32_t* src, const uint32_t* dst,
@@ -788,7 +805,7 @@ int update_stream(bingo_graph* g, uint64_t m, const uint32_t* op, const uint32_t
     bingo_update_stats sum{};
     // records applied here move edges without the edge locator: the next batch rebuilds it
     locator_invalidate(g);
-    const int rc = apply_stream(g, m, op, src, dst, w, &sum, STREAM_RETRIES, st);
+    const int rc = apply_stream(g, m, op, src, dst, w, &sum, STREAM_RETRIES, false, st);
     if (h_stats) *h_stats = sum;
     // every record of a stream that returns OK was applied exactly once: inserted, deleted or
     // counted as an absent delete
@@ -802,7 +819,7 @@ int update_stream(bingo_graph* g, uint64_t m, const uint32_t* op, const uint32_t
 
 namespace {
 int apply_stream(bingo_graph* g, uint64_t m, const uint32_t* op, const uint32_t* src, const uint32_t* dst,
-                 const uint32_t* w, bingo_update_stats* h_stats, uint32_t retries, hipStream_t st) {
+                 const uint32_t* w, bingo_update_stats* h_stats, uint32_t retries, bool exact, hipStream_t st) {
     if (m == 0) return BINGO_OK;
     if (m > (1ull << 31)) return BINGO_E_INVALID;
     auto al = [](uint64_t x) { return (x + 255) & ~255ull; };
@@ -839,13 +856,18 @@ int apply_stream(bingo_graph* g, uint64_t m, const uint32_t* op, const uint32_t*
     scan_u32_to_u64(head, hx, m, tmp, nseg, st);
     hipLaunchKernelGGL(k_st_starts, dim3(grid_for(m)), dim3(TB), 0, st, head, hx, m, sk, seg, seg_src);
     phase_mark(g, st, false);
-    hipLaunchKernelGGL(k_st_apply, dim3(ST_GRID), dim3(TB), 0, st, (const uint32_t*)g->d_err,
-                       (const unsigned long long*)nseg, m, sk, sv, seg, op, dst, w, g->hdr, g->pool, g->d_ctl,
-                       g->pool_words, g->rule, g->d_err, out, left, sdirty, big, nbig);
-    hipLaunchKernelGGL(k_st_apply_big, dim3(ST_BIG_GRID), dim3(STB), 0, st, (const uint32_t*)g->d_err,
-                       (const unsigned long long*)nseg, m, sk, sv, seg, op, dst, w, g->hdr, g->pool, g->d_ctl,
-                       g->pool_words, g->rule, g->d_err, out, left, sdirty, (const uint32_t*)big,
-                       (const unsigned long long*)nbig);
+    // as many waves as there can be sources; those that allocate at once set the line of the pool
+    const uint32_t grid = (uint32_t)std::min<uint64_t>((m + TB / 64 - 1) / (TB / 64), ST_GRID);
+    const uint32_t big_grid = (uint32_t)std::min<uint64_t>(m, ST_BIG_GRID);
+    const uint64_t margin = std::max<uint64_t>((uint64_t)grid * (TB / 64), big_grid) * ST_CHUNK;
+    if (g->pool_words <= 2 * margin) exact = true;
+    const StPool P{g->d_ctl, g->pool_words, exact ? 0ull : g->pool_words - margin};
+    hipLaunchKernelGGL(k_st_apply, dim3(grid), dim3(TB), 0, st, (const uint32_t*)g->d_err,
+                       (const unsigned long long*)nseg, m, sk, sv, seg, op, dst, w, g->hdr, g->pool, P, g->rule,
+                       g->d_err, out, left, sdirty, big, nbig);
+    hipLaunchKernelGGL(k_st_apply_big, dim3(big_grid), dim3(STB), 0, st, (const uint32_t*)g->d_err,
+                       (const unsigned long long*)nseg, m, sk, sv, seg, op, dst, w, g->hdr, g->pool, P, g->rule,
+                       g->d_err, out, left, sdirty, (const uint32_t*)big, (const unsigned long long*)nbig);
     // S(u) and the sparse indexes of the sources whose records touched a vertex with sparse groups
     sparse_rebuild(g, seg_src, nseg, m, sdirty, srwork, st);
     // alias-table mode: the sources' inter-group tables (with bad records nothing changed: rewritten as they were)
@@ -871,8 +893,9 @@ int apply_stream(bingo_graph* g, uint64_t m, const uint32_t* op, const uint32_t*
         add_stats(h_stats, part);
         if (!h_stats->touched_vertices) h_stats->touched_vertices = ns;  // the first pass saw every source
     }
-    if (err != ERR_OOM || !retries) return err ? err_to_code(err) : BINGO_OK;
-    // Out of pool: the records each stopped source did not apply are flagged.  Reclaim the
+    if (err != ERR_OOM || (exact && !retries)) return err ? err_to_code(err) : BINGO_OK;
+    // Out of pool: the records each stopped source did not apply are flagged.  First they are tried
+    // with every reservation by compare-and-swap, up to the pool's end; then reclaim the
     // replaced blocks, or grow a pool the library sized, and apply those records, in their
     // order, once more (records of different sources are independent, so this equals the
     // stream applied in one pass).
@@ -893,9 +916,14 @@ int apply_stream(bingo_graph* g, uint64_t m, const uint32_t* op, const uint32_t*
     const uint64_t bigger = std::min<uint64_t>(g->pool_words * 2, 1ull << 35);
     const bool grow = g->pool_auto && bigger > g->pool_words;
     int rc = BINGO_E_OOM;
-    if (ctl[1] > 0 || grow) rc = compact_pool(g, grow ? bigger : 0, st);
-    if (rc == BINGO_OK) rc = apply_stream(g, k, rest, rest + k, rest + 2 * k, rest + 3 * k, h_stats, retries - 1, st);
-    else rc = BINGO_E_OOM;
+    if (!exact) {
+        rc = apply_stream(g, k, rest, rest + k, rest + 2 * k, rest + 3 * k, h_stats, retries, true, st);
+    } else {
+        if (ctl[1] > 0 || grow) rc = compact_pool(g, grow ? bigger : 0, st);
+        if (rc == BINGO_OK)
+            rc = apply_stream(g, k, rest, rest + k, rest + 2 * k, rest + 3 * k, h_stats, retries - 1, false, st);
+        else rc = BINGO_E_OOM;
+    }
     HIPCHK(hipFreeAsync(rest, st));
     HIPCHK(hipStreamSynchronize(st));
     return rc;

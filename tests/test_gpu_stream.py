@@ -257,3 +257,39 @@ def test_stream_hub_above_block_threshold():
     og.update_stream(ops[:applied], s[:applied], d[:applied], ww[:applied])
     assert_same_structure(og, gg, "prefix of %d hub inserts" % applied)
     gg.close()
+
+
+@pytest.mark.parametrize("spare_kib", [0, 64, 700, 5000])
+def test_streams_up_to_the_pool_end(spare_kib):
+    """A pool with `spare_kib` KiB more than the build needs: records that find no room below the line
+    of the chunk reservations are applied up to the pool's exact end before anything is refused, and
+    what is refused is refused whatever the reservation form."""
+    from paper_2504_10233_amd import BingoError, Graph
+    rng = random.Random(spare_kib)
+    n = 3000
+    src = torch.tensor([rng.randrange(n) for _ in range(20000)])
+    dst = torch.tensor([rng.randrange(n) for _ in range(20000)])
+    w = torch.tensor([rng.randrange(1, 1 << 20) for _ in range(20000)])
+    probe = Graph(n, src, dst, w)
+    used = probe.memory()["pool_used_bytes"]
+    probe.close()
+    op = torch.tensor([0] * 4000 + [1] * 1000)
+    s = torch.tensor([rng.randrange(n) for _ in range(5000)])
+    d = torch.cat([torch.tensor([rng.randrange(n) for _ in range(4000)]), dst[:1000]])
+    s[4000:] = src[:1000]
+    x = torch.tensor([rng.randrange(1, 1 << 20) for _ in range(5000)])
+    free = Graph(n, src, dst, w)
+    want = free.update_stream(op, s, d, x)
+    need = free.memory()["pool_used_bytes"] - free.memory()["pool_garbage_bytes"]
+    g = Graph(n, src, dst, w, pool_bytes=used + 4096 + spare_kib * 1024)
+    try:
+        got = g.update_stream(op, s, d, x)
+    except BingoError as e:
+        # out of pool only where the live blocks themselves do not fit after compaction
+        assert e.code == -4 and spare_kib < 5000
+    else:
+        assert all(got[k] == want[k] for k in ("inserted", "deleted", "not_found"))
+        assert np.array_equal(g.export(), free.export())
+        assert used + 4096 + spare_kib * 1024 >= need
+    g.close()
+    free.close()
