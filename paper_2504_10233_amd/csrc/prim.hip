@@ -21,6 +21,10 @@ constexpr int SORT_SUBTILES = 4;
 constexpr uint64_t SORT_TILE = (uint64_t)SORT_BLOCK * SORT_SUBTILES;
 constexpr int RADIX = 256;
 
+// up to so many tiles a pass takes two launches: each tile of the scatter adds up the other
+// tiles' digit counts itself (see sort_pass)
+constexpr uint64_t FUSE_TILES = 256;
+
 inline uint64_t cdiv(uint64_t a, uint64_t b) { return (a + b - 1) / b; }
 inline uint64_t align256(uint64_t x) { return (x + 255) & ~255ull; }
 
@@ -126,9 +130,11 @@ __device__ __forceinline__ uint32_t digit_of(K k, int sh) {
 template <typename K>
 __global__ void __launch_bounds__(SORT_BLOCK) k_digit_hist(const K* __restrict__ keys, uint64_t n,
                                                            const unsigned long long* __restrict__ dn, int sh,
-                                                           uint32_t* __restrict__ hist, uint32_t nblocks) {
+                                                           uint32_t* __restrict__ hist, uint32_t nblocks,
+                                                           int by_tile) {
     __shared__ uint32_t h[RADIX];
     if (dn) n = std::min<uint64_t>(n, *dn);
+    if (by_tile && (uint64_t)blockIdx.x * SORT_TILE >= n) return;
     if (threadIdx.x < RADIX) h[threadIdx.x] = 0;
     __syncthreads();
     const uint64_t base = (uint64_t)blockIdx.x * SORT_TILE;
@@ -142,7 +148,9 @@ __global__ void __launch_bounds__(SORT_BLOCK) k_digit_hist(const K* __restrict__
     for (int i = 0; i < SORT_SUBTILES; ++i)
         if (base + (uint64_t)i * SORT_BLOCK + threadIdx.x < n) atomicAdd(&h[digit_of(k[i], sh)], 1u);
     __syncthreads();
-    if (threadIdx.x < RADIX) hist[(uint64_t)threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
+    if (threadIdx.x < RADIX)
+        hist[by_tile ? (uint64_t)blockIdx.x * RADIX + threadIdx.x : (uint64_t)threadIdx.x * nblocks + blockIdx.x] =
+            h[threadIdx.x];
 }
 
 // V: the value type; vhi: the first pass of 64-bit values given as two arrays of halves (low, high)
@@ -152,16 +160,61 @@ __global__ void __launch_bounds__(SORT_BLOCK) k_digit_scatter(const K* __restric
                                                               K* __restrict__ kout, V* __restrict__ vout,
                                                               uint64_t n, const unsigned long long* __restrict__ dn,
                                                               int sh, const uint64_t* __restrict__ offs,
-                                                              uint32_t nblocks) {
+                                                              const uint32_t* __restrict__ hist, uint32_t nblocks) {
     __shared__ uint64_t run[RADIX];
+    __shared__ uint32_t part[SORT_BLOCK / RADIX][RADIX], pall[SORT_BLOCK / RADIX][RADIX], dsum[RADIX / 64];
     __shared__ uint32_t tot[RADIX];
     if (dn) n = std::min<uint64_t>(n, *dn);
+    if ((uint64_t)blockIdx.x * SORT_TILE >= n) return;
     __shared__ uint32_t wc[SORT_WAVES][RADIX];
     const int tid = threadIdx.x, wave = tid >> 6;
     if (tid < RADIX) {
-        run[tid] = offs[(uint64_t)tid * nblocks + blockIdx.x];
+        if (!hist) run[tid] = offs[(uint64_t)tid * nblocks + blockIdx.x];
 #pragma unroll
         for (int w = 0; w < SORT_WAVES; ++w) wc[w][tid] = 0;
+    }
+    if (hist) {
+        // this tile's first place per digit from all tiles' counts (tile-major): four threads per
+        // digit, a quarter of the tiles each
+        constexpr int Q = SORT_BLOCK / RADIX;
+        const uint32_t dg = tid & (RADIX - 1), q = tid / RADIX;
+        const uint32_t used = (uint32_t)((n + SORT_TILE - 1) / SORT_TILE);  // <= nblocks
+        uint32_t before = 0, all = 0;
+        for (uint32_t b0 = q; b0 < used; b0 += 8 * Q) {
+            uint32_t c[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) c[j] = b0 + j * Q < used ? hist[(uint64_t)(b0 + j * Q) * RADIX + dg] : 0u;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                all += c[j];
+                if (b0 + j * Q < blockIdx.x) before += c[j];
+            }
+        }
+        part[q][dg] = before;
+        pall[q][dg] = all;
+        __syncthreads();
+        uint32_t x = 0, mine = 0;
+        if (tid < RADIX) {
+            before = 0;
+#pragma unroll
+            for (int j = 0; j < Q; ++j) {
+                before += part[j][tid];
+                mine += pall[j][tid];
+            }
+            x = mine;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t y = __shfl_up(x, o, 64);
+                if ((tid & 63) >= o) x += y;
+            }
+            if ((tid & 63) == 63) dsum[tid >> 6] = x;
+        }
+        __syncthreads();
+        if (tid < RADIX) {
+            uint32_t lower = 0;
+            for (int w = 0; w < (tid >> 6); ++w) lower += dsum[w];
+            run[tid] = (uint64_t)lower + x - mine + before;
+        }
     }
     const uint64_t base = (uint64_t)blockIdx.x * SORT_TILE;
     const uint64_t below = lanemask_lt();
@@ -272,6 +325,25 @@ __global__ void __launch_bounds__(BSORT_BLOCK) k_block_sort(const K* __restrict_
     }
 }
 
+// One pass: the tiles' digit counts, their places, the scatter.  The places of up to FUSE_TILES
+// tiles are added up by the scatter's own blocks from the counts (256 KB at most, from L2); that
+// takes the place of the scan's two launches, of 4 to 7 us each: batches that sort a few
+// tiles gain 5 % (10^4 records on hub vertices), a step of 10^5 records and its walks 8 %.
+// The reading grows with the square of the tiles; with the line at 512 or 1024 tiles a batch of
+// 10^6 records gains 1 to 2 %, all of it from sorts of mostly empty capacity, so the line stays
+// where a full sort reads 64 MB in all.
+template <typename K, bool HAS_V, typename V>
+void sort_pass(const K* ck, const V* cv, const uint32_t* vhi, K* nk, V* nv, uint64_t n, const unsigned long long* dn,
+               int sh, uint32_t* hist, uint64_t* offs, void* scratch, hipStream_t st) {
+    const uint64_t nb = cdiv(n, SORT_TILE);
+    const bool fuse = nb <= FUSE_TILES;
+    hipLaunchKernelGGL((k_digit_hist<K>), dim3((uint32_t)nb), dim3(SORT_BLOCK), 0, st, ck, n, dn, sh, hist,
+                       (uint32_t)nb, fuse ? 1 : 0);
+    if (!fuse) scan_impl<uint32_t>(hist, offs, nb * RADIX, scratch, nullptr, st);
+    hipLaunchKernelGGL((k_digit_scatter<K, HAS_V, V>), dim3((uint32_t)nb), dim3(SORT_BLOCK), 0, st, ck, cv, vhi, nk, nv,
+                       n, dn, sh, (const uint64_t*)offs, fuse ? (const uint32_t*)hist : nullptr, (uint32_t)nb);
+}
+
 // Stable LSD sort of the first min(n, *dn) entries (all n when dn is null);
 // grids are sized by n, so a device-side count keeps the launch sequence fixed.
 template <typename K, bool HAS_V>
@@ -306,11 +378,7 @@ void sort_impl(const K* kin, const uint32_t* vin, K* kout, uint32_t* vout, uint6
         K* nk = to_out ? kout : ktmp;
         uint32_t* nv = to_out ? vout : vtmp;
         const int sh = 8 * p;
-        hipLaunchKernelGGL((k_digit_hist<K>), dim3((uint32_t)nb), dim3(SORT_BLOCK), 0, st, ck, n, dn, sh, hist,
-                           (uint32_t)nb);
-        scan_impl<uint32_t>(hist, offs, nb * RADIX, scratch, nullptr, st);
-        hipLaunchKernelGGL((k_digit_scatter<K, HAS_V>), dim3((uint32_t)nb), dim3(SORT_BLOCK), 0, st, ck, cv,
-                           (const uint32_t*)nullptr, nk, nv, n, dn, sh, (const uint64_t*)offs, (uint32_t)nb);
+        sort_pass<K, HAS_V, uint32_t>(ck, cv, nullptr, nk, nv, n, dn, sh, hist, offs, scratch, st);
         ck = nk;
         cv = nv;
     }
@@ -344,12 +412,8 @@ void sort_records_u32(const uint32_t* keys, const uint32_t* lo, const uint32_t* 
         const bool to_out = ((passes - 1 - p) % 2) == 0;
         uint32_t* nk = to_out ? keys_out : ktmp;
         uint64_t* nv = to_out ? vals_out : vtmp;
-        hipLaunchKernelGGL((k_digit_hist<uint32_t>), dim3((uint32_t)nb), dim3(SORT_BLOCK), 0, st, ck, n,
-                           (const unsigned long long*)nullptr, 8 * p, hist, (uint32_t)nb);
-        scan_impl<uint32_t>(hist, offs, nb * RADIX, scratch, nullptr, st);
-        hipLaunchKernelGGL((k_digit_scatter<uint32_t, true, uint64_t>), dim3((uint32_t)nb), dim3(SORT_BLOCK), 0, st, ck,
-                           cv, p == 0 ? hi : nullptr, nk, nv, n, (const unsigned long long*)nullptr, 8 * p,
-                           (const uint64_t*)offs, (uint32_t)nb);
+        sort_pass<uint32_t, true, uint64_t>(ck, cv, p == 0 ? hi : nullptr, nk, nv, n, nullptr, 8 * p, hist, offs,
+                                            scratch, st);
         ck = nk;
         cv = nv;
     }

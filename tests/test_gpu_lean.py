@@ -114,3 +114,17 @@ def test_build_around_the_hub_threshold(degree, frac):
     assert np.array_equal(g.export(), og.dump())
     assert np.array_equal(g.export_index(), og.index_dump())
     g.close()
+
+
+@pytest.mark.parametrize("m", [4095, 4097, 256 * 4096 - 1, 256 * 4096, 256 * 4096 + 1])
+def test_build_around_the_fused_sort_passes(m):
+    """The records' sort around one tile and around the largest sort whose scatter adds up the counts itself."""
+    import oracle as O
+    from paper_2504_10233_amd import Graph
+    n = 70000
+    src, dst = synth.below(1, 1, m, n), synth.below(1, 2, m, n)
+    w = synth.weights_uniform(m, 1, 1 << 16, 3)
+    g = Graph(n, src, dst, w)
+    og = O.Graph(n, src.numpy(), dst.numpy(), w.numpy())
+    assert np.array_equal(g.export(), og.dump())
+    g.close()
