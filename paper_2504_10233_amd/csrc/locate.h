@@ -81,35 +81,6 @@ __device__ __forceinline__ uint64_t loc_find(const LocView& L, uint64_t k, uint3
     return found;
 }
 
-// Put (k, p) in the first free slot of its probe sequence.  Returns 0 when the
-// table has no free slot (never with the load the host keeps), 1 after taking
-// a TOMB, 2 after taking an EMPTY slot.
-__device__ __forceinline__ uint32_t loc_claim(const LocView& L, uint64_t k, uint32_t p) {
-    const uint64_t h0 = loc_hash(k) & L.mask;
-    uint64_t line = h0 & ~7ull;
-    uint32_t first = (uint32_t)(h0 & 7);
-    for (uint64_t s = 0; s <= L.mask; s += 8) {
-        uint64_t v[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = L.tab[2 * (line + j)];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            if ((uint32_t)j < first) continue;
-            const uint64_t cur = v[j];
-            if (cur != LOC_EMPTY && cur != LOC_TOMB) continue;
-            unsigned long long* kp = (unsigned long long*)(L.tab + 2 * (line + j));
-            if (atomicCAS(kp, (unsigned long long)cur, (unsigned long long)k) == cur) {
-                L.tab[2 * (line + j) + 1] = p;
-                return cur == LOC_EMPTY ? 2u : 1u;
-            }
-            // another claim took it first; a taken slot stays taken for the rest of the kernel
-        }
-        line = (line + 8) & L.mask;
-        first = 0;
-    }
-    return 0u;
-}
-
 // ---------------------------------------------------------------------------
 // Wave-cooperative probing.  Many copies of one edge make a run of slots of one
 // key, which a lane walking alone would cross one line per memory round trip.
@@ -171,9 +142,9 @@ __device__ __forceinline__ void loc_wave_find(const LocView& L, bool want, uint6
     }
 }
 
-// The first line of k's sequence for a claim of (k, p): 0 when the sequence goes on
-// past the line without a free slot taken (*next: the following line), else 1 or 2
-// as loc_claim returns.
+// A claim puts (k, p) in the first free slot of its probe sequence.  The first line of
+// the sequence: 0 when it goes on past the line without a free slot taken (*next: the
+// following line), 1 after taking a TOMB, 2 after taking an EMPTY slot.
 __device__ __forceinline__ uint32_t loc_claim_line(const LocView& L, uint64_t k, uint32_t p, uint64_t* next) {
     const uint64_t h0 = loc_hash(k) & L.mask;
     const uint64_t line = h0 & ~7ull;
@@ -196,7 +167,7 @@ __device__ __forceinline__ uint32_t loc_claim_line(const LocView& L, uint64_t k,
 }
 
 // Claims, for every lane with want set, the first free slot from *next on (*res: 0 when
-// none, else as loc_claim).
+// none, which the load the host keeps rules out; else as loc_claim_line).
 __device__ __forceinline__ void loc_wave_claim(const LocView& L, bool want, uint64_t k, uint32_t p, uint64_t next,
                                                uint32_t* res) {
     const uint32_t lane = lane_id();

@@ -128,3 +128,19 @@ def test_build_around_the_fused_sort_passes(m):
     og = O.Graph(n, src.numpy(), dst.numpy(), w.numpy())
     assert np.array_equal(g.export(), og.dump())
     g.close()
+
+
+@pytest.mark.parametrize("degrees", [(1023, 1024, 1025), (2048, 2049, 40001), (1, 63, 64), (5000,) * 64])
+@pytest.mark.parametrize("spread", [1, 3, 1 << 20])
+def test_locator_build_around_its_chunks(degrees, spread):
+    """Vertices at the edges of the chunks that building the locator splits hubs into, with many copies of an edge."""
+    import torch
+    from paper_2504_10233_amd import Graph
+    n = 70000
+    src = torch.cat([torch.full((d,), 60 + i) for i, d in enumerate(degrees)] + [synth.below(1, 1, 5000, n)])
+    dst = synth.below(1, 2, src.numel(), min(n, spread))
+    g = Graph(n, src, dst, synth.weights_uniform(src.numel(), 1, 1 << 12, 5))
+    st = g.update(src[:3], dst[:3], torch.tensor([1, 2, 3]), src[1:70], dst[1:70])
+    assert st["deleted"] == 69 and st["inserted"] == 3
+    assert g.check_locator() == (0, src.numel() + 3 - 69)
+    g.close()
