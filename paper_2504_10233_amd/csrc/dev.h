@@ -202,15 +202,11 @@ __host__ __device__ inline bool type_listed(uint32_t t) { return t == GT_SPARSE 
 // blocks (build, batched and streaming updates, compaction) uses these sizes.
 __host__ __device__ inline uint32_t adj_cap_for(uint32_t d) {
     if (d == 0) return 0;
-    uint32_t c = 2;
-    while (c < d) c <<= 1;
-    return c;
+    return d <= 2 ? 2u : 1u << (32 - __builtin_clz(d - 1));
 }
 __host__ __device__ inline uint64_t adj_block_words(uint32_t cap) { return ((uint64_t)cap * 3 + 7) & ~7ull; }
 __host__ __device__ inline uint32_t list_cap_for(uint32_t c) {
-    uint32_t x = 8;
-    while (x < c) x <<= 1;
-    return x;
+    return c <= 8 ? 8u : 1u << (32 - __builtin_clz(c - 1));
 }
 // index capacity of a listed group of type t: the adjacency capacity (regular)
 // or the S(u) capacity (sparse)

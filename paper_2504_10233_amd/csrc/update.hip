@@ -839,12 +839,15 @@ __global__ void __launch_bounds__(TB) k_loc_claim(unsigned long long* __restrict
 // ---------------------------------------------------------------------------
 // per-vertex state shared by the analysis and mutation kernels
 // ---------------------------------------------------------------------------
+// A value that every lane of the wave holds alike, in a scalar register.
+__device__ __forceinline__ uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+
 struct VState {
-    uint32_t u, d, cap, nseq, mask;
+    uint32_t u, d, cap, nseq;
     uint64_t adj;
     uint32_t ts, ni, nd, N, xoff;
     uint32_t d1, dn;
-    uint64_t W;  // fixed-point biases: sum of the weights after the batch (unused for integer biases)
+    uint64_t W;  // sum of the weights after the batch
     // group indexes: adjacency capacity after the batch; S(u) block, capacity before and after
     // (the new capacity covers an upper bound on |S(u)| after the batch); sparse masks before
     // and after
@@ -864,73 +867,101 @@ __device__ __forceinline__ uint32_t vweight(uint32_t x, const VState& s, const u
     return wv[s.ts + (x - s.d)];
 }
 
-__device__ void load_state(VState& s, uint32_t t, const uint32_t* __restrict__ tv, const uint32_t* __restrict__ ts,
-                           const uint32_t* __restrict__ tdl, const uint32_t* __restrict__ te,
-                           const uint32_t* __restrict__ ncnt, const uint64_t* __restrict__ xoff,
-                           const uint32_t* __restrict__ xs, const uint32_t* __restrict__ hdr,
-                           const uint32_t* __restrict__ pool, const uint32_t* __restrict__ wv, GroupRule rule) {
+// Word i of an array that the kernel does not write, i alike in the whole wave: a scalar load.
+template <typename T>
+__device__ __forceinline__ T uni_at(const T* a, uint64_t i) {
+    return ((const __attribute__((address_space(4))) T*)(uintptr_t)a)[i];
+}
+
+// A touched vertex's words in the batch's arrays.
+struct VRow {
+    uint32_t u, ts, tdl, te, N, xoff;
+};
+__device__ __forceinline__ VRow load_row(uint64_t t, const uint32_t* tv, const uint32_t* ts, const uint32_t* tdl,
+                                         const uint32_t* te, const uint32_t* ncnt, const uint64_t* xoff) {
+    return VRow{uni_at(tv, t), uni_at(ts, t), uni_at(tdl, t), uni_at(te, t), uni_at(ncnt, t),
+                (uint32_t)uni_at(xoff, t)};
+}
+
+// Header of the row's vertex.
+__device__ __forceinline__ void load_header(VState& s, const VRow& w, const uint32_t* __restrict__ hdr, GroupRule rule) {
     const uint32_t lane = lane_id();
-    s.u = tv[t];
+    s.u = w.u;
     const HdrCRef h = hdr_ref(hdr, s.u);
-    s.d = h[H_DEG]; s.cap = h[H_ACAP]; s.nseq = h[H_NSEQ]; s.mask = h[H_MASK];
-    s.adj = hdr_adj(h);
-    s.ts = ts[t]; s.ni = tdl[t] - ts[t]; s.nd = te[t] - tdl[t];
-    s.N = ncnt[t]; s.xoff = (uint32_t)xoff[t];
-    s.d1 = s.d + s.ni; s.dn = s.d1 - s.N;
-    s.c = lane < 32 ? slot_count(hdr_slot(h, lane, hdr_hi(h)), h[H_ONEMASK], lane) : 0u;
+    s.ts = w.ts; s.ni = w.tdl - w.ts; s.nd = w.te - w.tdl;
+    s.N = w.N; s.xoff = w.xoff;
+    const uint32_t d = h[H_DEG], cap = h[H_ACAP], nseq = h[H_NSEQ], sblk = h[H_SBLK], scap = h[H_SCAP];
+    const uint64_t adj = hdr_adj(h);
+    const uint32_t whi = h[H_WHI], wlo = h[H_WLO];
     s.info = lane < 32 ? h[H_INFO + lane] : 0u;
     s.lcap = lane < 32 ? (1u << ((h[H_LCAPLOG + (lane >> 2)] >> (8 * (lane & 3))) & 0xFFu)) : 0u;
+    s.c = lane < 32 ? slot_count(hdr_slot(h, lane, hdr_hi(h)), h[H_ONEMASK], lane) : 0u;
+    s.d = uni(d); s.cap = uni(cap); s.nseq = uni(nseq); s.sblk = uni(sblk); s.scap = uni(scap);
+    s.adj = (uint64_t)uni((uint32_t)(adj >> 32)) << 32 | uni((uint32_t)adj);
+    s.W = (uint64_t)uni(whi) << 32 | uni(wlo);
+    s.d1 = s.d + s.ni; s.dn = s.d1 - s.N;
     s.told = lane < 32 ? group_type(s.c, s.d, rule) : GT_EMPTY;
-    // group-membership counts of the inserts and of the deleted entries; for
-    // fixed-point biases also their weight sums (the decimal group's total is
-    // not a count times a power of two)
+}
+
+// Adds the members of the wave's words w (of the first n lanes, 0 in the others) to cnt, lane k < 32
+// those of group k, and the words to sum (alike in every lane).  A batch brings most vertices a word
+// or two: word by word, four instructions each, up to COUNT_ONE words, else a ballot per group.
+constexpr uint32_t COUNT_ONE = 32;
+__device__ __forceinline__ void count_bits(uint32_t w, uint32_t n, uint32_t fbits, uint32_t& cnt, uint64_t& sum) {
+    const uint32_t lane = lane_id(), m = member_word(w, fbits);
+    if (n <= COUNT_ONE) {
+        uint32_t c = 0;
+        for (uint32_t i = 0; i < n; ++i) {
+            sum += lane_get(w, i);
+            c += (lane_get(m, i) >> (lane & 31u)) & 1u;
+        }
+        if (lane < 32) cnt += c;
+    } else {
+#pragma unroll
+        for (int k = 0; k < 32; ++k) {
+            const uint64_t b = __ballot((m >> k) & 1u);
+            if (lane == (uint32_t)k) cnt += __popcll(b);
+        }
+        uint64_t x = w;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+        sum += lane_get64(x, 0);
+    }
+}
+
+// What the batch does to the vertex's groups.
+__device__ __forceinline__ void load_changes(VState& s, const uint32_t* __restrict__ xs,
+                                             const uint32_t* __restrict__ pool, const uint32_t* __restrict__ wv,
+                                             GroupRule rule) {
+    const uint32_t lane = lane_id();
+    // group-membership counts (lane k < 32) and weight sums of the inserts and the deleted entries
     uint32_t app = 0, del = 0;
     uint64_t wadd = 0, wsub = 0;
     for (uint32_t a0 = 0; a0 < s.ni; a0 += 64) {
         const uint32_t a = a0 + lane;
-        const uint32_t wr = a < s.ni ? wv[s.ts + a] : 0u;
-        wadd += wr;
-        const uint32_t w = member_word(wr, rule.fbits);
-#pragma unroll
-        for (int k = 0; k < 32; ++k) {
-            const uint64_t b = __ballot((w >> k) & 1u);
-            if (lane == (uint32_t)k) app += __popcll(b);
-        }
+        count_bits(a < s.ni ? wv[s.ts + a] : 0u, s.ni - a0, rule.fbits, app, wadd);
     }
     const uint32_t* X = xs + s.xoff;
     for (uint32_t j0 = 0; j0 < s.N; j0 += 64) {
         const uint32_t j = j0 + lane;
-        const uint32_t wr = j < s.N ? vweight(X[j], s, pool, wv) : 0u;
-        wsub += wr;
-        const uint32_t w = member_word(wr, rule.fbits);
-#pragma unroll
-        for (int k = 0; k < 32; ++k) {
-            const uint64_t b = __ballot((w >> k) & 1u);
-            if (lane == (uint32_t)k) del += __popcll(b);
-        }
+        count_bits(j < s.N ? vweight(X[j], s, pool, wv) : 0u, s.N - j0, rule.fbits, del, wsub);
     }
-    s.W = 0;
-    if (rule.fbits) {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            wadd += __shfl_xor(wadd, o);
-            wsub += __shfl_xor(wsub, o);
-        }
-        s.W = ((((uint64_t)h[H_WHI]) << 32) | h[H_WLO]) + wadd - wsub;
-    }
+    s.W = s.W + wadd - wsub;
     s.app = app; s.del = del;
     s.cn = s.c + app - del;
     s.tnew = lane < 32 ? group_type(s.cn, s.dn, rule) : GT_EMPTY;
     s.ncap = s.dn > s.cap ? adj_cap_for(s.dn) : s.cap;
-    s.sblk = h[H_SBLK];
-    s.scap = h[H_SCAP];
     s.smo = (uint32_t)(__ballot(s.told == GT_SPARSE) & 0xFFFFFFFFull);
     s.smn = (uint32_t)(__ballot(s.tnew == GT_SPARSE) & 0xFFFFFFFFull);
     // |S(u)| after the batch is at most min(d', sum of the new sparse counts)
-    uint64_t sub = s.tnew == GT_SPARSE ? s.cn : 0u;
+    uint64_t sub = 0;
+    if (s.smn) {
+        sub = s.tnew == GT_SPARSE ? s.cn : 0u;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) sub += __shfl_xor(sub, o);
-    sub = sub < s.dn ? sub : s.dn;
+        for (int o = 32; o > 0; o >>= 1) sub += __shfl_xor(sub, o);
+        sub = sub < s.dn ? sub : s.dn;
+        sub = uni((uint32_t)sub);
+    }
     s.scapn = s.smn ? (sub > s.scap ? s_cap_for((uint32_t)sub) : s.scap) : 0u;
 }
 
@@ -973,7 +1004,11 @@ __device__ __forceinline__ uint64_t wave_sum(uint64_t v) {
 // 2 not found, 3.. the 25 type transitions); k_stats_reduce sums the blocks.
 // No global atomics: a per-vertex atomic on a handful of addresses would
 // serialize in L2 across ~10^6 touched vertices.
-// Eight waves per SIMD fit without spilling (the default allocation allowed seven).
+// The kernel was bound by vector instructions (284 M for the 10^6 records of a batch on R-MAT 24, the
+// whole of its 475 us): ballots for each of 32 groups and 25 transitions, 64-bit sums through the LDS
+// crossbar.  What is alike in the wave is held in scalar registers and read through the scalar cache,
+// groups are counted word by word (count_bits), transitions in an LDS table, and sums are formed only
+// where a lane has something to add: 96 M instructions, 280 us.
 __global__ void __launch_bounds__(WB) __attribute__((amdgpu_waves_per_eu(8, 8))) k_analyze(const unsigned long long* __restrict__ uc, const uint32_t* __restrict__ tv,
                                                 const uint32_t* __restrict__ ts,
                                                 const uint32_t* __restrict__ tdl, const uint32_t* __restrict__ te,
@@ -982,33 +1017,45 @@ __global__ void __launch_bounds__(WB) __attribute__((amdgpu_waves_per_eu(8, 8)))
                                                 const uint32_t* __restrict__ pool, const uint32_t* __restrict__ wv,
                                                 GroupRule rule, uint64_t* __restrict__ need,
                                                 unsigned long long* __restrict__ partials) {
-    __shared__ unsigned long long red[WB / 64][32];
-    const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
+    __shared__ unsigned long long red[WB / 64][3];
+    __shared__ uint32_t trans[25][32];  // type transitions, a column per lane
+    for (uint32_t i = threadIdx.x; i < 25 * 32; i += WB) trans[i >> 5][i & 31] = 0;
+    __syncthreads();
+    const uint32_t lane = lane_id(), wave = uni(threadIdx.x >> 6);
     const uint64_t T = uc[UC_T];
-    uint64_t acc = 0;  // lane i < 28 accumulates counter i
-    for (uint64_t t = (uint64_t)blockIdx.x * (WB / 64) + wave; t < T; t += (uint64_t)gridDim.x * (WB / 64)) {
+    uint64_t ins = 0, del = 0, missed = 0;
+    const uint64_t step = (uint64_t)gridDim.x * (WB / 64);
+    uint64_t t = (uint64_t)blockIdx.x * (WB / 64) + wave;
+    VRow next{};
+    if (t < T) next = load_row(t, tv, ts, tdl, te, ncnt, xoff);
+    for (; t < T; t += step) {
+        const VRow row = next;
+        next = load_row(t + step < T ? t + step : t, tv, ts, tdl, te, ncnt, xoff);
         VState s;
-        load_state(s, (uint32_t)t, tv, ts, tdl, te, ncnt, xoff, xs, hdr, pool, wv, rule);
+        load_header(s, row, hdr, rule);
+        load_changes(s, xs, pool, wv, rule);
         uint64_t w = lane_list_need(s);
-        if (lane == 0 && s.dn > s.cap) w += adj_block_words(adj_cap_for(s.dn));
-        w = wave_sum(w);
+        w = __ballot(w != 0) ? wave_sum(w) : 0ull;
+        if (s.dn > s.cap) w += adj_block_words(adj_cap_for(s.dn));
         // type transitions over all 32 groups of the vertex
-        const uint32_t code = lane < 32 ? s.told * 5 + s.tnew : 31u;
-#pragma unroll
-        for (int c = 0; c < 25; ++c) {
-            const uint32_t k = __popcll(__ballot(code == (uint32_t)c));
-            if (lane == (uint32_t)(3 + c)) acc += k;
-        }
-        if (lane == 0) { need[t] = w; acc += s.ni; }
-        if (lane == 1) acc += s.N;
-        if (lane == 2) acc += s.nd - s.N;
+        if (lane < 32) atomicAdd(&trans[s.told * 5 + s.tnew][lane], 1u);
+        if (lane == 0) need[t] = w;
+        ins += s.ni;
+        del += s.N;
+        missed += s.nd - s.N;
     }
-    if (lane < 32) red[wave][lane] = acc;
+    if (lane == 0) {
+        red[wave][0] = ins;
+        red[wave][1] = del;
+        red[wave][2] = missed;
+    }
     __syncthreads();
     if (threadIdx.x < 32) {
         unsigned long long v = 0;
-#pragma unroll
-        for (int w = 0; w < WB / 64; ++w) v += red[w][threadIdx.x];
+        if (threadIdx.x < 3)
+            for (int w = 0; w < WB / 64; ++w) v += red[w][threadIdx.x];
+        else if (threadIdx.x < 28)
+            for (uint32_t j = 0; j < 32; ++j) v += trans[threadIdx.x - 3][(j + threadIdx.x) & 31];
         partials[(uint64_t)blockIdx.x * 32 + threadIdx.x] = v;
     }
 }
@@ -1062,8 +1109,48 @@ struct XView {
     const uint32_t* X;
     const uint32_t* L;  // nullptr: no LDS samples
     uint32_t N, nl, sh;
+    // N <= XV_OWN and no samples: the entries themselves (NF past them), in scalar registers; a
+    // search compares with all of them
+    uint32_t own[8];
 };
+constexpr uint32_t XV_OWN = 8;
+__device__ __forceinline__ bool xv_small(const XView& x) { return !x.L && x.N <= XV_OWN; }
+// a sorted set of N entries without samples, alike in the whole wave
+__device__ __forceinline__ XView xv_of(const uint32_t* X, uint32_t N) {
+    XView x{X, nullptr, N, 0u, 0u, {NF, NF, NF, NF, NF, NF, NF, NF}};
+    if (N && N <= XV_OWN) {
+#pragma unroll
+        for (uint32_t j = 0; j < XV_OWN; ++j) {
+            const uint32_t e = uni_at(X, j < N ? j : 0u);
+            x.own[j] = j < N ? e : NF;
+        }
+    }
+    return x;
+}
+// entries below v (NF is never one of them); *in: v is in the set
+__device__ __forceinline__ uint32_t xv_own_lb(const XView& x, uint32_t v, bool* in) {
+    uint32_t lo = 0;
+    bool eq = false;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        lo += x.own[j] < v ? 1u : 0u;
+        eq |= x.own[j] == v;
+    }
+    if (x.N > 4) {
+#pragma unroll
+        for (int j = 4; j < 8; ++j) {
+            lo += x.own[j] < v ? 1u : 0u;
+            eq |= x.own[j] == v;
+        }
+    }
+    *in = eq;
+    return lo;
+}
 __device__ __forceinline__ uint32_t xv_lb(const XView& x, uint32_t v) {
+    if (xv_small(x)) {
+        bool in;
+        return xv_own_lb(x, v, &in);
+    }
     if (!x.L) return lower_bound_u32(x.X, x.N, v);
     uint32_t lo = 0, hi = x.nl;  // samples below v
     while (lo < hi) {
@@ -1087,6 +1174,12 @@ __device__ __forceinline__ bool xv_in(const XView& x, uint32_t v) {
 }
 // in_set and rho with one search: NF for a deleted v, else its new index
 __device__ __forceinline__ uint32_t xv_rho(const XView& x, uint32_t v, uint32_t dn, uint32_t nholes) {
+    if (xv_small(x)) {
+        bool in;
+        const uint32_t lo = xv_own_lb(x, v, &in);
+        if (in) return NF;
+        return v < dn ? v : x.X[(v - dn) - (lo - nholes)];
+    }
     const uint32_t p = xv_lb(x, v);
     if (p < x.N && xv_at(x, p) == v) return NF;
     if (v < dn) return v;
@@ -1177,14 +1270,14 @@ struct MutArgs {
 };
 
 template <bool SPLIT>
-__device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, uint64_t abase0, const XView& xv, const BigCtx& bc,
+__device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, const VRow& row, uint64_t abase0, const XView& xv, const BigCtx& bc,
                                unsigned long long* uc, uint32_t split);
 
 // The large-vertex instance (SPLIT) runs one wave per block with the deleted
 // set's samples in dynamic LDS; the other runs WB-thread blocks, one vertex per
 // wave at a time.
 constexpr uint32_t XL_WORDS = 8192;  // LDS samples per large vertex (32 KiB)
-constexpr int MUT_WAVES = 5;  // waves per SIMD the small-vertex instance is compiled for
+constexpr int MUT_WAVES = 8;  // waves per SIMD the small-vertex instance is compiled for
 
 template <bool SPLIT>
 __device__ __forceinline__ void mutate_blocks(unsigned long long* __restrict__ uc, const uint32_t* __restrict__ err,
@@ -1199,30 +1292,35 @@ __device__ __forceinline__ void mutate_blocks(unsigned long long* __restrict__ u
     const uint32_t lane = lane_id();
     uint64_t freed_total = 0;  // lane 0 of each wave
     if constexpr (!SPLIT) {
-        for (uint64_t t = (uint64_t)blockIdx.x * (WB / 64) + (threadIdx.x >> 6); t < T;
-             t += (uint64_t)gridDim.x * (WB / 64)) {
+        const uint64_t step = (uint64_t)gridDim.x * (WB / 64);
+        uint64_t t = (uint64_t)blockIdx.x * (WB / 64) + uni(threadIdx.x >> 6);
+        VRow next{};
+        if (t < T) next = load_row(t, A.tv, A.ts, A.tdl, A.te, A.ncnt, A.xoff);
+        for (; t < T; t += step) {
+            const VRow row = next;
+            next = load_row(t + step < T ? t + step : t, A.tv, A.ts, A.tdl, A.te, A.ncnt, A.xoff);
             // vertices with more than `split` entries after the inserts belong to the other instance
             // (the degree from before the batch: headers are rewritten as vertices finish)
-            if (split && dold[t] + (A.tdl[t] - A.ts[t]) > split) continue;
-            const uint32_t N = A.ncnt[t];
-            const XView xv{A.xs + A.xoff[t], nullptr, N, 0u, 0u};
-            freed_total += mutate_one<false>(t, A, abase0, xv, bc, uc, split);
+            if (split && uni_at(dold, t) + (row.tdl - row.ts) > split) continue;
+            const XView xv = xv_of(A.xs + row.xoff, row.N);
+            freed_total += mutate_one<false>(t, A, row, abase0, xv, bc, uc, split);
         }
     } else {
         // one block (one wave) per listed large vertex
         const uint64_t nb = skip ? 0 : uc[UC_NBIG];
         for (uint64_t i = blockIdx.x; i < nb; i += gridDim.x) {
             const uint64_t t = blist[i];
-            const uint32_t N = A.ncnt[t];
-            const uint32_t* X = A.xs + A.xoff[t];
+            const VRow row = load_row(t, A.tv, A.ts, A.tdl, A.te, A.ncnt, A.xoff);
+            const uint32_t N = row.N;
+            const uint32_t* X = A.xs + row.xoff;
             uint32_t sh = 0;
             while ((N >> sh) >= XL_WORDS) ++sh;
             const uint32_t nl = (N + (1u << sh) - 1) >> sh;
             __syncthreads();  // the previous vertex is done with xl
             for (uint32_t j = lane; j < nl; j += 64) xl[j] = X[(uint64_t)j << sh];
             __syncthreads();
-            const XView xv{X, xl, N, nl, sh};
-            freed_total += mutate_one<true>(t, A, abase0, xv, bc, uc, split);
+            const XView xv{X, xl, N, nl, sh, {}};
+            freed_total += mutate_one<true>(t, A, row, abase0, xv, bc, uc, split);
         }
     }
     if (lane == 0) red[threadIdx.x >> 6] = freed_total;
@@ -1235,9 +1333,12 @@ __device__ __forceinline__ void mutate_blocks(unsigned long long* __restrict__ u
     }
 }
 
-// The vertices up to `split` entries: a wave's work on one vertex is a chain of dependent loads, so
-// the kernel is held to a register budget that keeps five waves per SIMD resident (4 without it;
-// 6 and 8 spill enough registers to be slower).
+// The vertices up to `split` entries.  A wave's work on one vertex is a chain of dependent loads with a
+// few hundred vector instructions between them.  With the wave's common values in scalar registers it
+// fits eight waves per SIMD (five before, in 96 registers), the searches of the deleted set need no
+// loads up to XV_OWN entries, and lists that only gain members are not walked: 10^6 records on R-MAT 24
+// 1160 -> 690 us, 419 -> 256 M vector instructions.  (Loading the next vertex's lines and the lists'
+// ends ahead took 810 us: it is bound by lines at random, not by waiting for them one by one.)
 __global__ void __launch_bounds__(WB) __attribute__((amdgpu_waves_per_eu(MUT_WAVES, MUT_WAVES)))
 k_mutate(unsigned long long* __restrict__ uc, const uint32_t* __restrict__ err, MutArgs A,
          unsigned long long* __restrict__ partials, const uint32_t* __restrict__ dold,
@@ -1271,20 +1372,21 @@ __device__ __forceinline__ uint64_t final_word_xv(uint32_t i, const uint64_t* __
 // SPLIT instance handles the vertices with more than `split` entries and may
 // hand its long passes to k_big_apply; the other one handles the rest.
 template <bool SPLIT>
-__device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, uint64_t abase0, const XView& xv, const BigCtx& bc,
+__device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, const VRow& row, uint64_t abase0, const XView& xv, const BigCtx& bc,
                                unsigned long long* uc, uint32_t split) {
     const uint32_t* __restrict__ wv = A.wv;
     const uint32_t* __restrict__ idest = A.idest;
     uint32_t* __restrict__ pool = A.pool;
     const uint32_t fb = A.rule.fbits;
     VState s;
-    load_state(s, (uint32_t)t, A.tv, A.ts, A.tdl, A.te, A.ncnt, A.xoff, A.xs, A.hdr, pool, wv, A.rule);
     const uint32_t lane = lane_id();
+    load_header(s, row, A.hdr, A.rule);
+    load_changes(s, A.xs, pool, wv, A.rule);
     const uint32_t N = s.N;
-    const uint32_t nholes = xv_lb(xv, s.dn);  // deleted entries below the new degree
+    const uint32_t nholes = uni(xv_lb(xv, s.dn));  // deleted entries below the new degree
     const uint32_t* W = wv + s.ts;            // insert weights
     const uint32_t* D = idest + s.ts;         // insert final indices (NF: deleted)
-    uint64_t abase = abase0 + A.aoff[t];
+    uint64_t abase = abase0 + uni_at(A.aoff, t);
     uint64_t freed = 0;
 
     // ---- adjacency
@@ -1356,23 +1458,24 @@ __device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, uint64_t abase0, co
     const uint64_t lneed = lane <= 32 ? lane_list_need(s) : 0ull;
     const uint32_t nlc = lane < 32 && type_listed(s.tnew) ? new_lcap(s) : 0u;
     uint64_t lx = lneed;
+    if (__ballot(lneed != 0)) {
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint64_t y = __shfl_up(lx, o, 64);
-        if (lane >= (uint32_t)o) lx += y;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint64_t y = __shfl_up(lx, o, 64);
+            if (lane >= (uint32_t)o) lx += y;
+        }
     }
     const uint64_t my_block = abase + (lx - lneed);
-    abase += __shfl(lx, 63, 64);
     uint32_t* S = A.sur + s.xoff;
     while (km) {
         const int k = __ffs(km) - 1;
         km &= km - 1;
-        const uint32_t ck = __shfl(s.c, k, 64), cnk = __shfl(s.cn, k, 64), appk = __shfl(s.app, k, 64);
-        const uint32_t lcapk = __shfl(s.lcap, k, 64);
-        const uint64_t oblk = (uint64_t)__shfl(s.info, k, 64) * LIST_UNIT_WORDS;
-        const uint64_t nblk = __shfl(lneed, k, 64) ? __shfl(my_block, k, 64) : oblk;
+        const uint32_t ck = lane_get(s.c, k), cnk = lane_get(s.cn, k), appk = lane_get(s.app, k);
+        const uint32_t lcapk = lane_get(s.lcap, k);
+        const uint64_t oblk = (uint64_t)lane_get(s.info, k) * LIST_UNIT_WORDS;
+        const uint64_t nblk = lane_get64(lneed, k) ? lane_get64(my_block, k) : oblk;
         // a regular group's inverted index follows its list in the block: entry i = position of i
-        const uint32_t iofs = ((s.smn >> k) & 1u) ? 0u : __shfl(nlc, k, 64);
+        const uint32_t iofs = ((s.smn >> k) & 1u) ? 0u : lane_get(nlc, k);
         const uint32_t lenv = ck + appk;
         const uint32_t* Lold = pool + oblk;
         uint32_t* Lnew = pool + nblk;
@@ -1388,7 +1491,7 @@ __device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, uint64_t abase0, co
         }
         // new-member part: inserts with bit k, position ck + rank
         uint32_t rank = 0;
-        for (uint32_t a0 = 0; a0 < s.ni; a0 += 64) {
+        for (uint32_t a0 = 0; a0 < s.ni && rank < appk; a0 += 64) {
             const uint32_t a = a0 + lane;
             const bool v = a < s.ni && ((member_word(W[a], fb) >> k) & 1u);
             const uint64_t b = __ballot(v);
@@ -1404,13 +1507,14 @@ __device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, uint64_t abase0, co
         __threadfence_block();
         // pass A: final entries [0, cnk): kept entries renamed, holes take S[] in rank order
         uint32_t nh = 0;
-        const uint32_t oldpart = ck < cnk ? ck : cnk;
+        // without deletes no old entry is renamed or leaves: only a list that moves is copied
+        const uint32_t oldpart = N || nblk != oblk ? (ck < cnk ? ck : cnk) : 0u;
         uint32_t it, cb, cs;
         bool defer = false;
         if (SPLIT && oldpart > split) {
             // holes among the first cnk virtual positions = deleted members of the group less the
             // deleted entries of the tail window; those among the new members are counted here
-            const uint32_t delk = __shfl(s.del, k, 64);
+            const uint32_t delk = lane_get(s.del, k);
             uint32_t hnew = 0;
             if (cnk > ck) {
                 uint32_t r2 = 0;
@@ -1430,14 +1534,14 @@ __device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, uint64_t abase0, co
             const uint32_t words = nsur + (listed ? nha : 0u);
             unsigned long long soff = 0;
             if (lane == 0) soff = atomicAdd(uc + UC_BIG_SUR, (unsigned long long)words);
-            soff = __shfl(soff, 0, 64);
+            soff = lane_get64(soff, 0);
             // A regular group whose block stays finds its holes and renamed entries through its
             // inverted index (Sec. 4.2): O(deleted + moved entries) instead of a pass over the list.
             const bool by_index = iofs != 0 && nblk == oblk && listed;
             if (by_index) {
                 unsigned long long it64 = 0;
                 if (lane == 0) it64 = atomicAdd(uc + UC_BIG_ITEMS, 1ull);
-                it64 = __shfl(it64, 0, 64);
+                it64 = lane_get64(it64, 0);
                 defer = soff + words <= bc.smax && it64 < bc.imax;
                 if (!defer && it64 < bc.imax && lane == 0) bc.items[it64].kind = 0;  // a slot k_big_holes skips
                 if (defer) {
@@ -1546,7 +1650,7 @@ __device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, uint64_t abase0, co
     if (fresh) { newinfo = (uint32_t)(my_block / LIST_UNIT_WORDS); newlcap = nlc; }
     if (lane < 32 && type_listed(s.told) && !kept_listed(s)) freed += old_block_words(s);
     // S(u): a new block (its old one is freed), or none when no group is sparse any more
-    const uint64_t nsblk = __shfl(lneed, 32, 64) ? __shfl(my_block, 32, 64) : (uint64_t)s.sblk * LIST_UNIT_WORDS;
+    const uint64_t nsblk = lane_get64(lneed, 32) ? lane_get64(my_block, 32) : (uint64_t)s.sblk * LIST_UNIT_WORDS;
     if (lane == 32 && s.scap && s.scapn != s.scap) freed += s.scap;
     const uint32_t fm = (uint32_t)(__ballot(fresh) & 0xFFFFFFFFull);
     // one-element groups: the surviving member
@@ -1559,13 +1663,14 @@ __device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, uint64_t abase0, co
             const uint32_t a = a0 + lane;
             const uint32_t dest = a < s.ni ? D[a] : NF;
             const uint32_t w = dest != NF ? member_word(W[a], fb) : 0u;
-#pragma unroll
-            for (int k = 0; k < 32; ++k) {
+            uint32_t mm = (uint32_t)(__ballot(one && member == NF) & 0xFFFFFFFFull);
+            while (mm) {
+                const int k = __ffs(mm) - 1;
+                mm &= mm - 1;
                 const uint64_t b = __ballot((w >> k) & 1u);
                 if (b) {
-                    const int src = __ffsll((long long)b) - 1;
-                    const uint32_t cand = __shfl(dest, src, 64);
-                    if (lane == (uint32_t)k && one && member == NF) member = cand;
+                    const uint32_t cand = lane_get(dest, __ffsll((long long)b) - 1);
+                    if (lane == (uint32_t)k) member = cand;
                 }
             }
         }
@@ -1579,9 +1684,9 @@ __device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, uint64_t abase0, co
             const int k = __ffs(mm) - 1;
             mm &= mm - 1;
             uint32_t it, cb, cs;
-            const uint64_t blk = (uint64_t)__shfl(newinfo, k, 64) * LIST_UNIT_WORDS;
+            const uint64_t blk = (uint64_t)lane_get(newinfo, k) * LIST_UNIT_WORDS;
             // a fresh regular list's inverted index follows the list (read in every lane)
-            const uint32_t iofs = ((fm >> k) & 1u) && ((s.smn >> k) & 1u) == 0u ? __shfl(nlc, k, 64) : 0u;
+            const uint32_t iofs = ((fm >> k) & 1u) && ((s.smn >> k) & 1u) == 0u ? lane_get(nlc, k) : 0u;
             if (big_reserve(bc, uc, s.dn, it, cb, cs)) {
                 if (lane == 0) {
                     BigItem& bi = bc.items[it];
@@ -1611,9 +1716,9 @@ __device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, uint64_t abase0, co
                 const bool bit = (w >> k) & 1u;
                 const uint64_t b = __ballot(bit);
                 if ((fm_seq >> k) & 1u) {
-                    const uint64_t blk = (uint64_t)__shfl(newinfo, k, 64) * LIST_UNIT_WORDS;
-                    const uint32_t f = __shfl(fill, k, 64);
-                    const uint32_t iofs = ((s.smn >> k) & 1u) ? 0u : __shfl(nlc, k, 64);
+                    const uint64_t blk = (uint64_t)lane_get(newinfo, k) * LIST_UNIT_WORDS;
+                    const uint32_t f = lane_get(fill, k);
+                    const uint32_t iofs = ((s.smn >> k) & 1u) ? 0u : lane_get(nlc, k);
                     if (bit) {
                         const uint32_t pos = f + __popcll(b & lanemask_lt());
                         pool[blk + pos] = i;
@@ -1631,7 +1736,7 @@ __device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, uint64_t abase0, co
     // ---- header: the inter-group sampling space of the vertex
     const HdrRef h = hdr_ref(A.hdr, s.u);
     const bool ne = lane < 32 && s.cn > 0;
-    const uint64_t wsum = fb ? s.W : wave_sum(ne ? ((uint64_t)s.cn << lane) : 0ull);
+    const uint64_t wsum = s.W;
     const uint32_t nmask = (uint32_t)(__ballot(ne) & 0xFFFFFFFFull);
     // one-element groups keep their member's destination in the count slot (a member
     // left to k_big_pass gets it from k_big_one_dst)
@@ -1653,7 +1758,7 @@ __device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, uint64_t abase0, co
     packed |= __shfl_xor(packed, 1);
     packed |= __shfl_xor(packed, 2);
     if (lane < 32 && (lane & 3) == 0) h[H_LCAPLOG + (lane >> 2)] = packed;
-    freed = wave_sum(freed);
+    if (__ballot(freed != 0)) freed = wave_sum(freed);
     if (lane == 0) {
         h[H_MASK] = nmask;
         h[H_ONEMASK] = onemask;
@@ -1689,7 +1794,7 @@ __device__ __forceinline__ XView big_stage_x(const BigItem& bi, const uint32_t* 
     while ((bi.N >> sh) >= BIG_XL) ++sh;
     const uint32_t nl = (bi.N + (1u << sh) - 1) >> sh;
     for (uint32_t j = threadIdx.x; j < nl; j += blockDim.x) xl[j] = X[(uint64_t)j << sh];
-    return XView{X, xl, bi.N, nl, sh};
+    return XView{X, xl, bi.N, nl, sh, {}};
 }
 
 // Entry p of an item in two steps, so a tile's loads are all in flight before
@@ -1879,7 +1984,7 @@ __global__ void __launch_bounds__(256) k_big_pass(const unsigned long long* __re
         for (uint32_t j = lane; j < nl; j += 64) xl[j] = X[(uint64_t)j << sh];
         __threadfence_block();
         __builtin_amdgcn_wave_barrier();
-        const XView xv{X, xl, N, nl, sh};
+        const XView xv{X, xl, N, nl, sh, {}};
         const uint32_t p0 = (uint32_t)(g - bi.cbase) * bi.csize;
         const uint32_t p1 = std::min(p0 + bi.csize, bi.n);
         if (kind == BK_COPY) {

@@ -144,3 +144,30 @@ def test_locator_build_around_its_chunks(degrees, spread):
     assert st["deleted"] == 69 and st["inserted"] == 3
     assert g.check_locator() == (0, src.numel() + 3 - 69)
     g.close()
+
+
+@pytest.mark.parametrize("k", [3, 4, 5, 8, 9, 31, 32, 33, 64, 65])
+@pytest.mark.parametrize("frac", [0, 8])
+def test_batches_around_the_small_set_sizes(k, frac):
+    """k inserts and k deletes on one vertex (low and high in its adjacency), on others one of the two."""
+    import oracle as O
+    import torch
+    from paper_2504_10233_amd import Graph
+    n, d, hot = 1200, 150, 12
+    src = torch.arange(hot).repeat_interleave(d)
+    dst = torch.arange(hot * d) % d  # no copies: a record names its edge
+    w = synth.weights_zipf(hot * d, 1.2, (1 << 30) - 1, 5)
+    g = Graph(n, src, dst, w, frac_bits=frac)
+    og = O.Graph(n, src.numpy(), dst.numpy(), w.numpy(), frac_bits=frac)
+    new = torch.arange(k) + 1000
+    at = [torch.arange(k), d - 1 - torch.arange(k), (torch.arange(k) * 37) % d]
+    ins = torch.cat([torch.full((k,), u) for u in (0, 1, 2, 3)])
+    iw = synth.weights_zipf(4 * k, 1.2, (1 << 30) - 1, 6)
+    dels = torch.cat([torch.full((k,), u) for u in (0, 1, 2, 4)])
+    dd = torch.cat(at + [at[1]])
+    for _ in range(2):
+        g.update(ins, new.repeat(4), iw, dels, dd)
+        og.update(ins.numpy(), new.repeat(4).numpy(), iw.numpy(), dels.numpy(), dd.numpy())
+        assert np.array_equal(g.export(), og.dump())
+        assert np.array_equal(g.export_index(), og.index_dump())
+    g.close()
