@@ -53,18 +53,37 @@ int bits_for(uint64_t v) {
 //   [48..79] freed pool words (entry 48)
 //   [80..84] edge locator: slots probed to match deletes, slots turned TOMB, claims,
 //            claims of EMPTY slots, lookups that found no slot (a locator out of step)
+//   [85] the error word at the end of the run
 // Every kernel reads its element counts from here, so the whole pipeline runs
 // without host round trips and can be captured in a hipGraph; grids and
 // buffers are sized by the batch-size bucket Rmax.
 enum { UC_NI = 0, UC_ND = 1, UC_T = 2, UC_F = 3, UC_C = 4, UC_X = 5, UC_ALLOC = 6, UC_BASE = 7, UC_FLAGS = 8,
        UC_R = 9, UC_BIG_ITEMS = 10, UC_BIG_CHUNKS = 11, UC_BIG_SUR = 12, UC_NBIG = 13,
        UC_STATS = 16, UC_FREED = 48, UC_LPROBE = 80, UC_LKILL = 81, UC_LCLAIM = 82, UC_LFRESH = 83, UC_LBAD = 84,
-       UC_WORDS = 96 };
+       UC_ERR = 85, UC_WORDS = 96 };
 
-__global__ void k_upd_begin(unsigned long long* __restrict__ uc, uint64_t ni, uint64_t nd, uint32_t* __restrict__ err) {
-    const uint32_t i = threadIdx.x;
-    if (i < UC_WORDS) uc[i] = i == UC_NI ? ni : (i == UC_ND ? nd : (i == UC_R ? ni + nd : 0ull));
-    if (i == 0) *err = 0;
+// The batch's control block, and its records in the plan's own arrays (one launch in place of five
+// copies, of some 4 us each).
+__global__ void k_upd_begin(unsigned long long* __restrict__ uc, uint64_t ni, uint64_t nd, uint32_t* __restrict__ err,
+                            const uint32_t* __restrict__ is, const uint32_t* __restrict__ id,
+                            const uint32_t* __restrict__ iw, const uint32_t* __restrict__ ds,
+                            const uint32_t* __restrict__ dd, uint32_t* __restrict__ pis, uint32_t* __restrict__ pid,
+                            uint32_t* __restrict__ piw, uint32_t* __restrict__ pds, uint32_t* __restrict__ pdd) {
+    GRID_LOOP(r, ni + nd) {
+        if (r < ni) {
+            pis[r] = is[r];
+            pid[r] = id[r];
+            piw[r] = iw[r];
+        } else {
+            pds[r - ni] = ds[r - ni];
+            pdd[r - ni] = dd[r - ni];
+        }
+    }
+    if (blockIdx.x == 0) {
+        const uint32_t i = threadIdx.x;
+        if (i < UC_WORDS) uc[i] = i == UC_NI ? ni : (i == UC_ND ? nd : (i == UC_R ? ni + nd : 0ull));
+        if (i == 0) *err = 0;
+    }
 }
 
 __global__ void k_fill_u32(uint32_t* __restrict__ a, uint64_t n, uint32_t v) {
@@ -2113,7 +2132,13 @@ __global__ void __launch_bounds__(256) k_big_one_dst(const unsigned long long* _
     }
 }
 
-__global__ void k_add_u64(unsigned long long* dst, const unsigned long long* src) { *dst += *src; }
+// The freed words enter the pool's garbage count, the error word the control block (so the host reads
+// one block).
+__global__ void k_upd_end(unsigned long long* __restrict__ garbage, unsigned long long* __restrict__ uc,
+                          const uint32_t* __restrict__ err) {
+    *garbage += uc[UC_FREED];
+    uc[UC_ERR] = *err;
+}
 
 // Reserve the batch's pool words with one bump, unless the batch is already
 // rejected (bad input or candidate overflow); no space sets ERR_OOM.
@@ -2126,6 +2151,262 @@ __global__ void k_alloc_check(unsigned long long* __restrict__ ctl, uint64_t poo
     } else {
         uc[UC_BASE] = used;
         ctl[0] = used + total;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Batches of up to SMALL_R records.  Their kernels have next to nothing to do, so the batch's time is
+// the number of its launches, at 4 to 5 us each; the steps between the searches run as three blocks of
+// one thread per record, with what the steps hand on in LDS.  They leave every array and count as the
+// kernels above do.  100 records on R-MAT 18: 295 -> 214 us with the staging in one launch and one
+// block read back.
+// ---------------------------------------------------------------------------
+constexpr uint32_t SMALL_R = 1024;   // records, and threads of the block
+constexpr uint32_t SMALL_C = 4096;   // candidates
+struct SmallArgs {
+    unsigned long long* uc;
+    uint32_t* err;
+    uint32_t n, split, ins_only;
+    int vb;
+    uint64_t cap, xpad;
+    const uint32_t *is, *id, *iw, *ds, *dd, *hdr;
+    uint64_t *sk, *foff, *vadj, *needw, *aoff, *xks, *xoff, *ckey;
+    uint32_t *sv, *rec_t, *tv, *tsa, *tdl, *te, *dold, *vacap, *vnseq, *blist, *matched, *ncnt, *cval, *xs, *wv, *idest,
+        *sdirty;
+};
+
+// Sums of the lower threads' v; *total: of all.  sh: a word per wave.
+__device__ __forceinline__ uint64_t block_excl(uint64_t v, uint64_t* sh, uint64_t* total) {
+    const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
+    uint64_t x = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint64_t y = __shfl_up(x, o, 64);
+        if (lane >= (uint32_t)o) x += y;
+    }
+    if (lane == 63) sh[wave] = x;
+    __syncthreads();
+    uint64_t before = 0, all = 0;
+    for (uint32_t w = 0; w < SMALL_R / 64; ++w) {
+        if (w < wave) before += sh[w];
+        all += sh[w];
+    }
+    __syncthreads();
+    *total = all;
+    return before + x - v;
+}
+
+// Sorts the first m entries of (key, idx), idx their places: the order of a stable sort.  Room for the
+// next power of two.
+__device__ __forceinline__ void block_sort(uint64_t* key, uint32_t* idx, uint32_t m) {
+    uint32_t P = 1;
+    while (P < m) P <<= 1;
+    for (uint32_t i = m + threadIdx.x; i < P; i += SMALL_R) {
+        key[i] = ~0ull;
+        idx[i] = ~0u;
+    }
+    __syncthreads();
+    for (uint32_t k = 2; k <= P; k <<= 1) {
+        for (uint32_t j = k >> 1; j > 0; j >>= 1) {
+            for (uint32_t q = threadIdx.x; q < (P >> 1); q += SMALL_R) {
+                const uint32_t a = 2 * (q & ~(j - 1)) + (q & (j - 1)), b = a + j;
+                const bool up = (a & k) == 0;
+                const uint64_t ka = key[a], kb = key[b];
+                const uint32_t ia = idx[a], ib = idx[b];
+                const bool gt = ka > kb || (ka == kb && ia > ib);
+                if (gt == up) {
+                    key[a] = kb; key[b] = ka;
+                    idx[a] = ib; idx[b] = ia;
+                }
+            }
+            __syncthreads();
+        }
+    }
+}
+
+// Validation, the sort by (src, op, dst), the touched vertices and the flat sizes.
+__global__ void __launch_bounds__(SMALL_R) k_small_front(SmallArgs A) {
+    __shared__ uint64_t key[SMALL_R], sums[SMALL_R / 64];
+    __shared__ uint32_t idx[SMALL_R], first[SMALL_R + 1], fdel[SMALL_R];
+    const uint32_t r = threadIdx.x;
+    const int vb = A.vb;
+    uint32_t ni = (uint32_t)A.uc[UC_NI], nd = (uint32_t)A.uc[UC_ND], bad = 0;
+    uint64_t k = ~0ull;
+    if (r < ni) {
+        const uint32_t u = A.is[r];
+        if (u >= A.n || A.id[r] >= A.n) bad |= ERR_RANGE;
+        if (A.iw[r] == 0) bad |= ERR_WEIGHT;
+        k = (uint64_t)u << (vb + 1);
+    } else if (r < ni + nd) {
+        const uint32_t u = A.ds[r - ni], d = A.dd[r - ni];
+        if (u >= A.n || d >= A.n) bad |= ERR_RANGE;
+        k = ((uint64_t)u << (vb + 1)) | (1ull << vb) | d;
+    }
+    if (bad) atomicOr(A.err, bad);
+    if (r < ni + nd) {
+        key[r] = k;
+        idx[r] = r;
+    }
+    fdel[r] = NF;
+    // a rejected batch runs on as an empty one
+    if (__syncthreads_or(bad != 0)) {
+        ni = nd = 0;
+        if (r == 0) A.uc[UC_NI] = A.uc[UC_ND] = A.uc[UC_R] = 0ull;
+    }
+    const uint32_t R = ni + nd;
+    block_sort(key, idx, R);
+    k = r < R ? key[r] : 0ull;
+    const uint64_t kp = r > 0 && r < R ? key[r - 1] : 0ull;
+    const bool head = r < R && (r == 0 || key_src(k, vb) != key_src(kp, vb));
+    uint64_t tot;
+    const uint32_t t = (uint32_t)block_excl(head ? 1u : 0u, sums, &tot) + (head ? 1u : 0u) - 1u;
+    const uint32_t T = (uint32_t)tot;
+    if (r < R) {
+        A.sk[r] = k;
+        A.sv[r] = idx[r];
+        A.rec_t[r] = t;
+        if (head) first[t] = r;
+        if (key_op(k, vb) && (head || !key_op(kp, vb))) fdel[t] = r;
+    }
+    if (r == 0) {
+        A.uc[UC_T] = T;
+        first[T] = R;
+    }
+    __syncthreads();
+    uint64_t v = 0;
+    if (r < T) {
+        const uint32_t s0 = first[r], end = first[r + 1], dl = fdel[r] == NF ? end : fdel[r];
+        const uint32_t u = key_src(key[s0], vb);
+        A.tv[r] = u;
+        A.tsa[r] = s0;
+        A.tdl[r] = dl;
+        A.te[r] = end;
+        const HdrCRef h = hdr_ref(A.hdr, u);
+        const uint32_t d = h[H_DEG];
+        A.dold[r] = d;
+        A.vacap[r] = h[H_ACAP];
+        A.vnseq[r] = h[H_NSEQ];
+        A.vadj[r] = hdr_adj(h);
+        v = end > dl ? (uint64_t)(A.ins_only ? 0u : d) + (dl - s0) : 0ull;
+        if (A.split && d + (dl - s0) > A.split) A.blist[atomicAdd(A.uc + UC_NBIG, 1ull)] = r;
+    }
+    A.foff[r] = block_excl(v, sums, &tot);
+    if (r == 0) A.uc[UC_F] = tot;
+    A.needw[r] = 0;
+    A.sdirty[r] = 0;
+}
+
+// The candidates sorted and assigned, the deleted sets sorted, the inserts placed.
+__global__ void __launch_bounds__(SMALL_R) k_small_assign(SmallArgs A) {
+    __shared__ uint64_t key[SMALL_C], sums[SMALL_R / 64];
+    __shared__ uint32_t idx[SMALL_C], first[SMALL_R], m[SMALL_R], cnt[SMALL_R];
+    const uint32_t r = threadIdx.x;
+    const uint32_t R = (uint32_t)(A.uc[UC_NI] + A.uc[UC_ND]);
+    const uint64_t found = A.uc[UC_C];
+    if (r == 0 && found > A.cap) A.uc[UC_FLAGS] |= 1ull;
+    const uint32_t C = (uint32_t)std::min<uint64_t>(found, A.cap);
+    for (uint32_t c = r; c < C; c += SMALL_R) {
+        key[c] = A.ckey[c];
+        idx[c] = c;
+    }
+    m[r] = NF;
+    cnt[r] = 0;
+    block_sort(key, idx, C);
+    for (uint32_t c = r; c < C; c += SMALL_R) {
+        const uint32_t run = (uint32_t)(key[c] >> 32);
+        if (c == 0 || (uint32_t)(key[c - 1] >> 32) != run) first[run] = c;
+    }
+    __syncthreads();
+    const uint32_t t = r < R ? A.rec_t[r] : 0u;
+    for (uint32_t c = r; c < C; c += SMALL_R) {
+        const uint32_t run = (uint32_t)(key[c] >> 32), rank = c - first[run];
+        // the rank-th oldest occurrence goes to the rank-th record of the run
+        if (run + rank < R && A.sk[run + rank] == A.sk[run]) {
+            m[run + rank] = A.cval[idx[c]];
+            atomicAdd(&cnt[A.rec_t[run]], 1u);
+        }
+    }
+    __syncthreads();
+    const uint64_t xk = r < R && m[r] != NF ? ((uint64_t)t << 32) | m[r] : A.xpad;
+    A.matched[r] = m[r];
+    if (r < R) {
+        key[r] = xk;
+        idx[r] = r;
+    }
+    block_sort(key, idx, R);
+    uint64_t tot;
+    const uint64_t xo = block_excl(cnt[r], sums, &tot);
+    A.ncnt[r] = cnt[r];
+    A.xoff[r] = xo;
+    if (r == 0) A.uc[UC_X] = tot;
+    first[r] = (uint32_t)xo;
+    const uint64_t x = r < R ? key[r] : A.xpad;
+    A.xks[r] = x;
+    A.xs[r] = (uint32_t)x;
+    idx[r] = (uint32_t)x;
+    __syncthreads();
+    if (r < R && r < A.tdl[t]) {  // an insert: as k_ins_prep
+        const uint32_t s0 = A.tsa[t], s1 = A.tdl[t], d = A.dold[t], N = cnt[t];
+        const uint32_t* X = idx + first[t];
+        const uint32_t e = d + (r - s0), dn = d + (s1 - s0) - N;
+        const uint32_t pe = lower_bound_u32(X, N, e);
+        uint32_t dest;
+        if (pe < N && X[pe] == e) dest = NF;
+        else if (e < dn) dest = e;
+        else dest = X[(e - dn) - (pe - lower_bound_u32(X, N, dn))];
+        A.wv[r] = A.iw[A.sv[r]];
+        A.idest[r] = dest;
+    }
+}
+
+// The analysis' counters summed and the blocks' places in the pool.
+__global__ void __launch_bounds__(SMALL_R) k_small_alloc(SmallArgs A, const unsigned long long* __restrict__ partials,
+                                                         uint32_t nblocks, unsigned long long* __restrict__ ctl,
+                                                         uint64_t pool_words) {
+    __shared__ unsigned long long red[SMALL_R / 32][33];
+    __shared__ uint64_t sums[SMALL_R / 64];
+    const uint32_t r = threadIdx.x, i = r & 31u, q = r >> 5;
+    unsigned long long v = 0;
+    for (uint32_t b = q; b < nblocks; b += SMALL_R / 32) v += partials[(uint64_t)b * 32 + i];
+    red[q][i] = v;
+    uint64_t tot;
+    A.aoff[r] = block_excl(A.needw[r], sums, &tot);
+    if (r < 32) {
+        v = 0;
+        for (uint32_t j = 0; j < SMALL_R / 32; ++j) v += red[j][r];
+        A.uc[UC_STATS + r] = v;
+    }
+    if (r == 0) {
+        A.uc[UC_ALLOC] = tot;
+        if (*A.err == 0 && A.uc[UC_FLAGS] == 0) {
+            const unsigned long long used = ctl[0];
+            if (used + tot > pool_words) {
+                atomicOr(A.err, ERR_OOM);
+            } else {
+                A.uc[UC_BASE] = used;
+                ctl[0] = used + tot;
+            }
+        }
+    }
+}
+
+// As k_stats_reduce over the freed words of both instances of the mutation, then as k_upd_end.
+__global__ void __launch_bounds__(256) k_small_end(unsigned long long* __restrict__ uc,
+                                                   const unsigned long long* __restrict__ partials, uint32_t nblocks,
+                                                   unsigned long long* __restrict__ garbage,
+                                                   const uint32_t* __restrict__ err) {
+    __shared__ unsigned long long red[4];
+    unsigned long long v = 0;
+    for (uint32_t b = threadIdx.x; b < nblocks; b += 256) v += partials[(uint64_t)b * 32];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    if (lane_id() == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const unsigned long long sum = red[0] + red[1] + red[2] + red[3];
+        uc[UC_FREED] = sum;
+        *garbage += sum;
+        uc[UC_ERR] = *err;
     }
 }
 
@@ -2262,25 +2543,37 @@ static void enqueue_update(bingo_graph* g, UpdPlan* p, hipStream_t st) {
     const uint32_t vgrid_m = (uint32_t)std::min<uint64_t>((R + 3) / 4, p->grid_mu);
     unsigned long long* uc = p->uc;
     uint32_t* err = g->d_err;
-    hipLaunchKernelGGL(k_upd_validate, dim3(grid_for(R)), dim3(TB), 0, st, g->n, (const unsigned long long*)uc, p->is,
-                       p->id, p->iw, p->ds, p->dd, err);
-    hipLaunchKernelGGL(k_upd_gate, dim3(1), dim3(1), 0, st, uc, (const uint32_t*)err);
-    // 1. records sorted by (src, op, dst); segments per touched vertex
-    hipLaunchKernelGGL(k_upd_keys, dim3(grid_for(R)), dim3(TB), 0, st, (const unsigned long long*)uc, R, p->is, p->ds,
-                       p->dd, vb, ~0ull, p->keys, p->vals);
-    sort_pairs_u64_dn(p->keys, p->vals, p->sk, p->sv, R, uc + UC_R, 2 * vb + 1, p->tmp, st);
-    hipLaunchKernelGGL(k_seg_heads, dim3(grid_for(R)), dim3(TB), 0, st, p->sk, (const unsigned long long*)uc, R, vb,
-                       p->head);
-    scan_u32_to_u64(p->head, p->hx, R, p->tmp, uc + UC_T, st);
-    hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(R)), dim3(TB), 0, st, p->tdl, R, NF);
-    hipLaunchKernelGGL(k_seg_fill, dim3(grid_for(R)), dim3(TB), 0, st, p->sk, (const unsigned long long*)uc, vb,
-                       p->head, p->hx, p->tv, p->tsa, p->tdl, p->rec_t);
-    hipLaunchKernelGGL(k_seg_end, dim3(grid_for(R)), dim3(TB), 0, st, (const unsigned long long*)uc, p->tsa, p->te,
-                       p->tdl);
-    hipLaunchKernelGGL(k_flat_size, dim3(grid_for(R)), dim3(TB), 0, st, uc, R, p->tv,
-                       p->tsa, p->tdl, p->te, g->hdr, p->fsz, p->dold, p->vacap, p->vnseq, p->vadj, g->update_split,
-                       p->blist, ins_only);
-    scan_u64(p->fsz, p->foff, R, p->tmp, uc + UC_F, st);
+    // one block a step where it can hold the batch (SMALL_R); larger plans, and a small one grown for
+    // more candidates than SMALL_C, take a kernel per step
+    const bool small = R == SMALL_R && C <= SMALL_C;
+    SmallArgs sa{};
+    if (small) {
+        sa = SmallArgs{uc, err, g->n, g->update_split, ins_only, vb, C, xpad, p->is, p->id, p->iw, p->ds, p->dd, g->hdr,
+                       p->sk, p->foff, p->vadj, p->needw, p->aoff, p->xks, p->xoff, p->ckey,
+                       p->sv, p->rec_t, p->tv, p->tsa, p->tdl, p->te, p->dold, p->vacap, p->vnseq, p->blist,
+                       p->matched, p->ncnt, p->cval, p->xs, p->wv, p->idest, p->sdirty};
+        hipLaunchKernelGGL(k_small_front, dim3(1), dim3(SMALL_R), 0, st, sa);
+    } else {
+        hipLaunchKernelGGL(k_upd_validate, dim3(grid_for(R)), dim3(TB), 0, st, g->n, (const unsigned long long*)uc, p->is,
+                           p->id, p->iw, p->ds, p->dd, err);
+        hipLaunchKernelGGL(k_upd_gate, dim3(1), dim3(1), 0, st, uc, (const uint32_t*)err);
+        // 1. records sorted by (src, op, dst); segments per touched vertex
+        hipLaunchKernelGGL(k_upd_keys, dim3(grid_for(R)), dim3(TB), 0, st, (const unsigned long long*)uc, R, p->is, p->ds,
+                           p->dd, vb, ~0ull, p->keys, p->vals);
+        sort_pairs_u64_dn(p->keys, p->vals, p->sk, p->sv, R, uc + UC_R, 2 * vb + 1, p->tmp, st);
+        hipLaunchKernelGGL(k_seg_heads, dim3(grid_for(R)), dim3(TB), 0, st, p->sk, (const unsigned long long*)uc, R, vb,
+                           p->head);
+        scan_u32_to_u64(p->head, p->hx, R, p->tmp, uc + UC_T, st);
+        hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(R)), dim3(TB), 0, st, p->tdl, R, NF);
+        hipLaunchKernelGGL(k_seg_fill, dim3(grid_for(R)), dim3(TB), 0, st, p->sk, (const unsigned long long*)uc, vb,
+                           p->head, p->hx, p->tv, p->tsa, p->tdl, p->rec_t);
+        hipLaunchKernelGGL(k_seg_end, dim3(grid_for(R)), dim3(TB), 0, st, (const unsigned long long*)uc, p->tsa, p->te,
+                           p->tdl);
+        hipLaunchKernelGGL(k_flat_size, dim3(grid_for(R)), dim3(TB), 0, st, uc, R, p->tv,
+                           p->tsa, p->tdl, p->te, g->hdr, p->fsz, p->dold, p->vacap, p->vnseq, p->vadj, g->update_split,
+                           p->blist, ins_only);
+        scan_u64(p->fsz, p->foff, R, p->tmp, uc + UC_F, st);
+    }
     // 2. delete matching: candidates, sorted by (run, seq); the k oldest per run
     hipLaunchKernelGGL(k_match, dim3(MATCH_GRID), dim3(TB), 0, st, uc, p->foff, p->tsa, p->tdl, p->te, p->dold,
                        p->vacap, p->vnseq, p->vadj, p->sk, p->sv, vb, p->id, g->pool, p->ckey, p->cval, C, ins_only);
@@ -2289,30 +2582,39 @@ static void enqueue_update(bingo_graph* g, UpdPlan* p, hipStream_t st) {
                            (const uint32_t*)p->rec_t, (const uint32_t*)p->tv, (const uint32_t*)p->tdl,
                            (const uint32_t*)p->dold, (const uint32_t*)p->vacap, (const uint64_t*)p->vadj,
                            (const uint32_t*)g->pool, lv, p->ckey, p->cval, C);
-    hipLaunchKernelGGL(k_check_overflow, dim3(1), dim3(1), 0, st, uc, C);
-    sort_pairs_u64_dn(p->ckey, p->cval, p->cks, p->cvs, C, uc + UC_C, cbits, p->tmp, st);
-    hipLaunchKernelGGL(k_cand_first, dim3(grid_for(C)), dim3(TB), 0, st, p->cks, (const unsigned long long*)uc, C,
-                       p->first);
-    hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(R)), dim3(TB), 0, st, p->matched, R, NF);
-    hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(R)), dim3(TB), 0, st, p->ncnt, R, 0u);
-    hipLaunchKernelGGL(k_cand_assign, dim3(grid_for(C)), dim3(TB), 0, st, p->cks, p->cvs,
-                       (const unsigned long long*)uc, C, p->first, p->sk, p->rec_t, p->matched, p->ncnt);
-    // 3. the deleted indices of every touched vertex, sorted
-    hipLaunchKernelGGL(k_xkeys, dim3(grid_for(R)), dim3(TB), 0, st, (const unsigned long long*)uc, R, p->matched,
-                       p->rec_t, xpad, p->xk);
-    sort_keys_u64(p->xk, p->xks, R, cbits, p->tmp, st);
-    hipLaunchKernelGGL(k_xextract, dim3(grid_for(R)), dim3(TB), 0, st, R, p->xks, p->xs);
-    scan_u32_to_u64(p->ncnt, p->xoff, R, p->tmp, uc + UC_X, st);
-    hipLaunchKernelGGL(k_ins_prep, dim3(grid_for(R)), dim3(TB), 0, st, (const unsigned long long*)uc, R, p->sv, p->iw,
-                       p->rec_t, p->tsa, p->tdl, p->dold, p->ncnt, p->xoff, p->xs, p->wv, p->idest);
+    if (small) {
+        hipLaunchKernelGGL(k_small_assign, dim3(1), dim3(SMALL_R), 0, st, sa);
+    } else {
+        hipLaunchKernelGGL(k_check_overflow, dim3(1), dim3(1), 0, st, uc, C);
+        sort_pairs_u64_dn(p->ckey, p->cval, p->cks, p->cvs, C, uc + UC_C, cbits, p->tmp, st);
+        hipLaunchKernelGGL(k_cand_first, dim3(grid_for(C)), dim3(TB), 0, st, p->cks, (const unsigned long long*)uc, C,
+                           p->first);
+        hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(R)), dim3(TB), 0, st, p->matched, R, NF);
+        hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(R)), dim3(TB), 0, st, p->ncnt, R, 0u);
+        hipLaunchKernelGGL(k_cand_assign, dim3(grid_for(C)), dim3(TB), 0, st, p->cks, p->cvs,
+                           (const unsigned long long*)uc, C, p->first, p->sk, p->rec_t, p->matched, p->ncnt);
+        // 3. the deleted indices of every touched vertex, sorted
+        hipLaunchKernelGGL(k_xkeys, dim3(grid_for(R)), dim3(TB), 0, st, (const unsigned long long*)uc, R, p->matched,
+                           p->rec_t, xpad, p->xk);
+        sort_keys_u64(p->xk, p->xks, R, cbits, p->tmp, st);
+        hipLaunchKernelGGL(k_xextract, dim3(grid_for(R)), dim3(TB), 0, st, R, p->xks, p->xs);
+        scan_u32_to_u64(p->ncnt, p->xoff, R, p->tmp, uc + UC_X, st);
+        hipLaunchKernelGGL(k_ins_prep, dim3(grid_for(R)), dim3(TB), 0, st, (const unsigned long long*)uc, R, p->sv, p->iw,
+                           p->rec_t, p->tsa, p->tdl, p->dold, p->ncnt, p->xoff, p->xs, p->wv, p->idest);
+        hipLaunchKernelGGL(k_fill_u64, dim3(grid_for(R)), dim3(TB), 0, st, p->needw, R, 0ull);
+    }
     // 4. analysis and one bump allocation
-    hipLaunchKernelGGL(k_fill_u64, dim3(grid_for(R)), dim3(TB), 0, st, p->needw, R, 0ull);
     hipLaunchKernelGGL(k_analyze, dim3(vgrid_a), dim3(WB), 0, st, (const unsigned long long*)uc, p->tv, p->tsa, p->tdl,
                        p->te, p->ncnt, p->xoff, p->xs, g->hdr, g->pool, p->wv, g->rule, p->needw, p->parts);
-    hipLaunchKernelGGL(k_stats_reduce, dim3(32), dim3(256), 0, st, (const unsigned long long*)p->parts, vgrid_a,
-                       uc + UC_STATS, 0);
-    scan_u64(p->needw, p->aoff, R, p->tmp, uc + UC_ALLOC, st);
-    hipLaunchKernelGGL(k_alloc_check, dim3(1), dim3(1), 0, st, g->d_ctl, g->pool_words, uc, err);
+    if (small) {
+        hipLaunchKernelGGL(k_small_alloc, dim3(1), dim3(SMALL_R), 0, st, sa, (const unsigned long long*)p->parts, vgrid_a,
+                           g->d_ctl, g->pool_words);
+    } else {
+        hipLaunchKernelGGL(k_stats_reduce, dim3(32), dim3(256), 0, st, (const unsigned long long*)p->parts, vgrid_a,
+                           uc + UC_STATS, 0);
+        scan_u64(p->needw, p->aoff, R, p->tmp, uc + UC_ALLOC, st);
+        hipLaunchKernelGGL(k_alloc_check, dim3(1), dim3(1), 0, st, g->d_ctl, g->pool_words, uc, err);
+    }
     // the edge locator in step with what the mutation will do (before it: the moved edges' dst
     // are read in the old adjacency; a rejected batch skips these as it skips the mutation)
     if (lv.tab) {
@@ -2334,18 +2636,23 @@ static void enqueue_update(bingo_graph* g, UpdPlan* p, hipStream_t st) {
     const uint32_t split = g->update_split;
     const MutArgs ma{p->tv, p->tsa, p->tdl, p->te, p->ncnt, p->xoff, p->xs, g->hdr, g->pool, p->sv, p->id, p->wv,
                      p->idest, p->aoff, p->sur, p->sdirty, g->rule};
-    hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(R)), dim3(TB), 0, st, p->sdirty, R, 0u);
+    if (!small) hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(R)), dim3(TB), 0, st, p->sdirty, R, 0u);
     hipLaunchKernelGGL(k_mutate, dim3(vgrid_m), dim3(WB), 0, st, uc, (const uint32_t*)err, ma, p->parts,
                        (const uint32_t*)p->dold, (const uint32_t*)p->blist, bc, split);
-    hipLaunchKernelGGL(k_stats_reduce, dim3(32), dim3(256), 0, st, (const unsigned long long*)p->parts, vgrid_m,
-                       uc + UC_FREED, 0);
+    if (!small)
+        hipLaunchKernelGGL(k_stats_reduce, dim3(32), dim3(256), 0, st, (const unsigned long long*)p->parts, vgrid_m,
+                           uc + UC_FREED, 0);
+    // a small batch sums both instances' partial sums at the end
+    const uint32_t sgrid = split ? (uint32_t)std::min<uint64_t>(R, PART_BLOCKS) : 0u;
+    unsigned long long* sparts = small ? p->parts + (uint64_t)vgrid_m * 32 : p->parts;
+    static_assert(SMALL_R / 4 + SMALL_R <= PART_BLOCKS, "room for both");
     if (split) {
         // vertices with more than `split` entries, then the passes they handed over
-        const uint32_t sgrid = (uint32_t)std::min<uint64_t>(R, PART_BLOCKS);
         hipLaunchKernelGGL(k_mutate_split, dim3(sgrid), dim3(64), XL_WORDS * 4, st, uc, (const uint32_t*)err, ma,
-                           p->parts, (const uint32_t*)p->dold, (const uint32_t*)p->blist, bc, split);
-        hipLaunchKernelGGL(k_stats_reduce, dim3(32), dim3(256), 0, st, (const unsigned long long*)p->parts, sgrid,
-                           uc + UC_FREED, 1);
+                           sparts, (const uint32_t*)p->dold, (const uint32_t*)p->blist, bc, split);
+        if (!small)
+            hipLaunchKernelGGL(k_stats_reduce, dim3(32), dim3(256), 0, st, (const unsigned long long*)p->parts, sgrid,
+                               uc + UC_FREED, 1);
         hipLaunchKernelGGL(k_big_pass, dim3(BIG_GRID), dim3(256), 0, st, (const unsigned long long*)uc, bc,
                            (const uint32_t*)p->xs, g->pool, g->hdr);
         hipLaunchKernelGGL(k_big_count, dim3(BIG_GRID), dim3(256), 0, st, (const unsigned long long*)uc, bc,
@@ -2356,7 +2663,11 @@ static void enqueue_update(bingo_graph* g, UpdPlan* p, hipStream_t st) {
         hipLaunchKernelGGL(k_big_one_dst, dim3(64), dim3(256), 0, st, (const unsigned long long*)uc, bc,
                            (const uint32_t*)g->pool, g->hdr);
     }
-    hipLaunchKernelGGL(k_add_u64, dim3(1), dim3(1), 0, st, g->d_ctl + 1, (const unsigned long long*)(uc + UC_FREED));
+    if (small)
+        hipLaunchKernelGGL(k_small_end, dim3(1), dim3(256), 0, st, uc, (const unsigned long long*)p->parts,
+                           vgrid_m + sgrid, g->d_ctl + 1, (const uint32_t*)err);
+    else
+        hipLaunchKernelGGL(k_upd_end, dim3(1), dim3(1), 0, st, g->d_ctl + 1, uc, (const uint32_t*)err);
     // S(u) and the sparse groups' indexes of the vertices whose reduced list may have changed
     sparse_rebuild(g, p->tv, uc + UC_T, R, p->sdirty, p->srwork, st);
     // alias-table mode: the touched vertices' inter-group tables (a rejected batch rewrites them unchanged)
@@ -2431,16 +2742,8 @@ int update_batch(bingo_graph* g, uint64_t n_ins, const uint32_t* is, const uint3
         UpdPlan* p = get_plan(g, rmax, cmin);
         if (!p) return BINGO_E_OOM;
         const LocView lv = locator_view(g);
-        if (n_ins) {
-            HIPCHK(hipMemcpyAsync(p->is, is, n_ins * 4, hipMemcpyDeviceToDevice, st));
-            HIPCHK(hipMemcpyAsync(p->id, id, n_ins * 4, hipMemcpyDeviceToDevice, st));
-            HIPCHK(hipMemcpyAsync(p->iw, iw, n_ins * 4, hipMemcpyDeviceToDevice, st));
-        }
-        if (n_del) {
-            HIPCHK(hipMemcpyAsync(p->ds, ds, n_del * 4, hipMemcpyDeviceToDevice, st));
-            HIPCHK(hipMemcpyAsync(p->dd, dd, n_del * 4, hipMemcpyDeviceToDevice, st));
-        }
-        hipLaunchKernelGGL(k_upd_begin, dim3(1), dim3(128), 0, st, p->uc, n_ins, n_del, g->d_err);
+        hipLaunchKernelGGL(k_upd_begin, dim3(grid_for(R)), dim3(TB), 0, st, p->uc, n_ins, n_del, g->d_err, is, id, iw, ds,
+                           dd, p->is, p->id, p->iw, p->ds, p->dd);
         phase_mark(g, st, true);
         bool launched = false;
         if (p->exec && (p->split != g->update_split || p->lv.tab != lv.tab || p->lv.mask != lv.mask)) {
@@ -2476,10 +2779,9 @@ int update_batch(bingo_graph* g, uint64_t n_ins, const uint32_t* is, const uint3
         }
         phase_mark(g, st, false);
         unsigned long long uc[UC_WORDS];
-        uint32_t err = 0;
         HIPCHK(hipMemcpyAsync(uc, p->uc, sizeof uc, hipMemcpyDeviceToHost, st));
-        HIPCHK(hipMemcpyAsync(&err, g->d_err, 4, hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
+        const uint32_t err = (uint32_t)uc[UC_ERR];
         if (err == ERR_OOM && !grown) {
             // the pool is full (nothing was applied): reclaim the blocks earlier batches replaced,
             // once; then, for a pool the library sized, move to an arena twice the size

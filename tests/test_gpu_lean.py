@@ -171,3 +171,40 @@ def test_batches_around_the_small_set_sizes(k, frac):
         assert np.array_equal(g.export(), og.dump())
         assert np.array_equal(g.export_index(), og.index_dump())
     g.close()
+
+
+@pytest.mark.parametrize("ni,nd", [(1, 0), (0, 1), (1, 1), (63, 1), (0, 65), (500, 523), (1023, 0), (0, 1024), (512, 512),
+                                   (512, 513), (700, 1348), (1025, 1024)])
+@pytest.mark.parametrize("locate,split", [(1, 4096), (0, 0), (1, 100)])
+def test_batches_around_the_one_block_steps(ni, nd, locate, split):
+    """Batches up to, at and past the size whose steps run in one block: equal to the oracle's, records
+    in random order, copies of edges, deletes of the batch's own inserts and of edges that are not there."""
+    import oracle as O
+    import torch
+    from paper_2504_10233_amd import Graph
+    n, m = 300, 9000
+    src, dst = (synth.below(1, 1, m, n) * synth.below(1, 2, m, n)) // n, synth.below(1, 3, m, 40)
+    w = synth.weights_zipf(m, 1.2, (1 << 30) - 1, 5)
+    g = Graph(n, src, dst, w)
+    g.set_tuning(update_locate=locate, update_split=split)
+    og = O.Graph(n, src.numpy(), dst.numpy(), w.numpy())
+    for b in range(3):
+        isrc, idst = synth.below(20 + b, 1, ni, n) // 2, synth.below(20 + b, 2, ni, 60)
+        iw = synth.weights_zipf(ni, 1.2, (1 << 30) - 1, 60 + b)
+        pick = synth.below(20 + b, 3, nd, m) if nd else torch.zeros(0, dtype=torch.int64)
+        ds, dd = src[pick], dst[pick] + (synth.below(20 + b, 4, nd, 10) == 0) * 20
+        k = min(ni, nd) // 4
+        ds[:k], dd[:k] = isrc[:k], idst[:k]
+        s1 = g.update(isrc, idst, iw, ds, dd)
+        s2 = og.update(isrc.numpy(), idst.numpy(), iw.numpy(), ds.numpy(), dd.numpy())
+        for key in ("inserted", "deleted", "not_found"):
+            assert s1[key] == s2[key], (b, key)
+        assert np.array_equal(s1["transitions"], s2["transitions"])
+        assert np.array_equal(g.export(), og.dump()) and np.array_equal(g.export_index(), og.index_dump())
+        if locate:
+            assert g.check_locator()[0] == 0
+    # nothing of a rejected batch is applied
+    with pytest.raises(Exception):
+        g.update(torch.tensor([1, n]), torch.tensor([1, 1]), torch.tensor([1, 1]), torch.tensor([0]), torch.tensor([0]))
+    assert np.array_equal(g.export(), og.dump())
+    g.close()
