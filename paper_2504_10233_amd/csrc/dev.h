@@ -328,6 +328,11 @@ __device__ __forceinline__ uint32_t lane_get(uint32_t v, int l) { return (uint32
 __device__ __forceinline__ uint64_t lane_get64(uint64_t v, int l) {
     return ((uint64_t)lane_get((uint32_t)(v >> 32), l) << 32) | lane_get((uint32_t)v, l);
 }
+// A value that every lane of the wave holds alike, in a scalar register.
+__device__ __forceinline__ uint32_t uni(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ uint64_t uni64(uint64_t v) {
+    return ((uint64_t)uni((uint32_t)(v >> 32)) << 32) | uni((uint32_t)v);
+}
 __device__ __forceinline__ uint64_t lanemask_lt() {
     const uint32_t l = __lane_id();
     return l == 0 ? 0ull : (~0ull >> (64 - l));

@@ -858,9 +858,6 @@ __global__ void __launch_bounds__(TB) k_loc_claim(unsigned long long* __restrict
 // ---------------------------------------------------------------------------
 // per-vertex state shared by the analysis and mutation kernels
 // ---------------------------------------------------------------------------
-// A value that every lane of the wave holds alike, in a scalar register.
-__device__ __forceinline__ uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-
 struct VState {
     uint32_t u, d, cap, nseq;
     uint64_t adj;
@@ -916,7 +913,7 @@ __device__ __forceinline__ void load_header(VState& s, const VRow& w, const uint
     s.lcap = lane < 32 ? (1u << ((h[H_LCAPLOG + (lane >> 2)] >> (8 * (lane & 3))) & 0xFFu)) : 0u;
     s.c = lane < 32 ? slot_count(hdr_slot(h, lane, hdr_hi(h)), h[H_ONEMASK], lane) : 0u;
     s.d = uni(d); s.cap = uni(cap); s.nseq = uni(nseq); s.sblk = uni(sblk); s.scap = uni(scap);
-    s.adj = (uint64_t)uni((uint32_t)(adj >> 32)) << 32 | uni((uint32_t)adj);
+    s.adj = uni64(adj);
     s.W = (uint64_t)uni(whi) << 32 | uni(wlo);
     s.d1 = s.d + s.ni; s.dn = s.d1 - s.N;
     s.told = lane < 32 ? group_type(s.c, s.d, rule) : GT_EMPTY;

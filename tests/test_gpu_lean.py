@@ -208,3 +208,35 @@ def test_batches_around_the_one_block_steps(ni, nd, locate, split):
         g.update(torch.tensor([1, n]), torch.tensor([1, 1]), torch.tensor([1, 1]), torch.tensor([0]), torch.tensor([0]))
     assert np.array_equal(g.export(), og.dump())
     g.close()
+
+
+@pytest.mark.parametrize("degree", [16383, 16384, 40001])
+@pytest.mark.parametrize("values", [30, 3000, 1 << 17])
+def test_streams_on_hubs(degree, values):
+    """A hub's chain of records, deletes located for 64 at a time (few destinations: more candidates than
+    the table holds; many: deletes that find nothing), inserts deleted again, the last edges deleted."""
+    import oracle as O
+    import torch
+    from paper_2504_10233_amd import Graph
+    n = 1 << 17
+    src = torch.cat([torch.full((degree,), 9), synth.below(1, 1, 2000, n)])
+    dst = synth.below(1, 2, src.numel(), values)
+    w = synth.weights_zipf(src.numel(), 1.2, (1 << 30) - 1, 5)
+    g = Graph(n, src, dst, w)
+    og = O.Graph(n, src.numpy(), dst.numpy(), w.numpy())
+    m = 323  # five windows and three records, the hub's records among others
+    op = (synth.below(4, 1, m, 5) < 3).to(torch.int64)
+    u = torch.where(synth.below(4, 2, m, 8) == 0, synth.below(4, 3, m, n), torch.full((m,), 9))
+    v = torch.where(synth.below(4, 4, m, 4) == 0, synth.below(4, 5, m, values), dst[synth.below(4, 6, m, degree)])
+    v[:20] = dst[degree - 20:degree].flip(0)
+    op[:20], u[:20] = 1, 9
+    op[40:80], u[40:80] = torch.arange(40) % 2, 9
+    v[41:80:2] = v[40:80:2]  # each insert deleted by the next record, or an older copy is
+    ww = synth.weights_zipf(m, 1.2, (1 << 30) - 1, 7)
+    s1 = g.update_stream(op, u, v, ww)
+    s2 = og.update_stream(op.numpy(), u.numpy(), v.numpy(), ww.numpy())
+    for key in ("inserted", "deleted", "not_found"):
+        assert s1[key] == s2[key]
+    assert np.array_equal(s1["transitions"], s2["transitions"])
+    assert np.array_equal(g.export(), og.dump()) and np.array_equal(g.export_index(), og.index_dump())
+    g.close()
