@@ -210,7 +210,7 @@ def test_batches_around_the_one_block_steps(ni, nd, locate, split):
     g.close()
 
 
-@pytest.mark.parametrize("degree", [16383, 16384, 40001])
+@pytest.mark.parametrize("degree", [4095, 4096, 16384, 40001])
 @pytest.mark.parametrize("values", [30, 3000, 1 << 17])
 def test_streams_on_hubs(degree, values):
     """A hub's chain of records, deletes located for 64 at a time (few destinations: more candidates than
