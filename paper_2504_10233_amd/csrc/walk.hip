@@ -1061,8 +1061,14 @@ __global__ void __launch_bounds__(256) k_hist_compact(const uint32_t* __restrict
                                                       const uint64_t* __restrict__ seg, uint32_t R, uint64_t C,
                                                       const uint32_t* __restrict__ ucount,
                                                       const uint64_t* __restrict__ off, uint32_t* __restrict__ vtx,
-                                                      uint32_t* __restrict__ cnt) {
+                                                      uint32_t* __restrict__ cnt, uint64_t* __restrict__ last,
+                                                      const unsigned long long* __restrict__ total,
+                                                      unsigned long long* __restrict__ entries) {
     const uint32_t q = blockIdx.x;
+    if (q == 0 && threadIdx.x == 0) {
+        *last = *total;  // the offset past the last source
+        if (entries) *entries = *total;
+    }
     const uint64_t S0 = C ? (uint64_t)q * C : seg[(uint64_t)q * R], o = off[q];
     const uint32_t U = ucount[q];
     for (uint32_t k = threadIdx.x; k < U; k += 256) {
@@ -1088,13 +1094,24 @@ __global__ void k_vis_keys(const uint32_t* __restrict__ vis, const uint64_t* __r
     }
 }
 
-__global__ void k_set_last_off(uint64_t* off, uint32_t nsrc, const unsigned long long* total) { off[nsrc] = *total; }
+// Before a binned query: its four control words, the error word and the bins' counts (one launch: a
+// query of a few sources is little more than its launches and copies: 20,000 walks 295 -> 275 us with
+// this, the error word read back with the counters and the last offset set by k_hist_compact).
+__global__ void k_ppr_begin(unsigned long long* __restrict__ ctl, uint32_t* __restrict__ err,
+                            uint32_t* __restrict__ cnt, uint32_t nsrc) {
+    if (blockIdx.x == 0 && threadIdx.x < 5) ctl[threadIdx.x] = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *err = 0;
+    for (uint64_t q = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; q < nsrc; q += (uint64_t)gridDim.x * blockDim.x)
+        cnt[q * BIN_STRIDE] = 0;
+}
 
-// Largest bin fill, reduced per block then one atomic per block.
+// Largest bin fill (out[0]), reduced per block then one atomic per block, and the error word (out[1]).
 __global__ void __launch_bounds__(256) k_bin_max(const uint32_t* __restrict__ cnt, uint32_t nsrc,
+                                                 const uint32_t* __restrict__ err,
                                                  unsigned long long* __restrict__ out) {
     __shared__ unsigned long long m[4];
     unsigned long long best = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) out[1] = *err;
     for (uint64_t q = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; q < nsrc; q += (uint64_t)gridDim.x * blockDim.x)
         best = std::max<unsigned long long>(best, cnt[q * BIN_STRIDE]);
 #pragma unroll
@@ -1363,7 +1380,7 @@ static int finish_lds_hist(bingo_graph* g, uint32_t* vis, uint32_t* hcnt, uint32
                            uint64_t* h_steps, hipStream_t st) {
     const int rc = ensure_ppr_off(g, nsrc);
     if (rc != BINGO_OK) return rc;
-    HIPCHK(hipMemsetAsync(ctl, 0, 8, st));
+    if (!C) HIPCHK(hipMemsetAsync(ctl, 0, 8, st));  // a binned query leaves it 0
 #define BINGO_HIST(E_)                                                                                     \
     hipLaunchKernelGGL((k_hist_seg<E_>), dim3(nsrc), dim3(HSB), 0, st, vis, hcnt, seg, R, nsrc, total, C, bin_cnt, \
                        ucount, ctl)
@@ -1390,9 +1407,9 @@ static int finish_lds_hist(bingo_graph* g, uint32_t* vis, uint32_t* hcnt, uint32
             return BINGO_E_OOM;
         }
     }
-    hipLaunchKernelGGL(k_set_last_off, dim3(1), dim3(1), 0, st, g->ppr_off, nsrc, (const unsigned long long*)(ctl + 1));
     hipLaunchKernelGGL(k_hist_compact, dim3(nsrc), dim3(256), 0, st, vis, hcnt, seg, R, C, ucount, g->ppr_off,
-                       g->ppr_vtx, g->ppr_cnt);
+                       g->ppr_vtx, g->ppr_cnt, g->ppr_off + nsrc, (const unsigned long long*)(ctl + 1),
+                       (unsigned long long*)nullptr);
     phase_mark(g, st, false);
     HIPCHK(hipStreamSynchronize(st));
     g->ppr_entries = U;
@@ -1424,7 +1441,6 @@ static int finish_lds_hist_async(bingo_graph* g, uint32_t* vis, uint32_t* hcnt, 
     HIPCHK(hipEventRecord(g->ppr_done, st));  // the walk phase
     HIPCHK(hipStreamWaitEvent(hs, g->ppr_done, 0));
     HIPCHK(hipEventRecord(g->ppr_h0, hs));
-    HIPCHK(hipMemsetAsync(ctl, 0, 8, hs));
 #define BINGO_HIST(E_)                                                                                            \
     hipLaunchKernelGGL((k_hist_seg<E_>), dim3(nsrc), dim3(HSB), 0, hs, vis, hcnt, (const uint64_t*)nullptr, R, nsrc, \
                        total, C, bin_cnt, ucount, ctl)
@@ -1436,10 +1452,9 @@ static int finish_lds_hist_async(bingo_graph* g, uint32_t* vis, uint32_t* hcnt, 
     else BINGO_HIST(32);
 #undef BINGO_HIST
     scan_u32_to_u64(ucount, g->ppr_off, nsrc, tmp, ctl + 1, hs);
-    hipLaunchKernelGGL(k_set_last_off, dim3(1), dim3(1), 0, hs, g->ppr_off, nsrc, (const unsigned long long*)(ctl + 1));
     hipLaunchKernelGGL(k_hist_compact, dim3(nsrc), dim3(256), 0, hs, vis, hcnt, (const uint64_t*)nullptr, R, C, ucount,
-                       g->ppr_off, g->ppr_vtx, g->ppr_cnt);
-    HIPCHK(hipMemcpyAsync(g->d_ctl + CTL_PPR_U, ctl + 1, 8, hipMemcpyDeviceToDevice, hs));
+                       g->ppr_off, g->ppr_vtx, g->ppr_cnt, g->ppr_off + nsrc, (const unsigned long long*)(ctl + 1),
+                       g->d_ctl + CTL_PPR_U);
     HIPCHK(hipEventRecord(g->ppr_h1, hs));
     HIPCHK(hipEventRecord(g->ppr_done, hs));
     g->ppr_pending = true;
@@ -1488,11 +1503,11 @@ static int run_ppr_binned(bingo_graph* g, uint32_t nsrc, const uint32_t* sources
     uint32_t* bin_cnt = (uint32_t*)ws;  ws += al((uint64_t)nsrc * BIN_STRIDE * 4);
     uint32_t* ucount = (uint32_t*)ws;   ws += al((uint64_t)nsrc * 4);
     void* tmp = ws;
-    unsigned long long* ctl = g->d_ctl + 2;  // [0] queue, [1] transitions, [2] overflow, [3] largest bin
-    HIPCHK(hipMemsetAsync(ctl, 0, 32, st));
-    HIPCHK(hipMemsetAsync(g->d_err, 0, 4, st));
+    // [0] queue, [1] transitions, [2] overflow, [3] largest bin, [4] the error word
+    unsigned long long* ctl = g->d_ctl + 2;
+    const uint32_t sgrid = (uint32_t)std::min<uint64_t>(((uint64_t)nsrc + 255) / 256, 1024);
     phase_mark(g, st, true);
-    HIPCHK(hipMemsetAsync(bin_cnt, 0, (uint64_t)nsrc * BIN_STRIDE * 4, st));
+    hipLaunchKernelGGL(k_ppr_begin, dim3(std::max(sgrid, 1u)), dim3(256), 0, st, ctl, g->d_err, bin_cnt, nsrc);
     phase_mark(g, st, false);
     const uint64_t nw = (uint64_t)nsrc * R;
 #define BINGO_COOP(G_, M_)                                                                                            \
@@ -1520,14 +1535,11 @@ static int run_ppr_binned(bingo_graph* g, uint32_t nsrc, const uint32_t* sources
 #undef BINGO_BINNED
 #undef BINGO_COOP
     phase_mark(g, st, false);
-    hipLaunchKernelGGL(k_bin_max, dim3((uint32_t)std::min<uint64_t>((nsrc + 255) / 256, 1024)), dim3(256), 0, st,
-                       bin_cnt, nsrc, ctl + 3);
-    unsigned long long c4[4];
-    uint32_t err = 0;
-    HIPCHK(hipMemcpyAsync(c4, ctl, 32, hipMemcpyDeviceToHost, st));
-    HIPCHK(hipMemcpyAsync(&err, g->d_err, 4, hipMemcpyDeviceToHost, st));
+    hipLaunchKernelGGL(k_bin_max, dim3(sgrid), dim3(256), 0, st, bin_cnt, nsrc, (const uint32_t*)g->d_err, ctl + 3);
+    unsigned long long c4[5];
+    HIPCHK(hipMemcpyAsync(c4, ctl, 40, hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
-    if (err) return err_to_code(err);
+    if (c4[4]) return err_to_code((uint32_t)c4[4]);
     if (c4[2] || c4[3] > C || c4[3] > HCAP) return PPR_RETRY;
     if (hs)
         return finish_lds_hist_async(g, vis, hcnt, ucount, R, C, bin_cnt, nsrc, cells, c4[3], tmp, ctl + 2, c4[1],
