@@ -593,8 +593,11 @@ constexpr uint32_t SR_LIST0 = 64;
 // vertices; the block list grows up from SR_LIST0 and the wave list down from
 // SR_LIST0 + mc - 1 (a vertex is in one of them); the large list (vertex, first
 // chunk, chunks) after them; then the chunk owners and counts.
-constexpr uint32_t SR_BIG = 1u << 15;
-constexpr uint32_t SR_CHUNK = 1u << 14;
+// 10^4 records on planted hubs of up to 3 x 10^5 edges, the block, index and write kernels (us), lines at
+// 2^15 and 2^14: 127 + 103 + 30 (the largest vertices of one block set the first); 2^13 both: 59 + 96 + 22;
+// 2^12 both: 43 + 152 + 22 (each chunk stages its vertex's samples of S(u)).
+constexpr uint32_t SR_BIG = 1u << 13;
+constexpr uint32_t SR_CHUNK = 1u << 13;
 constexpr uint32_t SR_NO_OWNER = 0xFFFFFFFFu;
 constexpr uint32_t SR_WAVE = 1024;  // largest degree rebuilt by one wave
 constexpr int SRW_TB = 256;         // blocks of the wave kernel

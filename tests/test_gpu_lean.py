@@ -240,3 +240,25 @@ def test_streams_on_hubs(degree, values):
     assert np.array_equal(s1["transitions"], s2["transitions"])
     assert np.array_equal(g.export(), og.dump()) and np.array_equal(g.export_index(), og.index_dump())
     g.close()
+
+
+@pytest.mark.parametrize("degree", [1023, 1024, 1025, 8190, 8191, 8192, 16384, 24577])
+def test_sparse_rebuild_around_its_classes(degree):
+    """S(u) and the sparse indexes after batches, around the degrees that one wave, one block and chunks rebuild."""
+    import oracle as O
+    import torch
+    from paper_2504_10233_amd import Graph
+    n = 50
+    src = torch.cat([torch.full((degree,), 7), torch.full((degree // 2,), 8), synth.below(1, 1, 2000, n)])
+    dst = synth.below(1, 2, src.numel(), n)
+    w = synth.weights_zipf(src.numel(), 1.2, (1 << 30) - 1, 5)
+    g = Graph(n, src, dst, w)
+    og = O.Graph(n, src.numpy(), dst.numpy(), w.numpy())
+    for b in range(3):
+        k = 2 + b  # the degree crosses a line by one either way
+        ins = (torch.full((k,), 7), synth.below(3 + b, 1, k, n), synth.weights_zipf(k, 1.2, (1 << 30) - 1, 9 + b))
+        dels = (torch.full((3,), 7), dst[100 * b:100 * b + 3])
+        g.update(*ins, *dels)
+        og.update(*(x.numpy() for x in ins + dels))
+        assert np.array_equal(g.export(), og.dump()) and np.array_equal(g.export_index(), og.index_dump())
+    g.close()
