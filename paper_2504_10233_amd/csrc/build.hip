@@ -290,7 +290,7 @@ __device__ __forceinline__ void fill_range(const uint64_t* __restrict__ e, uint3
             if (f.smask) {
                 const bool sb = (wv & f.smask) != 0u;
                 const uint64_t sbal = __ballot(sb);
-                spos = sfill + (uint32_t)__popcll(sbal & lanemask_lt());
+                spos = sfill + rank_below(sbal);
                 if (sb) pool[f.sblk + spos] = i;
                 sfill += (uint32_t)__popcll(sbal);
             }
@@ -302,7 +302,7 @@ __device__ __forceinline__ void fill_range(const uint64_t* __restrict__ e, uint3
                 const uint32_t at = lane_get(fill, k);
                 if (bit) {
                     uint32_t* L = pool + lane_get64(f.my_block, k);
-                    const uint32_t pos = at + (uint32_t)__popcll(bal & lanemask_lt());
+                    const uint32_t pos = at + rank_below(bal);
                     L[pos] = i;
                     // the group's index entry: a listed group that is not sparse is regular
                     L[lane_get(f.lcap, k) + (((f.smask >> k) & 1u) ? spos : i)] = pos;
@@ -469,7 +469,7 @@ __global__ void __launch_bounds__(WB) k_fill4(uint32_t n, const uint32_t* __rest
             const uint64_t bal = __ballot(bit);
             const uint64_t blk = __shfl(my_block, sg, 64);
             const uint32_t f = __shfl(fill, sg, 64);
-            if (bit) pool[blk + f + __popcll(bal & lanemask_lt())] = i;
+            if (bit) pool[blk + f + rank_below(bal)] = i;
             if (lane == (uint32_t)sg) fill += __popcll(bal);
         }
     }
@@ -524,7 +524,7 @@ __global__ void __launch_bounds__(ALIAS_TB) k_alias_rows(const uint32_t* __restr
         for (int k = 0; k < ALIAS_ENTRIES; ++k) {
             const uint32_t c = slot_count(hdr_slot(h, (uint32_t)k, hi), onem, (uint32_t)k);
             cnt[k][tx] = c;
-            W += (uint64_t)c << k;
+            W += shl32(c, k);
         }
         // slot k holds 32 T_k = c_k 2^(k+5) units (below 2^69); it is small when that is below W
         uint32_t S = 0, L = 0;
@@ -537,14 +537,14 @@ __global__ void __launch_bounds__(ALIAS_TB) k_alias_rows(const uint32_t* __restr
         // so both parts are in ascending k and each is a bit mask.
         uint32_t P = 0, done = 0;
         int cur = L ? __ffs(L) - 1 : -1;
-        unsigned __int128 R = cur >= 0 ? (unsigned __int128)cnt[cur][tx] << (cur + 5) : 0;
+        unsigned __int128 R = cur >= 0 ? (unsigned __int128)shl32(cnt[cur][tx], (uint32_t)cur) << 5 : 0;
         while ((S | P) != 0 && cur >= 0) {
             int sm;
             uint64_t us;
             if (S) {
                 sm = __ffs(S) - 1;
                 S &= S - 1;
-                us = (uint64_t)((unsigned __int128)cnt[sm][tx] << (sm + 5));
+                us = shl32(cnt[sm][tx], (uint32_t)sm) << 5;
             } else {
                 sm = __ffs(P) - 1;
                 P &= P - 1;
@@ -558,7 +558,7 @@ __global__ void __launch_bounds__(ALIAS_TB) k_alias_rows(const uint32_t* __restr
                 P |= 1u << cur;
                 L &= L - 1;
                 cur = L ? __ffs(L) - 1 : -1;
-                R = cur >= 0 ? (unsigned __int128)cnt[cur][tx] << (cur + 5) : 0;
+                R = cur >= 0 ? (unsigned __int128)shl32(cnt[cur][tx], (uint32_t)cur) << 5 : 0;
             }
         }
         // every slot not taken as small keeps exactly W units (the units sum to 32 W)
@@ -648,9 +648,8 @@ __global__ void k_sr_compact(uint32_t n, const uint32_t* __restrict__ hdr, const
         }
         basew = __shfl(basew, leader, 64);
         baseb = __shfl(baseb, leader, 64);
-        const uint64_t lt = lanemask_lt();
-        if (to_wave) work[SR_LIST0 + maxc - 1 - (basew + (uint32_t)__popcll(bw & lt))] = u;
-        if (to_block) work[SR_LIST0 + baseb + (uint32_t)__popcll(bb & lt)] = u;
+        if (to_wave) work[SR_LIST0 + maxc - 1 - (basew + rank_below(bw))] = u;
+        if (to_block) work[SR_LIST0 + baseb + rank_below(bb)] = u;
     }
 }
 
@@ -765,9 +764,9 @@ __global__ void __launch_bounds__(SRC_TB) k_sr_write(uint32_t* __restrict__ hdr,
             __syncthreads();
 #pragma unroll
             for (uint32_t q = 0; q < SRC_ROWS; ++q) {
-                uint32_t rk = base + (uint32_t)__popcll(bal[q] & lanemask_lt());
+                uint32_t rk = base + rank_below(bal[q]);
                 for (uint32_t w = 0; w < wave; ++w) rk += wc[q][w];
-                if ((bal[q] >> lane) & 1ull) S[rk] = r0 + q * SRC_TB + threadIdx.x;
+                if (bit64(bal[q], lane)) S[rk] = r0 + q * SRC_TB + threadIdx.x;
                 base += wc[q][0] + wc[q][1] + wc[q][2] + wc[q][3];
             }
             __syncthreads();  // wc is rewritten by the next step
@@ -896,7 +895,7 @@ __global__ void __launch_bounds__(SR_TB) k_srebuild(uint32_t* __restrict__ hdr, 
             __syncthreads();
 #pragma unroll
             for (uint32_t j = 0; j < SR_TPT; ++j) {
-                uint32_t rk = sfill + (uint32_t)__popcll(bal[j] & lanemask_lt()), row = 0;
+                uint32_t rk = sfill + rank_below(bal[j]), row = 0;
                 for (uint32_t w = 0; w < SR_TB / 64; ++w) {
                     const uint32_t x = wcnt[j][w];
                     if (w < wave) rk += x;
@@ -998,7 +997,7 @@ __global__ void __launch_bounds__(SRW_TB) k_srebuild_wave(uint32_t* __restrict__
                 const uint32_t i = i0 + j * 64 + lane;
                 const bool in = i < d && (member_word(wr[j], rule.fbits) & smask) != 0u;
                 const uint64_t b = __ballot(in);
-                const uint32_t rk = sfill + (uint32_t)__popcll(b & lanemask_lt());
+                const uint32_t rk = sfill + rank_below(b);
                 if (in) {
                     S[rk] = i;
                     S_l[rk] = i;

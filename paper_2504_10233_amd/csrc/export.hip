@@ -192,9 +192,7 @@ __global__ void __launch_bounds__(WB) k_mem(const uint32_t* __restrict__ hdr, co
         if (ne) {
             if (type_listed(t)) {
                 v[0] = 4ull * c;
-                // a 32-bit shift: 64-bit shifts have returned wrong values here with the amount in the last
-                // register of the kernel's allocation, where this kernel's register count put it
-                const uint64_t cap4 = (uint64_t)(1u << capb) * 4u;
+                const uint64_t cap4 = shl32(4u, capb);
                 v[1] = cap4;
                 v[4] = t == GT_REGULAR ? 4ull * d : 4ull * slen;
                 v[5] = list_block_words(1u << capb, index_cap_for(t, acap, scap)) * 4ull - cap4;

@@ -177,7 +177,8 @@ k_node2vec(const uint32_t* __restrict__ hdr, const uint32_t* __restrict__ pool, 
         bool won = fin && acc, lost = fin && !acc;
         uint32_t y = v;
         if constexpr (G > 1) {
-            const uint32_t fm = (uint32_t)(__ballot(fin) >> l0) & ALL, am = (uint32_t)(__ballot(fin && acc) >> l0) & ALL;
+            const uint32_t fm = (uint32_t)group_bits<G>(__ballot(fin), (uint32_t)l0),
+                           am = (uint32_t)group_bits<G>(__ballot(fin && acc), (uint32_t)l0);
             first = am ? (uint32_t)__ffs(am) - 1 : 0u;
             won = am && ((~fm) & ((1u << first) - 1u)) == 0u;
             lost = !am && fm == ALL;

@@ -217,7 +217,6 @@ __global__ void __launch_bounds__(SORT_BLOCK) k_digit_scatter(const K* __restric
         }
     }
     const uint64_t base = (uint64_t)blockIdx.x * SORT_TILE;
-    const uint64_t below = lanemask_lt();
     // the tile's keys and values, all loads issued before the first subtile is ranked
     K keys[SORT_SUBTILES];
     V vals[SORT_SUBTILES];
@@ -248,7 +247,7 @@ __global__ void __launch_bounds__(SORT_BLOCK) k_digit_scatter(const K* __restric
             const uint64_t bb = __ballot(bit);
             peers &= bit ? bb : ~bb;
         }
-        const uint32_t lrank = __popcll(peers & below);
+        const uint32_t lrank = rank_below(peers);
         if (valid && lrank == 0) wc[wave][dg] = __popcll(peers);
         __syncthreads();
         // per digit, the keys of the lower waves (an exclusive scan down each column)

@@ -61,7 +61,7 @@ __device__ __forceinline__ uint32_t step4(const uint32_t* __restrict__ hdr, cons
         if (sel < 0 && r < acc) { sel = s; csel = c; raw = slot; }
     }
     if (sel < 0) return STOP_VERTEX;  // only on an inconsistent header
-    if ((onem >> sel) & 1ull) return raw;
+    if (bit64(onem, (uint32_t)sel)) return raw;
     const uint64_t* __restrict__ edges = reinterpret_cast<const uint64_t*>(pool + adj);
     if (group_type(csel, d, rule) == GT_DENSE) {
         const uint32_t k = (uint32_t)sel / 3, v = (uint32_t)sel % 3 + 1;
@@ -158,7 +158,7 @@ __global__ void k_dump4_size(const uint32_t* __restrict__ hdr, uint32_t u0, uint
     uint64_t s = 3 + 2ull * d;
     for (uint64_t mm = mask; mm; mm &= mm - 1) {
         const int sg = __ffsll((long long)mm) - 1;
-        const uint32_t c = ((onem >> sg) & 1ull) ? 1u : h[H4_SLOT + sg];
+        const uint32_t c = bit64(onem, (uint32_t)sg) ? 1u : h[H4_SLOT + sg];
         s += 3 + stored4(group_type(c, d, rule), c);
     }
     sz[u - u0] = s;
@@ -183,8 +183,8 @@ __global__ void __launch_bounds__(TB4) k_dump4_write(const uint32_t* __restrict_
         o[3 + 2 * (uint64_t)i] = (uint32_t)e;
         o[4 + 2 * (uint64_t)i] = (uint32_t)(e >> 32);
     }
-    const bool ne = lane < R4_SUB && ((mask >> lane) & 1ull);
-    const uint32_t c = ne ? (((onem >> lane) & 1ull) ? 1u : h[H4_SLOT + lane]) : 0u;
+    const bool ne = lane < R4_SUB && bit64(mask, lane);
+    const uint32_t c = ne ? (bit64(onem, lane) ? 1u : h[H4_SLOT + lane]) : 0u;
     const uint32_t t = ne ? group_type(c, d, rule) : GT_EMPTY;
     const uint64_t sz = ne ? 3ull + stored4(t, c) : 0ull;
     uint64_t x = sz;
@@ -225,11 +225,11 @@ __global__ void __launch_bounds__(TB4) k_mem4(const uint32_t* __restrict__ hdr, 
         const uint32_t d = h[H4_DEG];
         const uint64_t mask = ((uint64_t)h[H4_MASKHI] << 32) | h[H4_MASKLO];
         const uint64_t onem = ((uint64_t)h[H4_ONEHI] << 32) | h[H4_ONELO];
-        const bool ne = lane < R4_SUB && ((mask >> lane) & 1ull);
-        const uint32_t c = ne ? (((onem >> lane) & 1ull) ? 1u : h[H4_SLOT + lane]) : 0u;
+        const bool ne = lane < R4_SUB && bit64(mask, lane);
+        const uint32_t c = ne ? (bit64(onem, lane) ? 1u : h[H4_SLOT + lane]) : 0u;
         const uint32_t t = ne ? group_type(c, d, rule) : GT_EMPTY;
         const uint32_t capb = lane < R4_SUB ? ((h[H4_LCAPLOG + (lane >> 2)] >> (8 * (lane & 3))) & 0xFFu) : 0u;
-        uint64_t v0 = type_listed(t) ? 4ull * c : 0ull, v1 = type_listed(t) ? (4ull << capb) : 0ull;
+        uint64_t v0 = type_listed(t) ? 4ull * c : 0ull, v1 = type_listed(t) ? shl32(4u, capb) : 0ull;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
             v0 += __shfl_xor(v0, o);

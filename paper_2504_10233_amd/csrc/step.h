@@ -28,7 +28,7 @@ __device__ __forceinline__ uint32_t dense_round(const uint64_t* __restrict__ edg
     uint32_t v = PENDING;
 #pragma unroll
     for (int a = SPEC - 1; a >= 0; --a)
-        if ((e[a] >> (32 + sel)) & 1ull) v = (uint32_t)e[a];
+        if (((uint32_t)(e[a] >> 32) >> sel) & 1u) v = (uint32_t)e[a];
     return v;
 }
 
@@ -135,7 +135,7 @@ __device__ __forceinline__ bool pick_group(const uint32_t* __restrict__ hdr, uin
                 const uint32_t k = g.hi - (uint32_t)q;
                 const uint32_t ck = ((g.onem >> k) & 1u) ? 1u : sl[q];
                 if (k == 0) g.slot0 = sl[q];
-                if (k >= rule.fbits) acc += (uint64_t)ck << k;
+                if (k >= rule.fbits) acc += shl32(ck, k);
                 if (g.sel < 0 && r < acc) { g.sel = (int)k; g.csel = ck; g.raw = sl[q]; }
             }
         }
@@ -147,7 +147,7 @@ __device__ __forceinline__ bool pick_group(const uint32_t* __restrict__ hdr, uin
             if (g.sel < 0 && (uint32_t)q <= g.hi) {
                 const uint32_t k = g.hi - (uint32_t)q;
                 const uint32_t ck = ((g.onem >> k) & 1u) ? 1u : sl[q];
-                acc += (uint64_t)ck << k;
+                acc += shl32(ck, k);
                 if (acc >= t) { g.sel = (int)k; g.csel = ck; g.raw = sl[q]; }
             }
         }
@@ -162,7 +162,7 @@ __device__ __forceinline__ bool pick_group(const uint32_t* __restrict__ hdr, uin
                 if (g.sel < 0 && (uint32_t)q <= g.hi) {
                     const uint32_t k = g.hi - (uint32_t)q;
                     const uint32_t ck = ((g.onem >> k) & 1u) ? 1u : sl[q];
-                    acc += (uint64_t)ck << k;
+                    acc += shl32(ck, k);
                     if (acc >= t) { g.sel = (int)k; g.csel = ck; g.raw = sl[q]; }
                 }
             }
@@ -175,7 +175,7 @@ __device__ __forceinline__ bool pick_group(const uint32_t* __restrict__ hdr, uin
                     if (g.sel < 0 && (uint32_t)q <= g.hi) {
                         const uint32_t k = g.hi - (uint32_t)q;
                         const uint32_t ck = ((g.onem >> k) & 1u) ? 1u : sl[q];
-                        acc += (uint64_t)ck << k;
+                        acc += shl32(ck, k);
                         if (acc >= t) { g.sel = (int)k; g.csel = ck; g.raw = sl[q]; }
                     }
                 }
@@ -260,7 +260,7 @@ __device__ __forceinline__ uint32_t odd_step(const uint32_t* __restrict__ hdr, c
                 uint64_t acc = 0;
 #pragma unroll 1
                 for (uint32_t k = MODE == 1 ? rule.fbits : 0u; k <= hi && sel == 32u; ++k) {
-                    acc += (uint64_t)slot_count(h.slot(hi - k), onem, k) << k;
+                    acc += shl32(slot_count(h.slot(hi - k), onem, k), k);
                     if (r < acc) sel = k;
                 }
             }
@@ -287,7 +287,7 @@ __device__ __forceinline__ uint32_t odd_step(const uint32_t* __restrict__ hdr, c
             const uint32_t i = (uint32_t)(m >> 32);
             if (want == DENSE) {
                 const uint64_t y = edges[i];
-                if ((y >> (32 + sel)) & 1ull) return (uint32_t)y;
+                if (((uint32_t)(y >> 32) >> sel) & 1u) return (uint32_t)y;
                 if (++att >= (1u << 16)) return STOP_VERTEX;
             } else {
                 e = edges[list == ~0ull ? i : pool[list + i]];
@@ -321,7 +321,7 @@ constexpr uint32_t LEAN_MAX_DEG = 1u << 21;
 __device__ __forceinline__ uint32_t lean_rank(const HdrCRef& h, const uint32_t (&sl)[HOT_RANKS], uint64_t tm1,
                                               uint32_t hi, uint32_t onem, uint32_t& raw) {
     uint32_t om = onem << (31 - hi);  // bit 31 - q: rank q is a one-element group
-    const uint32_t t9 = hi >= 9 ? (uint32_t)(tm1 >> (hi - 9)) : (uint32_t)tm1 << (9 - hi);
+    const uint32_t t9 = hi >= 9 ? shr64_lo(tm1, hi - 9) : (uint32_t)tm1 << (9 - hi);
     uint32_t A = 0, cnt = 0;
     raw = sl[0];
 #pragma unroll
@@ -335,7 +335,7 @@ __device__ __forceinline__ uint32_t lean_rank(const HdrCRef& h, const uint32_t (
     uint64_t rest = tm1;
     uint32_t top = hi;  // group of the chunk's first rank
     for (uint32_t base = HOT_RANKS; base <= hi; base += HOT_RANKS) {
-        rest -= (uint64_t)A << (top - 9);  // the ranks so far; top >= 10 here
+        rest -= shl32(A, top - 9);  // the ranks so far; top >= 10 here
         top = hi - base;
         om <<= HOT_RANKS;
         uint32_t x[HOT_RANKS];
@@ -346,7 +346,7 @@ __device__ __forceinline__ uint32_t lean_rank(const HdrCRef& h, const uint32_t (
             x[2 * q] = y.x;
             x[2 * q + 1] = y.y;
         }
-        const uint32_t t = top >= 9 ? (uint32_t)(rest >> (top - 9)) : (uint32_t)rest << (9 - top);
+        const uint32_t t = top >= 9 ? shr64_lo(rest, top - 9) : (uint32_t)rest << (9 - top);
         uint32_t n = 0;
         A = 0;
         raw = x[0];
@@ -427,20 +427,27 @@ __device__ __forceinline__ LeanPick lean_pick(const uint32_t* __restrict__ hdr, 
         // integer groups F..31 ascending, the decimal group last: from the top, with I the integer
         // groups' total, a draw r >= I picks the decimal group and t = I - r picks as in MODE 0
         const uint32_t nint = hi + 1 > rule.fbits ? hi + 1 - rule.fbits : 0u;  // ranks of integer groups
-        uint64_t I = 0;
+        // ranks summed in 32 bits as in lean_rank, eleven at a time past the hot line (d 2^11 is below 2^32)
+        const uint32_t om = onem << (31 - hi);  // bit 31 - i: rank i is a one-element group
+        uint32_t A = 0;
 #pragma unroll
         for (int i = 0; i < HOT_RANKS; ++i)
-            if ((uint32_t)i < nint) I += (uint64_t)((onem >> (hi - i)) & 1u ? 1u : sl[i]) << (hi - i);
+            if ((uint32_t)i < nint) A = 2 * A + ((om >> (31 - i)) & 1u ? 1u : sl[i]);
+        uint64_t I = shl32(A, hi + 1 - min(nint, (uint32_t)HOT_RANKS));
         if (nint > HOT_RANKS) {
             const uint2* c2 = reinterpret_cast<const uint2*>(h.cold + (H_SLOT10 - HDR_HOT));
             uint2 y[11];
 #pragma unroll
             for (int i = 0; i < 11; ++i) y[i] = c2[i];
 #pragma unroll
-            for (int i = 0; i < 22; ++i) {
-                const uint32_t c = i & 1 ? y[i / 2].y : y[i / 2].x;
-                if ((uint32_t)i + HOT_RANKS < nint)
-                    I += (uint64_t)((onem >> (hi - HOT_RANKS - i)) & 1u ? 1u : c) << (hi - HOT_RANKS - i);
+            for (int b0 = 0; b0 < 22; b0 += 11) {
+                A = 0;
+#pragma unroll
+                for (int i = b0; i < b0 + 11; ++i) {
+                    const uint32_t c = i & 1 ? y[i / 2].y : y[i / 2].x;
+                    if ((uint32_t)(i + HOT_RANKS) < nint) A = 2 * A + ((om >> (31 - HOT_RANKS - i)) & 1u ? 1u : c);
+                }
+                if (nint > (uint32_t)(b0 + HOT_RANKS)) I += shl32(A, hi + 1 - min(nint, (uint32_t)(b0 + 11 + HOT_RANKS)));
             }
         }
         if (r >= I) {
@@ -500,7 +507,7 @@ __device__ __forceinline__ uint32_t lane_attempts(const uint32_t* __restrict__ p
             }
 #pragma unroll
             for (int a = SPEC - 1; a >= 0; --a)
-                if (ok[a] && ((e[a] >> (32 + ls.sel)) & 1ull)) v = (uint32_t)e[a];
+                if (ok[a] && (((uint32_t)(e[a] >> 32) >> ls.sel) & 1u)) v = (uint32_t)e[a];
         }
     }
     return v;
@@ -678,8 +685,8 @@ __device__ __forceinline__ uint32_t coop_step(const uint32_t* __restrict__ hdr, 
             uint32_t got = PENDING;
 #pragma unroll
             for (int a = 3; a >= 0; --a)
-                if (ok[a] && ((e[a] >> (32 + p.sel)) & 1ull)) got = (uint32_t)e[a];
-            const uint64_t am = (__ballot(got != PENDING) >> l0) & (G == 64 ? ~0ull : (1ull << (G & 63)) - 1);
+                if (ok[a] && (((uint32_t)(e[a] >> 32) >> p.sel) & 1u)) got = (uint32_t)e[a];
+            const uint64_t am = group_bits<G>(__ballot(got != PENDING), (uint32_t)l0);
             const int src = am ? l0 + __ffsll((long long)am) - 1 : (int)lane;
             const uint32_t y = __shfl(got, src, 64);
             if (dense && am) {
@@ -723,7 +730,7 @@ __device__ __forceinline__ uint64_t wave_take_chunked(bool need, WaveQueue& q, u
     const uint64_t want = __ballot(need);
     if (!want) return NO_WALK;
     const uint32_t cnt = __popcll(want);
-    const uint32_t rank = __popcll(want & lanemask_lt());
+    const uint32_t rank = rank_below(want);
     const uint64_t avail = q.end - q.next;
     uint64_t id;
     if (avail >= cnt) {

@@ -206,7 +206,7 @@ __device__ void st_fresh_lists(uint32_t todo, const uint64_t* __restrict__ edges
             const uint32_t f = __shfl(fill, k, 64);
             const uint32_t io = __shfl(iofs, k, 64);
             if (bit) {
-                const uint32_t pos = f + __popcll(b & lanemask_lt());
+                const uint32_t pos = f + rank_below(b);
                 pool[kb + pos] = i;
                 if (io) pool[kb + io + i] = pos;
             }
@@ -770,7 +770,7 @@ __global__ void __launch_bounds__(STB) k_st_apply_big(const uint32_t* __restrict
                         if (!hb) continue;
                         uint32_t c = 0;
                         if (lane == 0) c = atomicAdd(&s_nc, (uint32_t)__popcll(hb));
-                        c = lane_get(c, 0) + (uint32_t)__popcll(hb & lanemask_lt());
+                        c = lane_get(c, 0) + rank_below(hb);
                         if (hit && c < ST_CAND - 64) {
                             c_dst[c] = v[j];
                             c_idx[c] = i;

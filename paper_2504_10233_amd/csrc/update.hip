@@ -699,9 +699,9 @@ __global__ void __launch_bounds__(TB) k_loc_match(unsigned long long* __restrict
             for (uint64_t s = 0; s <= L.mask && run < nn; s += 64) {
                 const LocSlot c = loc_slot(L, (start + lane) & L.mask);
                 const uint64_t em = __ballot(c.key == LOC_EMPTY);
-                const bool mine = c.key == kk && (uint32_t)c.pos < dd && ((loc_before_empty(em) >> lane) & 1ull);
+                const bool mine = c.key == kk && (uint32_t)c.pos < dd && bit64(loc_before_empty(em), lane);
                 const uint64_t m = __ballot(mine);
-                const uint32_t rank = run + (uint32_t)__popcll(m & lanemask_lt());
+                const uint32_t rank = run + rank_below(m);
                 if (mine && rank >= HOLD && rank < nn && oo + rank < cap) {
                     ckey[oo + rank] = (rr << 32) | pool[sb + (uint32_t)c.pos];
                     cval[oo + rank] = (uint32_t)c.pos;
@@ -1502,7 +1502,7 @@ __device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, const VRow& row, ui
             const uint32_t p = p0 + lane;
             const uint32_t r = p < ck ? xv_rho(xv, Lold[p], s.dn, nholes) : NF;
             const uint64_t b = __ballot(r != NF);
-            if (r != NF) S[nsur + __popcll(b & lanemask_lt())] = r;
+            if (r != NF) S[nsur + rank_below(b)] = r;
             nsur += __popcll(b);
         }
         // new-member part: inserts with bit k, position ck + rank
@@ -1512,10 +1512,10 @@ __device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, const VRow& row, ui
             const bool v = a < s.ni && ((member_word(W[a], fb) >> k) & 1u);
             const uint64_t b = __ballot(v);
             if (b) {
-                const uint32_t p = ck + rank + __popcll(b & lanemask_lt());
+                const uint32_t p = ck + rank + rank_below(b);
                 const uint32_t r = v && p >= cnk ? D[a] : NF;
                 const uint64_t sb = __ballot(r != NF);
-                if (r != NF) S[nsur + __popcll(sb & lanemask_lt())] = r;
+                if (r != NF) S[nsur + rank_below(sb)] = r;
                 nsur += __popcll(sb);
                 rank += __popcll(b);
             }
@@ -1538,7 +1538,7 @@ __device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, const VRow& row, ui
                     const uint32_t a = a0 + lane;
                     const bool v = a < s.ni && ((member_word(W[a], fb) >> k) & 1u);
                     const uint64_t b = __ballot(v);
-                    const uint32_t p = ck + r2 + __popcll(b & lanemask_lt());
+                    const uint32_t p = ck + r2 + rank_below(b);
                     hnew += __popcll(__ballot(v && p < cnk && D[a] == NF));
                     r2 += __popcll(b);
                 }
@@ -1575,7 +1575,7 @@ __device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, const VRow& row, ui
                         const uint32_t pos = x < s.d ? Iold[x] : NF;
                         const bool hole = pos < ck && Lold[pos] == x && pos < cnk;
                         const uint64_t hb = __ballot(hole);
-                        if (hole) H[nhf + __popcll(hb & lanemask_lt())] = pos;
+                        if (hole) H[nhf + rank_below(hb)] = pos;
                         nhf += __popcll(hb);
                     }
                     __threadfence_block();
@@ -1624,7 +1624,7 @@ __device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, const VRow& row, ui
                 const bool hole = v && r == NF;
                 const uint64_t hb = __ballot(hole);
                 if (v) {
-                    const uint32_t val = hole ? S[nh + __popcll(hb & lanemask_lt())] : r;
+                    const uint32_t val = hole ? S[nh + rank_below(hb)] : r;
                     if (val != e || nblk != oblk) {
                         Lnew[p] = val;
                         if (iofs) Lnew[iofs + val] = p;
@@ -1640,13 +1640,13 @@ __device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, const VRow& row, ui
                 const uint32_t a = a0 + lane;
                 const bool v = a < s.ni && ((member_word(W[a], fb) >> k) & 1u);
                 const uint64_t b = __ballot(v);
-                const uint32_t p = ck + r2 + __popcll(b & lanemask_lt());
+                const uint32_t p = ck + r2 + rank_below(b);
                 const bool inpre = v && p < cnk;
                 const uint32_t r = inpre ? D[a] : 0u;
                 const bool hole = inpre && r == NF;
                 const uint64_t hb = __ballot(hole);
                 if (inpre) {
-                    const uint32_t val = hole ? S[nh + __popcll(hb & lanemask_lt())] : r;
+                    const uint32_t val = hole ? S[nh + rank_below(hb)] : r;
                     Lnew[p] = val;
                     if (iofs) Lnew[iofs + val] = p;
                 }
@@ -1736,7 +1736,7 @@ __device__ uint64_t mutate_one(uint64_t t, const MutArgs& A, const VRow& row, ui
                     const uint32_t f = lane_get(fill, k);
                     const uint32_t iofs = ((s.smn >> k) & 1u) ? 0u : lane_get(nlc, k);
                     if (bit) {
-                        const uint32_t pos = f + __popcll(b & lanemask_lt());
+                        const uint32_t pos = f + rank_below(b);
                         pool[blk + pos] = i;
                         if (iofs) pool[blk + iofs + i] = pos;  // a regular group's inverted index
                     }
@@ -1943,10 +1943,10 @@ __global__ void __launch_bounds__(256) k_big_apply(const unsigned long long* __r
 #pragma unroll
             for (uint32_t j = 0; j < BIG_TPT; ++j) {
                 const uint32_t p = q0 + j * 256 + threadIdx.x;
-                uint32_t rk = base + (uint32_t)__popcll(b[j] & lanemask_lt());
+                uint32_t rk = base + rank_below(b[j]);
                 for (uint32_t w = 0; w < wave; ++w) rk += wsum[j][w];
                 base += wsum[j][0] + wsum[j][1] + wsum[j][2] + wsum[j][3];
-                const bool pr = (b[j] >> lane) & 1ull;
+                const bool pr = bit64(b[j], lane);
                 if (bi.kind == BK_FRESH) {
                     if (pr) {
                         L[rk] = p;
@@ -2061,7 +2061,7 @@ __global__ void __launch_bounds__(256) k_big_pass(const unsigned long long* __re
                         unsigned long long base = 0;
                         if (lane == 0) base = atomicAdd(hc, (unsigned long long)__popcll(hb));
                         base = __shfl(base, 0, 64);
-                        const uint64_t slot = base + __popcll(hb & lanemask_lt());
+                        const uint64_t slot = base + rank_below(hb);
                         if (hole && slot < nh) H[slot] = p;
                     }
                     if (p < p1 && !hole && (r != e[j] || moved)) {

@@ -78,12 +78,12 @@ __device__ __forceinline__ uint32_t wave_dense_serve(const uint32_t* __restrict_
                 i = (uint32_t)(mm >> 32);
             }
             const uint64_t vm = __ballot(valid);
-            const uint32_t att = tries + (uint32_t)__popcll(vm & lanemask_lt());
+            const uint32_t att = tries + rank_below(vm);
             uint64_t e = 0;
             bool acc = false;
             if (valid && att < DENSE_MAX_ATTEMPTS) {
                 e = edges[i];
-                acc = (e >> (32 + sel)) & 1ull;
+                acc = ((uint32_t)(e >> 32) >> sel) & 1u;
             }
             const uint64_t am = __ballot(acc);
             if (am) {
@@ -386,7 +386,7 @@ __global__ void __launch_bounds__(TB) k_deepwalk_batch(const uint32_t* __restric
             const int leader = __ffsll((long long)m) - 1;
             const uint32_t qq = __shfl(qi, leader, 64);
             const uint64_t same = __ballot(fin && qi == qq) & m;
-            uint64_t add = ((same >> lane) & 1ull) ? s : 0u;
+            uint64_t add = bit64(same, lane) ? s : 0u;
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) add += __shfl_xor(add, o, 64);
             if ((int)lane == leader && tab.q[qq].steps) atomicAdd(tab.q[qq].steps, (unsigned long long)add);
@@ -444,7 +444,7 @@ __global__ void __launch_bounds__(TB) k_ppr_bound(uint64_t nw, uint64_t base, ui
             }
             const uint64_t b = __ballot(fin);
             if (fin) {
-                j = next + __popcll(b & lanemask_lt());
+                j = next + rank_below(b);
                 s = 0;
             }
             next += __popcll(b);
@@ -598,7 +598,7 @@ struct BinStage {
     __device__ __forceinline__ void add(bool emit, uint32_t vertex, uint32_t src) {
         const uint64_t m = __ballot(emit);
         if (emit) {
-            const uint32_t p = n + (uint32_t)__popcll(m & lanemask_lt());
+            const uint32_t p = n + rank_below(m);
             v[p] = vertex;
             q[p] = src;
         }
@@ -641,8 +641,8 @@ struct BinStage {
             uint64_t pos = __shfl(b, 0, 64);
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                if ((same[k] >> lane) & 1ull) {
-                    const uint64_t p = pos + (uint64_t)__popcll(same[k] & lanemask_lt());
+                if (bit64(same[k], lane)) {
+                    const uint64_t p = pos + rank_below(same[k]);
                     if (p < C) vis[(uint64_t)qq * C + p] = ev[k];
                     else ovf = true;
                 }
@@ -845,7 +845,7 @@ __global__ void __launch_bounds__(TB) k_ppr_step(const uint32_t* __restrict__ hd
             if ((int)lane_id() == leader) b = atomicAdd(ctl + 3 + (in_slot ^ 1), (unsigned long long)__popcll(m));
             b = __shfl(b, leader, 64);
             if (alive) {
-                const uint64_t pos = b + __popcll(m & lanemask_lt());
+                const uint64_t pos = b + rank_below(m);
                 out_id[pos] = id;
                 out_v[pos] = v;
             }
