@@ -578,9 +578,10 @@ __device__ __forceinline__ uint32_t lane_advance(const uint32_t* __restrict__ hd
             ++ls.blk;
             v = lane_attempts<SPEC>(pool, ls, w0, w1, w2, w3, 0u);
         }
-        // acceptance is above alpha % per attempt: the bound only keeps a corrupted structure from spinning
-        if (v == PENDING && ls.blk >= (1u << 14)) v = STOP_VERTEX;
-        if (v != PENDING) ls.pending = false;
+        // 2^14 blocks without an acceptance hold a few attempts less than the 2^16 that end a step (a group of a
+        // few members in a large vertex is dense where alpha is next to nothing): odd_step counts them
+        odd |= v == PENDING && ls.blk >= (1u << 14);
+        if (v != PENDING || odd) ls.pending = false;
     }
     if (lcnt) {
         // the list position's word follows the group draw

@@ -262,3 +262,52 @@ def test_sparse_rebuild_around_its_classes(degree):
         og.update(*(x.numpy() for x in ins + dels))
         assert np.array_equal(g.export(), og.dump()) and np.array_equal(g.export_index(), og.index_dump())
     g.close()
+
+
+def _philox(ids, step, blk, seed):
+    """Words of the streams (seed, ids, step) at block blk; ids and blk broadcast (uint64 arrays)."""
+    m32 = np.uint64(0xFFFFFFFF)
+    ids, blk = np.broadcast_arrays(np.asarray(ids, np.uint64), np.asarray(blk, np.uint64))
+    c = [ids & m32, ids >> np.uint64(32), np.full(ids.shape, step, np.uint64), blk.copy()]
+    k0, k1 = seed & 0xFFFFFFFF, seed >> 32
+    for _ in range(10):
+        a, b = np.uint64(0xD2511F53) * c[0], np.uint64(0xCD9E8D57) * c[2]
+        c = [(b >> np.uint64(32)) ^ c[1] ^ np.uint64(k0), b & m32, (a >> np.uint64(32)) ^ c[3] ^ np.uint64(k1), a & m32]
+        k0, k1 = (k0 + 0x9E3779B9) & 0xFFFFFFFF, (k1 + 0xBB67AE85) & 0xFFFFFFFF
+    return np.stack(c, -1)
+
+
+@pytest.mark.parametrize("head", [2, 3])  # words before the first attempt: walk, personalized PageRank
+def test_the_last_attempts_of_a_dense_step(head):
+    """A dense step ends after 2^16 attempts, in every form alike.  With alpha = 0 a group of two members is
+    dense in a vertex of 2^17 edges; walks whose first acceptance is among the last attempts find it."""
+    import torch
+    from paper_2504_10233_amd import MODE_PER_STEP, Graph
+    d, seed = 1 << 17, 91
+    dst = torch.full((d,), 2, dtype=torch.int64)
+    w = torch.ones(d, dtype=torch.int64)
+    hits = (70001, 70002)
+    for i in hits:
+        w[i], dst[i] = 1 << 20, 1
+    # d is a power of two: a word w names the edge w >> 15, and none is drawn again
+    accepts = lambda words: ((words >> np.uint64(15)) == hits[0]) | ((words >> np.uint64(15)) == hits[1])
+    ids = np.arange(1 << 20, dtype=np.uint64)
+    late = accepts(_philox(ids, 0, 1 << 14, seed)[:, :head]).any(1)  # words 2^16 .. of the stream
+    W = (1 << 21) + d - 2
+    picked = []
+    for j in ids[late]:
+        words = _philox(j, 0, np.arange(1 << 14, dtype=np.uint64), seed).reshape(-1)
+        x = (int(words[head - 2]) << 32) | int(words[head - 1])
+        if (x * W) >> 64 >= d - 2 and not accepts(words[head:]).any():
+            picked.append(int(j))
+    assert len(picked) >= 3
+    g = Graph(3, torch.zeros(d, dtype=torch.int64), dst, w, alpha=0)
+    for wave in (0, 1, 1 << 31):  # several lanes per walk; wave-served steps; a lane per walk
+        g.set_tuning(wave_degree=wave)
+        for j in picked[:4]:
+            for mode in (0, MODE_PER_STEP):
+                if head == 2:
+                    assert g.walk(torch.zeros(1, dtype=torch.int32), 1, seed, base=j, mode=mode)[0][0].tolist() == [0, 1]
+                else:
+                    assert g.ppr(torch.zeros(1, dtype=torch.int32), 1, 0, 1, seed, base=j, mode=mode)[1].tolist() == [0, 1]
+    g.close()
