@@ -716,7 +716,7 @@ __device__ __forceinline__ void wave_pad_row(bool stop, uint32_t* row, uint32_t 
         const uint64_t r = ((uint64_t)__shfl((uint32_t)((uint64_t)row >> 32), l, 64) << 32) |
                            __shfl((uint32_t)(uint64_t)row, l, 64);
         uint32_t* p = reinterpret_cast<uint32_t*>(r);
-        for (uint32_t x = __shfl(from, l, 64) + lane; x <= L; x += 64) p[x] = STOP_VERTEX;
+        for (uint64_t x = (uint64_t)__shfl(from, l, 64) + lane; x <= L; x += 64) p[x] = STOP_VERTEX;  // L up to 2^32 - 2
     }
 }
 

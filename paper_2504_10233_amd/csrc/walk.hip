@@ -241,7 +241,7 @@ __global__ void __launch_bounds__(TB) k_deepwalk_coop(const uint32_t* __restrict
         if (sub == 0) row[0] = u;
         if (u >= n) {
             if (sub == 0) atomicOr(err, ERR_RANGE);
-            for (uint32_t x = 1 + sub; x <= L; x += G) row[x] = STOP_VERTEX;
+            for (uint64_t x = 1ull + sub; x <= L; x += G) row[x] = STOP_VERTEX;
             act = false;
         }
     }
@@ -254,7 +254,7 @@ __global__ void __launch_bounds__(TB) k_deepwalk_coop(const uint32_t* __restrict
         cw = nx;
         if (act) {
             if (v == STOP_VERTEX) {
-                for (uint32_t x = s + 1 + sub; x <= L; x += G) row[x] = STOP_VERTEX;
+                for (uint64_t x = s + 1ull + sub; x <= L; x += G) row[x] = STOP_VERTEX;
                 act = false;
             } else {
                 if (sub == 0) {

@@ -311,3 +311,24 @@ def test_the_last_attempts_of_a_dense_step(head):
                 else:
                     assert g.ppr(torch.zeros(1, dtype=torch.int32), 1, 0, 1, seed, base=j, mode=mode)[1].tolist() == [0, 1]
     g.close()
+
+
+def test_the_longest_rows():
+    """Walks of 2^32 - 2 steps that end at once: the rest of each row, up to entry 2^32 - 2, is padding."""
+    import torch
+    from paper_2504_10233_amd import Graph
+    L = (1 << 32) - 2
+    g = Graph(2, torch.tensor([0]), torch.tensor([1]), torch.tensor([5]))
+    out = torch.empty((1, L + 1), dtype=torch.int32, device="cuda")
+    for form in ("lanes", "lane", "node2vec", "bad start"):
+        out.zero_()
+        g.set_tuning(wave_degree=(1 << 31) if form == "lane" else 0)
+        start = torch.tensor([2 if form == "bad start" else 0], dtype=torch.int32)
+        if form == "node2vec":
+            g.node2vec(start, L, 3, 0.5, 2.0, out=out)
+        else:
+            g.walk(start, L, 3, out=out)
+        if form != "bad start":
+            assert out[0, :2].tolist() == [0, 1], form
+        assert bool((out[0, 2:] == -1).all()), form
+    g.close()
