@@ -15,7 +15,11 @@
  *
  * Ownership.  Input and output buffers belong to the caller and must stay
  * valid until the stream work that uses them has finished.  A bingo_graph owns
- * all of its device memory and releases it in bingo_destroy().
+ * all of its device memory until bingo_destroy().  Of a destroyed graph the
+ * library keeps the headers, pool and workspace, where they have 1 MiB and more,
+ * for graphs of about the same sizes: at most 4 GiB in the process, a block for
+ * at most 32 later frees.  bingo_trim() gives them back to the device, and so
+ * does any of the library's device allocations before it fails.
  *
  * Concurrency.  A handle is not thread-safe.  bingo_walk and bingo_walk_batch
  * calls may overlap each other on different streams, any number of them: each
@@ -649,8 +653,17 @@ int bingo_probe_replay(bingo_graph* g, const uint32_t* d_visits, uint64_t n_visi
 /* bingo_num_vertices -- n of the handle. */
 uint32_t bingo_num_vertices(const bingo_graph* g);
 
-/* bingo_destroy -- release the handle and all its device memory. */
+/* bingo_destroy -- release the handle and its device memory (large blocks may stay with the library for the
+ * next graph: see Ownership above, and bingo_trim). */
 void bingo_destroy(bingo_graph* g);
+
+/*
+ * bingo_trim -- give back the device memory that the library keeps from
+ * destroyed graphs (a program that has destroyed its last graph, or whose other
+ * parts need the memory).  *h_bytes (optional) receives its size.  Graphs that
+ * live are not touched; may be called from any thread.
+ */
+int bingo_trim(uint64_t* h_bytes);
 
 /* bingo_strerror -- static description of a return code. */
 const char* bingo_strerror(int code);

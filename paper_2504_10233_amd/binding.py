@@ -59,7 +59,7 @@ EXPORTS = ["bingo_build", "bingo_update_batch", "bingo_walk", "bingo_ppr", "bing
            "bingo_server_submit_walk", "bingo_server_submit_update", "bingo_server_wait", "bingo_server_destroy",
            "bingo_probe_random_reads", "bingo_node2vec", "bingo_quantize_biases", "bingo_update_stream",
            "bingo_compact", "bingo_walk_batch", "bingo_walk_noalloc", "bingo_export_index_range", "bingo_probe_replay",
-           "bingo_check_locator", "bingo_ppr_async", "bingo_ppr_wait"]
+           "bingo_check_locator", "bingo_ppr_async", "bingo_ppr_wait", "bingo_trim"]
 
 
 class _ServerConfig(C.Structure):
@@ -136,10 +136,28 @@ def load():
         L.bingo_num_vertices.restype = u32
         L.bingo_destroy.argtypes = [vp]
         L.bingo_destroy.restype = None
+        L.bingo_trim.argtypes = [C.POINTER(u64)]
         L.bingo_strerror.argtypes = [C.c_int]
         L.bingo_strerror.restype = C.c_char_p
         _lib = L
         return L
+
+
+def trim() -> int:
+    """Give back the device memory kept from destroyed graphs (bingo_trim); returns its bytes."""
+    n = C.c_uint64(0)
+    _check(load().bingo_trim(C.byref(n)), "bingo_trim")
+    return int(n.value)
+
+
+def _empty(shape, dtype, device):
+    """torch.empty that gives the memory kept from destroyed graphs back before it fails."""
+    try:
+        return torch.empty(shape, dtype=dtype, device=device)
+    except torch.OutOfMemoryError:
+        if not trim():
+            raise
+        return torch.empty(shape, dtype=dtype, device=device)
 
 
 def probe_random_reads(table, lanes, reads, dependent, line_bytes=64, seed=1, stream=None) -> dict:
@@ -235,7 +253,7 @@ class Graph:
         """DeepWalk paths (n_walks, length + 1) as int32 bit patterns of uint32; returns (paths, steps)."""
         st = as_u32(starts, self.device)
         nw = st.numel()
-        paths = out if out is not None else torch.empty((nw, length + 1), dtype=torch.int32, device=self.device)
+        paths = out if out is not None else _empty((nw, length + 1), torch.int32, self.device)
         steps = torch.zeros(1, dtype=torch.int64, device=self.device)
         rc = load().bingo_walk(self.h, nw, _ptr(st), base, length, seed, _ptr(paths), _ptr(steps), mode,
                                _stream(stream))
@@ -257,7 +275,7 @@ class Graph:
         keep, out = [], []
         for i, (starts, length, seed, base) in enumerate(queries):
             st = as_u32(starts, self.device)
-            paths = torch.empty((st.numel(), length + 1), dtype=torch.int32, device=self.device)
+            paths = _empty((st.numel(), length + 1), torch.int32, self.device)
             steps = torch.zeros(1, dtype=torch.int64, device=self.device)
             qs[i] = _WalkQuery(st.numel(), _ptr(st).value, base, length, 0, seed, _ptr(paths).value,
                                steps.data_ptr())
@@ -271,7 +289,7 @@ class Graph:
         (paths, counts) with counts = int64 [transitions, proposals] on the device."""
         st = as_u32(starts, self.device)
         nw = st.numel()
-        paths = out if out is not None else torch.empty((nw, length + 1), dtype=torch.int32, device=self.device)
+        paths = out if out is not None else _empty((nw, length + 1), torch.int32, self.device)
         counts = torch.zeros(2, dtype=torch.int64, device=self.device)
         rc = load().bingo_node2vec(self.h, nw, _ptr(st), base, length, float(p), float(q), seed, _ptr(paths),
                                    _ptr(counts), _stream(stream))
@@ -286,9 +304,9 @@ class Graph:
         rc = L.bingo_ppr(self.h, src.numel(), _ptr(src), walks_per_source, thr, max_len, seed, base, mode,
                          C.byref(ne), C.byref(ns), _stream(stream))
         _check(rc, "bingo_ppr")
-        off = torch.empty(src.numel() + 1, dtype=torch.int64, device=self.device)
-        vtx = torch.empty(max(ne.value, 1), dtype=torch.int32, device=self.device)
-        cnt = torch.empty(max(ne.value, 1), dtype=torch.int32, device=self.device)
+        off = _empty(src.numel() + 1, torch.int64, self.device)
+        vtx = _empty(max(ne.value, 1), torch.int32, self.device)
+        cnt = _empty(max(ne.value, 1), torch.int32, self.device)
         rc = L.bingo_ppr_fetch(self.h, _ptr(off), _ptr(vtx), _ptr(cnt), vtx.numel(), _stream(stream))
         _check(rc, "bingo_ppr_fetch")
         return off, vtx[: ne.value], cnt[: ne.value], int(ns.value)
@@ -316,9 +334,9 @@ class Graph:
         """(offsets, vertex, count) of the last PPR query (waits for a pending histogram)."""
         ne, _ = self.ppr_wait()
         L = load()
-        off = torch.empty(self._async_nsrc + 1, dtype=torch.int64, device=self.device)
-        vtx = torch.empty(max(ne, 1), dtype=torch.int32, device=self.device)
-        cnt = torch.empty(max(ne, 1), dtype=torch.int32, device=self.device)
+        off = _empty(self._async_nsrc + 1, torch.int64, self.device)
+        vtx = _empty(max(ne, 1), torch.int32, self.device)
+        cnt = _empty(max(ne, 1), torch.int32, self.device)
         rc = L.bingo_ppr_fetch(self.h, _ptr(off), _ptr(vtx), _ptr(cnt), vtx.numel(), _stream(stream))
         _check(rc, "bingo_ppr_fetch")
         return off, vtx[:ne], cnt[:ne]

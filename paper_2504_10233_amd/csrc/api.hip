@@ -18,12 +18,14 @@
 // takes 3 ms of device time.  A destroyed graph's headers, pool and workspace
 // are therefore kept for the next one: at most DEV_KEEP bytes in the process, a
 // block of at most a quarter more than is asked for, and not for longer than
-// DEV_AGE later frees; they are given back as well when an allocation fails.  Blocks
+// DEV_AGE later frees; bingo_trim gives them all back, and so does every device
+// allocation of the library that fails, which is then tried once more.  Blocks
 // under 1 MiB are not kept.  A block belongs to the device that was current at
 // its allocation, and is kept only by calls that have waited for that device.
 // ---------------------------------------------------------------------------
 namespace {
 constexpr size_t DEV_KEEP = 4ull << 30;
+constexpr size_t DEV_LEAST = 1ull << 20;
 constexpr uint64_t DEV_AGE = 32;
 struct DevBlock {
     void* p;
@@ -33,24 +35,26 @@ struct DevBlock {
 };
 struct DevBlocks {
     std::mutex mu;
-    std::vector<DevBlock> idle;
-    std::unordered_map<void*, DevBlock> live;
+    std::vector<DevBlock> idle;                // in order of freeing
+    std::unordered_map<void*, DevBlock> live;  // blocks in use that may be kept
     size_t idle_bytes = 0;
     uint64_t tick = 0;
-    // give back idle blocks: all, or those past the bounds
-    void trim(bool all) {
-        size_t keep = 0;
+    // give back idle blocks, all or those past the bounds; returns their bytes
+    size_t trim(bool all) {
+        size_t keep = 0, given = 0;
         for (size_t i = 0; i < idle.size(); ++i) {
             DevBlock& b = idle[i];
-            // the oldest come first (idle is in order of freeing)
+            // the oldest come first
             if (all || idle_bytes > DEV_KEEP || tick - b.tick > DEV_AGE) {
                 hipFree(b.p);
                 idle_bytes -= b.bytes;
+                given += b.bytes;
             } else {
                 idle[keep++] = b;
             }
         }
         idle.resize(keep);
+        return given;
     }
 };
 DevBlocks& dev_blocks() {
@@ -63,38 +67,77 @@ size_t dev_round(size_t bytes) {
     while ((step << 4) <= bytes) step <<= 1;
     return (bytes + step - 1) & ~(step - 1);
 }
+// `get` until it succeeds, at most twice: the idle blocks are given back in between
+template <class F>
+hipError_t dev_try(F get) {
+    hipError_t e = get();
+    if (e == hipSuccess) return e;
+    (void)hipGetLastError();
+    if (!dev_trim()) return e;
+    e = get();
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
+}
 }  // namespace
+
+size_t dev_trim() {
+    DevBlocks& d = dev_blocks();
+    std::lock_guard<std::mutex> lk(d.mu);
+    return d.trim(true);
+}
+
+hipError_t dev_malloc(void** p, size_t bytes) {
+    const hipError_t e = dev_try([&] { return hipMalloc(p, bytes); });
+    if (e != hipSuccess) *p = nullptr;
+    return e;
+}
+
+hipError_t dev_malloc_async(void** p, size_t bytes, hipStream_t st) {
+    const hipError_t e = dev_try([&] { return hipMallocAsync(p, bytes, st); });
+    if (e != hipSuccess) *p = nullptr;
+    return e;
+}
 
 void* dev_alloc(size_t bytes) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return nullptr;
-    const bool large = bytes >= (1u << 20);
-    const size_t want = large ? dev_round(bytes) : bytes;
+    // what is never kept is not rounded up either
+    const bool keep = bytes >= DEV_LEAST && dev_round(bytes) <= DEV_KEEP;
+    void* p = nullptr;
+    if (!keep) return dev_malloc(&p, bytes) == hipSuccess ? p : nullptr;
     DevBlocks& d = dev_blocks();
-    std::lock_guard<std::mutex> lk(d.mu);
-    size_t best = d.idle.size();
-    for (size_t i = 0; large && i < d.idle.size(); ++i) {
-        const DevBlock& b = d.idle[i];
-        if (b.dev == dev && b.bytes >= want && b.bytes <= want + want / 4 &&
-            (best == d.idle.size() || b.bytes < d.idle[best].bytes))
-            best = i;
-    }
-    DevBlock b{nullptr, want, dev, 0};
-    if (best < d.idle.size()) {
-        b = d.idle[best];
-        d.idle.erase(d.idle.begin() + (long)best);
-        d.idle_bytes -= b.bytes;
-    } else {
-        hipError_t e = hipMalloc(&b.p, want);
-        if (e != hipSuccess && !d.idle.empty()) {
-            (void)hipGetLastError();
-            d.trim(true);
-            e = hipMalloc(&b.p, want);
+    size_t want = dev_round(bytes);
+    try {
+        std::lock_guard<std::mutex> lk(d.mu);
+        size_t best = d.idle.size();
+        for (size_t i = 0; i < d.idle.size(); ++i) {
+            const DevBlock& b = d.idle[i];
+            if (b.dev == dev && b.bytes >= want && b.bytes <= want + want / 4 &&
+                (best == d.idle.size() || b.bytes < d.idle[best].bytes))
+                best = i;
         }
-        if (e != hipSuccess) return nullptr;
+        if (best < d.idle.size()) {
+            const DevBlock b = d.idle[best];
+            d.live[b.p] = b;
+            d.idle.erase(d.idle.begin() + (long)best);
+            d.idle_bytes -= b.bytes;
+            return b.p;
+        }
+    } catch (const std::bad_alloc&) {
+        // no host memory for the list's entry: the block stays idle
     }
-    if (large) d.live[b.p] = b;
-    return b.p;
+    if (hipMalloc(&p, want) != hipSuccess) {
+        (void)hipGetLastError();
+        want = bytes;  // near the end of the memory: the exact size
+        if (dev_malloc(&p, want) != hipSuccess) return nullptr;
+    }
+    try {
+        std::lock_guard<std::mutex> lk(d.mu);
+        d.live[p] = DevBlock{p, want, dev, 0};
+    } catch (const std::bad_alloc&) {
+        // not listed: dev_free gives it back instead of keeping it
+    }
+    return p;
 }
 
 void dev_free(void* p, bool idle) {
@@ -103,17 +146,22 @@ void dev_free(void* p, bool idle) {
     if (hipGetDevice(&dev) != hipSuccess) dev = -1;
     DevBlocks& d = dev_blocks();
     std::lock_guard<std::mutex> lk(d.mu);
-    auto it = d.live.find(p);
-    if (it == d.live.end() || !idle || it->second.dev != dev || it->second.bytes > DEV_KEEP) {
-        if (it != d.live.end()) d.live.erase(it);
-        hipFree(p);
-    } else {
+    const auto it = d.live.find(p);
+    bool kept = false;
+    if (it != d.live.end()) {
         DevBlock b = it->second;
         d.live.erase(it);
-        b.tick = d.tick;
-        d.idle.push_back(b);
-        d.idle_bytes += b.bytes;
+        if (idle && b.dev == dev) {
+            b.tick = d.tick;
+            try {
+                d.idle.push_back(b);
+                d.idle_bytes += b.bytes;
+                kept = true;
+            } catch (const std::bad_alloc&) {
+            }
+        }
     }
+    if (!kept) hipFree(p);
     ++d.tick;
     d.trim(false);
 }
@@ -122,8 +170,7 @@ void* ws_get(bingo_graph* g, size_t bytes) {
     // a pending asynchronous PPR histogram still reads its visit bins here
     if (ppr_drain(g) != BINGO_OK) return nullptr;
     if (bytes <= g->ws_bytes && g->ws) return g->ws;
-    hipDeviceSynchronize();
-    dev_free(g->ws, true);
+    dev_free(g->ws, hipDeviceSynchronize() == hipSuccess);
     g->ws = nullptr;
     g->ws_bytes = 0;
     const size_t want = bytes + bytes / 4 + 4096;
@@ -149,8 +196,8 @@ int err_to_code(uint32_t bits) {
     return BINGO_OK;
 }
 
-// Free everything the handle owns; nothing on the current device uses it any more.
-static void release(bingo_graph* g) {
+// Free everything the handle owns; idle: the current device has finished all work on it.
+static void release(bingo_graph* g, bool idle) {
     if (!g) return;
     update_release(g);
     locator_release(g);
@@ -160,15 +207,15 @@ static void release(bingo_graph* g) {
         if (g->slot_ev[i]) hipEventDestroy(g->slot_ev[i]);
     for (hipEvent_t e : {g->ppr_done, g->ppr_h0, g->ppr_h1})
         if (e) hipEventDestroy(e);
-    dev_free(g->hdr_mem, true);
+    dev_free(g->hdr_mem, idle);
     hipFree(g->alias);
-    dev_free(g->pool, true);
+    dev_free(g->pool, idle);
     hipFree(g->d_ctl);
     hipFree(g->d_err);
     hipFree(g->ppr_off);
     hipFree(g->ppr_vtx);
     hipFree(g->ppr_cnt);
-    dev_free(g->ws, true);
+    dev_free(g->ws, idle);
     hipFree(g->aux);
     hipFree(g->n2v_idx);
     hipFree(g->n2v_off);
@@ -205,20 +252,19 @@ int bingo_build(const bingo_config* cfg, uint32_t n, uint64_t m, const uint32_t*
     const uint64_t hdr_words = radix == 4 ? (uint64_t)n * H4_WORDS : hdr_total_words(n);
     g->hdr = g->hdr_mem = nullptr; g->pool = nullptr; g->d_ctl = nullptr; g->d_err = nullptr; g->alias = nullptr;
     if (!(g->hdr_mem = (uint32_t*)dev_alloc(hdr_words * 4)) ||
-        hipMalloc(&g->d_ctl, CTL_WORDS * 8) != hipSuccess || hipMalloc(&g->d_err, 4) != hipSuccess) {
-        release(g);
+        dev_malloc(&g->d_ctl, CTL_WORDS * 8) != hipSuccess || dev_malloc(&g->d_err, 4) != hipSuccess) {
+        release(g, true);
         return BINGO_E_OOM;
     }
     g->hdr = radix == 4 ? g->hdr_mem : g->hdr_mem + hdr_front_words(n);
     if (hipMemsetAsync(g->hdr_mem, 0, hdr_words * 4, st) != hipSuccess ||
         hipMemsetAsync(g->d_ctl, 0, CTL_WORDS * 8, st) != hipSuccess) {
-        release(g);
+        release(g, hipStreamSynchronize(st) == hipSuccess);
         return BINGO_E_HIP;
     }
     const int rc = build_graph(g, m, d_src, d_dst, d_w, st);
     if (rc != BINGO_OK) {
-        hipStreamSynchronize(st);
-        release(g);
+        release(g, hipStreamSynchronize(st) == hipSuccess);
         return rc;
     }
     *out = g;
@@ -420,8 +466,13 @@ int bingo_last_phase_ms(bingo_graph* g, float* h_ms, uint32_t cap, uint32_t* h_n
 
 void bingo_destroy(bingo_graph* g) {
     if (!g) return;
-    hipDeviceSynchronize();
-    release(g);
+    release(g, hipDeviceSynchronize() == hipSuccess);
+}
+
+int bingo_trim(uint64_t* h_bytes) {
+    const size_t given = dev_trim();
+    if (h_bytes) *h_bytes = given;
+    return BINGO_OK;
 }
 
 const char* bingo_strerror(int code) {

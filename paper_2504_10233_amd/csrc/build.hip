@@ -1135,7 +1135,7 @@ int build_graph(bingo_graph* g, uint64_t m, const uint32_t* src, const uint32_t*
                                (uint64_t)tot[0], g->hdr, g->pool, (const uint32_t*)hub, g->rule);
     }
     if (g->alias_mode) {
-        if (hipMalloc(&g->alias, (size_t)n * ALIAS_ENTRIES * sizeof(uint4)) != hipSuccess) {
+        if (dev_malloc(&g->alias, (size_t)n * ALIAS_ENTRIES * sizeof(uint4)) != hipSuccess) {
             g->alias = nullptr;
             return BINGO_E_OOM;
         }

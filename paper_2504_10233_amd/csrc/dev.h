@@ -554,9 +554,17 @@ int update_batch(bingo_graph* g, uint64_t n_ins, const uint32_t* is, const uint3
 int update_stream(bingo_graph* g, uint64_t m, const uint32_t* op, const uint32_t* src, const uint32_t* dst,
                   const uint32_t* w, bingo_update_stats* h_stats, hipStream_t st);
 // api.hip
-// device memory that is kept for the next graph (see there): dev_free's `idle` says that the
-// current device has finished all work on the block
+// Device memory.  dev_alloc / dev_free: blocks that are kept for the next graph (see there); `idle` says that
+// the current device has finished all work on the block.  dev_malloc / dev_malloc_async: all others (freed by
+// hipFree / hipFreeAsync).  Each gives the kept blocks back before it fails; dev_trim gives them back at once.
 void* dev_alloc(size_t bytes);
 void dev_free(void* p, bool idle);
+hipError_t dev_malloc(void** p, size_t bytes);
+hipError_t dev_malloc_async(void** p, size_t bytes, hipStream_t st);
+size_t dev_trim();
+template <class T>
+inline hipError_t dev_malloc(T** p, size_t bytes) {
+    return dev_malloc((void**)p, bytes);
+}
 void* ws_get(bingo_graph* g, size_t bytes);  // grow-only scratch (synchronizes when it grows)
 int err_to_code(uint32_t bits);

@@ -203,7 +203,7 @@ bool loc_build(bingo_graph* g, uint64_t cap, hipStream_t st) {
         hipFree(g->loc_tab);
         g->loc_tab = nullptr;
         g->loc_cap = 0;
-        if (hipMalloc(&g->loc_tab, (2 * cap + chunk_list_words(cap)) * 8) != hipSuccess) {
+        if (dev_malloc(&g->loc_tab, (2 * cap + chunk_list_words(cap)) * 8) != hipSuccess) {
             (void)hipGetLastError();
             g->loc_tab = nullptr;
             return false;

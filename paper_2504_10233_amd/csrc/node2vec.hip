@@ -229,7 +229,7 @@ int build_index(bingo_graph* g, hipStream_t st) {
     const uint32_t n = g->n;
     auto al = [](uint64_t x) { return (x + 255) & ~255ull; };
     if (!g->n2v_off) {
-        if (hipMalloc(&g->n2v_off, ((uint64_t)n + 1) * 8) != hipSuccess) { g->n2v_off = nullptr; return BINGO_E_OOM; }
+        if (dev_malloc(&g->n2v_off, ((uint64_t)n + 1) * 8) != hipSuccess) { g->n2v_off = nullptr; return BINGO_E_OOM; }
     }
     char* w = (char*)ws_get(g, al((uint64_t)n * 4) + scan_temp_bytes((uint64_t)n + 1) + 512);
     if (!w) return BINGO_E_OOM;
@@ -245,7 +245,7 @@ int build_index(bingo_graph* g, hipStream_t st) {
     if (m > g->n2v_cap || !g->n2v_idx) {
         hipFree(g->n2v_idx);
         g->n2v_cap = std::max<uint64_t>(m, 1024) + m / 8;
-        if (hipMalloc(&g->n2v_idx, g->n2v_cap * 4) != hipSuccess) {
+        if (dev_malloc(&g->n2v_idx, g->n2v_cap * 4) != hipSuccess) {
             g->n2v_idx = nullptr;
             g->n2v_cap = 0;
             return BINGO_E_OOM;

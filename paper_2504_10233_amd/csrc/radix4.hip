@@ -304,7 +304,7 @@ int export_graph4(bingo_graph* g, uint32_t u0, uint32_t u1, uint32_t* h_buf, uin
     if (!h_buf) return BINGO_OK;
     if (cap < T) return BINGO_E_CAPACITY;
     uint32_t* dbuf = nullptr;
-    if (hipMalloc(&dbuf, std::max<uint64_t>(T, 1) * 4) != hipSuccess) return BINGO_E_OOM;
+    if (dev_malloc(&dbuf, std::max<uint64_t>(T, 1) * 4) != hipSuccess) return BINGO_E_OOM;
     hipLaunchKernelGGL(k_dump4_write, dim3((nv + 3) / 4), dim3(TB4), 0, st, g->hdr, g->pool, u0, u1, g->rule,
                        (const uint64_t*)off, dbuf);
     hipError_t e1 = hipMemcpyAsync(h_buf, dbuf, T * 4, hipMemcpyDeviceToHost, st);

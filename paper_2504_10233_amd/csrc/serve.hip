@@ -123,7 +123,7 @@ bool try_admit(bingo_server* s, std::unique_lock<std::mutex>& lk) {
         uint32_t* d = nullptr;
         const uint64_t words = 3 * ni + 2 * nd;
         if (words) {
-            if (hipMallocAsync((void**)&d, words * 4, s->ustream) != hipSuccess) rc = BINGO_E_OOM;
+            if (dev_malloc_async((void**)&d, words * 4, s->ustream) != hipSuccess) rc = BINGO_E_OOM;
             if (rc == BINGO_OK) {
                 uint32_t* p = d;
                 auto put = [&](const std::vector<uint32_t>& v) {
@@ -178,7 +178,7 @@ bool try_admit(bingo_server* s, std::unique_lock<std::mutex>& lk) {
         q->t_start = Clock::now();
         const uint64_t nw = q->starts.size(), pw = nw * ((uint64_t)q->length + 1);
         if (rc == BINGO_OK &&
-            hipMallocAsync((void**)&q->d_buf, std::max<uint64_t>(nw + pw, 1) * 4 + 32, st) != hipSuccess) {
+            dev_malloc_async((void**)&q->d_buf, std::max<uint64_t>(nw + pw, 1) * 4 + 32, st) != hipSuccess) {
             q->d_buf = nullptr;
             rc = BINGO_E_OOM;
         }

@@ -1041,7 +1041,7 @@ int apply_stream(bingo_graph* g, uint64_t m, const uint32_t* op, const uint32_t*
     HIPCHK(hipStreamSynchronize(st));
     if (k == 0) return BINGO_E_OOM;
     uint32_t* rest = nullptr;
-    if (hipMallocAsync((void**)&rest, k * 16, st) != hipSuccess) return BINGO_E_OOM;
+    if (dev_malloc_async((void**)&rest, k * 16, st) != hipSuccess) return BINGO_E_OOM;
     hipLaunchKernelGGL(k_st_gather, dim3(grid_for(m)), dim3(TB), 0, st, m, (const uint32_t*)left, (const uint64_t*)hx,
                        op, src, dst, w, rest, (uint64_t)k);
     unsigned long long ctl[2] = {0, 0};

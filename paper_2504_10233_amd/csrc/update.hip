@@ -2484,7 +2484,7 @@ static UpdPlan* plan_make(uint64_t rmax, uint64_t cmax) {
     p->cmax = C;
     p->grid_an = resident_grid((const void*)k_analyze, WB);
     p->grid_mu = resident_grid((const void*)k_mutate, WB);
-    if (hipMalloc(&p->ws, bytes) != hipSuccess) { delete p; return nullptr; }
+    if (dev_malloc(&p->ws, bytes) != hipSuccess) { delete p; return nullptr; }
     p->bytes = bytes;
     char* w = p->ws;
     auto take = [&](uint64_t b) { char* r = w; w += al(b); return r; };

@@ -1363,7 +1363,7 @@ static int ensure_ppr_off(bingo_graph* g, uint32_t nsrc) {
     if (g->ppr_off_cap < nsrc + 1 || !g->ppr_off) {
         hipFree(g->ppr_off);
         g->ppr_off_cap = nsrc + 1;
-        if (hipMalloc(&g->ppr_off, (uint64_t)(nsrc + 1) * 8) != hipSuccess) {
+        if (dev_malloc(&g->ppr_off, (uint64_t)(nsrc + 1) * 8) != hipSuccess) {
             g->ppr_off = nullptr; g->ppr_off_cap = 0;
             return BINGO_E_OOM;
         }
@@ -1402,7 +1402,7 @@ static int finish_lds_hist(bingo_graph* g, uint32_t* vis, uint32_t* hcnt, uint32
         // sized for every visit a distinct vertex (as the asynchronous form needs), so that a
         // later query of the same shape, synchronous or not, allocates nothing
         g->ppr_cap = std::max<uint64_t>(std::max(U, total), 1024);
-        if (hipMalloc(&g->ppr_vtx, g->ppr_cap * 4) != hipSuccess || hipMalloc(&g->ppr_cnt, g->ppr_cap * 4) != hipSuccess) {
+        if (dev_malloc(&g->ppr_vtx, g->ppr_cap * 4) != hipSuccess || dev_malloc(&g->ppr_cnt, g->ppr_cap * 4) != hipSuccess) {
             g->ppr_vtx = g->ppr_cnt = nullptr; g->ppr_cap = 0;
             return BINGO_E_OOM;
         }
@@ -1431,7 +1431,7 @@ static int finish_lds_hist_async(bingo_graph* g, uint32_t* vis, uint32_t* hcnt, 
     if (g->ppr_cap < total || !g->ppr_vtx) {
         hipFree(g->ppr_vtx); hipFree(g->ppr_cnt);
         g->ppr_cap = std::max<uint64_t>(total, 1024);
-        if (hipMalloc(&g->ppr_vtx, g->ppr_cap * 4) != hipSuccess || hipMalloc(&g->ppr_cnt, g->ppr_cap * 4) != hipSuccess) {
+        if (dev_malloc(&g->ppr_vtx, g->ppr_cap * 4) != hipSuccess || dev_malloc(&g->ppr_cnt, g->ppr_cap * 4) != hipSuccess) {
             g->ppr_vtx = g->ppr_cnt = nullptr; g->ppr_cap = 0;
             return BINGO_E_OOM;
         }
@@ -1578,7 +1578,7 @@ int run_ppr(bingo_graph* g, uint32_t nsrc, const uint32_t* sources, uint32_t R, 
         hipFree(g->aux);
         g->aux = nullptr;
         g->aux_bytes = 0;
-        if (hipMalloc(&g->aux, aux_need + aux_need / 4) != hipSuccess) { g->aux = nullptr; return BINGO_E_OOM; }
+        if (dev_malloc(&g->aux, aux_need + aux_need / 4) != hipSuccess) { g->aux = nullptr; return BINGO_E_OOM; }
         g->aux_bytes = aux_need + aux_need / 4;
     }
     char* a = (char*)g->aux;
@@ -1662,8 +1662,8 @@ int run_ppr(bingo_graph* g, uint32_t nsrc, const uint32_t* sources, uint32_t R, 
     if (g->ppr_cap < U || !g->ppr_vtx) {
         hipFree(g->ppr_vtx); hipFree(g->ppr_cnt);
         g->ppr_cap = std::max<uint64_t>(U, 1024) * 5 / 4;
-        if (hipMalloc(&g->ppr_vtx, g->ppr_cap * 4) != hipSuccess ||
-            hipMalloc(&g->ppr_cnt, g->ppr_cap * 4) != hipSuccess) {
+        if (dev_malloc(&g->ppr_vtx, g->ppr_cap * 4) != hipSuccess ||
+            dev_malloc(&g->ppr_cnt, g->ppr_cap * 4) != hipSuccess) {
             g->ppr_vtx = g->ppr_cnt = nullptr; g->ppr_cap = 0;
             return BINGO_E_OOM;
         }
