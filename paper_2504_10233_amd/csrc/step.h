@@ -385,11 +385,20 @@ __device__ __forceinline__ HotLine load_hot(const uint32_t* __restrict__ hdr, ui
     return HotLine{h4[0], h4[1], h4[2], h4[3]};
 }
 
+// The alias entry that word a of the stream names (MODE 2), loaded beside the header.
+template <int MODE>
+__device__ __forceinline__ uint4 load_alias(bool want, uint32_t u, uint32_t a, GroupRule rule) {
+    uint4 e = make_uint4(0u, 0u, 0u, 0u);
+    if constexpr (MODE == 2)
+        if (want) e = rule.alias[(size_t)u * ALIAS_ENTRIES + (a >> 27)];
+    return e;
+}
+
 // Group choice from the words of the step's stream behind the termination word:
-// MODE 0 and 1: x = a << 32 | b; MODE 2: slot from a, x = b << 32 | c.
+// MODE 0 and 1: x = a << 32 | b; MODE 2: slot from a with its entry e, x = b << 32 | c.
 template <int MODE>
 __device__ __forceinline__ LeanPick lean_pick(const uint32_t* __restrict__ hdr, uint32_t u, const HotLine& q,
-                                              uint32_t a, uint32_t b, uint32_t c, GroupRule rule) {
+                                              uint32_t a, uint32_t b, uint32_t c, const uint4& e, GroupRule rule) {
     LeanPick p;
     p.kind = LK_DONE;
     p.v = STOP_VERTEX;
@@ -411,9 +420,7 @@ __device__ __forceinline__ LeanPick lean_pick(const uint32_t* __restrict__ hdr, 
     if constexpr (MODE == 0) {
         rank = lean_rank(h, sl, W - 1 - r, hi, onem, raw);
     } else if constexpr (MODE == 2) {
-        const uint32_t j = a >> 27;
-        const uint4 e = rule.alias[(size_t)u * ALIAS_ENTRIES + j];
-        const uint32_t k = r < (((uint64_t)e.y << 32) | e.x) ? j : e.z;
+        const uint32_t k = r < (((uint64_t)e.y << 32) | e.x) ? a >> 27 : e.z;
         rank = k > hi ? 32u : hi - k;  // above hi: only on an inconsistent structure
         raw = 0;
         if (rank < HOT_RANKS) {
@@ -541,6 +548,7 @@ __device__ __forceinline__ uint32_t lane_advance(const uint32_t* __restrict__ hd
         philox_uniform((uint32_t)id, (uint32_t)(id >> 32), s, blk0 + blk, seed, w0, w1, w2, w3);
         ls.blk = blk + 1;
     }
+    const uint4 al = load_alias<MODE>(begin && !(TERM && w0 < thr), u, TERM ? w1 : w0, rule);
     uint32_t skip = act ? 0u : 4u;  // words of the block that are no attempts
     uint32_t lcnt = 0, linfo = 0;
     bool odd = false;
@@ -550,8 +558,8 @@ __device__ __forceinline__ uint32_t lane_advance(const uint32_t* __restrict__ hd
             ended = true;
             skip = 4;
         } else {
-            const LeanPick p = TERM ? lean_pick<MODE>(hdr, u, q, w1, w2, w3, rule)
-                                    : lean_pick<MODE>(hdr, u, q, w0, w1, w2, rule);
+            const LeanPick p = TERM ? lean_pick<MODE>(hdr, u, q, w1, w2, w3, al, rule)
+                                    : lean_pick<MODE>(hdr, u, q, w0, w1, w2, al, rule);
             if (p.kind == LK_DENSE) {
                 ls.adj = p.adj; ls.d = p.d; ls.sel = p.sel; ls.pending = true;
                 if (WAVE && p.d >= wave_deg) {
@@ -569,11 +577,17 @@ __device__ __forceinline__ uint32_t lane_advance(const uint32_t* __restrict__ hd
             }
         }
     }
+    if (HEAD > 3 && begin && ((ls.pending && !serve) || lcnt)) {
+        // the first block is used up: the member's words come from the next one
+        philox_uniform((uint32_t)id, (uint32_t)(id >> 32), s, blk0 + ls.blk, seed, w0, w1, w2, w3);
+        ++ls.blk;
+        skip = 0;
+    }
     if (ls.pending && act && !serve) {
         v = lane_attempts<SPEC>(pool, ls, w0, w1, w2, w3, skip);
-        if (TERM && v == PENDING) {
-            // a walk with a termination word has one word left in block 0 for its first attempt; a
-            // second block here spares every other step an iteration of its own
+        if (HEAD == 3 && v == PENDING) {
+            // block 0 has one word left for the first attempt; a second block here spares every other step an
+            // iteration of its own
             philox_uniform((uint32_t)id, (uint32_t)(id >> 32), s, blk0 + ls.blk, seed, w0, w1, w2, w3);
             ++ls.blk;
             v = lane_attempts<SPEC>(pool, ls, w0, w1, w2, w3, 0u);
@@ -585,9 +599,9 @@ __device__ __forceinline__ uint32_t lane_advance(const uint32_t* __restrict__ hd
     }
     if (lcnt) {
         // the list position's word follows the group draw
-        const uint32_t w = HEAD == 2 ? w2 : w3;
+        const uint32_t w = HEAD == 2 ? w2 : HEAD == 3 ? w3 : w0;
         uint32_t i;
-        if (HEAD > 3 || lean_reject(w, lcnt, i)) {
+        if (lean_reject(w, lcnt, i)) {
             odd = true;
         } else {
             const uint32_t e = pool[(uint64_t)linfo * LIST_UNIT_WORDS + i];
@@ -643,13 +657,14 @@ __device__ __forceinline__ uint32_t coop_step(const uint32_t* __restrict__ hdr, 
 #pragma unroll
         for (int i = 0; i < IPL; ++i) inf[i] = G <= 32 || sub < 32 ? I[sub * IPL + i] : 0u;
     }
+    const uint4 al = load_alias<MODE>(act, u, cw.z[TERM], rule);
     mid();
     LeanPick p;
     p.kind = LK_DONE;
     p.v = STOP_VERTEX;
     if (act)
-        p = TERM ? lean_pick<MODE>(hdr, u, q, cw.z[1], cw.z[2], cw.z[3], rule)
-                 : lean_pick<MODE>(hdr, u, q, cw.z[0], cw.z[1], cw.z[2], rule);
+        p = TERM ? lean_pick<MODE>(hdr, u, q, cw.z[1], cw.z[2], cw.z[3], al, rule)
+                 : lean_pick<MODE>(hdr, u, q, cw.z[0], cw.z[1], cw.z[2], al, rule);
     // the list position's word, the list's offset
     uint32_t li = 0, info = 0;
     bool list = act && p.kind == LK_LIST;
