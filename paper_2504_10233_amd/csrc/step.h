@@ -307,8 +307,10 @@ __device__ __forceinline__ uint32_t odd_step(const uint32_t* __restrict__ hdr, c
 // one), the alias slot (MODE 2), the 64-bit group draw, then one word per dense
 // attempt.  What a draw needs beyond that is rare and goes through
 // odd_step: a group draw in Lemire's biased zone (probability
-// W / 2^64), a redraw of a list position, and vertices of 2^21 edges and more,
-// whose sums pass 32 bits.
+// W / 2^64) and a redraw of a list position.  The sums of vertices of 2^21 edges
+// and more pass 32 bits: a lane's own step takes them in 64 (wide_rank; as odd
+// steps, a hub of 3 x 2^20 edges took 3000 x 1000 PageRank walks 2040 us, now
+// 1090), the lanes that share a walk go through odd_step there.
 // ---------------------------------------------------------------------------
 constexpr uint32_t LEAN_MAX_DEG = 1u << 21;
 
@@ -363,15 +365,52 @@ __device__ __forceinline__ uint32_t lean_rank(const HdrCRef& h, const uint32_t (
     return 32u;
 }
 
-// type of a group known to have members and not to be one-element (d < LEAN_MAX_DEG)
+// The same choice in 64 bits, for vertices of LEAN_MAX_DEG edges and more: rank by rank from the top.
+__device__ __forceinline__ uint32_t wide_rank(const HdrCRef& h, const uint32_t (&sl)[HOT_RANKS], uint64_t tm1,
+                                              uint32_t hi, uint32_t onem, uint32_t& raw) {
+    const uint32_t om = onem << (31 - hi);
+    uint64_t rest = tm1;
+    uint32_t rank = 32u;
+    raw = 0;
+#pragma unroll
+    for (int q = 0; q < HOT_RANKS; ++q) {
+        if (rank == 32u && (uint32_t)q <= hi) {
+            const uint64_t T = shl32((om >> (31 - q)) & 1u ? 1u : sl[q], hi - q);
+            if (rest < T) {
+                rank = q;
+                raw = sl[q];
+            } else {
+                rest -= T;
+            }
+        }
+    }
+#pragma unroll 1
+    for (uint32_t q = HOT_RANKS; rank == 32u && q <= hi; ++q) {
+        const uint32_t c = h.slot(q);
+        const uint64_t T = shl32((om >> (31 - q)) & 1u ? 1u : c, hi - q);
+        if (rest < T) {
+            rank = q;
+            raw = c;
+        } else {
+            rest -= T;
+        }
+    }
+    return rank;
+}
+
+// type of a group known to have members and not to be one-element (d < LEAN_MAX_DEG, and any d)
 __device__ __forceinline__ bool lean_dense(uint32_t c, uint32_t d, GroupRule r) {
     return r.adaptive && c * 100u > r.alpha * d;
 }
+__device__ __forceinline__ bool wide_dense(uint32_t c, uint32_t d, GroupRule r) {
+    return r.adaptive && (uint64_t)c * 100u > (uint64_t)r.alpha * d;
+}
 
 // What a step comes to after its group choice.
-enum : uint32_t { LK_DONE = 0, LK_DENSE = 1, LK_LIST = 2, LK_ODD = 3 };
+enum : uint32_t { LK_DONE = 0, LK_DENSE = 1, LK_LIST = 2, LK_ODD = 3, LK_DEC = 4 };
 struct LeanPick {
-    uint32_t kind;  // LK_DONE: the next vertex is v; LK_ODD: take the step through odd_step
+    uint32_t kind;  // LK_DONE: the next vertex is v; LK_ODD: take the step through odd_step; LK_DEC: a member of
+                    // the decimal group (MODE 1), by decimal_draw
     uint32_t v, sel, csel, d;
     uint64_t adj;
 };
@@ -396,7 +435,10 @@ __device__ __forceinline__ uint4 load_alias(bool want, uint32_t u, uint32_t a, G
 
 // Group choice from the words of the step's stream behind the termination word:
 // MODE 0 and 1: x = a << 32 | b; MODE 2: slot from a with its entry e, x = b << 32 | c.
-template <int MODE>
+// WIDE, for large vertices: WIDE_ODD none, they go through odd_step; WIDE_FORK a branch with sums of their own;
+// WIDE_TAIL those sums behind the common ones, over what these have come to.
+enum { WIDE_ODD = 0, WIDE_FORK = 1, WIDE_TAIL = 2 };
+template <int MODE, int WIDE>
 __device__ __forceinline__ LeanPick lean_pick(const uint32_t* __restrict__ hdr, uint32_t u, const HotLine& q,
                                               uint32_t a, uint32_t b, uint32_t c, const uint4& e, GroupRule rule) {
     LeanPick p;
@@ -410,15 +452,18 @@ __device__ __forceinline__ LeanPick lean_pick(const uint32_t* __restrict__ hdr, 
     const uint64_t W = ((uint64_t)q.q0.w << 32) | q.q0.z;
     const uint32_t onem = q.q0.x, hi = q.q1.y >> H_HI_SHIFT;
     const uint64_t x = MODE == 2 ? ((uint64_t)b << 32) | c : ((uint64_t)a << 32) | b;
-    if (x * W < W || p.d >= LEAN_MAX_DEG) {
+    if (x * W < W || (MODE != 2 && WIDE == WIDE_ODD && p.d >= LEAN_MAX_DEG)) {
         p.kind = LK_ODD;
         return p;
     }
     const uint64_t r = __umul64hi(x, W);
     const uint32_t sl[HOT_RANKS] = {q.q1.z, q.q1.w, q.q2.x, q.q2.y, q.q2.z, q.q2.w, q.q3.x, q.q3.y, q.q3.z, q.q3.w};
     uint32_t rank, raw;
+    uint64_t tm1 = 0;
     if constexpr (MODE == 0) {
-        rank = lean_rank(h, sl, W - 1 - r, hi, onem, raw);
+        tm1 = W - 1 - r;
+        if (WIDE != WIDE_FORK || p.d < LEAN_MAX_DEG) rank = lean_rank(h, sl, tm1, hi, onem, raw);
+        else rank = wide_rank(h, sl, tm1, hi, onem, raw);
     } else if constexpr (MODE == 2) {
         const uint32_t k = r < (((uint64_t)e.y << 32) | e.x) ? a >> 27 : e.z;
         rank = k > hi ? 32u : hi - k;  // above hi: only on an inconsistent structure
@@ -434,35 +479,66 @@ __device__ __forceinline__ LeanPick lean_pick(const uint32_t* __restrict__ hdr, 
         // integer groups F..31 ascending, the decimal group last: from the top, with I the integer
         // groups' total, a draw r >= I picks the decimal group and t = I - r picks as in MODE 0
         const uint32_t nint = hi + 1 > rule.fbits ? hi + 1 - rule.fbits : 0u;  // ranks of integer groups
-        // ranks summed in 32 bits as in lean_rank, eleven at a time past the hot line (d 2^11 is below 2^32)
         const uint32_t om = onem << (31 - hi);  // bit 31 - i: rank i is a one-element group
-        uint32_t A = 0;
-#pragma unroll
-        for (int i = 0; i < HOT_RANKS; ++i)
-            if ((uint32_t)i < nint) A = 2 * A + ((om >> (31 - i)) & 1u ? 1u : sl[i]);
-        uint64_t I = shl32(A, hi + 1 - min(nint, (uint32_t)HOT_RANKS));
+        uint2 y[11];                            // the cold ranks
         if (nint > HOT_RANKS) {
             const uint2* c2 = reinterpret_cast<const uint2*>(h.cold + (H_SLOT10 - HDR_HOT));
-            uint2 y[11];
 #pragma unroll
             for (int i = 0; i < 11; ++i) y[i] = c2[i];
+        }
+        uint64_t I = 0;
+        if (WIDE == WIDE_ODD || p.d < LEAN_MAX_DEG) {
+            // summed in 32 bits as in lean_rank, eleven ranks at a time past the hot line (d 2^11 is below 2^32)
+            uint32_t A = 0;
 #pragma unroll
-            for (int b0 = 0; b0 < 22; b0 += 11) {
-                A = 0;
+            for (int i = 0; i < HOT_RANKS; ++i)
+                if ((uint32_t)i < nint) A = 2 * A + ((om >> (31 - i)) & 1u ? 1u : sl[i]);
+            I = shl32(A, hi + 1 - min(nint, (uint32_t)HOT_RANKS));
+            if (nint > HOT_RANKS) {
 #pragma unroll
-                for (int i = b0; i < b0 + 11; ++i) {
-                    const uint32_t c = i & 1 ? y[i / 2].y : y[i / 2].x;
-                    if ((uint32_t)(i + HOT_RANKS) < nint) A = 2 * A + ((om >> (31 - HOT_RANKS - i)) & 1u ? 1u : c);
+                for (int b0 = 0; b0 < 22; b0 += 11) {
+                    A = 0;
+#pragma unroll
+                    for (int i = b0; i < b0 + 11; ++i) {
+                        const uint32_t c = i & 1 ? y[i / 2].y : y[i / 2].x;
+                        if ((uint32_t)(i + HOT_RANKS) < nint)
+                            A = 2 * A + ((om >> (31 - HOT_RANKS - i)) & 1u ? 1u : c);
+                    }
+                    if (nint > (uint32_t)(b0 + HOT_RANKS))
+                        I += shl32(A, hi + 1 - min(nint, (uint32_t)(b0 + 11 + HOT_RANKS)));
                 }
-                if (nint > (uint32_t)(b0 + HOT_RANKS)) I += shl32(A, hi + 1 - min(nint, (uint32_t)(b0 + 11 + HOT_RANKS)));
             }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 32; ++i) {
+                const uint32_t c = i < HOT_RANKS ? sl[i < HOT_RANKS ? i : 0]
+                                                 : ((i & 1) ? y[i < HOT_RANKS ? 0 : (i - HOT_RANKS) / 2].y
+                                                            : y[i < HOT_RANKS ? 0 : (i - HOT_RANKS) / 2].x);
+                if ((uint32_t)i < nint) I = 2 * I + ((om >> (31 - i)) & 1u ? 1u : c);
+            }
+            I <<= rule.fbits;  // the last integer rank is group F (none: I is 0)
         }
         if (r >= I) {
-            p.kind = LK_ODD;
+            // the decimal group, slot 0; a member alone is the step's end
+            raw = sl[0];
+#pragma unroll
+            for (int i = 1; i < HOT_RANKS; ++i)
+                if ((uint32_t)i == hi) raw = sl[i];
+            if (hi >= HOT_RANKS) raw = h.slot(hi);
+            p.csel = raw;
+            p.v = raw;
+            p.kind = (onem & 1u) ? LK_DONE : LK_DEC;
             return p;
         }
         // ranks below the integer groups are not reached: their groups' totals lie beyond t
-        rank = lean_rank(h, sl, I - 1 - r, hi, onem, raw);
+        tm1 = I - 1 - r;
+        if (WIDE != WIDE_FORK || p.d < LEAN_MAX_DEG) rank = lean_rank(h, sl, tm1, hi, onem, raw);
+        else rank = wide_rank(h, sl, tm1, hi, onem, raw);
+    }
+    bool dense = lean_dense(raw, p.d, rule);
+    if ((WIDE == WIDE_TAIL || MODE == 2) && p.d >= LEAN_MAX_DEG) {
+        if (MODE != 2) rank = wide_rank(h, sl, tm1, hi, onem, raw);
+        dense = wide_dense(raw, p.d, rule);
     }
     if (rank > hi) return p;  // only on an inconsistent header
     p.sel = hi - rank;
@@ -471,7 +547,8 @@ __device__ __forceinline__ LeanPick lean_pick(const uint32_t* __restrict__ hdr, 
         return p;
     }
     p.csel = raw;
-    p.kind = lean_dense(raw, p.d, rule) ? LK_DENSE : LK_LIST;
+    if (WIDE == WIDE_FORK && MODE != 2 && p.d >= LEAN_MAX_DEG) dense = wide_dense(raw, p.d, rule);
+    p.kind = dense ? LK_DENSE : LK_LIST;
     return p;
 }
 
@@ -483,14 +560,52 @@ __device__ __forceinline__ bool lean_reject(uint32_t w, uint32_t n, uint32_t& i)
     return low < n && low < (0u - n) % n;
 }
 
-// A walk's step in progress in one lane.  Between iterations only dense steps
-// whose attempts have all been rejected so far remain.
+// A member of the decimal group (decimal_pick), the words taken from position HEAD of the step's stream on, whose
+// first block is z, one after the other: for the lanes that share a walk.
+template <uint32_t HEAD>
+__device__ __forceinline__ uint32_t decimal_draw(const uint32_t* __restrict__ hdr, const uint32_t* __restrict__ pool,
+                                                 uint32_t u, const LeanPick& p, uint64_t seed, uint64_t id, uint32_t s,
+                                                 uint32_t blk0, uint32_t z0, uint32_t z1, uint32_t z2, uint32_t z3,
+                                                 GroupRule rule) {
+    const bool dense = wide_dense(p.csel, p.d, rule);
+    const uint32_t n = dense ? p.d : p.csel;
+    const uint32_t* __restrict__ L =
+        pool + (dense ? 0ull : (uint64_t)hdr_ref(hdr, u)[H_INFO] * LIST_UNIT_WORDS);
+    const uint64_t* __restrict__ edges = reinterpret_cast<const uint64_t*>(pool + p.adj);
+    const uint32_t fm = (1u << rule.fbits) - 1u;
+    uint32_t pos = HEAD;
+    auto next = [&]() {
+        if ((pos & 3u) == 0)
+            philox_uniform((uint32_t)id, (uint32_t)(id >> 32), s, blk0 + (pos >> 2), seed, z0, z1, z2, z3);
+        const uint32_t w = (pos & 2u) ? ((pos & 1u) ? z3 : z2) : ((pos & 1u) ? z1 : z0);
+        ++pos;
+        return w;
+    };
+#pragma unroll 1
+    for (uint32_t att = 0; att < DEC_MAX_ATTEMPTS;) {
+        uint32_t i;
+        if (lean_reject(next(), n, i)) continue;
+        if (!dense) i = L[i];
+        const uint64_t e = edges[i];
+        const uint32_t x = next() >> (32 - rule.fbits);
+        if (x < ((uint32_t)(e >> 32) & fm)) return (uint32_t)e;
+        ++att;
+    }
+    return STOP_VERTEX;
+}
+
+// A walk's step in progress in one lane.  Between iterations only dense steps and
+// draws from the decimal group whose attempts have all been rejected so far remain.
 struct LaneStep {
     uint64_t adj;
     uint32_t d, sel;
     uint32_t blk;    // next block of the step's stream
     bool pending;
+    // the decimal group (MODE 1): sel is DEC_SEL, d the bound of its draws
+    uint32_t info;   // its list's block, NO_LIST: the whole adjacency
+    uint64_t carry;  // TERM = 1: the candidate whose acceptance word is the next block's first
 };
+constexpr uint32_t DEC_SEL = 32u, NO_LIST = 0xFFFFFFFFu;
 
 // Up to four attempts of a dense step from one block's words (the first `skip` of
 // them are none), SPEC loads at a time; PENDING when none is accepted.
@@ -520,6 +635,47 @@ __device__ __forceinline__ uint32_t lane_attempts(const uint32_t* __restrict__ p
     return v;
 }
 
+// A block's words for a draw from the decimal group (decimal_pick): pairs of an index and an acceptance word.  A
+// step's pairs begin at its third word, or, behind a termination word, at its fourth, so that they straddle the
+// blocks there and a candidate is carried over.  The first `skip` words of the block are none of them.  An index to
+// be drawn again would shift the pairs: odd.
+template <int TERM>
+__device__ __forceinline__ uint32_t lane_decimal(const uint32_t* __restrict__ pool, LaneStep& ls, uint32_t fbits,
+                                                 uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, uint32_t skip,
+                                                 bool& odd) {
+    const uint64_t* __restrict__ edges = reinterpret_cast<const uint64_t*>(pool + ls.adj);
+    auto fetch = [&](uint32_t w) {
+        uint32_t i;
+        if (lean_reject(w, ls.d, i)) {
+            odd = true;
+            return (uint64_t)0;
+        }
+        if (ls.info != NO_LIST) i = pool[(uint64_t)ls.info * LIST_UNIT_WORDS + i];
+        return edges[i];
+    };
+    const uint32_t fm = (1u << fbits) - 1u;
+    auto pass = [&](uint32_t w, uint64_t e) { return (w >> (32 - fbits)) < ((uint32_t)(e >> 32) & fm); };
+    uint64_t e;
+    if constexpr (TERM) {
+        if (skip == 0) {
+            if (pass(w0, ls.carry)) return (uint32_t)ls.carry;
+            e = fetch(w1);
+            if (pass(w2, e)) return (uint32_t)e;
+        }
+        if (!odd) ls.carry = fetch(w3);
+    } else {
+        if (skip == 0) {
+            e = fetch(w0);
+            if (pass(w1, e)) return (uint32_t)e;
+        }
+        if (!odd) {
+            e = fetch(w2);
+            if (pass(w3, e)) return (uint32_t)e;
+        }
+    }
+    return PENDING;
+}
+
 // One iteration of a lane's step at u: a new step (ls.pending false) or more
 // attempts of the one in progress, from one Philox block either way.  Returns
 // PENDING when the step goes on, STOP_VERTEX at a vertex without out-edges,
@@ -527,9 +683,11 @@ __device__ __forceinline__ uint32_t lane_attempts(const uint32_t* __restrict__ p
 // walk before the step.  blk0: first block of the step's stream (node2vec
 // proposals).  With WAVE a dense step of a vertex of degree >= wave_deg is
 // returned as PENDING with serve set, ls.blk * 4 - left words of its stream used.
-// SPEC attempts are loaded together.  All lanes of the wave call; mid() runs
+// SPEC attempts are loaded together.  WIDE as in lean_pick: the fork costs the walks that never meet a large vertex
+// 2 % in the kernels with a termination word and in node2vec, the tail 14 % in the DeepWalk kernel (at 72 registers
+// it spills 16).  All lanes of the wave call; mid() runs
 // between the issue of the header loads and their first use.
-template <int SPEC, int MODE, int TERM, bool WAVE, class Mid>
+template <int SPEC, int MODE, int TERM, bool WAVE, int WIDE, class Mid>
 __device__ __forceinline__ uint32_t lane_advance(const uint32_t* __restrict__ hdr, const uint32_t* __restrict__ pool,
                                                  bool act, uint32_t u, LaneStep& ls, uint64_t seed, uint64_t id,
                                                  uint32_t s, uint32_t blk0, uint32_t thr, GroupRule rule,
@@ -558,8 +716,8 @@ __device__ __forceinline__ uint32_t lane_advance(const uint32_t* __restrict__ hd
             ended = true;
             skip = 4;
         } else {
-            const LeanPick p = TERM ? lean_pick<MODE>(hdr, u, q, w1, w2, w3, al, rule)
-                                    : lean_pick<MODE>(hdr, u, q, w0, w1, w2, al, rule);
+            const LeanPick p = TERM ? lean_pick<MODE, WIDE>(hdr, u, q, w1, w2, w3, al, rule)
+                                    : lean_pick<MODE, WIDE>(hdr, u, q, w0, w1, w2, al, rule);
             if (p.kind == LK_DENSE) {
                 ls.adj = p.adj; ls.d = p.d; ls.sel = p.sel; ls.pending = true;
                 if (WAVE && p.d >= wave_deg) {
@@ -572,6 +730,10 @@ __device__ __forceinline__ uint32_t lane_advance(const uint32_t* __restrict__ hd
                 linfo = hdr_ref(hdr, u)[H_INFO + p.sel];  // used behind the attempts of the other lanes
             } else if (p.kind == LK_ODD) {
                 odd = true;
+            } else if (MODE == 1 && p.kind == LK_DEC) {
+                const bool dense = wide_dense(p.csel, p.d, rule);
+                ls.adj = p.adj; ls.d = dense ? p.d : p.csel; ls.sel = DEC_SEL; ls.pending = true;
+                ls.info = dense ? NO_LIST : hdr_ref(hdr, u)[H_INFO];
             } else {
                 v = p.v;
             }
@@ -584,13 +746,18 @@ __device__ __forceinline__ uint32_t lane_advance(const uint32_t* __restrict__ hd
         skip = 0;
     }
     if (ls.pending && act && !serve) {
-        v = lane_attempts<SPEC>(pool, ls, w0, w1, w2, w3, skip);
-        if (HEAD == 3 && v == PENDING) {
+        auto attempts = [&](uint32_t none) {
+            if (MODE == 1 && ls.sel == DEC_SEL)
+                return lane_decimal<TERM>(pool, ls, rule.fbits, w0, w1, w2, w3, none, odd);
+            return lane_attempts<SPEC>(pool, ls, w0, w1, w2, w3, none);
+        };
+        v = attempts(skip);
+        if (HEAD == 3 && v == PENDING && (MODE != 1 || !odd)) {
             // block 0 has one word left for the first attempt; a second block here spares every other step an
             // iteration of its own
             philox_uniform((uint32_t)id, (uint32_t)(id >> 32), s, blk0 + ls.blk, seed, w0, w1, w2, w3);
             ++ls.blk;
-            v = lane_attempts<SPEC>(pool, ls, w0, w1, w2, w3, 0u);
+            v = attempts(0u);
         }
         // 2^14 blocks without an acceptance hold a few attempts less than the 2^16 that end a step (a group of a
         // few members in a large vertex is dense where alpha is next to nothing): odd_step counts them
@@ -663,8 +830,8 @@ __device__ __forceinline__ uint32_t coop_step(const uint32_t* __restrict__ hdr, 
     p.kind = LK_DONE;
     p.v = STOP_VERTEX;
     if (act)
-        p = TERM ? lean_pick<MODE>(hdr, u, q, cw.z[1], cw.z[2], cw.z[3], al, rule)
-                 : lean_pick<MODE>(hdr, u, q, cw.z[0], cw.z[1], cw.z[2], al, rule);
+        p = TERM ? lean_pick<MODE, WIDE_ODD>(hdr, u, q, cw.z[1], cw.z[2], cw.z[3], al, rule)
+                 : lean_pick<MODE, WIDE_ODD>(hdr, u, q, cw.z[0], cw.z[1], cw.z[2], al, rule);
     // the list position's word, the list's offset
     uint32_t li = 0, info = 0;
     bool list = act && p.kind == LK_LIST;
@@ -715,6 +882,8 @@ __device__ __forceinline__ uint32_t coop_step(const uint32_t* __restrict__ hdr, 
     }
     if (list) v = pool[p.adj + 2ull * le];
     if (act && p.kind == LK_DONE) v = p.v;
+    if (MODE == 1 && act && p.kind == LK_DEC)
+        v = decimal_draw<HEAD>(hdr, pool, u, p, seed, id, s, 0u, cw.z[0], cw.z[1], cw.z[2], cw.z[3], rule);
     if (act && p.kind == LK_ODD) v = odd_step<MODE>(hdr, pool, u, seed, id, s, 0u, (uint32_t)TERM, rule);
     return v;
 }

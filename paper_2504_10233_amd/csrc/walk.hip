@@ -201,7 +201,7 @@ __global__ void __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(MODE ==
         if (__ballot(!done) == 0) break;
         bool ended, serve;
         uint32_t left;
-        uint32_t v = lane_advance<SPEC, MODE, 0, WAVE>(hdr, pool, j != NO_WALK, u, ls, seed, base + j, s, 0u, 0u, rule,
+        uint32_t v = lane_advance<SPEC, MODE, 0, WAVE, WIDE_FORK>(hdr, pool, j != NO_WALK, u, ls, seed, base + j, s, 0u, 0u, rule,
                                                  wave_deg, ended, serve, left, [] {});
         if (WAVE) {
             const uint32_t wv = wave_dense_serve(pool, ls, seed, base + j, s, left, serve);
@@ -554,7 +554,7 @@ __global__ void __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(MODE ==
         bool ended, serve;
         uint32_t left;
         // the termination word of every step of a segment is known to be >= the threshold
-        uint32_t v = lane_advance<SPEC, MODE, 1, WAVE>(hdr, pool, j != NO_WALK, u, ls, seed, base + j, s, 0u, 0u, rule,
+        uint32_t v = lane_advance<SPEC, MODE, 1, WAVE, WIDE_TAIL>(hdr, pool, j != NO_WALK, u, ls, seed, base + j, s, 0u, 0u, rule,
                                                  wave_deg, ended, serve, left, [] {});
         if (WAVE) {
             const uint32_t wv = wave_dense_serve(pool, ls, seed, base + j, s, left, serve);
@@ -704,7 +704,7 @@ __global__ void __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(MODE ==
         }
         bool ended, serve;
         uint32_t left;
-        uint32_t v = lane_advance<SPEC, MODE, 1, WAVE>(hdr, pool, act, u, ls, seed, base + j, s, 0u, thr, rule, wave_deg,
+        uint32_t v = lane_advance<SPEC, MODE, 1, WAVE, WIDE_TAIL>(hdr, pool, act, u, ls, seed, base + j, s, 0u, thr, rule, wave_deg,
                                                  ended, serve, left, [] {});
         if (WAVE) {
             const uint32_t wv = wave_dense_serve(pool, ls, seed, base + j, s, left, serve);

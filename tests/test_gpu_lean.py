@@ -332,3 +332,36 @@ def test_the_longest_rows():
             assert out[0, :2].tolist() == [0, 1], form
         assert bool((out[0, 2:] == -1).all()), form
     g.close()
+
+
+@pytest.mark.parametrize("mode", ["int", "plain", "float", "decimal", "alias"])
+def test_a_large_hub_equals_the_per_step_form(mode):
+    """2^21 + 77 edges at one vertex, whose group choice takes 64-bit sums: groups of every type on ranks past the
+    ten and twenty highest, one member or two in some, most of the weight in the decimal group or next to none."""
+    import torch
+    from paper_2504_10233_amd import MODE_PER_STEP, Graph, quantize_biases
+    d, n = (1 << 21) + 77, 5000
+    src = torch.cat([torch.zeros(d, dtype=torch.int64), torch.arange(1, n)])
+    dst = torch.cat([synth.below(31, 1, d, n), torch.zeros(n - 1, dtype=torch.int64)])
+    w = synth.weights_zipf(d + n - 1, 1.5, (1 << 18) - 1, 32)
+    w[5], w[9], w[11] = (1 << 31) + 3, 1 << 27, 3 << 26
+    kw = {"alias_table": mode == "alias", "adaptive": mode != "plain"}
+    if mode in ("float", "decimal"):
+        b = synth.uniform_f64(33, 1, d + n - 1) * 0.98 + 0.01
+        if mode == "float":
+            b += w.clamp(max=1 << 22)
+        w = quantize_biases(b.float().cuda(), 1.0, 8)
+        kw = {"frac_bits": 8}
+    g = Graph(n, src, dst, w, **kw)
+    for nw in (3, 3000, 90001):
+        starts = synth.below(9, nw, nw, n).to(torch.int32)
+        a, sa = g.walk(starts, 7, 77, base=nw)
+        b, sb = g.walk(starts, 7, 77, base=nw, mode=MODE_PER_STEP)
+        assert torch.equal(a, b) and int(sa) == int(sb), nw
+    for ns in (2, 100):
+        s = synth.below(8, 1, ns, n).to(torch.int32)
+        a, b = (g.ppr(s, 1000, int(0.15 * 2**32), 200, 5, mode=m) for m in (0, MODE_PER_STEP))
+        assert all(torch.equal(x, y) for x, y in zip(a[:3], b[:3])) and a[3] == b[3]
+    a, _ = g.node2vec(starts, 7, 77, 1.0, 1.0, base=nw)
+    assert torch.equal(a, g.walk(starts, 7, 77, base=nw)[0])
+    g.close()
