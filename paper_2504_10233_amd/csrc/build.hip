@@ -595,7 +595,11 @@ constexpr uint32_t SR_LIST0 = 64;
 // chunk, chunks) after them; then the chunk owners and counts.
 // 10^4 records on planted hubs of up to 3 x 10^5 edges, the block, index and write kernels (us), lines at
 // 2^15 and 2^14: 127 + 103 + 30 (the largest vertices of one block set the first); 2^13 both: 59 + 96 + 22;
-// 2^12 both: 43 + 152 + 22 (each chunk stages its vertex's samples of S(u)).
+// 2^12 both: 43 + 152 + 22 (each chunk stages its vertex's samples of S(u)).  A small stream that touches one or two
+// such vertices waits for the block and the index kernel one after the other, and each took its groups one after the
+// other, with a round of dependent loads per group: 47 + 52 us where the line at 2^15 had 61 + 4.  The waves of a
+// block take a group each now: 20 + 21 us; 100 streamed records on R-MAT 18 320 -> 252 us (249 before the line
+// moved), the batch on hubs 1131 -> 1076 us.
 constexpr uint32_t SR_BIG = 1u << 13;
 constexpr uint32_t SR_CHUNK = 1u << 13;
 constexpr uint32_t SR_NO_OWNER = 0xFFFFFFFFu;
@@ -801,18 +805,20 @@ __global__ void __launch_bounds__(SRC_TB) k_sr_index(const uint32_t* __restrict_
         const uint32_t nl = (sfill + (1u << sh) - 1) >> sh;
         for (uint32_t q = tid; q < nl; q += SRC_TB) smp[q] = S[(uint64_t)q << sh];
         __syncthreads();
+        uint32_t turn = 0;  // the groups go to the waves in turn
         for (uint32_t mm = s_smask; mm; mm &= mm - 1) {
             const int k = __ffs(mm) - 1;
+            if ((turn++ & (SRC_TB / 64 - 1)) != (tid >> 6)) continue;
             const uint32_t ck = g_c[k];
             uint32_t* L = pool + (uint64_t)g_info[k] * LIST_UNIT_WORDS;
             uint32_t* I = L + g_lcap[k];
             const uint32_t p0 = (uint32_t)((uint64_t)ck * j / nch), p1 = (uint32_t)((uint64_t)ck * (j + 1) / nch);
-            // SR_ILV members per thread at a time, their global search steps interleaved
-            for (uint32_t pb = p0 + tid; pb < p1; pb += SRC_TB * SR_ILV) {
+            // SR_ILV members per lane at a time, their global search steps interleaved
+            for (uint32_t pb = p0 + (tid & 63u); pb < p1; pb += 64 * SR_ILV) {
                 uint32_t v[SR_ILV], a[SR_ILV], bb[SR_ILV];
 #pragma unroll
                 for (uint32_t x = 0; x < SR_ILV; ++x) {
-                    const uint32_t p = pb + x * SRC_TB;
+                    const uint32_t p = pb + x * 64;
                     v[x] = p < p1 ? L[p] : 0u;
                 }
 #pragma unroll
@@ -836,7 +842,7 @@ __global__ void __launch_bounds__(SRC_TB) k_sr_index(const uint32_t* __restrict_
                 }
 #pragma unroll
                 for (uint32_t x = 0; x < SR_ILV; ++x) {
-                    const uint32_t p = pb + x * SRC_TB;
+                    const uint32_t p = pb + x * 64;
                     if (p < p1) I[a[x]] = p;
                 }
             }
@@ -914,17 +920,19 @@ __global__ void __launch_bounds__(SR_TB) k_srebuild(uint32_t* __restrict__ hdr, 
         const uint32_t nl = (sfill + (1u << sh) - 1) >> sh;
         for (uint32_t j = tid; j < nl; j += SR_TB) smp[j] = S[(uint64_t)j << sh];
         __syncthreads();
+        uint32_t turn = 0;  // the groups go to the waves in turn
         for (uint32_t mm = smask; mm; mm &= mm - 1) {
             const int k = __ffs(mm) - 1;
+            if ((turn++ & (SR_TB / 64 - 1)) != wave) continue;
             const uint32_t c = g_c[k];
             uint32_t* L = pool + (uint64_t)g_info[k] * LIST_UNIT_WORDS;
             uint32_t* I = L + g_lcap[k];
-            // SR_ILV members per thread at a time, their global search steps interleaved
-            for (uint32_t p0 = tid; p0 < c; p0 += SR_TB * SR_ILV) {
+            // SR_ILV members per lane at a time, their global search steps interleaved
+            for (uint32_t p0 = lane; p0 < c; p0 += 64 * SR_ILV) {
                 uint32_t v[SR_ILV], a[SR_ILV], b[SR_ILV];
 #pragma unroll
                 for (uint32_t j = 0; j < SR_ILV; ++j) {
-                    const uint32_t p = p0 + j * SR_TB;
+                    const uint32_t p = p0 + j * 64;
                     v[j] = p < c ? L[p] : 0u;
                 }
 #pragma unroll
@@ -948,7 +956,7 @@ __global__ void __launch_bounds__(SR_TB) k_srebuild(uint32_t* __restrict__ hdr, 
                 }
 #pragma unroll
                 for (uint32_t j = 0; j < SR_ILV; ++j) {
-                    const uint32_t p = p0 + j * SR_TB;
+                    const uint32_t p = p0 + j * 64;
                     if (p < c) I[a[j]] = p;
                 }
             }
