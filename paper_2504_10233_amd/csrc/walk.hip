@@ -219,7 +219,7 @@ __global__ void __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(MODE ==
             if (s == L) j = NO_WALK;
         }
     }
-    wave_add_u64(ctl + 1, steps);
+    block_add_u64<TB>(ctl + 1, steps);
 }
 
 // G lanes per walk (coop_step): for queries of fewer walks than the chip holds lanes.  The
@@ -265,7 +265,7 @@ __global__ void __launch_bounds__(TB) k_deepwalk_coop(const uint32_t* __restrict
             }
         }
     }
-    wave_add_u64(ctl + 1, steps);
+    block_add_u64<TB>(ctl + 1, steps);
 }
 
 template <int SPEC, int MODE>
@@ -724,7 +724,7 @@ __global__ void __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(MODE ==
         if (stage.full()) stage.flush(cnt, vis, C, ovf);
     }
     stage.flush(cnt, vis, C, ovf);
-    wave_add_u64(ctl + 1, steps);
+    block_add_u64<TB>(ctl + 1, steps);
     if (__ballot(ovf) && lane == 0) atomicOr(ctl + 2, 1ull);
 }
 
@@ -770,7 +770,7 @@ __global__ void __launch_bounds__(TB) k_ppr_coop(const uint32_t* __restrict__ hd
         if (stage.full()) stage.flush(cnt, vis, C, ovf);
     }
     stage.flush(cnt, vis, C, ovf);
-    wave_add_u64(ctl + 1, steps);
+    block_add_u64<TB>(ctl + 1, steps);
     if (__ballot(ovf) && lane_id() == 0) atomicOr(ctl + 2, 1ull);
 }
 
