@@ -293,3 +293,33 @@ def test_streams_up_to_the_pool_end(spare_kib):
         assert used + 4096 + spare_kib * 1024 >= need
     g.close()
     free.close()
+
+
+@pytest.mark.parametrize("spare_words", [0, 50000, 60000, 131072 - 512, 131072 + 512, 131072 + 20000, 300000])
+def test_streams_around_the_line_of_the_reservations(spare_words):
+    """256 inserts, each moving a block of 96 words to one of 192, in a pool of more than two margins (a margin is 512
+    words for each of the 256 waves: the line lies one below the pool's end).  With less than a margin free the first
+    pass applies nothing and the exact pass finishes; with a little more it applies some.  What fits is applied, and
+    the stream is refused only where the live blocks alone do not fit."""
+    from paper_2504_10233_amd import BingoError, Graph
+    n, d, k = 4096, 32, 256
+    src = torch.arange(n).repeat_interleave(d)
+    dst = (torch.arange(n * d) * 7) % n
+    w = torch.ones(n * d, dtype=torch.int64)  # one dense group: the adjacency is a vertex's only block
+    free = Graph(n, src, dst, w)
+    used = free.memory()["pool_used_bytes"]
+    assert used >= 4 * n * 96 > 4 * 2 * 131072
+    rec = [torch.zeros(k, dtype=torch.int64), torch.arange(k) * 5, torch.arange(k), torch.ones(k, dtype=torch.int64)]
+    g = Graph(n, src, dst, w, pool_bytes=used + 4 * spare_words + 4096)
+    if spare_words < k * 96 - 1024:
+        with pytest.raises(BingoError) as e:
+            g.update_stream(*rec)
+        assert e.value.code == -4
+    else:
+        assert g.update_stream(*rec)["inserted"] == k
+        free.update_stream(*rec)
+        assert np.array_equal(g.export(), free.export())
+        mem = g.memory()
+        assert mem["pool_used_bytes"] <= mem["pool_bytes"] == used + 4 * spare_words + 4096
+    g.close()
+    free.close()
