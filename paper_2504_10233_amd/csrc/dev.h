@@ -268,12 +268,6 @@ __device__ __forceinline__ void rs_init(RandStream& s, uint64_t seed, uint64_t w
     s.step = step; s.blk = 0; s.left = 0;
 }
 
-// The same stream starting at block blk0 (node2vec proposals use disjoint block ranges of a step's stream).
-__device__ __forceinline__ void rs_init_blk(RandStream& s, uint64_t seed, uint64_t walk, uint32_t step, uint32_t blk0) {
-    rs_init(s, seed, walk, step);
-    s.blk = blk0;
-}
-
 __device__ __forceinline__ uint32_t rs_next32(RandStream& s) {
     if (s.left == 0) {
         philox_block(s.w0, s.w1, s.step, s.blk, s.k0, s.k1, s.b0, s.b1, s.b2, s.b3);

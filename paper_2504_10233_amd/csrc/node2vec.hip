@@ -152,7 +152,7 @@ k_node2vec(const uint32_t* __restrict__ hdr, const uint32_t* __restrict__ pool, 
         bool ended, serve;
         uint32_t left;
         const uint32_t x = lane_advance<SPEC, MODE, 0, false, WIDE_TAIL>(hdr, pool, on && !fin, u, ls, seed, id, s,
-                                                              (t + sub) << 16, 0u, rule, 0u, ended, serve, left, [] {});
+                                                              (t + sub) << 16, 0u, rule, 0u, ended, serve, left);
         if (on && !fin && x != PENDING) {
             fin = acc = true;
             v = x;

@@ -390,7 +390,7 @@ void sort_impl(const K* kin, const uint32_t* vin, K* kout, uint32_t* vout, uint6
 // sorting record numbers and then gathering costs two random sectors per record.
 size_t sort_records_temp_bytes(uint64_t n) {
     const uint64_t nb = cdiv(n ? n : 1, SORT_TILE);
-    return align256(nb * RADIX * 4) + align256(nb * RADIX * 8) + 2 * align256(n * 4) + align256(n * 8) +
+    return align256(nb * RADIX * 4) + align256(nb * RADIX * 8) + align256(n * 4) + align256(n * 8) +
            scan_temp_bytes(nb * RADIX) + 256;
 }
 // keys_out (n u32) and vals_out (n u64: lo | hi << 32); bits in 1..32

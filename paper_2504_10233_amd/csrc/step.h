@@ -685,13 +685,12 @@ __device__ __forceinline__ uint32_t lane_decimal(const uint32_t* __restrict__ po
 // returned as PENDING with serve set, ls.blk * 4 - left words of its stream used.
 // SPEC attempts are loaded together.  WIDE as in lean_pick: the fork costs the walks that never meet a large vertex
 // 2 % in the kernels with a termination word and in node2vec, the tail 14 % in the DeepWalk kernel (at 72 registers
-// it spills 16).  All lanes of the wave call; mid() runs
-// between the issue of the header loads and their first use.
-template <int SPEC, int MODE, int TERM, bool WAVE, int WIDE, class Mid>
+// it spills 16).  All lanes of the wave call.
+template <int SPEC, int MODE, int TERM, bool WAVE, int WIDE>
 __device__ __forceinline__ uint32_t lane_advance(const uint32_t* __restrict__ hdr, const uint32_t* __restrict__ pool,
                                                  bool act, uint32_t u, LaneStep& ls, uint64_t seed, uint64_t id,
                                                  uint32_t s, uint32_t blk0, uint32_t thr, GroupRule rule,
-                                                 uint32_t wave_deg, bool& ended, bool& serve, uint32_t& left, Mid mid) {
+                                                 uint32_t wave_deg, bool& ended, bool& serve, uint32_t& left) {
     constexpr uint32_t HEAD = TERM + (MODE == 2 ? 3 : 2);  // words before the first attempt
     ended = serve = false;
     left = 0;
@@ -699,7 +698,6 @@ __device__ __forceinline__ uint32_t lane_advance(const uint32_t* __restrict__ hd
     const bool begin = act && !ls.pending;
     HotLine q;
     if (begin) q = load_hot(hdr, u);
-    mid();
     uint32_t w0 = 0, w1 = 0, w2 = 0, w3 = 0;
     if (act) {
         const uint32_t blk = begin ? 0u : ls.blk;

@@ -2153,8 +2153,8 @@ __global__ void k_alloc_check(unsigned long long* __restrict__ ctl, uint64_t poo
 
 // ---------------------------------------------------------------------------
 // Batches of up to SMALL_R records.  Their kernels have next to nothing to do, so the batch's time is
-// the number of its launches, at 4 to 5 us each; the steps between the searches run as three blocks of
-// one thread per record, with what the steps hand on in LDS.  They leave every array and count as the
+// the number of its launches, at 4 to 5 us each; the steps between the searches run as four launches of one block with
+// a thread per record, with what the steps hand on in LDS.  They leave every array and count as the
 // kernels above do.  100 records on R-MAT 18: 295 -> 214 us with the staging in one launch and one
 // block read back.
 // ---------------------------------------------------------------------------

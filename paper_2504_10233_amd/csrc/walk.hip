@@ -202,7 +202,7 @@ __global__ void __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(MODE ==
         bool ended, serve;
         uint32_t left;
         uint32_t v = lane_advance<SPEC, MODE, 0, WAVE, WIDE_FORK>(hdr, pool, j != NO_WALK, u, ls, seed, base + j, s, 0u, 0u, rule,
-                                                 wave_deg, ended, serve, left, [] {});
+                                                 wave_deg, ended, serve, left);
         if (WAVE) {
             const uint32_t wv = wave_dense_serve(pool, ls, seed, base + j, s, left, serve);
             if (serve) { v = wv; ls.pending = false; }
@@ -511,7 +511,7 @@ __global__ void __launch_bounds__(TB) k_ppr_persistent(const uint32_t* __restric
 }
 
 template <int SPEC, int MODE, bool WAVE>
-__global__ void __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(MODE == 1 ? 5 : 5, 8))) k_ppr_interleaved(const uint32_t* __restrict__ hdr, const uint32_t* __restrict__ pool,
+__global__ void __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(5, 8))) k_ppr_interleaved(const uint32_t* __restrict__ hdr, const uint32_t* __restrict__ pool,
                                                         uint32_t n, uint32_t nsrc, const uint32_t* __restrict__ sources,
                                                         uint32_t R, uint64_t seed, uint64_t base, GroupRule rule,
                                                         const uint64_t* __restrict__ seg,
@@ -555,7 +555,7 @@ __global__ void __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(MODE ==
         uint32_t left;
         // the termination word of every step of a segment is known to be >= the threshold
         uint32_t v = lane_advance<SPEC, MODE, 1, WAVE, WIDE_TAIL>(hdr, pool, j != NO_WALK, u, ls, seed, base + j, s, 0u, 0u, rule,
-                                                 wave_deg, ended, serve, left, [] {});
+                                                 wave_deg, ended, serve, left);
         if (WAVE) {
             const uint32_t wv = wave_dense_serve(pool, ls, seed, base + j, s, left, serve);
             if (serve) { v = wv; ls.pending = false; }
@@ -656,7 +656,7 @@ struct BinStage {
 };
 
 template <int SPEC, int MODE, bool WAVE>
-__global__ void __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(MODE == 1 ? 5 : 5, 8))) k_ppr_binned(const uint32_t* __restrict__ hdr, const uint32_t* __restrict__ pool,
+__global__ void __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(5, 8))) k_ppr_binned(const uint32_t* __restrict__ hdr, const uint32_t* __restrict__ pool,
                                                    uint32_t n, uint32_t nsrc, const uint32_t* __restrict__ sources,
                                                    uint32_t R, uint64_t seed, uint64_t base, uint32_t thr,
                                                    uint32_t cap, GroupRule rule, uint64_t C,
@@ -705,7 +705,7 @@ __global__ void __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(MODE ==
         bool ended, serve;
         uint32_t left;
         uint32_t v = lane_advance<SPEC, MODE, 1, WAVE, WIDE_TAIL>(hdr, pool, act, u, ls, seed, base + j, s, 0u, thr, rule, wave_deg,
-                                                 ended, serve, left, [] {});
+                                                 ended, serve, left);
         if (WAVE) {
             const uint32_t wv = wave_dense_serve(pool, ls, seed, base + j, s, left, serve);
             if (serve) { v = wv; ls.pending = false; }
@@ -1175,12 +1175,12 @@ int resident_grid(const void* kernel, uint32_t blocks_per_cu) {
 }
 
 // Walk ids per queue atomic of a persistent launch: the tuned chunk, but no more than leaves every
-// wave of the grid two chunks, down to one id per lane.  (A query of 50,000 walks has 784 waves: with
+// wave of the grid a chunk, down to one id per lane.  (A query of 50,000 walks has 784 waves: with
 // chunks of 256 ids three of four would find the queue empty, and the fourth walk four times in turn.)
 uint32_t chunk_for(const bingo_graph* g, uint64_t nw, uint32_t grid) {
     const uint64_t per_wave = nw / std::max<uint64_t>((uint64_t)grid * (TB / 64), 1);
     uint32_t c = g->queue_chunk;
-    while (c > 64 && 1ull * c > per_wave) c >>= 1;
+    while (c > 64 && c > per_wave) c >>= 1;
     return c;
 }
 
