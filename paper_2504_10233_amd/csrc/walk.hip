@@ -159,8 +159,11 @@ __global__ void __launch_bounds__(TB) k_deepwalk_persistent(const uint32_t* __re
     wave_add_u64(ctl + 1, steps);
 }
 
+// Seven waves per SIMD where the kernel fits them with next to no spills (2 of 72 registers); the other instances, at
+// seven waves, spilled 8 (alias rows) to 16 and lost by it: a walk per vertex of R-MAT 22 with alias rows 9360 us, now
+// 9210, with wave-served steps 8290 and 7630.
 template <int SPEC, int MODE, bool WAVE>
-__global__ void __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(MODE == 1 ? 5 : 7, 8))) k_deepwalk_interleaved(const uint32_t* __restrict__ hdr,
+__global__ void __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(MODE == 0 && !WAVE ? 7 : 5, 8))) k_deepwalk_interleaved(const uint32_t* __restrict__ hdr,
                                                              const uint32_t* __restrict__ pool, uint32_t n,
                                                              uint64_t nw, const uint32_t* __restrict__ starts,
                                                              uint64_t base, uint32_t L, uint64_t seed,
