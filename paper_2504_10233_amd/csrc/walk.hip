@@ -1188,18 +1188,19 @@ uint32_t chunk_for(const bingo_graph* g, uint64_t nw, uint32_t grid) {
 }
 
 // Lanes per walk for a query of nw walks (1: a lane each, by the persistent kernels), with
-// `resident_blocks` of them on the chip at once.  Measured on R-MAT 18 / 22, walks of 40 steps with
-// 1, 8, 16 and 64 lanes, in us: 1000 walks 155 / 111 / 108 / 102; 4000 walks 214 / 139 / 135 / 144;
-// 16,000 walks 215 / 157 / 173 / 285; 32,000 walks 185 / 165 / 227 / 337; 65,000 walks 200 / 257.
-// Personalized PageRank, 10 x 1000 walks: 145 / 98 / 93 / 175; 60 x 1000: 219 / 171 / 262.  So the wide
-// forms end where they fill a quarter of the lanes; the last one, of 8, where it fills them all
-// (walks that end at random leave lanes idle) or five eighths (walks of one length).
+// `resident_blocks` of them on the chip at once.  The walk kernel on R-MAT 18, walks of 40 steps, with 1, 8, 16 and 64
+// lanes, in us: 1000 walks 183 / 85 / 80 / 71; 4000 walks 195 / 108 / 104 / 109; 10,000 walks 194 / 116 / 119 / 208;
+// 20,000 walks 196 / 127 / 148 / 347; 40,000 walks 207 / 156 / 262; 50,000 walks 210 / 228.  So the wide forms end
+// where they fill a quarter of the lanes and the last one, of 8, at five eighths of them.  Walks that end at random
+// leave lanes idle, and their groups of 8 stay ahead well past the lanes: personalized PageRank (stop 0.15) of 10,000
+// walks 143 / 91 / 91 / 102, 40,000 186 / 134 / 140, 80,000 208 / 172, 160,000 285 / 223, on R-MAT 22 274 / 216; that
+// form ends at four times the lanes, as far as it was measured.
 int coop_lanes(const bingo_graph* g, uint64_t nw, int resident_blocks, bool ends_early) {
     if (!g->walk_variant || g->wave_degree) return 1;
     const uint64_t lanes = (uint64_t)resident_blocks * TB;
     if (nw * 64 <= lanes / 4) return 64;
     if (nw * 16 <= lanes / 4) return 16;
-    if (nw * 8 <= (ends_early ? lanes : lanes / 8 * 5)) return 8;
+    if (nw * 8 <= (ends_early ? 4 * lanes : lanes / 8 * 5)) return 8;
     return 1;
 }
 

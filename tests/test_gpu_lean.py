@@ -358,10 +358,23 @@ def test_a_large_hub_equals_the_per_step_form(mode):
         a, sa = g.walk(starts, 7, 77, base=nw)
         b, sb = g.walk(starts, 7, 77, base=nw, mode=MODE_PER_STEP)
         assert torch.equal(a, b) and int(sa) == int(sb), nw
-    for ns in (2, 100):
+    for ns in (2, 100, 200):  # the last on a lane each, the others on several lanes per walk
         s = synth.below(8, 1, ns, n).to(torch.int32)
         a, b = (g.ppr(s, 1000, int(0.15 * 2**32), 200, 5, mode=m) for m in (0, MODE_PER_STEP))
         assert all(torch.equal(x, y) for x, y in zip(a[:3], b[:3])) and a[3] == b[3]
     a, _ = g.node2vec(starts, 7, 77, 1.0, 1.0, base=nw)
     assert torch.equal(a, g.walk(starts, 7, 77, base=nw)[0])
+    g.close()
+
+
+@pytest.mark.parametrize("mode", ["int", "plain", "float", "alias"])
+def test_ppr_around_the_end_of_the_forms_with_several_lanes(mode):
+    """163,000 walks on eight lanes each, 165,000 on one (327,680 lanes are resident), equal the per-step form."""
+    import torch
+    from paper_2504_10233_amd import MODE_PER_STEP
+    n, g = _graph(mode)
+    for ns in (163, 165, 240):
+        src = synth.below(8, ns, ns, n).to(torch.int32)
+        a, b = (g.ppr(src, 1000, int(0.15 * 2**32), 200, 5, base=1 << 33, mode=m) for m in (0, MODE_PER_STEP))
+        assert all(torch.equal(x, y) for x, y in zip(a[:3], b[:3])) and a[3] == b[3]
     g.close()
