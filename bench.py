@@ -1193,9 +1193,7 @@ def main():
             roof["achievable_note"] = ("the query's own visits replayed over the graph (bingo_probe_replay) at the "
                                        "walk's lines per visit; the best of three orders: shuffled within each "
                                        "source with dependent chains, shuffled with independent visits, and each "
-                                       "source's visits by vertex (the most reuse the per-source grouping allows). "
-                                       "The walk itself lies between the shuffled and the ordered replays: its "
-                                       "wave's lanes walk from one source in step")
+                                       "source's visits by vertex (the most reuse the per-source grouping allows)")
             roof["frac_of_shuffled_replay"] = roof["achieved"] / max(replay["independent_GBps_at_walk_mix"],
                                                                      replay["dependent_GBps_at_walk_mix"])
         result["update_roofline"] = update_roofline(timed, mem, m, r_rand, r_stream)
